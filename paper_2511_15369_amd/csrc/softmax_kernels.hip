@@ -156,11 +156,8 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
     // 4.1 / 4.9 us against 5.5 / 5.3 / 4.9 us with the slab kernel; 392 to 3136 rows of 49 with a
     // table: 3.5-4.2 against 5.3-4.7 us; the slab kernels win from about 4000 rows on).
     constexpr int64_t kTinyRows = 3072;
-    // (a per-window mask and the second-degree exponential exist in the compiled-row-length and
-    // the three-pass kernels only)
-    auto slab_only = [](const SoftmaxCall &c) {
-        return c.mask != nullptr || c.mask_bits != nullptr || c.P.variant == 2;
-    };
+    // (a per-window mask exists in the compiled-row-length and the three-pass kernels only)
+    auto slab_only = [](const SoftmaxCall &c) { return c.mask != nullptr || c.mask_bits != nullptr; };
     if (n_calls == 1 && calls[0].algo == IPTQ_ALGO_AUTO && calls[0].rows <= kTinyRows && !slab_only(calls[0])) {
         int64_t served = 0;
         const hipError_t e = softmax_wide_launch(calls[0], cols, post_mode_of(calls[0].P, calls[0].out_bits),

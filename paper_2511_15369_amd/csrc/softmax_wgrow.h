@@ -151,8 +151,10 @@ softmax_wgrow_kernel(WideArgs A)
     const WorkgroupSum<WAVES> wg_sum{part_sum, wv, lane};
     if (P.variant == 0)
         softmax_slab_math<64, SLOTS, MODE, 0, PM_NONE, WorkgroupSum<WAVES>>(x, w, mx, lower, low_row, lut, P, wg_sum);
-    else
+    else if (P.variant == 1)
         softmax_slab_math<64, SLOTS, MODE, 1, PM_NONE, WorkgroupSum<WAVES>>(x, w, mx, lower, low_row, lut, P, wg_sum);
+    else
+        softmax_slab_math<64, SLOTS, MODE, 2, PM_NONE, WorkgroupSum<WAVES>>(x, w, mx, lower, low_row, lut, P, wg_sum);
 
     // ---- post step on the packed bytes (a probability is at most 128)
     if (post_mode == PM_CLAMP127) {

@@ -147,7 +147,8 @@ softmax_wide_kernel(WideArgs A)
     const int32_t lower = low_row ? kI32Min : mx - D;
     uint32_t w[SLOTS];                                // four probabilities per block, one per byte
     if (P.variant == 0) softmax_slab_math<64, SLOTS, MODE, 0, PM_NONE>(x, w, mx, lower, low_row, lut, P);
-    else softmax_slab_math<64, SLOTS, MODE, 1, PM_NONE>(x, w, mx, lower, low_row, lut, P);
+    else if (P.variant == 1) softmax_slab_math<64, SLOTS, MODE, 1, PM_NONE>(x, w, mx, lower, low_row, lut, P);
+    else softmax_slab_math<64, SLOTS, MODE, 2, PM_NONE>(x, w, mx, lower, low_row, lut, P);
 
     // ---- post step on the packed bytes (a probability is at most 128)
     if (post_mode == PM_CLAMP127) {
