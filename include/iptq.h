@@ -182,7 +182,7 @@ int iptq_requant(const int32_t *d_in, void *d_out, int64_t n, int32_t out_is_sig
  * 16-byte grid); an additive table of any size is fused (a little faster when
  * bias_period_rows * cols is a multiple of 4, as with 4, 8, 16 or 32 Swin heads), except a
  * table with fewer rows than one wavefront's slab (64 rows divided by the lanes per row: 32 at
- * 49 columns, 8 or 16 at 197), or of 2^30 entries and more, which takes the three-pass kernel
+ * 49 columns, 8 or 16 at 197; 32 rows suffice for rows of up to 29 scores), or of 2^30 entries and more, which takes the three-pass kernel
  * (about a sixth of the speed).
  */
 int iptq_softmax_i32(const int32_t *d_scores, const int32_t *d_bias, int64_t bias_period_rows,
@@ -200,9 +200,9 @@ int iptq_softmax_i32(const int32_t *d_scores, const int32_t *d_bias, int64_t bia
  * [heads * cols, cols] with bias_period_rows = heads * cols); either table may be NULL.  Nothing
  * is materialised: both tables are read beside the scores.  n_windows >= 1, heads >= 1,
  * n_windows * heads * cols < 2^31 (else IPTQ_ERR_SHAPE).
- * Speed: windows of 49 or 144 tokens with a bias run in the slab kernels (the extra table costs
- * about a sixth of the time; the packed form below costs almost nothing); any other shape, or a
- * mask without a bias, takes the slow three-pass kernel.
+ * Speed: windows of up to about 635 tokens run in the slab kernels, fastest at 49 or 144 tokens with
+ * a bias (the extra table costs about a sixth of the time; the packed form below costs less);
+ * longer windows take the slow three-pass kernel.
  */
 int iptq_softmax_i32_windowed(const int32_t *d_scores, const int32_t *d_bias,
                               int64_t bias_period_rows, const int32_t *d_mask, int32_t n_windows,
@@ -218,8 +218,8 @@ int iptq_softmax_i32_windowed(const int32_t *d_scores, const int32_t *d_bias,
  * 8-byte load per row and two instructions per score instead of a third table read beside the
  * scores (Swin-B stage 1 at batch 64: 35 us against 34 us without a mask and 40 us with the int32
  * mask).
- * Speed: windows of 49 or 144 tokens with a bias run in the slab kernels; any other shape takes
- * the slow three-pass kernel.  Errors as for iptq_softmax_i32_windowed; IPTQ_ERR_ALIGN if
+ * Speed: windows of up to about 635 tokens run in the slab kernels, fastest at 49 or 144 tokens with
+ * a bias; longer ones take the slow three-pass kernel.  Errors as for iptq_softmax_i32_windowed; IPTQ_ERR_ALIGN if
  * d_mask_bits is not 8-byte aligned; a batched problem that carries both forms of the mask is
  * refused with IPTQ_ERR_PARAM.
  */

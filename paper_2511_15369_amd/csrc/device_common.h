@@ -50,6 +50,11 @@ __device__ __forceinline__ i32x4 load_i32x4_at(const int32_t *base, uint32_t byt
 {
     return *reinterpret_cast<const i32x4_a4 *>(reinterpret_cast<const char *>(base) + byte_offset);
 }
+// one dword at any byte address: uniform base, vector byte offset, compile-time byte offset
+__device__ __forceinline__ uint32_t load_u32_at(const void *base, uint32_t byte_offset, int fixed)
+{
+    return *reinterpret_cast<const u32_a1 *>(reinterpret_cast<const char *>(base) + fixed + byte_offset);
+}
 __device__ __forceinline__ void stream_store_bytes16(u32x4 v, uint8_t *p)
 {
     __builtin_nontemporal_store(v, reinterpret_cast<u32x4_a1 *>(p));

@@ -156,7 +156,8 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
     // 4.1 / 4.9 us against 5.5 / 5.3 / 4.9 us with the slab kernel; 392 to 3136 rows of 49 with a
     // table: 3.5-4.2 against 5.3-4.7 us; the slab kernels win from about 4000 rows on).
     constexpr int64_t kTinyRows = 3072;
-    // (a per-window mask exists in the compiled-row-length and the three-pass kernels only)
+    // (a per-window mask exists in the slab kernels, compiled and run-time row length, and in the
+    // three-pass kernel)
     auto slab_only = [](const SoftmaxCall &c) { return c.mask != nullptr || c.mask_bits != nullptr; };
     if (n_calls == 1 && calls[0].algo == IPTQ_ALGO_AUTO && calls[0].rows <= kTinyRows && !slab_only(calls[0])) {
         int64_t served = 0;
@@ -258,7 +259,7 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
             const SoftmaxCall &c = calls[base + i];
             const bool has_pre = !(c.P.pre_m == 1 && c.P.pre_s == 0);
             // a call no compiled row length served goes to the run-time-row-length kernels
-            if (done[i] == 0 && !slab_only(c) && (c.algo == IPTQ_ALGO_AUTO || c.algo == IPTQ_ALGO_DYNAMIC || c.algo == IPTQ_ALGO_SLAB)) {
+            if (done[i] == 0 && (c.algo == IPTQ_ALGO_AUTO || c.algo == IPTQ_ALGO_DYNAMIC || c.algo == IPTQ_ALGO_SLAB)) {
                 err = softmax_rowsdyn_launch(c, cols, post_mode_of(c.P, c.out_bits), &done[i], stream);
                 if (err != hipSuccess) break;
             }

@@ -16,6 +16,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <stddef.h>
+
 #include <type_traits>
 
 #include "device_common.h"
@@ -38,21 +40,63 @@ struct DynArgs {
     // the same table rows (see SoftmaxItem); 0: consecutive slabs
     uint32_t share_q, share_magic;
     int32_t share_sh;
+    uint32_t wpb;         // wavefronts per workgroup (here and not from the launch's implicit arguments,
+                          // which lie behind the lines touched at entry: a cold read in front of all else)
     SoftmaxDev P;
+    // (last, so that a kernel without a mask does not touch them)
+    // per-window mask, at most one form: int32 entries (MASKKIND 1) or one bit per key (2)
+    const int32_t *mask;
+    const uint64_t *mask_bits;
+    uint32_t cols_magic;  // query of a row (row mod cols) by multiply-high, cols >= 2
+    int32_t cols_sh;
 };
 
-template <int K, int SLOTS, int MODE>
+// Four entries of a row-major table of `total` entries from entry `idx` on, where idx may lie up
+// to three entries before the table or run past its end (the first and last block of a row that
+// starts off the 16-byte grid): the load is moved inside the table and the entries that exist are
+// shifted back to their places (a rare case, one wavefront-uniform branch); the others are
+// arbitrary.  total >= 4.
+IPTQ_DEV i32x4 table_block_at(const int32_t *table, int32_t idx, int32_t total)
+{
+    const int32_t a = clamp_i32(idx, 0, total - 4);
+    i32x4 m = load_i32x4_at(table, 4u * (uint32_t)a);
+    const int32_t d = idx - a;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(d != 0) != 0, 0)) {
+        const i32x4 t = m;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int32_t k = e + d;
+            m[e] = k == 0 ? t.x : (k == 1 ? t.y : (k == 2 ? t.z : t.w));
+        }
+    }
+    return m;
+}
+
+// MASKKIND: 0 no mask; 1 int32 entries, 2 one bit per key: the per-window mask of shifted-window
+// attention, for windows of any size.  Both forms are
+// applied to the registers once the row has been read back from LDS (the int32 entries load per
+// block straight into the lane that needs them; a mask row is shared by `heads` rows and comes out
+// of L1/L2), so the copy loop stays the one of the unmasked kernel.  What bounds it is still HBM,
+// with the mask's lane-ops (two per score packed, four as int32) next: 524,288 rows of 8 x 8-token
+// windows with a bias table 34.4 us packed and 35 us as int32 entries against 32 us without a mask
+// and 251 us in the three-pass kernel; 16 x 16 tokens (262,144 rows) 60 / 65 / 57 us.  At 49 and 144
+// tokens the compiled row lengths stay faster (144: 73 / 81 us against 85 / 89 us here).
+//
+// VARIANT is a template argument because every launch starts with a cold instruction cache: with a
+// branch over the three exponentials 122,880 rows of 100 scores with a table took 16.3 us against
+// 15.7 us (a launch of this kernel has one set of parameters, so nothing needs the branch).
+template <int K, int SLOTS, int MODE, int MASKKIND, int VARIANT>
 __global__ void __launch_bounds__(256)
 softmax_rowsdyn_kernel(DynArgs A)
 {
     constexpr int RPW = 64 / K;                       // rows per wavefront, a multiple of 4
     extern __shared__ __attribute__((aligned(16))) uint8_t dyn_lds[];
-    touch_kernel_arguments<sizeof(DynArgs)>();
+    touch_kernel_arguments<MASKKIND == 0 ? offsetof(DynArgs, mask) : sizeof(DynArgs)>();
     const SoftmaxDev &P = A.P;
     const int lane = threadIdx.x & 63;
     // (a scalar: the slab, its table offsets and every test on them then run on the scalar unit)
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t wpb = blockDim.x >> 6;
+    const uint32_t wpb = A.wpb;
     int64_t slab = (int64_t)blockIdx.x * wpb + wv;
     if (A.share_q != 0) {
         const uint32_t g = mulhi_u32(blockIdx.x, A.share_magic) >> A.share_sh;
@@ -75,9 +119,68 @@ softmax_rowsdyn_kernel(DynArgs A)
     const bool partial = A.tail_rows != 0 && slab == A.n_slabs - 1;
     const int valid_el = (partial ? A.tail_rows : RPW) * cols;
 
+    // ---- the mask of this lane's blocks, in flight with the scores.  Packed form: the bits of
+    // slot s start at key 4 (s K + j) - phi; one 4-byte load at the byte that holds that key
+    // (moved inside the mask row where it would leave it) covers the bits of GROUP slots.  (8-byte
+    // words take half the loads and two quarter-rate 64-bit shifts each: 20 x 20 tokens 102 us
+    // against 85 us.)
+    constexpr int GROUP = K == 1 ? 6 : (K == 2 ? 3 : (K == 4 ? 2 : 1));
+    constexpr int NG = (SLOTS + GROUP - 1) / GROUP;
+    static_assert(4 * K * (GROUP - 1) + 4 + 7 <= 32, "the bits of a group of slots at any offset inside a byte");
+    uint32_t mask_word[MASKKIND == 2 ? NG : 1];
+    i32x4 mask_block[MASKKIND == 1 ? SLOTS : 1];
+    if (MASKKIND != 0) {
+        const int lr = lane / K, j = lane % K, phi = (lr * cols) & 3;    // as below
+        // rows past the end of a partial slab take the last row's mask (never stored)
+        const uint32_t row = (uint32_t)(slab * RPW) + (uint32_t)(partial ? min(lr, A.tail_rows - 1) : lr);
+        uint32_t rm = 0;
+        if (P.mask_period_rows >= 2)
+            rm = row - (mulhi_u32(row, P.mperiod_magic) >> P.mperiod_sh) * (uint32_t)P.mask_period_rows;
+        const uint32_t w = P.group_rows >= 2 ? mulhi_u32(rm, P.group_magic) >> P.group_sh : rm;
+        uint32_t q = rm - w * (uint32_t)P.group_rows;
+        if (cols >= 2) q -= (mulhi_u32(q, A.cols_magic) >> A.cols_sh) * (uint32_t)cols;
+        else q = 0;
+        const uint32_t mrow = w * (uint32_t)cols + q;
+        if (MASKKIND == 1) {
+            const int32_t total = P.n_windows * cols * cols;     // below 2^30 (host)
+            const int32_t first = (int32_t)(mrow * (uint32_t)cols) + 4 * j - phi;
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s)
+                mask_block[s] = (s == 0 || s >= SLOTS - 2)      // only there can a block leave the table
+                    ? table_block_at(A.mask, first + 4 * s * K, total)
+                    : load_i32x4_at(A.mask + (4 * s * K - 4), 4u * (uint32_t)(first + 4));   // first >= -3
+        } else {
+            const int32_t row_bytes = 8 * ((cols + 63) >> 6);
+            const uint32_t row_at = mrow * (uint32_t)row_bytes;          // below 2^31 (host)
+            const int32_t sh = 4 * j - phi;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                const int32_t p = 4 * K * GROUP * g + sh;
+                if (K >= 8 && g >= 1 && g <= NG - 3) {
+                    // inside the mask row for every lane (the blocks of slots 0 .. SLOTS-2 exist in
+                    // every row): one address for all of these (sh >= -3: one byte is moved from
+                    // the fixed offset to the unsigned one), one shift
+                    mask_word[g] = load_u32_at(A.mask_bits, row_at + (uint32_t)((sh >> 3) + 1), 4 * K * g / 8 - 1) >> (sh & 7);
+                } else {
+                    const int32_t at = min(g == 0 ? max(p >> 3, 0) : p >> 3, row_bytes - 4);
+                    const int32_t d = p - 8 * at;     // negative only for the first block of a row off the grid
+                    const uint32_t v = load_u32_at(A.mask_bits, row_at + (uint32_t)at, 0);
+                    mask_word[g] = v >> (d & 31);
+                    if (g == 0) mask_word[g] = d < 0 ? v << (-d & 31) : mask_word[g];
+                }
+            }
+        }
+    }
+
     // ---- flat copy of the slab into LDS, bias added on the way.  Every load is issued before
     // the first LDS write and none sits behind a branch: in the last two passes the lanes
     // beyond the slab's last chunk load that chunk again and write it to its place again.
+    // (with one lane per row a slab has 64 rows and the table may have as few as 32: two wraps)
+    auto wrap = [](uint32_t o, uint32_t pe) -> uint32_t {
+        if (o >= pe) o -= pe;
+        if (K == 1 && o >= pe) o -= pe;
+        return o;
+    };
     auto add_bias = [](i32x4 v, const i32x4 bv) {
         v = add_table_chunk(v, bv);
         return v;
@@ -107,8 +210,7 @@ softmax_rowsdyn_kernel(DynArgs A)
         i32x4 first4 = {0, 0, 0, 0};
         if (STRADDLE) first4 = load_i32x4(bias);
         auto bias_chunk = [&](int i) {
-            uint32_t o = boff + 4u * (uint32_t)chunk_of(i);
-            if (o >= pe) o -= pe;
+            uint32_t o = wrap(boff + 4u * (uint32_t)chunk_of(i), pe);
             return STRADDLE ? bias_chunk_wrapping(bias, o, pe, first4) : load_i32x4(bias + o);
         };
         i32x4 v[SLOTS], bv[BIAS ? kAhead : 1];
@@ -156,8 +258,7 @@ softmax_rowsdyn_kernel(DynArgs A)
                 if (4 * idx + 2 < valid_el) v.z = src1[4 * idx + 2];
             }
             if (bias != nullptr) {
-                uint32_t o = boff + 4u * (uint32_t)idx;
-                if (o >= pe) o -= pe;
+                const uint32_t o = wrap(boff + 4u * (uint32_t)idx, pe);
                 v = add_bias(v, bias_chunk_wrapping(bias, o, pe, load_i32x4(bias)));
             }
             lds4[idx] = v;
@@ -201,6 +302,23 @@ softmax_rowsdyn_kernel(DynArgs A)
     }
     wave_lds_fence();                                 // the slab area is reused for the output
 
+    if (MASKKIND == 1) {
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[s][e] = add_table_entry(x[s][e], mask_block[s][e]);
+    }
+    if (MASKKIND == 2) {
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int pos = 4 * K * (s % GROUP) + e;          // compile-time position in the group's word
+                const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int32_t)mask_word[s / GROUP], pos, 1);
+                x[s][e] = select_bits_i32(m, kI32Min, x[s][e]);
+            }
+    }
+
     // ---- fused requantization of the scores (after the bias, before the maximum)
     if (P.pre_mode == 1) {
         const int32_t pre_mul = P.pre_mul, pre_sh2 = P.pre_sh2;
@@ -237,11 +355,7 @@ softmax_rowsdyn_kernel(DynArgs A)
     const bool any_low = __builtin_amdgcn_ballot_w64(low_row) != 0;
     uint32_t w[SLOTS];                                // four probabilities per block, one per byte
 
-    // (the second-degree exponential too: 150,528 x 196 scores 26.3 us, HBM-bound like the other
-    // two, against 142.9 us in the three-pass kernel)
-    if (P.variant == 0) softmax_slab_math<K, SLOTS, MODE, 0, PM_NONE>(x, w, mx, lower, any_low, lut, P);
-    else if (P.variant == 1) softmax_slab_math<K, SLOTS, MODE, 1, PM_NONE>(x, w, mx, lower, any_low, lut, P);
-    else softmax_slab_math<K, SLOTS, MODE, 2, PM_NONE>(x, w, mx, lower, any_low, lut, P);
+    softmax_slab_math<K, SLOTS, MODE, VARIANT, PM_NONE>(x, w, mx, lower, any_low, lut, P);
 
     // ---- post step on the packed bytes (a probability is at most 128)
     if (post_mode == PM_CLAMP127) {
@@ -312,8 +426,22 @@ softmax_rowsdyn_kernel(DynArgs A)
 template <int K, int SLOTS>
 static void rowsdyn_launch_ks(const DynArgs &A, int mode, dim3 grid, dim3 block, size_t lds, hipStream_t stream)
 {
-    if (mode == 0) hipLaunchKernelGGL((softmax_rowsdyn_kernel<K, SLOTS, 0>), grid, block, lds, stream, A);
-    else hipLaunchKernelGGL((softmax_rowsdyn_kernel<K, SLOTS, 2>), grid, block, lds, stream, A);
+#define IPTQ_ROWSDYN_LAUNCH(MODE, MASKKIND)                                                       \
+    do {                                                                                          \
+        if (A.P.variant == 0) hipLaunchKernelGGL((softmax_rowsdyn_kernel<K, SLOTS, MODE, MASKKIND, 0>), grid, block, lds, stream, A);      \
+        else if (A.P.variant == 1) hipLaunchKernelGGL((softmax_rowsdyn_kernel<K, SLOTS, MODE, MASKKIND, 1>), grid, block, lds, stream, A); \
+        else hipLaunchKernelGGL((softmax_rowsdyn_kernel<K, SLOTS, MODE, MASKKIND, 2>), grid, block, lds, stream, A);                       \
+    } while (0)
+#define IPTQ_ROWSDYN_LAUNCH_MASK(MODE)                                                            \
+    do {                                                                                          \
+        if (A.mask != nullptr) IPTQ_ROWSDYN_LAUNCH(MODE, 1);                                      \
+        else if (A.mask_bits != nullptr) IPTQ_ROWSDYN_LAUNCH(MODE, 2);                            \
+        else IPTQ_ROWSDYN_LAUNCH(MODE, 0);                                                        \
+    } while (0)
+    if (mode == 0) IPTQ_ROWSDYN_LAUNCH_MASK(0);
+    else IPTQ_ROWSDYN_LAUNCH_MASK(2);
+#undef IPTQ_ROWSDYN_LAUNCH_MASK
+#undef IPTQ_ROWSDYN_LAUNCH
 }
 
 // One launcher per group of layouts, each defined in its own translation unit so that the

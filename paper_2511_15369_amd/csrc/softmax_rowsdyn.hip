@@ -25,6 +25,12 @@ bool rowsdyn_geometry(int32_t cols, int *lanes, int *slots)
     return true;
 }
 
+static int64_t gcd_i64(int64_t a, int64_t b)
+{
+    while (b != 0) { const int64_t t = a % b; a = b; b = t; }
+    return a;
+}
+
 // Every row of one call if the call qualifies; returns the number of rows served through
 // *done (0: not served, nothing enqueued).
 hipError_t softmax_rowsdyn_launch(const SoftmaxCall &c, int32_t cols, int post_mode, int64_t *done,
@@ -36,9 +42,16 @@ hipError_t softmax_rowsdyn_launch(const SoftmaxCall &c, int32_t cols, int post_m
     const int rpw = 64 / k;
     const bool has_bias = c.bias != nullptr;
     const bool aligned = ((reinterpret_cast<uintptr_t>(c.scores) | reinterpret_cast<uintptr_t>(c.bias)) & 3) == 0;
+    // a slab wraps around the table once at most, twice with one lane per row (64 rows per slab)
     const bool bias_ok = !has_bias || ((int64_t)c.P.bias_period_rows * cols >= 4 &&
                                        (int64_t)c.P.bias_period_rows * cols < ((int64_t)1 << 31) &&
-                                       c.P.bias_period_rows >= rpw);
+                                       c.P.bias_period_rows >= (k == 1 ? 32 : rpw));
+    // int32 masks are loaded in blocks of four entries at 32-bit byte offsets
+    const bool int_mask = c.mask != nullptr;
+    const int64_t mask_el = int_mask ? (int64_t)c.P.n_windows * cols * cols : 0;
+    if (int_mask && (mask_el < 4 || mask_el >= ((int64_t)1 << 30))) return hipSuccess;
+    if (c.mask_bits != nullptr && (int64_t)c.P.n_windows * cols * ((cols + 63) / 64) * 8 >= ((int64_t)1 << 31))
+        return hipSuccess;
     const int64_t n_slabs = (c.rows + rpw - 1) / rpw;
     if (!aligned || !bias_ok || n_slabs == 0) return hipSuccess;
     DynArgs A;
@@ -46,21 +59,36 @@ hipError_t softmax_rowsdyn_launch(const SoftmaxCall &c, int32_t cols, int post_m
     A.n_slabs = n_slabs; A.tail_rows = (int32_t)(c.rows % rpw);
     A.cols = cols; A.post_mode = post_mode;
     A.wave_lds = (int32_t)((((int64_t)rpw * cols * 4 + 15) & ~(int64_t)15) + kPostLutBytes);
+    A.mask = c.mask; A.mask_bits = c.mask_bits;
+    A.cols_magic = 0; A.cols_sh = 0;
+    if ((c.mask != nullptr || c.mask_bits != nullptr) && cols >= 2 &&
+        !make_magic_u32((uint32_t)cols, 31, &A.cols_magic, &A.cols_sh))
+        return hipSuccess;
     A.P = c.P;
     int wpb = 65536 / A.wave_lds;                     // wavefronts per workgroup: 1..4
     if (wpb > 4) wpb = 4;
     if (wpb < 1) return hipSuccess;
+    A.wpb = (uint32_t)wpb;
     int64_t n_wgs = (n_slabs + wpb - 1) / wpb;
     A.share_q = 0; A.share_magic = 0; A.share_sh = 0;
-    if (has_bias && wpb > 1) {
-        int64_t a = c.P.bias_period_rows, b = rpw;
-        while (b != 0) { const int64_t t = a % b; a = b; b = t; }              // a = gcd
-        const int64_t q = c.P.bias_period_rows / a;
-        if (q >= 2 && q < 65536 && q * wpb <= n_slabs &&
-            make_magic_u32((uint32_t)q, 31, &A.share_magic, &A.share_sh)) {
-            A.share_q = (uint32_t)q;
-            n_wgs = (n_slabs + (int64_t)wpb * q - 1) / ((int64_t)wpb * q) * q;
+    auto share_every = [&](int64_t period) {          // wavefronts of a workgroup that many rows apart
+        const int64_t q = period / gcd_i64(period, rpw);
+        if (q < 2 || q >= 65536 || q * wpb > n_slabs ||
+            !make_magic_u32((uint32_t)q, 31, &A.share_magic, &A.share_sh))
+            return false;
+        A.share_q = (uint32_t)q;
+        n_wgs = (n_slabs + (int64_t)wpb * q - 1) / ((int64_t)wpb * q) * q;
+        return true;
+    };
+    if (wpb > 1) {
+        // an int32 mask is as large a stream through L1 as the scores: share it together with the
+        // bias (least common multiple of both periods) where the call is long enough for that
+        bool shared = false;
+        if (int_mask) {
+            const int64_t mp = c.P.mask_period_rows, bp = has_bias ? c.P.bias_period_rows : 1;
+            shared = share_every(mp / gcd_i64(mp, bp) * bp);
         }
+        if (!shared && has_bias) share_every(c.P.bias_period_rows);
     }
     const dim3 grid((unsigned)n_wgs), block(64 * wpb);
     const size_t lds = (size_t)A.wave_lds * wpb;

@@ -36,7 +36,7 @@ struct WorkgroupSum {
     }
 };
 
-template <int WAVES, int SLOTS, int MODE>
+template <int WAVES, int SLOTS, int MODE, int VARIANT>
 __global__ void __launch_bounds__(64 * WAVES)
 softmax_wgrow_kernel(WideArgs A)
 {
@@ -149,12 +149,7 @@ softmax_wgrow_kernel(WideArgs A)
     const int32_t lower = low_row ? kI32Min : mx - D;
     uint32_t w[SLOTS];                                // four probabilities per block, one per byte
     const WorkgroupSum<WAVES> wg_sum{part_sum, wv, lane};
-    if (P.variant == 0)
-        softmax_slab_math<64, SLOTS, MODE, 0, PM_NONE, WorkgroupSum<WAVES>>(x, w, mx, lower, low_row, lut, P, wg_sum);
-    else if (P.variant == 1)
-        softmax_slab_math<64, SLOTS, MODE, 1, PM_NONE, WorkgroupSum<WAVES>>(x, w, mx, lower, low_row, lut, P, wg_sum);
-    else
-        softmax_slab_math<64, SLOTS, MODE, 2, PM_NONE, WorkgroupSum<WAVES>>(x, w, mx, lower, low_row, lut, P, wg_sum);
+    softmax_slab_math<64, SLOTS, MODE, VARIANT, PM_NONE, WorkgroupSum<WAVES>>(x, w, mx, lower, low_row, lut, P, wg_sum);
 
     // ---- post step on the packed bytes (a probability is at most 128)
     if (post_mode == PM_CLAMP127) {
@@ -192,8 +187,15 @@ softmax_wgrow_kernel(WideArgs A)
 template <int WAVES, int SLOTS>
 static void wgrow_launch_ws(const WideArgs &A, int mode, dim3 grid, hipStream_t stream)
 {
-    if (mode == 0) hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, 0>), grid, dim3(64 * WAVES), 0, stream, A);
-    else hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, 2>), grid, dim3(64 * WAVES), 0, stream, A);
+#define IPTQ_WGROW_LAUNCH(MODE)                                                                   \
+    do {                                                                                          \
+        if (A.P.variant == 0) hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 0>), grid, dim3(64 * WAVES), 0, stream, A);      \
+        else if (A.P.variant == 1) hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 1>), grid, dim3(64 * WAVES), 0, stream, A); \
+        else hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 2>), grid, dim3(64 * WAVES), 0, stream, A);                       \
+    } while (0)
+    if (mode == 0) IPTQ_WGROW_LAUNCH(0);
+    else IPTQ_WGROW_LAUNCH(2);
+#undef IPTQ_WGROW_LAUNCH
 }
 
 // one translation unit per workgroup size and group of pass counts; each returns false for a

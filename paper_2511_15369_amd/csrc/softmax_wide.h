@@ -37,7 +37,7 @@ struct WideArgs {
     SoftmaxDev P;
 };
 
-template <int SLOTS, int MODE>
+template <int SLOTS, int MODE, int VARIANT>
 __global__ void __launch_bounds__(256)
 softmax_wide_kernel(WideArgs A)
 {
@@ -146,9 +146,7 @@ softmax_wide_kernel(WideArgs A)
     const bool low_row = mx < kI32Min + D;            // wavefront-uniform here; see softmax_rows_kernel
     const int32_t lower = low_row ? kI32Min : mx - D;
     uint32_t w[SLOTS];                                // four probabilities per block, one per byte
-    if (P.variant == 0) softmax_slab_math<64, SLOTS, MODE, 0, PM_NONE>(x, w, mx, lower, low_row, lut, P);
-    else if (P.variant == 1) softmax_slab_math<64, SLOTS, MODE, 1, PM_NONE>(x, w, mx, lower, low_row, lut, P);
-    else softmax_slab_math<64, SLOTS, MODE, 2, PM_NONE>(x, w, mx, lower, low_row, lut, P);
+    softmax_slab_math<64, SLOTS, MODE, VARIANT, PM_NONE>(x, w, mx, lower, low_row, lut, P);
 
     // ---- post step on the packed bytes (a probability is at most 128)
     if (post_mode == PM_CLAMP127) {
@@ -186,8 +184,15 @@ softmax_wide_kernel(WideArgs A)
 template <int SLOTS>
 static void wide_launch_s(const WideArgs &A, int mode, dim3 grid, hipStream_t stream)
 {
-    if (mode == 0) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, 0>), grid, dim3(256), 0, stream, A);
-    else hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, 2>), grid, dim3(256), 0, stream, A);
+#define IPTQ_WIDE_LAUNCH(MODE)                                                                    \
+    do {                                                                                          \
+        if (A.P.variant == 0) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 0>), grid, dim3(256), 0, stream, A);      \
+        else if (A.P.variant == 1) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 1>), grid, dim3(256), 0, stream, A); \
+        else hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 2>), grid, dim3(256), 0, stream, A);                       \
+    } while (0)
+    if (mode == 0) IPTQ_WIDE_LAUNCH(0);
+    else IPTQ_WIDE_LAUNCH(2);
+#undef IPTQ_WIDE_LAUNCH
 }
 
 // one translation unit per group of pass counts; each returns false for a count it does not hold

@@ -1,0 +1,84 @@
+"""Per-window masks, both forms, for windows of any size in the run-time-row-length slab kernel,
+against the oracle: every lane layout's edges, first and last mask rows (blocks that reach past either
+end of the table), ragged row counts, with and without a bias, views off the 16-byte grid."""
+import numpy as np
+import pytest
+
+import paper_2511_15369_amd as ip
+from oracle import prepare, ref
+from tests.helpers import gpu_softmax_windowed, gpu_softmax_windowed_bits, lib_softmax
+
+pytestmark = pytest.mark.gpu
+I32_MIN = -(2 ** 31)
+
+
+def _problem(t, heads, n_w, images, drop, seed):
+    rng = np.random.default_rng(seed)
+    rows = images * n_w * heads * t - drop
+    scores = np.rint(rng.standard_normal((rows, t)) * 400).astype(np.int32)
+    scores[rng.random(scores.shape) < 0.01] = I32_MIN
+    bias = np.rint(rng.standard_normal((heads * t, t)) * 8).astype(np.int32)
+    bias[rng.random(bias.shape) < 0.01] = I32_MIN
+    bias[0, 0] = I32_MIN + 5                                 # saturates low: minus infinity from there on
+    mask = np.where(rng.random((n_w, t, t)) < 0.4, I32_MIN, 0).astype(np.int32)
+    mask[n_w - 1, t - 1, :] = I32_MIN                        # the table's last row masked in full
+    return rng, scores, bias, mask
+
+
+@pytest.mark.parametrize("t,heads,n_w", [
+    (1, 3, 5), (2, 40, 3), (3, 12, 2), (4, 8, 3), (9, 4, 3), (16, 2, 3), (25, 2, 4), (25, 1, 4), (25, 3, 4), (29, 2, 3),
+    (30, 1, 3), (36, 3, 4), (49, 2, 4), (58, 2, 3), (61, 2, 3), (62, 2, 3), (64, 3, 4), (65, 1, 3), (100, 3, 3), (125, 1, 3),
+    (126, 2, 2), (128, 1, 3), (129, 1, 3), (144, 2, 3), (196, 2, 3), (225, 1, 3), (253, 1, 2), (256, 1, 2), (257, 1, 2),
+    (400, 1, 2), (511, 1, 1), (577, 1, 2), (576, 1, 2), (635, 1, 1)])
+def test_masks_match_the_oracle(t, heads, n_w):
+    images = 4 if t < 100 else 2
+    rng, scores, bias, mask = _problem(t, heads, n_w, images, int(np.random.default_rng(t).integers(0, min(t, 30))), t * 100 + heads)
+    finite = mask.copy()
+    finite[0] = np.rint(rng.standard_normal((t, t)) * 150).astype(np.int32)      # ordinary addends
+    if n_w > 1:
+        finite[1, 0, :] = 2 ** 31 - 1                        # saturates high
+    bits = ref.pack_window_mask(mask)
+    if t % 64:
+        bits[:, :, -1] |= np.uint64(((1 << 64) - 1) ^ ((1 << (t % 64)) - 1))     # no such keys
+    for variant, signed, s_delta in ((1, 0, 2.0 ** -6.5), (0, 1, 2.0 ** -14), (2, 0, 2.0 ** -5)):
+        p = prepare.softmax_prepare(s_delta, t, variant, signed)
+        for b, period in ((bias, heads * t), (None, 0)):
+            want = ref.softmax_i32_windowed(scores, p, b, period, mask, heads)
+            assert np.array_equal(gpu_softmax_windowed_bits(scores, p, b, period, bits, heads), want)
+            want = ref.softmax_i32_windowed(scores, p, b, period, finite, heads)
+            if b is not None and t in (49, 144):
+                continue                                     # compiled row lengths with a bias: tested elsewhere
+            assert np.array_equal(gpu_softmax_windowed(scores, p, b, period, finite, heads), want)
+
+
+@pytest.mark.parametrize("t", [25, 64, 100, 196])
+def test_views_off_the_grid_and_requantization(t):
+    import torch
+    heads, n_w, images = 3, 3, 2
+    rng, scores, bias, mask = _problem(t, heads, n_w, images, 1, t)
+    scores = np.where(scores == I32_MIN, I32_MIN, scores * 40).astype(np.int32)
+    p = prepare.softmax_prepare(2.0 ** -5, t, 1)
+    p.pre_m, p.pre_s = 20000, 20
+    want = ref.softmax_i32_windowed(scores, p, bias, heads * t, mask, heads).reshape(-1)
+    n = scores.size
+    d_bits = torch.from_numpy(ref.pack_window_mask(mask).view(np.int64)).cuda()
+    d_mask = torch.zeros(mask.size + 8, dtype=torch.int32, device="cuda")
+    for off in (0, 1, 2, 3):
+        d_in = torch.zeros(n + 8, dtype=torch.int32, device="cuda")
+        d_in[off:off + n] = torch.from_numpy(scores.reshape(-1)).cuda()
+        d_bias = torch.zeros(bias.size + 8, dtype=torch.int32, device="cuda")
+        d_bias[off:off + bias.size] = torch.from_numpy(bias.reshape(-1)).cuda()
+        d_mask[off:off + mask.size] = torch.from_numpy(mask.reshape(-1)).cuda()
+        for kind in ("int32", "bits"):
+            d_out = torch.full((n + 16,), 0x5A, dtype=torch.uint8, device="cuda")
+            b = d_bias[off:off + bias.size]
+            if kind == "int32":
+                ip.softmax_i32_windowed(d_in[off:off + n], b, heads * t, d_mask[off:off + mask.size], n_w, heads,
+                                        d_out[off:off + n], scores.shape[0], t, lib_softmax(p))
+            else:
+                ip.softmax_i32_windowed_bits(d_in[off:off + n], b, heads * t, d_bits, n_w, heads,
+                                             d_out[off:off + n], scores.shape[0], t, lib_softmax(p))
+            torch.cuda.synchronize()
+            got = d_out.cpu().numpy()
+            assert np.array_equal(got[off:off + n], want), (kind, off)
+            assert (got[:off] == 0x5A).all() and (got[off + n:] == 0x5A).all(), (kind, off)
