@@ -53,7 +53,7 @@ extern "C" {
                                (rows up to about 635 scores), also where a compiled row length
                                would serve */
 #define IPTQ_ALGO_WIDE 3    /* softmax only: one wavefront (rows up to 4096 scores) or one workgroup
-                               (up to 40957) per row, row in registers, no LDS staging, also where
+                               (beyond) per row, row in registers, also where
                                another kernel would serve */
 #define IPTQ_ALGO_SLAB 4    /* softmax only: the slab kernels (compiled row length if there is one,
                                else run-time row length) also for a call of few rows, which
@@ -176,8 +176,9 @@ int iptq_requant(const int32_t *d_in, void *d_out, int64_t n, int32_t out_is_sig
  * signed codes p - 128 (post = {1, 0, -128, -128, qmax >= 0}: the operand form of a signed 8-bit
  * matrix instruction for the product with V); any other post step goes through a small table.
  * Every shape gives the same bytes; speed depends on it.  Fastest: a row length of 197, 49, 198,
- * 144, 257 or 577; any other row length up to 40957 runs in the register-resident kernels with
- * a run-time row length, longer rows in a slower multi-pass kernel.  The tensors need their
+ * 144, 257 or 577; any other row length runs in the register-resident kernels with a run-time row
+ * length (but for rows of 65530 and more whose blocks do not sit on the 16-byte grid, which take a
+ * slower multi-pass kernel).  The tensors need their
  * natural alignment only (views into larger tensors run at the same speed as tensors on the
  * 16-byte grid); an additive table of any size is fused (a little faster when
  * bias_period_rows * cols is a multiple of 4, as with 4, 8, 16 or 32 Swin heads), except a

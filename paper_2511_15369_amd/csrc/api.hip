@@ -261,6 +261,7 @@ extern "C" int iptq_softmax_kernel_family(int32_t cols, int32_t *family, int32_t
     if (rowsdyn_geometry(cols, &a, &b)) { *family = IPTQ_FAMILY_SLAB; *lanes = a; *blocks = b; return IPTQ_OK; }
     if (wide_geometry(cols, &a, &b)) { *family = IPTQ_FAMILY_WAVEFRONT_PER_ROW; *lanes = 64; *blocks = a; return IPTQ_OK; }
     if (wgrow_geometry(cols, &a, &b)) { *family = IPTQ_FAMILY_WORKGROUP_PER_ROW; *lanes = 64 * a; *blocks = b; return IPTQ_OK; }
+    if (long_geometry(cols, &b)) { *family = IPTQ_FAMILY_WORKGROUP_PER_ROW; *lanes = 1024; *blocks = b; return IPTQ_OK; }
     *family = IPTQ_FAMILY_THREE_PASS;
     return IPTQ_OK;
 }

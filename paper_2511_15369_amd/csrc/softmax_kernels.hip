@@ -271,6 +271,10 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
                 err = softmax_wgrow_launch(c, cols, post_mode_of(c.P, c.out_bits), &done[i], stream);
                 if (err != hipSuccess) break;
             }
+            if (done[i] == 0 && !slab_only(c) && (c.algo == IPTQ_ALGO_AUTO || c.algo == IPTQ_ALGO_WIDE)) {
+                err = softmax_long_launch(c, cols, post_mode_of(c.P, c.out_bits), &done[i], stream);
+                if (err != hipSuccess) break;
+            }
             err = launch_generic(c.scores, c.bias, c.mask, c.mask_bits, c.out, done[i], c.rows, cols, c.bias != nullptr,
                                  has_pre, c.P, stream);
         }

@@ -204,7 +204,6 @@ bool wgrow_launch_w4_lo(const WideArgs &A, int passes, int mode, dim3 grid, hipS
 bool wgrow_launch_w4_hi(const WideArgs &A, int passes, int mode, dim3 grid, hipStream_t stream);
 bool wgrow_launch_w8_lo(const WideArgs &A, int passes, int mode, dim3 grid, hipStream_t stream);
 bool wgrow_launch_w8_hi(const WideArgs &A, int passes, int mode, dim3 grid, hipStream_t stream);
-bool wgrow_launch_w16(const WideArgs &A, int passes, int mode, dim3 grid, hipStream_t stream);
 
 #define IPTQ_WGROW_CASE(W, S)                                                                     \
     case S: wgrow_launch_ws<W, S>(A, mode, grid, stream); return true;

@@ -6,20 +6,19 @@
 namespace iptq {
 
 // Wavefronts per workgroup and pass count for a row length (exactly the passes a row needs at its
-// worst alignment: the kernels rely on it); false beyond 40957 scores.  Up to 13 passes keep a
+// worst alignment: the kernels rely on it); false beyond 26618 scores.  Up to 13 passes keep a
 // lane within 128 registers, so two workgroups share a compute unit and one loads while the
-// other computes (66-78 % of the HBM roofline); the 14 to 20 passes that 8 wavefronts would
-// need beyond 26618 scores leave one workgroup per compute unit, and so do 16 wavefronts
-// (both 46-50 %; 16 wavefronts compile faster).
+// other computes (66-78 % of the HBM roofline).  Beyond, one workgroup fills a compute unit and the
+// kernel that walks over rows is faster (softmax_long.h; 2000 x 32768 67.8 us against 78.5 us with 16
+// wavefronts here, 3000 x 26000 89 us there against 69.5 us here).
 bool wgrow_geometry(int32_t cols, int *waves, int *slots, bool off_grid)
 {
     // off_grid: as for wide_geometry
     const int nb_max = (off_grid || cols % 2 != 0) ? (cols + 3 + 3) / 4 : ((cols % 4 == 0) ? cols / 4 : (cols + 2 + 3) / 4);
     int w = 4;
     if ((nb_max + 255) / 256 > 13) w = 8;
-    if ((nb_max + 511) / 512 > 13) w = 16;
     const int n = (nb_max + 64 * w - 1) / (64 * w);
-    if (n > (w == 16 ? 10 : 13)) return false;
+    if (n > 13) return false;
     *waves = w;
     *slots = n;
     return true;
@@ -54,8 +53,7 @@ hipError_t softmax_wgrow_launch(const SoftmaxCall &c, int32_t cols, int post_mod
     const int mode = c.P.mode16;
     bool launched;
     if (waves == 4) launched = slots <= 9 ? wgrow_launch_w4_lo(A, slots, mode, grid, stream) : wgrow_launch_w4_hi(A, slots, mode, grid, stream);
-    else if (waves == 8) launched = slots <= 10 ? wgrow_launch_w8_lo(A, slots, mode, grid, stream) : wgrow_launch_w8_hi(A, slots, mode, grid, stream);
-    else launched = wgrow_launch_w16(A, slots, mode, grid, stream);
+    else launched = slots <= 10 ? wgrow_launch_w8_lo(A, slots, mode, grid, stream) : wgrow_launch_w8_hi(A, slots, mode, grid, stream);
     if (!launched) return hipSuccess;
     *done = rows;
     return hipGetLastError();
