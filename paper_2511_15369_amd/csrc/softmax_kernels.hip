@@ -234,10 +234,12 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
             it.share_q = 0; it.share_magic = 0; it.share_sh = 0;
             int64_t n_wgs = (n_slabs + kRowsWpb - 1) / kRowsWpb;
             if (has_bias) {
-                // rows after which the tables repeat: the bias period, or with a mask the least
-                // common multiple of both periods
+                // rows after which the tables repeat: the bias period, or with an int32 mask the least
+                // common multiple of both periods.  (A packed mask is too small to be worth sharing:
+                // with it in the period 147,456 rows of 12 x 12-token windows take 69.2 us against
+                // 66.8 us, 7 x 7 tokens the same.)
                 int64_t period = c.P.bias_period_rows;
-                if (has_mask != 0) {
+                if (has_mask == 1) {
                     int64_t a = period, b = c.P.mask_period_rows;
                     while (b != 0) { const int64_t t = a % b; a = b; b = t; }
                     period = period / a * c.P.mask_period_rows;
