@@ -71,6 +71,19 @@ IPTQ_DEV int32_t pre_requant_narrow(int32_t x, int32_t pre_mul, int64_t pre_rnd,
     return (int32_t)(t >> 32) >> pre_sh2;
 }
 
+// Requantization folded into Eq. 6 (SoftmaxDev::pre_rowconst), from a row's raw maximum mr: whether
+// the clamp at pre_dmax cannot tell its masked scores from live ones, and the row's constant.
+IPTQ_DEV bool pre_fold_low_row(int32_t mr, const SoftmaxDev &P)
+{
+    return ((uint32_t)mr ^ 0x80000000u) < P.pre_dmax;                      // mr - INT32_MIN as unsigned
+}
+IPTQ_DEV uint32_t pre_fold_row_constant(int32_t mr, const SoftmaxDev &P)
+{
+    const int64_t t = (int64_t)mr * (int64_t)P.pre_m + ((int64_t)1 << (P.pre_s - 1));
+    const uint32_t smask = (1u << P.pre_s) - 1u;                           // pre_s <= 31 here
+    return smask - ((uint32_t)t & smask);
+}
+
 // One exponential in 32-bit lanes (Eq. 7-10 / 13-14).  x is the (biased) score, `lower`
 // is max(row) - D saturated, mx the row maximum.  Elements at or below `lower` get the
 // same all-zero result as their true value, which keeps every intermediate in 32 bits.
@@ -714,11 +727,8 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxBatch &B)
 #pragma unroll
             for (int e = 0; e < 4; ++e) mr = max(mr, x[s][e]);
         mr = group_max_i32<K>(mr);
-        const bool low = ((uint32_t)mr ^ 0x80000000u) < P.pre_dmax;        // mr - INT32_MIN as unsigned
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(low) == 0, 1)) {
-            const int64_t t = (int64_t)mr * (int64_t)P.pre_m + ((int64_t)1 << (P.pre_s - 1));
-            const uint32_t smask = (1u << P.pre_s) - 1u;                   // pre_s <= 31 here
-            const uint32_t c_row = smask - ((uint32_t)t & smask);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(pre_fold_low_row(mr, P)) == 0, 1)) {
+            const uint32_t c_row = pre_fold_row_constant(mr, P);
             if (P.variant == 0)
                 softmax_slab_math<K, SLOTS, MODE, 0, POSTMODE, LaneGroupSum<K>, true>(x, w, mr, 0, false, lut, P, LaneGroupSum<K>(), c_row);
             else

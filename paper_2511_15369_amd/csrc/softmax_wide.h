@@ -37,7 +37,11 @@ struct WideArgs {
     SoftmaxDev P;
 };
 
-template <int SLOTS, int MODE, int VARIANT>
+// PRE: the requantization in front folded into Eq. 6, as in the slab kernel (60,000 rows of 1025
+// scores 52.6 us against 53.9 us).  Up to eight passes: with more the folded form needs so many
+// registers that it is the slower one (12,000 rows of 3000 scores 33.2 against 32.3 us).
+constexpr int kWideFoldMaxSlots = 8;
+template <int SLOTS, int MODE, int VARIANT, bool PRE>
 __global__ void __launch_bounds__(256)
 softmax_wide_kernel(WideArgs A)
 {
@@ -112,6 +116,27 @@ softmax_wide_kernel(WideArgs A)
         }
     }
 
+    uint32_t w[SLOTS];                                // four probabilities per block, one per byte
+    if constexpr (PRE) {
+        int32_t mr = kI32Min;                         // the raw row maximum (the requantization is monotone)
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) mr = max(mr, x[s][e]);
+        mr = group_max_i32<64>(mr);
+        if (__builtin_expect(pre_fold_low_row(mr, P), 0)) {
+            // The clamp of the differences cannot tell masked scores from live ones: they take the
+            // (wrapping) value whose difference is the clamp, where the exponential is 0.  Nothing
+            // else of the folded form depends on where the row lies.
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    x[s][e] = x[s][e] == kI32Min ? (int32_t)((uint32_t)mr - P.pre_dmax) : x[s][e];
+        }
+        softmax_slab_math<64, SLOTS, MODE, VARIANT, PM_NONE, LaneGroupSum<64>, true>(
+            x, w, mr, 0, false, lut, P, LaneGroupSum<64>(), pre_fold_row_constant(mr, P));
+    } else {
     // ---- fused requantization of the scores (after the bias, before the maximum)
     if (P.pre_mode == 1) {
         const int32_t pre_mul = P.pre_mul, pre_sh2 = P.pre_sh2;
@@ -145,8 +170,8 @@ softmax_wide_kernel(WideArgs A)
     const int32_t D = P.d_clamp;
     const bool low_row = mx < kI32Min + D;            // wavefront-uniform here; see softmax_rows_kernel
     const int32_t lower = low_row ? kI32Min : mx - D;
-    uint32_t w[SLOTS];                                // four probabilities per block, one per byte
     softmax_slab_math<64, SLOTS, MODE, VARIANT, PM_NONE>(x, w, mx, lower, low_row, lut, P);
+    }
 
     // ---- post step on the packed bytes (a probability is at most 128)
     if (post_mode == PM_CLAMP127) {
@@ -184,11 +209,18 @@ softmax_wide_kernel(WideArgs A)
 template <int SLOTS>
 static void wide_launch_s(const WideArgs &A, int mode, dim3 grid, hipStream_t stream)
 {
+    if constexpr (SLOTS <= kWideFoldMaxSlots) {
+        if (A.P.pre_rowconst != 0) {                  // packed arithmetic and a first-degree exponential
+            if (A.P.variant == 0) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, 2, 0, true>), grid, dim3(256), 0, stream, A);
+            else hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, 2, 1, true>), grid, dim3(256), 0, stream, A);
+            return;
+        }
+    }
 #define IPTQ_WIDE_LAUNCH(MODE)                                                                    \
     do {                                                                                          \
-        if (A.P.variant == 0) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 0>), grid, dim3(256), 0, stream, A);      \
-        else if (A.P.variant == 1) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 1>), grid, dim3(256), 0, stream, A); \
-        else hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 2>), grid, dim3(256), 0, stream, A);                       \
+        if (A.P.variant == 0) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 0, false>), grid, dim3(256), 0, stream, A);      \
+        else if (A.P.variant == 1) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 1, false>), grid, dim3(256), 0, stream, A); \
+        else hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 2, false>), grid, dim3(256), 0, stream, A);                       \
     } while (0)
     if (mode == 0) IPTQ_WIDE_LAUNCH(0);
     else IPTQ_WIDE_LAUNCH(2);
