@@ -36,6 +36,9 @@ struct WorkgroupSum {
     }
 };
 
+// VARIANT -1: by the parameters.  With 8 wavefronts per row a kernel per variant needs fewer
+// registers and is the faster one (1000 rows of 16384 scores 16.3 us against 17.6 us); with 4 it is
+// not (49,164 rows of 4097 scores 162.8 us against 161.1 us with the branch).
 template <int WAVES, int SLOTS, int MODE, int VARIANT>
 __global__ void __launch_bounds__(64 * WAVES)
 softmax_wgrow_kernel(WideArgs A)
@@ -149,7 +152,12 @@ softmax_wgrow_kernel(WideArgs A)
     const int32_t lower = low_row ? kI32Min : mx - D;
     uint32_t w[SLOTS];                                // four probabilities per block, one per byte
     const WorkgroupSum<WAVES> wg_sum{part_sum, wv, lane};
-    softmax_slab_math<64, SLOTS, MODE, VARIANT, PM_NONE, WorkgroupSum<WAVES>>(x, w, mx, lower, low_row, lut, P, wg_sum);
+    if (VARIANT == 0 || (VARIANT < 0 && P.variant == 0))
+        softmax_slab_math<64, SLOTS, MODE, 0, PM_NONE, WorkgroupSum<WAVES>>(x, w, mx, lower, low_row, lut, P, wg_sum);
+    else if (VARIANT == 1 || (VARIANT < 0 && P.variant == 1))
+        softmax_slab_math<64, SLOTS, MODE, 1, PM_NONE, WorkgroupSum<WAVES>>(x, w, mx, lower, low_row, lut, P, wg_sum);
+    else
+        softmax_slab_math<64, SLOTS, MODE, 2, PM_NONE, WorkgroupSum<WAVES>>(x, w, mx, lower, low_row, lut, P, wg_sum);
 
     // ---- post step on the packed bytes (a probability is at most 128)
     if (post_mode == PM_CLAMP127) {
@@ -189,7 +197,8 @@ static void wgrow_launch_ws(const WideArgs &A, int mode, dim3 grid, hipStream_t 
 {
 #define IPTQ_WGROW_LAUNCH(MODE)                                                                   \
     do {                                                                                          \
-        if (A.P.variant == 0) hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 0>), grid, dim3(64 * WAVES), 0, stream, A);      \
+        if constexpr (WAVES == 4) hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, -1>), grid, dim3(64 * WAVES), 0, stream, A); \
+        else if (A.P.variant == 0) hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 0>), grid, dim3(64 * WAVES), 0, stream, A); \
         else if (A.P.variant == 1) hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 1>), grid, dim3(64 * WAVES), 0, stream, A); \
         else hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 2>), grid, dim3(64 * WAVES), 0, stream, A);                       \
     } while (0)
