@@ -15,6 +15,7 @@ from typing import Optional, Sequence
 HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(HERE, "libiptq.so")
 _lib = None
+torch = None                      # bound by load(): a call does not pay for an import statement
 
 ALGO_AUTO = 0
 ALGO_GENERIC = 1
@@ -78,7 +79,7 @@ def lib_path() -> str:
 
 def load():
     """Load the shared library (built by ``python -m paper_2511_15369_amd.build``)."""
-    global _lib
+    global _lib, torch
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -87,7 +88,8 @@ def load():
     # torch first: it brings its own copy of the HIP runtime, and the library must bind to that
     # one (the device buffers and streams come from it).  Loaded before torch, libiptq.so would
     # pull in the system's copy and every launch would go to a second runtime that has no device.
-    import torch  # noqa: F401
+    import torch as _t
+    torch = _t
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i64, i32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32
     lib.iptq_version.restype = ctypes.c_int
@@ -151,25 +153,26 @@ def _check(rc: int, what: str):
 _raw_stream = None
 
 
-def _stream():
+def _stream() -> int:
     """The current torch stream of the current device as a raw hipStream_t."""
     global _raw_stream
-    import torch
     if _raw_stream is None:
+        torch.cuda.current_device()           # initialises torch's GPU state, or raises
+        # from then on the two C functions beneath torch.cuda.current_stream()
         fast = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
         if fast is not None:
-            _raw_stream = lambda: fast(torch.cuda.current_device())
+            _raw_stream = lambda: fast(device())
         else:
             _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
-    return ctypes.c_void_p(_raw_stream())
+    return _raw_stream()
 
 
 def _dptr(t) -> Optional[int]:
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _need(t, dtype, what):
-    import torch
     if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype != dtype or not t.is_contiguous():
         raise TypeError("%s must be a contiguous %s tensor on the GPU" % (what, dtype))
 
@@ -239,30 +242,30 @@ def softmax_kernel_family(cols: int) -> str:
 
 
 def requant(d_in, d_out, n: int, out_is_signed: int, p: Dyadic):
-    import torch
+    lib = load()
     _need(d_in, torch.int32, "d_in")
     _need(d_out, torch.int8 if out_is_signed else torch.uint8, "d_out")
     assert d_in.numel() >= n and d_out.numel() >= n
-    _check(load().iptq_requant(_dptr(d_in), _dptr(d_out), n, out_is_signed, ctypes.byref(p),
-                               _stream()), "iptq_requant")
+    _check(lib.iptq_requant(_dptr(d_in), _dptr(d_out), n, out_is_signed, ctypes.byref(p),
+                            _stream()), "iptq_requant")
 
 
 def softmax_i32(d_scores, d_bias, bias_period_rows: int, d_out, rows: int, cols: int,
                 p: SoftmaxParams):
-    import torch
+    lib = load()
     _need(d_scores, torch.int32, "d_scores")
     _need(d_out, torch.int8 if p.out_is_signed else torch.uint8, "d_out")
     assert d_scores.numel() >= rows * cols and d_out.numel() >= rows * cols
     if d_bias is not None:
         _need(d_bias, torch.int32, "d_bias")
         assert d_bias.numel() >= bias_period_rows * cols
-    _check(load().iptq_softmax_i32(_dptr(d_scores), _dptr(d_bias), bias_period_rows, _dptr(d_out),
-                                   rows, cols, ctypes.byref(p), _stream()), "iptq_softmax_i32")
+    _check(lib.iptq_softmax_i32(_dptr(d_scores), _dptr(d_bias), bias_period_rows, _dptr(d_out),
+                                rows, cols, ctypes.byref(p), _stream()), "iptq_softmax_i32")
 
 
 def softmax_i32_windowed(d_scores, d_bias, bias_period_rows: int, d_mask, n_windows: int, heads: int,
                          d_out, rows: int, cols: int, p: SoftmaxParams):
-    import torch
+    lib = load()
     _need(d_scores, torch.int32, "d_scores")
     _need(d_out, torch.int8 if p.out_is_signed else torch.uint8, "d_out")
     assert d_scores.numel() >= rows * cols and d_out.numel() >= rows * cols
@@ -272,15 +275,15 @@ def softmax_i32_windowed(d_scores, d_bias, bias_period_rows: int, d_mask, n_wind
     if d_mask is not None:
         _need(d_mask, torch.int32, "d_mask")
         assert d_mask.numel() >= n_windows * cols * cols
-    _check(load().iptq_softmax_i32_windowed(_dptr(d_scores), _dptr(d_bias), bias_period_rows,
-                                            _dptr(d_mask), n_windows, heads, _dptr(d_out), rows,
-                                            cols, ctypes.byref(p), _stream()),
+    _check(lib.iptq_softmax_i32_windowed(_dptr(d_scores), _dptr(d_bias), bias_period_rows,
+                                         _dptr(d_mask), n_windows, heads, _dptr(d_out), rows,
+                                         cols, ctypes.byref(p), _stream()),
            "iptq_softmax_i32_windowed")
 
 
 def softmax_i32_windowed_bits(d_scores, d_bias, bias_period_rows: int, d_mask_bits, n_windows: int,
                               heads: int, d_out, rows: int, cols: int, p: SoftmaxParams):
-    import torch
+    lib = load()
     _need(d_scores, torch.int32, "d_scores")
     _need(d_out, torch.int8 if p.out_is_signed else torch.uint8, "d_out")
     assert d_scores.numel() >= rows * cols and d_out.numel() >= rows * cols
@@ -290,43 +293,43 @@ def softmax_i32_windowed_bits(d_scores, d_bias, bias_period_rows: int, d_mask_bi
     if d_mask_bits is not None:
         _need(d_mask_bits, torch.int64, "d_mask_bits")        # torch has no uint64 arithmetic: the words travel as int64
         assert d_mask_bits.numel() >= n_windows * cols * ((cols + 63) // 64)
-    _check(load().iptq_softmax_i32_windowed_bits(_dptr(d_scores), _dptr(d_bias), bias_period_rows,
-                                                 _dptr(d_mask_bits), n_windows, heads, _dptr(d_out),
-                                                 rows, cols, ctypes.byref(p), _stream()),
+    _check(lib.iptq_softmax_i32_windowed_bits(_dptr(d_scores), _dptr(d_bias), bias_period_rows,
+                                              _dptr(d_mask_bits), n_windows, heads, _dptr(d_out),
+                                              rows, cols, ctypes.byref(p), _stream()),
            "iptq_softmax_i32_windowed_bits")
 
 
 def pack_window_mask(d_mask, n_windows: int, cols: int, d_mask_bits):
-    import torch
+    lib = load()
     _need(d_mask, torch.int32, "d_mask")
     _need(d_mask_bits, torch.int64, "d_mask_bits")
     assert d_mask.numel() >= n_windows * cols * cols
     assert d_mask_bits.numel() >= n_windows * cols * ((cols + 63) // 64)
-    _check(load().iptq_pack_window_mask(_dptr(d_mask), n_windows, cols, _dptr(d_mask_bits), _stream()),
+    _check(lib.iptq_pack_window_mask(_dptr(d_mask), n_windows, cols, _dptr(d_mask_bits), _stream()),
            "iptq_pack_window_mask")
 
 
 def gelu_i8(d_in, d_out, n: int, p: GeluParams):
-    import torch
+    lib = load()
     _need(d_in, torch.int8, "d_in")
     _need(d_out, torch.int8, "d_out")
     assert d_in.numel() >= n and d_out.numel() >= n
-    _check(load().iptq_gelu_i8(_dptr(d_in), _dptr(d_out), n, ctypes.byref(p), _stream()),
+    _check(lib.iptq_gelu_i8(_dptr(d_in), _dptr(d_out), n, ctypes.byref(p), _stream()),
            "iptq_gelu_i8")
 
 
 def gelu_i32(d_in, d_out, n: int, p: GeluParams):
-    import torch
+    lib = load()
     _need(d_in, torch.int32, "d_in")
     _need(d_out, torch.int8, "d_out")
     assert d_in.numel() >= n and d_out.numel() >= n
-    _check(load().iptq_gelu_i32(_dptr(d_in), _dptr(d_out), n, ctypes.byref(p), _stream()),
+    _check(lib.iptq_gelu_i32(_dptr(d_in), _dptr(d_out), n, ctypes.byref(p), _stream()),
            "iptq_gelu_i32")
 
 
 def softmax_i32_layers(d_scores, in_stride: int, d_out, out_stride: int, rows: int, cols: int,
                        n_layers: int, params: Sequence[SoftmaxParams]):
-    import torch
+    lib = load()
     _need(d_scores, torch.int32, "d_scores")
     assert len(params) == n_layers
     signed = params[0].out_is_signed if n_layers else 0
@@ -335,14 +338,14 @@ def softmax_i32_layers(d_scores, in_stride: int, d_out, out_stride: int, rows: i
         assert d_scores.numel() >= (n_layers - 1) * in_stride + rows * cols
         assert d_out.numel() >= (n_layers - 1) * out_stride + rows * cols
     arr = (SoftmaxParams * max(n_layers, 1))(*params)
-    _check(load().iptq_softmax_i32_layers(_dptr(d_scores), in_stride, _dptr(d_out), out_stride,
-                                          rows, cols, n_layers, arr, _stream()),
+    _check(lib.iptq_softmax_i32_layers(_dptr(d_scores), in_stride, _dptr(d_out), out_stride,
+                                       rows, cols, n_layers, arr, _stream()),
            "iptq_softmax_i32_layers")
 
 
 def gelu_i8_layers(d_in, in_stride: int, d_out, out_stride: int, n: int, n_layers: int,
                    params: Sequence[GeluParams]):
-    import torch
+    lib = load()
     _need(d_in, torch.int8, "d_in")
     _need(d_out, torch.int8, "d_out")
     assert len(params) == n_layers
@@ -350,15 +353,15 @@ def gelu_i8_layers(d_in, in_stride: int, d_out, out_stride: int, n: int, n_layer
         assert d_in.numel() >= (n_layers - 1) * in_stride + n
         assert d_out.numel() >= (n_layers - 1) * out_stride + n
     arr = (GeluParams * max(n_layers, 1))(*params)
-    _check(load().iptq_gelu_i8_layers(_dptr(d_in), in_stride, _dptr(d_out), out_stride, n,
-                                      n_layers, arr, _stream()), "iptq_gelu_i8_layers")
+    _check(lib.iptq_gelu_i8_layers(_dptr(d_in), in_stride, _dptr(d_out), out_stride, n,
+                                   n_layers, arr, _stream()), "iptq_gelu_i8_layers")
 
 
 def softmax_problem(d_scores, d_bias, bias_period_rows: int, d_out, rows: int, cols: int,
                     p: SoftmaxParams, d_mask=None, n_windows: int = 0, heads: int = 0,
                     d_mask_bits=None) -> SoftmaxProblem:
     """One entry of a softmax batch (same checks as softmax_i32)."""
-    import torch
+    load()
     _need(d_scores, torch.int32, "d_scores")
     _need(d_out, torch.int8 if p.out_is_signed else torch.uint8, "d_out")
     assert d_scores.numel() >= rows * cols and d_out.numel() >= rows * cols
@@ -378,7 +381,7 @@ def softmax_problem(d_scores, d_bias, bias_period_rows: int, d_out, rows: int, c
 
 
 def gelu_problem(d_in, d_out, n: int, p: GeluParams) -> GeluProblem:
-    import torch
+    load()
     _need(d_in, torch.int8, "d_in")
     _need(d_out, torch.int8, "d_out")
     assert d_in.numel() >= n and d_out.numel() >= n
@@ -387,13 +390,15 @@ def gelu_problem(d_in, d_out, n: int, p: GeluParams) -> GeluProblem:
 
 def softmax_i32_batch(problems, n_problems: int, cols: int):
     """problems: a ctypes array (SoftmaxProblem * n) or a sequence of SoftmaxProblem."""
+    lib = load()
     if not isinstance(problems, ctypes.Array):
         problems = (SoftmaxProblem * max(n_problems, 1))(*problems)
-    _check(load().iptq_softmax_i32_batch(problems, n_problems, cols, _stream()),
+    _check(lib.iptq_softmax_i32_batch(problems, n_problems, cols, _stream()),
            "iptq_softmax_i32_batch")
 
 
 def gelu_i8_batch(problems, n_problems: int):
+    lib = load()
     if not isinstance(problems, ctypes.Array):
         problems = (GeluProblem * max(n_problems, 1))(*problems)
-    _check(load().iptq_gelu_i8_batch(problems, n_problems, _stream()), "iptq_gelu_i8_batch")
+    _check(lib.iptq_gelu_i8_batch(problems, n_problems, _stream()), "iptq_gelu_i8_batch")
