@@ -46,8 +46,6 @@ def test_masks_match_the_oracle(t, heads, n_w):
             want = ref.softmax_i32_windowed(scores, p, b, period, mask, heads)
             assert np.array_equal(gpu_softmax_windowed_bits(scores, p, b, period, bits, heads), want)
             want = ref.softmax_i32_windowed(scores, p, b, period, finite, heads)
-            if b is not None and t in (49, 144):
-                continue                                     # compiled row lengths with a bias: tested elsewhere
             assert np.array_equal(gpu_softmax_windowed(scores, p, b, period, finite, heads), want)
 
 
@@ -82,3 +80,27 @@ def test_views_off_the_grid_and_requantization(t):
             got = d_out.cpu().numpy()
             assert np.array_equal(got[off:off + n], want), (kind, off)
             assert (got[:off] == 0x5A).all() and (got[off + n:] == 0x5A).all(), (kind, off)
+
+
+@pytest.mark.parametrize("t", [49, 64, 144])
+def test_minus_infinity_at_every_stage(t):
+    """A score, a bias entry, their (saturated) sum or a mask entry that is INT32_MIN masks the key,
+    whatever is added to it afterwards; one above INT32_MIN does not."""
+    heads, n_w, images = 2, 3, 3
+    rng = np.random.default_rng(t)
+    rows = images * n_w * heads * t - 3
+    scores = rng.choice(np.array([I32_MIN, I32_MIN + 1, I32_MIN + 10, I32_MIN + 100], np.int32), size=(rows, t))
+    scores[::3] = rng.choice(np.array([I32_MIN, I32_MIN + 1, -50, 0, 50], np.int32), size=scores[::3].shape)
+    bias = rng.choice(np.array([I32_MIN, -100, -10, -1, 0, 1, 100], np.int32), size=(heads * t, t))
+    # windows 0 and 1: what a masked key would be lifted to lies as high as the live keys of its row
+    mask = rng.choice(np.array([I32_MIN, 0, 1, 99], np.int32), size=(n_w, t, t))
+    mask[1] = rng.choice(np.array([I32_MIN, 2 ** 31 - 1], np.int32), size=(t, t))
+    first = scores[:heads * t].astype(np.int64) + bias
+    lifted = (first <= I32_MIN) & (scores[:heads * t] != I32_MIN) & (bias != I32_MIN) & (np.tile(mask[0], (heads, 1)) > 0)
+    assert lifted.sum() > t                                  # the sum alone masks it, the mask entry is positive
+    for variant, signed, s_delta in ((1, 0, 2.0 ** -6.5), (0, 1, 2.0 ** -14), (2, 0, 2.0 ** -5)):
+        p = prepare.softmax_prepare(s_delta, t, variant, signed)
+        want = ref.softmax_i32_windowed(scores, p, bias, heads * t, mask, heads)
+        for algo in (0, 1, 4):
+            got = gpu_softmax_windowed(scores, p, bias, heads * t, mask, heads, algo=algo)
+            assert np.array_equal(got, want), (variant, signed, algo)
