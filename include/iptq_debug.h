@@ -31,8 +31,13 @@ int iptq_debug_softmax_plan(const iptq_softmax_params_t *p, int64_t rows, int32_
 /* Layouts the run-time-row-length kernels would use for a row length.  out12 (12 values):
  * {slab kernel serves it, its lanes per row, its blocks per lane, the same again,
  *  wavefront-per-row kernel serves it, its passes, its slots, row length has a compiled kernel,
- *  0, workgroup-per-row kernel serves it, its wavefronts, its slots}. */
+ *  passes of the workgroup that walks over rows (0: it does not serve it),
+ *  workgroup-per-row kernel serves it, its wavefronts, its slots}. */
 int iptq_debug_softmax_layout(int32_t cols, int32_t *out12);
+
+/* Which of the two kernels for rows that fill a compute unit takes a call: 1 a workgroup of 16
+ * wavefronts per row, 0 the workgroups that walk over rows. */
+int iptq_debug_wgrow16_is_faster(int64_t rows, int32_t has_bias, int32_t has_pre, int32_t variant);
 
 /* Exponentials (Eq. 7-14) of n stabilised scores (row maximum 0; n even) through both arithmetic
  * paths of the softmax kernels: d_out32 from the 32-bit lanes, d_out16 from the packed 16-bit

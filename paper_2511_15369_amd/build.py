@@ -17,7 +17,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libiptq.so")
 TIMELINE_LIB = os.path.join(HERE, "libiptq_timeline.so")
 # the slowest translation units first (the pool takes them in this order)
-SOURCES = ["softmax_long_p13_16.hip", "softmax_long_p9_12.hip", "softmax_long_p7_8.hip", "softmax_wgrow_w4_hi.hip", "softmax_wgrow_w8_hi.hip", "softmax_wgrow_w4_lo.hip", "softmax_wgrow_w8_lo.hip",
+SOURCES = ["softmax_long_p13_16.hip", "softmax_long_p9_12.hip", "softmax_long_p7_8.hip", "softmax_wgrow_w4_hi.hip", "softmax_wgrow_w8_hi.hip", "softmax_wgrow_w16.hip", "softmax_wgrow_w4_lo.hip", "softmax_wgrow_w8_lo.hip",
            "softmax_wide_p14_16.hip", "softmax_wide_p11_13.hip", "softmax_wide_p7_10.hip", "softmax_wide_p1_6.hip", "softmax_rowsdyn_k16_long.hip",
            "softmax_rows_577.hip", "softmax_rows_257.hip", "softmax_rows_197.hip", "softmax_rows_198.hip",
            "softmax_rows_144.hip", "softmax_rows_49.hip", "softmax_rows_197_k8.hip", "softmax_rows_198_k8.hip",

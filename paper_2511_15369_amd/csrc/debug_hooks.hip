@@ -33,8 +33,8 @@ extern "C" int iptq_debug_softmax_plan(const iptq_softmax_params_t *p, int64_t r
 
 // Layout the run-time-row-length kernels would use for a row length:
 // out12 = {slab ok, its lanes per row, its blocks per lane, the same again, wide ok, wide passes, wide slots,
-//          1 if the row length has a compiled kernel, 0, workgroup-per-row ok, its wavefronts,
-//          its slots}.
+//          1 if the row length has a compiled kernel, passes of the walking workgroup (0: none),
+//          workgroup-per-row ok, its wavefronts, its slots}.
 extern "C" int iptq_debug_softmax_layout(int32_t cols, int32_t *out12)
 {
     if (!out12) return IPTQ_ERR_NULL;
@@ -47,11 +47,17 @@ extern "C" int iptq_debug_softmax_layout(int32_t cols, int32_t *out12)
     out12[5] = a; out12[6] = b;
     a = b = 0;
     out12[7] = softmax_rows_compiled(cols) ? 1 : 0;
-    out12[8] = 0;
+    a = b = 0;
+    out12[8] = long_geometry(cols, &a) ? a : 0;
     a = b = 0;
     out12[9] = wgrow_geometry(cols, &a, &b) ? 1 : 0;
     out12[10] = a; out12[11] = b;
     return IPTQ_OK;
+}
+
+extern "C" int iptq_debug_wgrow16_is_faster(int64_t rows, int32_t has_bias, int32_t has_pre, int32_t variant)
+{
+    return wgrow16_is_faster(rows, has_bias != 0, has_pre != 0, variant) ? 1 : 0;
 }
 
 // Exponentials of an array of stabilised scores (row maximum 0) through both arithmetic

@@ -38,11 +38,12 @@ hipError_t softmax_rowsdyn_launch(const SoftmaxCall &c, int32_t cols, int post_m
 // alignment, 4096 if a multiple of 4): every row of one call, or none.
 hipError_t softmax_wide_launch(const SoftmaxCall &c, int32_t cols, int post_mode, int64_t *done,
                                hipStream_t stream);
-// One workgroup per row, row in the workgroup's registers (rows of up to 26618 scores).
+// One workgroup per row, row in the workgroup's registers (rows of up to 26621 scores, 26624 if a
+// multiple of 4 on the 16-byte grid; up to 40957 and 40960 where wgrow16_is_faster says so).
 hipError_t softmax_wgrow_launch(const SoftmaxCall &c, int32_t cols, int post_mode, int64_t *done,
                                 hipStream_t stream);
 // One workgroup of 16 wavefronts per row that walks over the rows and fetches the next one while it
-// computes (beyond that, up to 65536 scores).
+// computes (beyond that, up to 65533 scores, 65536 on the 16-byte grid).
 hipError_t softmax_long_launch(const SoftmaxCall &c, int32_t cols, int post_mode, int64_t *done,
                                hipStream_t stream);
 // Host-side layout choices of the run-time-row-length kernels (false: the kernel does not
@@ -52,6 +53,7 @@ bool rowsdyn_geometry(int32_t cols, int *lanes, int *slots);
 bool wide_geometry(int32_t cols, int *passes, int *slots, bool off_grid = false);
 bool wgrow_geometry(int32_t cols, int *waves, int *slots, bool off_grid = false);
 bool long_geometry(int32_t cols, int *slots, bool off_grid = false);
+bool wgrow16_is_faster(int64_t rows, bool has_bias, bool has_pre, int variant);
 hipError_t gelu_i8_dispatch(const GeluCall *calls, int n_calls, hipStream_t stream);
 hipError_t gelu_i32_dispatch(const int32_t *in, int8_t *out, int64_t n, const GeluDev &P,
                              bool force_direct, hipStream_t stream);

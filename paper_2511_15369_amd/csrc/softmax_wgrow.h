@@ -36,9 +36,16 @@ struct WorkgroupSum {
     }
 };
 
-// VARIANT -1: by the parameters.  With 8 wavefronts per row a kernel per variant needs fewer
-// registers and is the faster one (1000 rows of 16384 scores 16.3 us against 17.6 us); with 4 it is
-// not (49,164 rows of 4097 scores 162.8 us against 161.1 us with the branch).
+// VARIANT: 0, 1, 2, or one of these.
+// With 8 wavefronts per row a kernel per variant needs fewer registers.  At 7 and 8 passes that is
+// a third workgroup per compute unit (69 and 77 registers against 81 and 92): 600 x 14000 scores 10.8
+// us against 11.8, 1000 x 16000 16.1 against 17.5.  At 9 to 13 passes the occupancy is the same and so
+// is the vector code; sizes of one to two workgroups per compute unit differ either way (300 x 26000
+// 13.4 us against 12.6, 400 x 24000 12.0 against 12.7, 1000 x 26000 25.8 against 26.4, 1000 x 22000 23.4
+// against 23.1).  With 4 wavefronts the branch is the faster one (49,164 rows of 4097 scores 161.1 us
+// against 162.8); 16 wavefronts serve the first-degree variants only (wgrow16_is_faster).
+constexpr int kAnyVariant = -1;                       // by the parameters
+constexpr int kFirstDegree = -2;                      // 0 or 1, by the parameters
 template <int WAVES, int SLOTS, int MODE, int VARIANT>
 __global__ void __launch_bounds__(64 * WAVES)
 softmax_wgrow_kernel(WideArgs A)
@@ -154,7 +161,7 @@ softmax_wgrow_kernel(WideArgs A)
     const WorkgroupSum<WAVES> wg_sum{part_sum, wv, lane};
     if (VARIANT == 0 || (VARIANT < 0 && P.variant == 0))
         softmax_slab_math<64, SLOTS, MODE, 0, PM_NONE, WorkgroupSum<WAVES>>(x, w, mx, lower, low_row, lut, P, wg_sum);
-    else if (VARIANT == 1 || (VARIANT < 0 && P.variant == 1))
+    else if (VARIANT == 1 || VARIANT == kFirstDegree || (VARIANT == kAnyVariant && P.variant == 1))
         softmax_slab_math<64, SLOTS, MODE, 1, PM_NONE, WorkgroupSum<WAVES>>(x, w, mx, lower, low_row, lut, P, wg_sum);
     else
         softmax_slab_math<64, SLOTS, MODE, 2, PM_NONE, WorkgroupSum<WAVES>>(x, w, mx, lower, low_row, lut, P, wg_sum);
@@ -197,7 +204,8 @@ static void wgrow_launch_ws(const WideArgs &A, int mode, dim3 grid, hipStream_t 
 {
 #define IPTQ_WGROW_LAUNCH(MODE)                                                                   \
     do {                                                                                          \
-        if constexpr (WAVES == 4) hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, -1>), grid, dim3(64 * WAVES), 0, stream, A); \
+        if constexpr (WAVES == 4) hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, kAnyVariant>), grid, dim3(64 * WAVES), 0, stream, A); \
+        else if constexpr (WAVES == 16) hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, kFirstDegree>), grid, dim3(64 * WAVES), 0, stream, A); \
         else if (A.P.variant == 0) hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 0>), grid, dim3(64 * WAVES), 0, stream, A); \
         else if (A.P.variant == 1) hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 1>), grid, dim3(64 * WAVES), 0, stream, A); \
         else hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 2>), grid, dim3(64 * WAVES), 0, stream, A);                       \
@@ -213,6 +221,7 @@ bool wgrow_launch_w4_lo(const WideArgs &A, int passes, int mode, dim3 grid, hipS
 bool wgrow_launch_w4_hi(const WideArgs &A, int passes, int mode, dim3 grid, hipStream_t stream);
 bool wgrow_launch_w8_lo(const WideArgs &A, int passes, int mode, dim3 grid, hipStream_t stream);
 bool wgrow_launch_w8_hi(const WideArgs &A, int passes, int mode, dim3 grid, hipStream_t stream);
+bool wgrow_launch_w16(const WideArgs &A, int passes, int mode, dim3 grid, hipStream_t stream);
 
 #define IPTQ_WGROW_CASE(W, S)                                                                     \
     case S: wgrow_launch_ws<W, S>(A, mode, grid, stream); return true;

@@ -306,3 +306,32 @@ def test_run_time_row_length_layouts_fit_what_the_kernels_assume():
             assert nb_max > 512 * 20
         served_by_registers += bool(dyn_ok or wide_ok or wg_ok)
     assert served_by_registers >= 6199
+
+
+def test_layout_of_the_walking_workgroup_and_who_takes_which_rows():
+    """The kernel for rows that fill a compute unit relies on its exact pass count; up to 40957 scores
+    a workgroup per row takes the calls with nothing to fetch ahead and those beside a table."""
+    import ctypes
+    lib = ip.load()
+    fn = lib.iptq_debug_softmax_layout
+    fn.argtypes = [ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
+    fn.restype = ctypes.c_int
+    out = (ctypes.c_int32 * 12)()
+    for cols in list(range(26600, 65537, 13)) + list(range(26600, 26640)) + list(range(40940, 40970)) + list(range(65500, 65537)):
+        assert fn(cols, out) == 0
+        passes, wg_ok, waves = out[8], out[9], out[10]
+        nb_max = cols // 4 if cols % 4 == 0 else ((cols + 2 + 3) // 4 if cols % 2 == 0 else (cols + 3 + 3) // 4)
+        nb_min = (cols + 3) // 4
+        if passes:
+            assert 7 <= passes <= 16 and passes == -(-nb_max // 1024)
+            assert nb_min - 2 >= 1024 * (passes - 2)         # passes 0 .. passes-3 are full even without a cut last block
+        assert passes or (wg_ok and waves == 8) or cols == 65535
+        assert bool(wg_ok) == (cols <= 40957 or (cols in (40958, 40960)))
+        assert (waves == 16) == bool(wg_ok and nb_max > 13 * 512)
+    rule = lib.iptq_debug_wgrow16_is_faster
+    rule.argtypes = [ctypes.c_int64] + [ctypes.c_int32] * 3
+    rule.restype = ctypes.c_int
+    assert rule(10, 0, 0, 1) and rule(256, 0, 0, 0) and not rule(257, 0, 0, 1)
+    assert rule(600, 0, 1, 1) and not rule(1500, 0, 1, 1)
+    assert rule(2500, 1, 0, 1) and rule(2500, 1, 1, 0)
+    assert not rule(10, 0, 0, 2) and not rule(2500, 1, 0, 2)     # not instantiated for the second degree
