@@ -201,9 +201,10 @@ int iptq_softmax_i32(const int32_t *d_scores, const int32_t *d_bias, int64_t bia
  * [heads * cols, cols] with bias_period_rows = heads * cols); either table may be NULL.  Nothing
  * is materialised: both tables are read beside the scores.  n_windows >= 1, heads >= 1,
  * n_windows * heads * cols < 2^31 (else IPTQ_ERR_SHAPE).
- * Speed: windows of up to about 635 tokens run in the slab kernels, fastest at 49 or 144 tokens with
- * a bias (the extra table costs about a sixth of the time; the packed form below costs less);
- * longer windows take the slow three-pass kernel.
+ * Speed: windows of up to about 635 tokens run in the slab kernels (short calls in the three-pass
+ * kernel where that is done sooner), fastest at 49 or 144 tokens with a bias (the extra table costs
+ * about a sixth of the time; the packed form below costs less); longer windows take the slow
+ * three-pass kernel.
  */
 int iptq_softmax_i32_windowed(const int32_t *d_scores, const int32_t *d_bias,
                               int64_t bias_period_rows, const int32_t *d_mask, int32_t n_windows,
@@ -219,8 +220,7 @@ int iptq_softmax_i32_windowed(const int32_t *d_scores, const int32_t *d_bias,
  * 8-byte load per row and two instructions per score instead of a third table read beside the
  * scores (Swin-B stage 1 at batch 64: 35 us against 34 us without a mask and 40 us with the int32
  * mask).
- * Speed: windows of up to about 635 tokens run in the slab kernels, fastest at 49 or 144 tokens with
- * a bias; longer ones take the slow three-pass kernel.  Errors as for iptq_softmax_i32_windowed; IPTQ_ERR_ALIGN if
+ * Speed: as for the int32 form.  Errors as for iptq_softmax_i32_windowed; IPTQ_ERR_ALIGN if
  * d_mask_bits is not 8-byte aligned; a batched problem that carries both forms of the mask is
  * refused with IPTQ_ERR_PARAM.
  */

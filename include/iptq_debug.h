@@ -35,6 +35,10 @@ int iptq_debug_softmax_plan(const iptq_softmax_params_t *p, int64_t rows, int32_
  *  workgroup-per-row kernel serves it, its wavefronts, its slots}. */
 int iptq_debug_softmax_layout(int32_t cols, int32_t *out12);
 
+/* Whether a short call with a mask (0 none, 1 int32, 2 packed), a second-degree exponential or a short
+ * table leaves the run-time-row-length slab kernel: 1 it does. */
+int iptq_debug_rowsdyn_loses_short_call(int64_t rows, int32_t cols, int32_t has_bias, int32_t mask_kind);
+
 /* Which of the two kernels for rows that fill a compute unit takes a call: 1 a workgroup of 16
  * wavefronts per row, 0 the workgroups that walk over rows. */
 int iptq_debug_wgrow16_is_faster(int64_t rows, int32_t has_bias, int32_t has_pre, int32_t variant);

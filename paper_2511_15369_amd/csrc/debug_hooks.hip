@@ -55,6 +55,11 @@ extern "C" int iptq_debug_softmax_layout(int32_t cols, int32_t *out12)
     return IPTQ_OK;
 }
 
+extern "C" int iptq_debug_rowsdyn_loses_short_call(int64_t rows, int32_t cols, int32_t has_bias, int32_t mask_kind)
+{
+    return rowsdyn_loses_short_call(rows, cols, has_bias != 0, mask_kind == 1, mask_kind == 2) ? 1 : 0;
+}
+
 extern "C" int iptq_debug_wgrow16_is_faster(int64_t rows, int32_t has_bias, int32_t has_pre, int32_t variant)
 {
     return wgrow16_is_faster(rows, has_bias != 0, has_pre != 0, variant) ? 1 : 0;

@@ -1,8 +1,8 @@
 // Integer softmax for gfx950 (Section 4.4, Eq. 6-15): the any-row-length kernel and the
-// dispatch between it and the fixed-row-length kernels of softmax_rows.h.
+// dispatch between it and the others.
 //   softmax_generic_kernel - run-time row length, one wavefront per row, three passes.
-//                          Serves odd shapes, the tail rows of the fixed-length kernels and
-//                          the fused pre-requantization.
+//                          Serves what no other kernel takes (tables and masks beside long rows
+//                          that do not qualify) and short calls whose kernel would start later.
 #include <hip/hip_runtime.h>
 
 #include "../../include/iptq.h"
@@ -260,8 +260,13 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
         for (int i = 0; i < cnt && err == hipSuccess; ++i) {
             const SoftmaxCall &c = calls[base + i];
             const bool has_pre = !(c.P.pre_m == 1 && c.P.pre_s == 0);
-            // a call no compiled row length served goes to the run-time-row-length kernels
-            if (done[i] == 0 && (c.algo == IPTQ_ALGO_AUTO || c.algo == IPTQ_ALGO_DYNAMIC || c.algo == IPTQ_ALGO_SLAB)) {
+            // a call no compiled row length served goes to the run-time-row-length kernels; the slab
+            // kernel leaves short calls with a mask, a second-degree exponential or a table of fewer
+            // rows than its slab to the others where they are faster
+            const bool may_lose = slab_only(c) || c.P.variant == 2 || (c.bias != nullptr && c.P.bias_period_rows < 64 && cols <= 29);
+            const bool leave = c.algo == IPTQ_ALGO_AUTO && may_lose &&
+                               rowsdyn_loses_short_call(c.rows, cols, c.bias != nullptr, c.mask != nullptr, c.mask_bits != nullptr);
+            if (done[i] == 0 && !leave && (c.algo == IPTQ_ALGO_AUTO || c.algo == IPTQ_ALGO_DYNAMIC || c.algo == IPTQ_ALGO_SLAB)) {
                 err = softmax_rowsdyn_launch(c, cols, post_mode_of(c.P, c.out_bits), &done[i], stream);
                 if (err != hipSuccess) break;
             }

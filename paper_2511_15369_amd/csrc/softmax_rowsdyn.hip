@@ -25,6 +25,32 @@ bool rowsdyn_geometry(int32_t cols, int *lanes, int *slots)
     return true;
 }
 
+// Whether a short call is faster in the three-pass kernel (or one wavefront per row, where the call
+// qualifies for it).  A call of a few thousand rows lasts as long as one wavefront takes from a cold
+// start: here that grows with the code, which is unrolled over the blocks per lane, more so with an
+// int32 mask, for odd row lengths and where the last slab is a partial one (a second copy loop); the
+// three-pass kernel's code is short, and it pays per 64 scores of a row and per row.  Both times as
+// linear models, in nanoseconds without what they share, fitted to 2556 calls of 256 to 8192 rows of 7
+// to 200 scores with either mask, the second-degree exponential or a short table: the choice is at most
+// 15 % and on average 0.4 % slower than the faster kernel (always this one: 117 % and 12 %).  With
+// fewer than three blocks per lane this kernel is always the faster one, beyond 256 scores nearly
+// always.  600 rows of 25 scores with an int32 mask and a table 3.2 us in the three-pass kernel, 6.2
+// here; 9600 rows 6.7 and 5.5; 768 rows of 64 with a packed mask and a table 3.2 and 4.8.
+bool rowsdyn_loses_short_call(int64_t rows, int32_t cols, bool has_bias, bool int_mask, bool bit_mask)
+{
+    int lanes = 0, slots = 0;
+    if (rows > 8192 || cols > 256 || !rowsdyn_geometry(cols, &lanes, &slots) || slots < 3) return false;
+    const bool partial = rows % (64 / lanes) != 0;
+    int64_t here = 960 + slots * (210 + (int_mask ? 70 : 0) + (partial ? 100 : 0));
+    if (cols % 2 != 0) here += 360;
+    if (lanes == 1) here -= 440;
+    if (partial) here += has_bias ? 310 : -360;
+    const int64_t passes = (cols + 63) / 64;
+    int64_t three_pass = 810 * passes + (int_mask || bit_mask ? 440 : 0);
+    if (rows > 1024) three_pass += 170 * (passes + 1) * (rows - 1024) / 1024;
+    return three_pass < here;
+}
+
 static int64_t gcd_i64(int64_t a, int64_t b)
 {
     while (b != 0) { const int64_t t = a % b; a = b; b = t; }

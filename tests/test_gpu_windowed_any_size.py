@@ -44,9 +44,11 @@ def test_masks_match_the_oracle(t, heads, n_w):
         p = prepare.softmax_prepare(s_delta, t, variant, signed)
         for b, period in ((bias, heads * t), (None, 0)):
             want = ref.softmax_i32_windowed(scores, p, b, period, mask, heads)
-            assert np.array_equal(gpu_softmax_windowed_bits(scores, p, b, period, bits, heads), want)
+            for algo in (0, 4):                              # 0 leaves some short calls to the three-pass kernel
+                assert np.array_equal(gpu_softmax_windowed_bits(scores, p, b, period, bits, heads, algo=algo), want)
             want = ref.softmax_i32_windowed(scores, p, b, period, finite, heads)
-            assert np.array_equal(gpu_softmax_windowed(scores, p, b, period, finite, heads), want)
+            for algo in (0, 4):
+                assert np.array_equal(gpu_softmax_windowed(scores, p, b, period, finite, heads, algo=algo), want)
 
 
 @pytest.mark.parametrize("t", [25, 64, 100, 196])
@@ -67,19 +69,19 @@ def test_views_off_the_grid_and_requantization(t):
         d_bias = torch.zeros(bias.size + 8, dtype=torch.int32, device="cuda")
         d_bias[off:off + bias.size] = torch.from_numpy(bias.reshape(-1)).cuda()
         d_mask[off:off + mask.size] = torch.from_numpy(mask.reshape(-1)).cuda()
-        for kind in ("int32", "bits"):
+        for kind, algo in (("int32", 0), ("bits", 0), ("int32", 4), ("bits", 4)):
             d_out = torch.full((n + 16,), 0x5A, dtype=torch.uint8, device="cuda")
             b = d_bias[off:off + bias.size]
             if kind == "int32":
                 ip.softmax_i32_windowed(d_in[off:off + n], b, heads * t, d_mask[off:off + mask.size], n_w, heads,
-                                        d_out[off:off + n], scores.shape[0], t, lib_softmax(p))
+                                        d_out[off:off + n], scores.shape[0], t, lib_softmax(p, algo))
             else:
                 ip.softmax_i32_windowed_bits(d_in[off:off + n], b, heads * t, d_bits, n_w, heads,
-                                             d_out[off:off + n], scores.shape[0], t, lib_softmax(p))
+                                             d_out[off:off + n], scores.shape[0], t, lib_softmax(p, algo))
             torch.cuda.synchronize()
             got = d_out.cpu().numpy()
-            assert np.array_equal(got[off:off + n], want), (kind, off)
-            assert (got[:off] == 0x5A).all() and (got[off + n:] == 0x5A).all(), (kind, off)
+            assert np.array_equal(got[off:off + n], want), (kind, algo, off)
+            assert (got[:off] == 0x5A).all() and (got[off + n:] == 0x5A).all(), (kind, algo, off)
 
 
 @pytest.mark.parametrize("t", [49, 64, 144])

@@ -335,3 +335,21 @@ def test_layout_of_the_walking_workgroup_and_who_takes_which_rows():
     assert rule(600, 0, 1, 1) and not rule(1500, 0, 1, 1)
     assert rule(2500, 1, 0, 1) and rule(2500, 1, 1, 0)
     assert not rule(10, 0, 0, 2) and not rule(2500, 1, 0, 2)     # not instantiated for the second degree
+
+
+def test_short_calls_that_leave_the_run_time_row_length_slab_kernel():
+    """A masked call, a second-degree exponential or a short table: the slab kernel keeps the calls in
+    which its wavefronts have enough to do, and every call of few blocks per lane or long rows."""
+    import ctypes
+    rule = ip.load().iptq_debug_rowsdyn_loses_short_call
+    rule.argtypes = [ctypes.c_int64] + [ctypes.c_int32] * 3
+    rule.restype = ctypes.c_int
+    for mask in (0, 1, 2):
+        for rows in (1, 300, 3072):
+            assert rule(rows, 25, 1, mask) and rule(rows, 55, 1, mask) and rule(min(rows, 1000), 121, 0, mask)
+        for cols in (25, 64, 100, 256):
+            assert not rule(9600, cols, 1, mask)
+            seen = [rule(rows, cols, 0, mask) for rows in range(64, 10240, 64)]      # no partial slab
+            assert seen == sorted(seen, reverse=True)        # short calls leave, long ones stay
+        assert not rule(300, 8, 1, mask) and not rule(300, 257, 1, mask) and not rule(300, 600, 0, mask)
+        assert not rule(2048, 144, 0, mask)
