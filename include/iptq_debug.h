@@ -43,6 +43,10 @@ int iptq_debug_rowsdyn_loses_short_call(int64_t rows, int32_t cols, int32_t has_
  * wavefronts per row, 0 the workgroups that walk over rows. */
 int iptq_debug_wgrow16_is_faster(int64_t rows, int32_t has_bias, int32_t has_pre, int32_t variant);
 
+/* Whether the int32 GELU of n values runs as one looping generation of workgroups (1) or as many
+ * short-lived ones (0); out_on_line: its output starts on a 64-byte line. */
+int iptq_debug_gelu32_looping_grid(int64_t n, int32_t out_on_line);
+
 /* Exponentials (Eq. 7-14) of n stabilised scores (row maximum 0; n even) through both arithmetic
  * paths of the softmax kernels: d_out32 from the 32-bit lanes, d_out16 from the packed 16-bit
  * lanes (0xFFFFFFFF where the parameters do not enable that path).  All three device arrays

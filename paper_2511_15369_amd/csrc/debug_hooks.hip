@@ -65,6 +65,11 @@ extern "C" int iptq_debug_wgrow16_is_faster(int64_t rows, int32_t has_bias, int3
     return wgrow16_is_faster(rows, has_bias != 0, has_pre != 0, variant) ? 1 : 0;
 }
 
+extern "C" int iptq_debug_gelu32_looping_grid(int64_t n, int32_t out_on_line)
+{
+    return gelu32_looping_grid(n, out_on_line != 0) ? 1 : 0;
+}
+
 // Exponentials of an array of stabilised scores (row maximum 0) through both arithmetic
 // paths of the softmax kernels: out32 from the 32-bit lanes, out16 from the packed 16-bit
 // lanes (pairs (2i, 2i+1); 0xFFFFFFFF where the plan does not enable that path).  n even.

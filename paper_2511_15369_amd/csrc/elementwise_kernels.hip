@@ -250,12 +250,25 @@ gelu_i32_kernel(const int32_t *in, uint8_t *out, int64_t n, int32_t head, GeluDe
 // element costs one multiply-shift, a clamp and a byte gather from LDS.
 constexpr int kGelu32TableMaxQ = 511;
 constexpr int64_t kGelu32TableGridCap = 256 * 64;
-// Up to 40 million values one resident generation of workgroups (8 per compute unit) that loop is
-// faster than many short-lived ones, each of which builds the table: 19.4 M values with the
-// requantization of 4.8 M behind them 22.9 us against 23.8, 38.4 M 36.0 against 36.8; 76.8 M 69.2
-// against 66.6.  (Evening out the trips per workgroup is slower than either: 23.5 us.)
-constexpr int64_t kGelu32ShortCall = 40 * 1000 * 1000;
+// Whether one resident generation of workgroups (8 per compute unit) that loop is faster than as
+// many short-lived ones as there are values, each of which builds the table.  (n: values in groups
+// that start on a dword of the output; measured against the uncapped grid.)
+//   - up to 40 million values: 5 M 6.0 us against 6.3, 12 M 11.5 against 11.9, 19.4 M 17.3 against 18.2,
+//     38.4 M 32.4 against 33.0; from 40 M on both grids take the same time up to 46 M, and 76.8 M take
+//     69.2 against 66.6;
+//   - up to 24 million if the output does not start on a 64-byte line (neighbouring wavefronts then
+//     share lines, and the short-lived workgroups write them closer together): 19 M 18.4 against 18.7,
+//     24 M 22.6 against 22.7, 30 M 27.7 against 27.3, 36 M 32.5 against 32.1;
+//   - not where most of the generation would make a second trip while the others are done: 2.6 M 4.0
+//     against 4.2, 3.0 M 4.6 against 4.4, 3.4 M 5.1 against 4.7, 4.1 M 5.6 against 5.4, 4.3 M 5.6 against 5.7.
+// Evening out the trips per workgroup is slower than either (19.4 M 23.5 us with a requantization
+// behind it, 22.9 as here).  The kernel for unaligned groups serves calls of less than 64 values only.
 constexpr int64_t kGelu32ShortGridCap = 256 * 8;
+bool gelu32_looping_grid(int64_t n, bool out_on_line)
+{
+    if (n > 2800 * 1000 && n < 4200 * 1000) return false;
+    return n <= (out_on_line ? 40 : 24) * 1000 * 1000;
+}
 template <bool ALIGNED>
 __global__ void __launch_bounds__(256)
 gelu_i32_table_kernel(const int32_t *in, uint8_t *out, int64_t n, int32_t head, GeluDev P)
@@ -395,8 +408,9 @@ hipError_t gelu_i32_dispatch(const int32_t *in, int8_t *out, int64_t n, const Ge
     const bool table = !force_direct && P.max_abs_q <= kGelu32TableMaxQ;
     if (aligned) {
         const dim3 grid(grid_for(n >> 2, 256, 256 * 64)), block(256);
+        const bool looping = gelu32_looping_grid(n, (reinterpret_cast<uintptr_t>(uout) & 63) == 0);
         if (table)
-            hipLaunchKernelGGL(gelu_i32_table_kernel<true>, dim3(grid_for(n >> 2, 256, n <= kGelu32ShortCall ? kGelu32ShortGridCap : kGelu32TableGridCap)),
+            hipLaunchKernelGGL(gelu_i32_table_kernel<true>, dim3(grid_for(n >> 2, 256, looping ? kGelu32ShortGridCap : kGelu32TableGridCap)),
                                block, 0, stream, in, uout, n, head, P);
         else if (mode == 0) hipLaunchKernelGGL((gelu_i32_kernel<true, 0>), grid, block, 0, stream, in, uout, n, head, P);
         else if (mode == 1) hipLaunchKernelGGL((gelu_i32_kernel<true, 1>), grid, block, 0, stream, in, uout, n, head, P);

@@ -58,6 +58,7 @@ bool wgrow16_is_faster(int64_t rows, bool has_bias, bool has_pre, int variant);
 hipError_t gelu_i8_dispatch(const GeluCall *calls, int n_calls, hipStream_t stream);
 hipError_t gelu_i32_dispatch(const int32_t *in, int8_t *out, int64_t n, const GeluDev &P,
                              bool force_direct, hipStream_t stream);
+bool gelu32_looping_grid(int64_t n, bool out_on_line);
 // [n_windows, cols, cols] int32 -> [n_windows, cols, ceil(cols / 64)] words, bit k set where the entry is INT32_MIN
 hipError_t pack_window_mask_dispatch(const int32_t *mask, int64_t n_queries, int32_t cols, uint64_t *bits,
                                      hipStream_t stream);

@@ -353,3 +353,14 @@ def test_short_calls_that_leave_the_run_time_row_length_slab_kernel():
             assert seen == sorted(seen, reverse=True)        # short calls leave, long ones stay
         assert not rule(300, 8, 1, mask) and not rule(300, 257, 1, mask) and not rule(300, 600, 0, mask)
         assert not rule(2048, 144, 0, mask)
+
+
+def test_int32_gelu_grid():
+    """One looping generation of workgroups where it was the faster grid: not around one and a half
+    trips, not beyond 40 million values, not beyond 24 million off the 64-byte lines."""
+    import ctypes
+    rule = ip.load().iptq_debug_gelu32_looping_grid
+    rule.argtypes = [ctypes.c_int64, ctypes.c_int32]
+    rule.restype = ctypes.c_int
+    assert [rule(n, 1) for n in (2600000, 3400000, 4300000, 19400000, 38400000, 41000000)] == [1, 0, 1, 1, 1, 0]
+    assert [rule(n, 0) for n in (2600000, 3400000, 4300000, 19400000, 38400000, 41000000)] == [1, 0, 1, 1, 0, 0]
