@@ -153,6 +153,15 @@ def _check(rc: int, what: str):
 _raw_stream = None
 
 
+def _forget_stream():
+    global _raw_stream
+    _raw_stream = None
+
+
+# a forked child asks torch again, which refuses a GPU state inherited from its parent
+os.register_at_fork(after_in_child=_forget_stream)
+
+
 def _stream() -> int:
     """The current torch stream of the current device as a raw hipStream_t."""
     global _raw_stream

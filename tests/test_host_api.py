@@ -364,3 +364,14 @@ def test_int32_gelu_grid():
     rule.restype = ctypes.c_int
     assert [rule(n, 1) for n in (2600000, 3400000, 4300000, 19400000, 38400000, 41000000)] == [1, 0, 1, 1, 1, 0]
     assert [rule(n, 0) for n in (2600000, 3400000, 4300000, 19400000, 38400000, 41000000)] == [1, 0, 1, 1, 0, 0]
+
+
+def test_a_forked_child_asks_torch_for_its_stream_again(monkeypatch):
+    """torch refuses GPU work in a forked child; the shortcut past its check must not outlive a fork."""
+    import paper_2511_15369_amd.binding as b
+    monkeypatch.setattr(b, "_raw_stream", lambda: 0)
+    pid = os.fork()
+    if pid == 0:
+        os._exit(0 if b._raw_stream is None else 1)
+    assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
+    assert b._raw_stream() == 0                              # the parent keeps it
