@@ -77,9 +77,16 @@ def lib_path() -> str:
     return _LIB_PATH
 
 
+def _bind_torch():
+    global torch
+    if torch is None:
+        import torch as _t
+        torch = _t
+
+
 def load():
     """Load the shared library (built by ``python -m paper_2511_15369_amd.build``)."""
-    global _lib, torch
+    global _lib
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -88,8 +95,7 @@ def load():
     # torch first: it brings its own copy of the HIP runtime, and the library must bind to that
     # one (the device buffers and streams come from it).  Loaded before torch, libiptq.so would
     # pull in the system's copy and every launch would go to a second runtime that has no device.
-    import torch as _t
-    torch = _t
+    _bind_torch()
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i64, i32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32
     lib.iptq_version.restype = ctypes.c_int
@@ -370,7 +376,7 @@ def softmax_problem(d_scores, d_bias, bias_period_rows: int, d_out, rows: int, c
                     p: SoftmaxParams, d_mask=None, n_windows: int = 0, heads: int = 0,
                     d_mask_bits=None) -> SoftmaxProblem:
     """One entry of a softmax batch (same checks as softmax_i32)."""
-    load()
+    _bind_torch()
     _need(d_scores, torch.int32, "d_scores")
     _need(d_out, torch.int8 if p.out_is_signed else torch.uint8, "d_out")
     assert d_scores.numel() >= rows * cols and d_out.numel() >= rows * cols
@@ -390,7 +396,7 @@ def softmax_problem(d_scores, d_bias, bias_period_rows: int, d_out, rows: int, c
 
 
 def gelu_problem(d_in, d_out, n: int, p: GeluParams) -> GeluProblem:
-    load()
+    _bind_torch()
     _need(d_in, torch.int8, "d_in")
     _need(d_out, torch.int8, "d_out")
     assert d_in.numel() >= n and d_out.numel() >= n

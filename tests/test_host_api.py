@@ -375,3 +375,16 @@ def test_a_forked_child_asks_torch_for_its_stream_again(monkeypatch):
         os._exit(0 if b._raw_stream is None else 1)
     assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
     assert b._raw_stream() == 0                              # the parent keeps it
+
+
+def test_batch_entries_are_checked_without_the_library(monkeypatch):
+    """Filling in an entry of a batch needs torch only: a wrong tensor is refused as such."""
+    import paper_2511_15369_amd.binding as b
+    import torch
+    monkeypatch.setattr(b, "_lib", None)
+    monkeypatch.setattr(b, "_LIB_PATH", os.path.join(ROOT, "no_such_dir", "libiptq.so"))
+    x = torch.zeros((2, 4), dtype=torch.int32)
+    with pytest.raises(TypeError):
+        b.softmax_problem(x, None, 0, torch.zeros((2, 4), dtype=torch.uint8), 2, 4, b.SoftmaxParams())
+    with pytest.raises(TypeError):
+        b.gelu_problem(torch.zeros(4, dtype=torch.int8), torch.zeros(4, dtype=torch.int8), 4, b.GeluParams())
