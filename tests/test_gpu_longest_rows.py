@@ -1,7 +1,10 @@
-"""Rows of up to 65536 scores (one walking workgroup per row, the next row fetched while this one is
-computed) against the oracle: every pass count at its edges, one and several rows per workgroup,
-partly filled last passes, tensors off the 16-byte grid, rows near INT32_MIN in between ordinary
-ones, tables and the requantization in front, 32-bit and packed arithmetic, guard bytes."""
+"""Rows of up to 65536 scores (a workgroup of 16 wavefronts per row, up to 40957 scores for some calls,
+else workgroups that walk over rows and fetch the next one while one is computed) against the oracle:
+every pass count at its edges, one and several rows per workgroup, partly filled last passes, tensors
+off the 16-byte grid, rows near INT32_MIN in between ordinary ones, tables and the requantization in
+front, 32-bit and packed arithmetic, guard bytes, more than 2^31 scores."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -53,7 +56,7 @@ def test_pass_counts(slots, edge):
         _check(_scores(rng, rows, cols, p.i0), p, None, 0, off, int(rng.integers(0, 17)))
 
 
-@pytest.mark.parametrize("cols", [26620, 32768, 40001, 53249, 65536])
+@pytest.mark.parametrize("cols", [26620, 26625, 32768, 40001, 53249, 65536])
 def test_several_rows_per_workgroup(cols):
     """More rows than workgroups: the prefetch of the next row, the last row ending off the grid."""
     import torch
@@ -84,3 +87,89 @@ def test_tables_requantization_and_post_steps(cols):
         bias[rng.random(bias.shape) < 0.01] = I32_MIN
         _check(x, p, None, 0, 2, 1)
         _check(x, p, bias, 2, 0, 5)
+
+
+def _mode16(p, cols):
+    fn = ip.load().iptq_debug_softmax_plan
+    fn.argtypes = [ctypes.POINTER(ip.SoftmaxParams), ctypes.c_int64, ctypes.c_int32, ctypes.c_int32,
+                   ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]
+    out = (ctypes.c_int64 * 12)()
+    lp = lib_softmax(p)
+    assert fn(ctypes.byref(lp), 1, cols, 0, 0, out) == 0
+    return int(out[8])
+
+
+# five rows for most workgroups, and more than a requantization in front leaves to a workgroup per row
+WALKED_ROWS = 1200
+WALKS = [
+    # variant, scale, packed arithmetic, requantization in front, post step, table
+    (0, 2.0 ** -7, True, (1, 0), None, False),
+    (1, 2.0 ** -13, False, (1, 0), None, False),
+    (1, 2.0 ** -6, True, (1, 0), (3, 2, 5), False),
+    (2, 2.0 ** -6, True, (1, 0), (1, 0, -128), False),
+    (1, 2.0 ** -6, True, (20000, 20), None, False),
+    (0, 2.0 ** -13, False, (300, 9), (3, 2, 5), False),
+    (2, 2.0 ** -6, True, (1, 0), None, True),
+    (1, 2.0 ** -6, True, (1, 0), (3, 2, 5), True),
+    (0, 2.0 ** -13, False, (20000, 20), None, True),
+    (2, 2.0 ** -12, False, (300, 9), (1, 0, -128), True),
+]
+
+
+@pytest.mark.parametrize("cols", [26625, 28672, 33001, 36864, 36866, 40957, 41000, 53251, 65533])
+@pytest.mark.parametrize("walk", range(len(WALKS)))
+def test_every_kernel_walks(cols, walk):
+    """Several rows per workgroup in every instantiation: the prefetch of the next row beside a table,
+    a requantization, 32-bit lanes, every variant and post step, 7 passes to 16, either side of the 9
+    passes that LDS holds and 10 of the workgroup per row, tensors that start and end off the grid."""
+    import torch
+    variant, s_delta, packed, pre, post, table = WALKS[walk]
+    signed = 1 if post == (1, 0, -128) else 0
+    rng = np.random.default_rng(cols * 10 + walk)
+    p = prepare.softmax_prepare(s_delta, cols, variant, signed)
+    p.pre_m, p.pre_s = pre
+    if post is not None:
+        p.post = ref.Dyadic(post[0], post[1], post[2], -128 if signed else 0, 127 if signed else 255)
+    assert (_mode16(p, cols) != 0) == packed
+    unit = p.i0 * (1 << pre[1]) // pre[0]
+    few = _scores(rng, 28, cols, unit)                                # a multiple of four: the table's size too
+    few[4:26:2] = _scores(rng, 15, cols, 4 * unit)[3:14]              # rows with large probabilities
+    bias, period, off = None, 0, (cols + walk) % 4
+    if table:                                                         # needs both tensors on the grid
+        period, off = 28, 0
+        bias = np.rint(rng.standard_normal((period, cols)) * 3 * p.i0).astype(np.int32)
+        bias[rng.random(bias.shape) < 0.01] = I32_MIN
+    want_few = torch.from_numpy(ref.softmax_i32(few, p, bias, period).view(np.uint8)).cuda()
+    rows, n = WALKED_ROWS, WALKED_ROWS * cols
+    which = torch.arange(rows, device="cuda") % 28
+    d_in = torch.zeros(n + 4, dtype=torch.int32, device="cuda")
+    d_in[off:off + n].view(rows, cols)[:] = torch.from_numpy(few).cuda()[which]
+    d_bias = None if bias is None else torch.from_numpy(bias).cuda()
+    d_out = torch.full((n + 16,), 0x5A, dtype=torch.uint8, device="cuda")
+    ooff = walk % 3
+    view = d_out.view(torch.int8) if signed else d_out
+    print("walk", walk, "of", rows, "x", cols, "at", off, flush=True)
+    ip.softmax_i32(d_in[off:off + n], d_bias, period, view[ooff:ooff + n], rows, cols, lib_softmax(p))
+    torch.cuda.synchronize()
+    assert torch.equal(d_out[ooff:ooff + n].view(rows, cols), want_few[which])
+    assert bool((d_out[:ooff] == 0x5A).all()) and bool((d_out[ooff + n:] == 0x5A).all())
+
+
+@pytest.mark.parametrize("cols", [20001, 50177])
+def test_more_than_2_31_scores(cols):
+    """64-bit element offsets in the workgroup-per-row kernels, row by row and walking."""
+    import torch
+    rng = np.random.default_rng(cols)
+    p = prepare.softmax_prepare(2.0 ** -7.4, cols, 1)
+    few = _scores(rng, 7, cols, p.i0)
+    want_few = torch.from_numpy(ref.softmax_i32(few, p)).cuda()
+    rows = 2 ** 31 // cols + 300
+    which = torch.arange(rows, device="cuda") % 7
+    print("softmax of", rows, "x", cols, flush=True)
+    x = torch.from_numpy(few).cuda()[which]
+    out = torch.full((rows, cols), 0x5A, dtype=torch.uint8, device="cuda")
+    ip.softmax_i32(x, None, 0, out, rows, cols, lib_softmax(p))
+    torch.cuda.synchronize()
+    del x
+    for lo in range(0, rows, 8192):
+        assert torch.equal(out[lo:lo + 8192], want_few[which[lo:lo + 8192]]), lo
