@@ -177,14 +177,16 @@ int iptq_requant(const int32_t *d_in, void *d_out, int64_t n, int32_t out_is_sig
  * matrix instruction for the product with V); any other post step goes through a small table.
  * Every shape gives the same bytes; speed depends on it.  Fastest: a row length of 197, 49, 198,
  * 144, 257 or 577; any other row length runs in the register-resident kernels with a run-time row
- * length (but for rows of 65530 and more whose blocks do not sit on the 16-byte grid, which take a
+ * length (but for rows of 65534 and more whose blocks do not sit on the 16-byte grid, which take a
  * slower multi-pass kernel).  The tensors need their
  * natural alignment only (views into larger tensors run at the same speed as tensors on the
- * 16-byte grid); an additive table of any size is fused (a little faster when
- * bias_period_rows * cols is a multiple of 4, as with 4, 8, 16 or 32 Swin heads), except a
- * table with fewer rows than one wavefront's slab (64 rows divided by the lanes per row: 32 at
- * 49 columns, 8 or 16 at 197; 32 rows suffice for rows of up to 29 scores), or of 2^30 entries and more, which takes the three-pass kernel
- * (about a sixth of the speed).
+ * 16-byte grid); beside rows of up to about 635 scores an additive table of any size is fused (a
+ * little faster when bias_period_rows * cols is a multiple of 4, as with 4, 8, 16 or 32 Swin heads),
+ * except a table with fewer rows than one wavefront's slab (64 rows divided by the lanes per row: 32
+ * at 49 columns, 8 or 16 at 197; 32 rows suffice for rows of up to 29 scores), or of 2^30 entries and
+ * more, which takes the three-pass kernel (about a sixth of the speed).  Beside longer rows it is
+ * fused if scores and table start on the 16-byte grid and bias_period_rows * cols is a multiple of 4,
+ * else the call takes the three-pass kernel.
  */
 int iptq_softmax_i32(const int32_t *d_scores, const int32_t *d_bias, int64_t bias_period_rows,
                      void *d_out, int64_t rows, int32_t cols, const iptq_softmax_params_t *p,

@@ -236,7 +236,7 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
             if (has_bias) {
                 // rows after which the tables repeat: the bias period, or with an int32 mask the least
                 // common multiple of both periods.  (A packed mask is too small to be worth sharing:
-                // with it in the period 147,456 rows of 12 x 12-token windows take 69.2 us against
+                // with it in the period 589,824 rows of 12 x 12-token windows take 69.2 us against
                 // 66.8 us, 7 x 7 tokens the same.)
                 int64_t period = c.P.bias_period_rows;
                 if (has_mask == 1) {

@@ -1,5 +1,5 @@
 // Integer softmax (Section 4.4, Eq. 6-15) for the longest rows (up to the interface's 65536
-// scores): a workgroup of 16 wavefronts holds one row in its registers (the layout of
+// scores; up to 40957 wgrow16_is_faster decides between this and a workgroup per row): a workgroup of 16 wavefronts holds one row in its registers (the layout of
 // softmax_wgrow.h with 1024 lanes) and walks over rows.  Such a row fills a compute unit (64 KB of
 // LDS would not hold it, two of them do not fit the register file), so nothing else is resident
 // to load while this one computes, and a kernel that ends with its row leaves the memory pipe
@@ -10,7 +10,8 @@
 // 2048 rows of 50176 scores 93.6 us (5.5 TB/s; 1212 us in the three-pass kernel, one wavefront per
 // row), of 65536 129 us (1567 us), 2000 rows of 32768 67.8 us (78.5 us as 16 wavefronts without the
 // prefetch), 10 rows of 62000 12.9 us (720 us).  What is left: the last passes are asked for while
-// the row is computed and not before, so the memory pipe still drains a little once per row.
+// the row is computed and not before, so the memory pipe still drains a little once per row; and the
+// wait in front of a row is for every vector-memory operation, the stores of the row before among them.
 // Tried instead: a ring of 9 passes in LDS alone, refilled pass by pass as the row is read (no
 // registers, fewer loads in flight: 108 us at 2048 x 50176).
 #pragma once
@@ -80,7 +81,8 @@ struct LongRowSum {
 };
 
 // EXTRA: an additive table, or the scores requantized in front; a kernel of its own because either
-// takes registers, also when it is not used.
+// takes registers, also when it is not used.  No register is left to fetch the next row's last passes
+// into before the probabilities exist, and the table's blocks come two at a time.
 template <int SLOTS, int MODE, int VARIANT, bool EXTRA>
 __global__ void __launch_bounds__(64 * kLongWaves)
 softmax_long_kernel(WideArgs A)

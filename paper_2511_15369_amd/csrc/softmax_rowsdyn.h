@@ -77,18 +77,21 @@ IPTQ_DEV i32x4 table_block_at(const int32_t *table, int32_t idx, int32_t total)
 // applied to the registers once the row has been read back from LDS (the int32 entries load per
 // block straight into the lane that needs them; a mask row is shared by `heads` rows and comes out
 // of L1/L2), so the copy loop stays the one of the unmasked kernel.  What bounds it is still HBM,
-// with the mask's lane-ops (two per score packed, four as int32) next: 524,288 rows of 8 x 8-token
-// windows with a bias table 34.4 us packed and 35 us as int32 entries against 32 us without a mask
-// and 251 us in the three-pass kernel; 16 x 16 tokens (262,144 rows) 60 / 65 / 57 us.  At 49 and 144
-// tokens the compiled row lengths stay faster (144: 73 / 81 us against 85 / 89 us here).
+// with the mask's lane-ops (two per score packed, four as int32) next.  Launches back to back in a
+// graph, random masks, a bias table, Bit-exp: 524,288 rows of 8 x 8-token windows 31.5 us packed and
+// 34.7 us as int32 entries, 29.6 us without a mask, 254 us in the three-pass kernel; 16 x 16 tokens
+// (262,144 rows) 60.0 / 63.8 / 54.7 / 370 us.  At 49 and 144 tokens the compiled row lengths stay faster
+// (589,824 rows of 144: 67.6 / 78.7 us against 85.9 / 91.9 us here).
 //
 // VARIANT is a template argument because every launch starts with a cold instruction cache: with a
 // branch over the three exponentials 122,880 rows of 100 scores with a table took 16.3 us against
-// 15.7 us (a launch of this kernel has one set of parameters, so nothing needs the branch).
+// 15.7 us (a launch of this kernel has one set of parameters, so nothing needs the branch).  In 32-bit
+// lanes the branch costs between nothing and 4 % (122,880 x 100 15.1 us against 14.5, 30,000 x 401 16.2
+// against 15.9, with a mask up to 2 %) and would save a tenth of the library's size.
 //
 // PRE: the requantization in front folded into Eq. 6 where the parameters allow it
-// (SoftmaxDev::pre_rowconst, see softmax_rows_body): 153,984 rows of
-// 401 scores 53.3 us, what they take without a requantization, against 54.7 us.
+// (SoftmaxDev::pre_rowconst, see softmax_rows_body): 153,984 rows of 401 scores 53.4 us (Bit-exp) and
+// 53.6 us (Shiftmax), what they take without a requantization, against 54.6 and 53.9 us.
 template <int K, int SLOTS, int MODE, int MASKKIND, int VARIANT, bool PRE>
 __global__ void __launch_bounds__(256)
 softmax_rowsdyn_kernel(DynArgs A)
@@ -126,8 +129,8 @@ softmax_rowsdyn_kernel(DynArgs A)
     // ---- the mask of this lane's blocks, in flight with the scores.  Packed form: the bits of
     // slot s start at key 4 (s K + j) - phi; one 4-byte load at the byte that holds that key
     // (moved inside the mask row where it would leave it) covers the bits of GROUP slots.  (8-byte
-    // words take half the loads and two quarter-rate 64-bit shifts each: 20 x 20 tokens 102 us
-    // against 85 us.)
+    // words take half the loads and two quarter-rate 64-bit shifts each: 204,800 rows of 20 x 20
+    // tokens 102 us against 85 us.)
     constexpr int GROUP = K == 1 ? 6 : (K == 2 ? 3 : (K == 4 ? 2 : 1));
     constexpr int NG = (SLOTS + GROUP - 1) / GROUP;
     static_assert(4 * K * (GROUP - 1) + 4 + 7 <= 32, "the bits of a group of slots at any offset inside a byte");
