@@ -348,26 +348,7 @@ softmax_rowsdyn_kernel(DynArgs A)
             x, w, mr, 0, false, lut, P, LaneGroupSum<K>(), pre_fold_row_constant(mr, P));
     } else {
     // ---- fused requantization of the scores (after the bias, before the maximum)
-    if (P.pre_mode == 1) {
-        const int32_t pre_mul = P.pre_mul, pre_sh2 = P.pre_sh2;
-        const int64_t pre_rnd = P.pre_rnd;
-#pragma unroll
-        for (int s = 0; s < SLOTS; ++s)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int32_t r = pre_requant_narrow(x[s][e], pre_mul, pre_rnd, pre_sh2);
-                x[s][e] = x[s][e] == kI32Min ? kI32Min : r;
-            }
-    } else if (P.pre_mode == 2) {                     // shifts below 16: the general 64-bit form
-        const int32_t pre_m = P.pre_m, pre_s = P.pre_s;
-#pragma unroll
-        for (int s = 0; s < SLOTS; ++s)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int32_t r = pre_requant_dev(x[s][e], pre_m, pre_s);
-                x[s][e] = x[s][e] == kI32Min ? kI32Min : r;
-            }
-    }
+    pre_requant_registers<SLOTS>(x, P);
 
     // ---- Eq. 6: row maximum
     int32_t mx = kI32Min;

@@ -41,8 +41,13 @@ struct WideArgs {
 // scores 52.6 us against 53.9 us).  Up to eight passes: with more the folded form needs so many
 // registers that it is the slower one (12,000 rows of 3000 scores 33.2 against 32.3 us).
 constexpr int kWideFoldMaxSlots = 8;
+// Most wavefronts per SIMD, where the registers would allow one or two more: a wavefront's loads are
+// all in flight at once, and in a long launch more rows in flight than this are slower (17,143 rows of
+// 2100 scores 31.5 us against 32.0 with seven, 12,414 rows of 2900 scores 31.6 us against 32.1 with
+// five; short launches take the same time or, with twelve passes, up to 4 % less).
+constexpr int wide_max_waves(int slots) { return slots == 9 ? 5 : (slots == 11 || slots == 12 ? 4 : 8); }
 template <int SLOTS, int MODE, int VARIANT, bool PRE>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, wide_max_waves(SLOTS))))
 softmax_wide_kernel(WideArgs A)
 {
     __shared__ uint8_t lut_all[4][kPostLutBytes];
@@ -138,26 +143,7 @@ softmax_wide_kernel(WideArgs A)
             x, w, mr, 0, false, lut, P, LaneGroupSum<64>(), pre_fold_row_constant(mr, P));
     } else {
     // ---- fused requantization of the scores (after the bias, before the maximum)
-    if (P.pre_mode == 1) {
-        const int32_t pre_mul = P.pre_mul, pre_sh2 = P.pre_sh2;
-        const int64_t pre_rnd = P.pre_rnd;
-#pragma unroll
-        for (int s = 0; s < SLOTS; ++s)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int32_t r = pre_requant_narrow(x[s][e], pre_mul, pre_rnd, pre_sh2);
-                x[s][e] = x[s][e] == kI32Min ? kI32Min : r;
-            }
-    } else if (P.pre_mode == 2) {                     // shifts below 16: the general 64-bit form
-        const int32_t pre_m = P.pre_m, pre_s = P.pre_s;
-#pragma unroll
-        for (int s = 0; s < SLOTS; ++s)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int32_t r = pre_requant_dev(x[s][e], pre_m, pre_s);
-                x[s][e] = x[s][e] == kI32Min ? kI32Min : r;
-            }
-    }
+    pre_requant_registers<SLOTS>(x, P);
 
     // ---- Eq. 6: row maximum
     int32_t mx = kI32Min;
