@@ -192,6 +192,21 @@ IPTQ_DEV i32x4 add_table_chunk(i32x4 v, i32x4 t)
     return v;
 }
 
+// The saturating sums alone, with the smallest operand seen beside them: the exact rule's values as
+// long as that is not INT32_MIN.
+IPTQ_DEV i32x4 add_tracking_lowest(i32x4 v, i32x4 t, i32x4 &lowest)
+{
+    lowest.x = min(min(lowest.x, v.x), t.x);
+    lowest.y = min(min(lowest.y, v.y), t.y);
+    lowest.z = min(min(lowest.z, v.z), t.z);
+    lowest.w = min(min(lowest.w, v.w), t.w);
+    v.x = sat_add_i32(v.x, t.x);
+    v.y = sat_add_i32(v.y, t.y);
+    v.z = sat_add_i32(v.z, t.z);
+    v.w = sat_add_i32(v.w, t.w);
+    return v;
+}
+
 // ---- cross-lane exchange on the DPP path (no LDS traffic) -----------------------------
 // DPP control words: quad_perm [1,0,3,2] = 0xB1, quad_perm [2,3,0,1] = 0x4E,
 // row_half_mirror = 0x141, row_mirror = 0x140.

@@ -169,17 +169,19 @@ IPTQ_DEV uint32_t row_mod_period(uint32_t row, const SoftmaxDev &P)
 // four (Swin with 3 or 6 heads: 147 * 49 entries): the load is placed so that it ends inside
 // the table (`a`), and a chunk that straddles the end takes its last entries from `first4`
 // (entries 0..3, loaded once per wavefront).  Branch-free; `sh` is 0 for every other chunk.
-IPTQ_DEV i32x4 bias_chunk_wrapping(const int32_t *bias, uint32_t o, uint32_t pe, const i32x4 first4)
+IPTQ_DEV i32x4 bias_chunk_wrapped(const i32x4 A, uint32_t o, uint32_t pe, const i32x4 first4)
 {
-    const uint32_t a = min(o, pe - 4u);
-    const uint32_t sh = o - a;
-    const i32x4 A = load_i32x4(bias + a);
+    const uint32_t sh = o - min(o, pe - 4u);
     i32x4 r;
     r.x = sh == 0 ? A.x : (sh == 1 ? A.y : (sh == 2 ? A.z : A.w));
     r.y = sh == 0 ? A.y : (sh == 1 ? A.z : (sh == 2 ? A.w : first4.x));
     r.z = sh == 0 ? A.z : (sh == 1 ? A.w : (sh == 2 ? first4.x : first4.y));
     r.w = sh == 0 ? A.w : (sh == 1 ? first4.x : (sh == 2 ? first4.y : first4.z));
     return r;
+}
+IPTQ_DEV i32x4 bias_chunk_wrapping(const int32_t *bias, uint32_t o, uint32_t pe, const i32x4 first4)
+{
+    return bias_chunk_wrapped(load_i32x4(bias + min(o, pe - 4u)), o, pe, first4);
 }
 
 // Where the rows of a slab find their rows of the per-window mask.  Consecutive score rows are
@@ -234,12 +236,17 @@ IPTQ_DEV MaskRuns mask_runs_of_slab(const int32_t *mask, uint32_t row0, const So
 // general form 79.5 us).  Otherwise the straddling chunk's load is placed inside the first run and its
 // result replaced.
 template <int COLS>
-IPTQ_DEV i32x4 mask_chunk(const int32_t *mask, const MaskRuns &R, uint32_t o)
+IPTQ_DEV i32x4 mask_chunk_load(const int32_t *mask, const MaskRuns &R, uint32_t o)
 {
     const uint32_t in2 = 0u - (uint32_t)(o >= R.e1);
     if constexpr (COLS % 4 == 0) return load_i32x4(mask + (o + R.off1 + ((R.off2 - R.e1 - R.off1) & in2)));
     const uint32_t off = ((R.off2 + (o - R.e1)) & in2) | ((R.off1 + min(o, R.e1 - 4u)) & ~in2);
-    i32x4 m = load_i32x4(mask + off);
+    return load_i32x4(mask + off);
+}
+template <int COLS>
+IPTQ_DEV i32x4 mask_chunk_entries(i32x4 m, const MaskRuns &R, uint32_t o)
+{
+    if constexpr (COLS % 4 == 0) return m;
     const bool st = o == R.o_s;
     m.x = st ? R.straddle.x : m.x;
     m.y = st ? R.straddle.y : m.y;
@@ -598,9 +605,8 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxBatch &B)
         i32x4 first4 = {0, 0, 0, 0};
         if (BIAS && STRADDLE) first4 = load_i32x4(bias);
         constexpr int NPASS = (IN_CHUNKS + 63) / 64;
-        // With the mask there are three loads per chunk, more than the registers hold in flight
-        // at once: the scores (the loads that go to HBM) are all issued first, the two tables'
-        // entries (cache hits) follow pass by pass.
+        // With the mask there are three loads per chunk: the scores (the loads that go to HBM) are all
+        // issued first,
         i32x4 sv[MASK ? NPASS : 1];
         if (MASK) {
 #pragma unroll
@@ -618,6 +624,27 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxBatch &B)
                     if (4 * idx + 2 < valid_el) sv[i].z = s[2];
                 }
             }
+        }
+        // then both tables' entries (cache hits), and only then is any of them waited for.  Pass by pass,
+        // as the sums left registers free, every pass waited for an L2 access of its own: 589,824 rows
+        // of 12 x 12-token windows 78.4 us against 77.1, 7 x 7 tokens 42.4 against 41.6 (401,408 rows) and
+        // 6.87 against 6.58 (50,176 rows).  Leaving the mask out where a slab's entries are all zero brings
+        // nothing more here (41.2 us against 41.3): the loads are what it costs.
+        constexpr bool AHEAD = MASK && BIAS && !PARTIAL;
+        i32x4 mvs[AHEAD ? NPASS : 1], bvs[AHEAD ? NPASS : 1];
+        auto bias_at = [&](int li) -> uint32_t {
+            const uint32_t o = boff + 4u * (uint32_t)li;
+            return o >= pe ? o - pe : o;
+        };
+        if (AHEAD) {
+            auto chunk_of = [&](int i) { return (i + 1) * 64 <= IN_CHUNKS ? i * 64 + lane : min(i * 64 + lane, IN_CHUNKS - 1); };
+#pragma unroll
+            for (int i = 0; i < NPASS; ++i) {
+                const uint32_t o = bias_at(chunk_of(i));
+                bvs[i] = load_i32x4_at(bias, 4u * (STRADDLE ? min(o, pe - 4u) : o));
+                mvs[i] = mask_chunk_load<COLS>(I.mask, MR, 4u * (uint32_t)chunk_of(i));
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int i = 0; i < NPASS; ++i) {
@@ -643,12 +670,12 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxBatch &B)
             }
             i32x4 bv = {0, 0, 0, 0};
             if (BIAS) {
-                uint32_t o = boff + 4u * (uint32_t)li;
-                if (o >= pe) o -= pe;
-                bv = STRADDLE ? bias_chunk_wrapping(bias, o, pe, first4) : load_i32x4_at(bias, 4u * o);   // table below 4 GiB
+                const uint32_t o = bias_at(li);
+                if (AHEAD) bv = STRADDLE ? bias_chunk_wrapped(bvs[AHEAD ? i : 0], o, pe, first4) : bvs[AHEAD ? i : 0];
+                else bv = STRADDLE ? bias_chunk_wrapping(bias, o, pe, first4) : load_i32x4_at(bias, 4u * o);   // table below 4 GiB
             }
             if (MASK) {
-                const i32x4 mv = mask_chunk<COLS>(I.mask, MR, 4u * (uint32_t)li);
+                const i32x4 mv = mask_chunk_entries<COLS>(AHEAD ? mvs[AHEAD ? i : 0] : mask_chunk_load<COLS>(I.mask, MR, 4u * (uint32_t)li), MR, 4u * (uint32_t)li);
                 if (BIAS) {
                     v.x = add_two_table_entries(v.x, bv.x, mv.x);
                     v.y = add_two_table_entries(v.y, bv.y, mv.y);
@@ -661,14 +688,7 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxBatch &B)
                 if (EXACT) {
                     v = add_table_chunk(v, bv);
                 } else {
-                    lowest.x = min(min(lowest.x, v.x), bv.x);
-                    lowest.y = min(min(lowest.y, v.y), bv.y);
-                    lowest.z = min(min(lowest.z, v.z), bv.z);
-                    lowest.w = min(min(lowest.w, v.w), bv.w);
-                    v.x = sat_add_i32(v.x, bv.x);
-                    v.y = sat_add_i32(v.y, bv.y);
-                    v.z = sat_add_i32(v.z, bv.z);
-                    v.w = sat_add_i32(v.w, bv.w);
+                    v = add_tracking_lowest(v, bv, lowest);
                 }
             }
             lds4[li] = v;
@@ -866,9 +886,9 @@ softmax_rows_kernel(SoftmaxBatch B)
     softmax_rows_body<COLS, K, MODE, BIAS, POSTMODE, 0>(B);
 }
 
-// The same with the per-window mask beside the bias: three loads per chunk.  Compiled for five
-// wavefronts per SIMD instead of the six the LDS staging would allow, so that a wavefront has
-// the registers to keep all its loads in flight at once.
+// The same with the per-window mask beside the bias: three loads per chunk.  Compiled for four or
+// five wavefronts per SIMD (LDS would allow six with 49 tokens), so that a wavefront has the
+// registers to keep all its loads in flight at once.
 template <int COLS, int K, int MODE, int POSTMODE>
 __global__ void __launch_bounds__(64 * kRowsWpb) __attribute__((amdgpu_waves_per_eu(4, 5)))
 softmax_rows_masked_kernel(SoftmaxBatch B)

@@ -232,14 +232,7 @@ softmax_rowsdyn_kernel(DynArgs A)
             i32x4 t = v[i];
             if (BIAS) {
                 const i32x4 b = bv[i % kAhead];
-                lowest.x = min(min(lowest.x, t.x), b.x);
-                lowest.y = min(min(lowest.y, t.y), b.y);
-                lowest.z = min(min(lowest.z, t.z), b.z);
-                lowest.w = min(min(lowest.w, t.w), b.w);
-                t.x = sat_add_i32(t.x, b.x);
-                t.y = sat_add_i32(t.y, b.y);
-                t.z = sat_add_i32(t.z, b.z);
-                t.w = sat_add_i32(t.w, b.w);
+                t = add_tracking_lowest(t, b, lowest);
             }
             if (BIAS && i + kAhead < SLOTS) bv[i % kAhead] = bias_chunk(i + kAhead);
             lds4[chunk_of(i)] = t;
