@@ -745,7 +745,17 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxBatch &B)
     }
     wave_lds_fence();                                 // the slab area is reused for the output
 
+    // Most slabs of a shifted-window call lie in windows that the shift leaves whole: no key of theirs is
+    // masked, and the two lane-ops per score are left out (64 images' 7 x 7-token windows of an 8 x 8
+    // grid, four heads: 34.6 us against 35.0).
+    bool any_masked = false;                          // wavefront-uniform
     if (MASKKIND == 2) {
+        uint64_t any = 0;
+#pragma unroll
+        for (int i = 0; i < MW; ++i) any |= mask_words[i];
+        any_masked = __builtin_amdgcn_ballot_w64(any != 0) != 0;
+    }
+    if (MASKKIND == 2 && any_masked) {
         // element e of slot s is key 4 (s K + j) + e - phi: shift the row's bits once, by
         // sh = 4 j - phi in [-3, 4 K - 1], so that this bit sits at the compile-time position
         // 4 s K + e (keys below 0 and beyond the row read zeros; those elements are minus infinity

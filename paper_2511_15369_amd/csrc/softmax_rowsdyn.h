@@ -302,13 +302,28 @@ softmax_rowsdyn_kernel(DynArgs A)
     }
     wave_lds_fence();                                 // the slab area is reused for the output
 
-    if (MASKKIND == 1) {
+    // Most slabs lie in windows that the shift leaves whole: nothing of theirs is masked, and the lane-ops
+    // are left out (9 x 9 tokens, 20 images, 36 windows, four heads 20.7 us packed against 21.9 with
+    // them, 22.5 against 23.2 as int32 entries; 14 x 14 tokens 37.5 against 39.4 as int32 entries).
+    bool any_masked = false;                          // wavefront-uniform
+    if (MASKKIND != 0) {
+        uint32_t any = 0;
+        if (MASKKIND == 1) {
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s) any |= (uint32_t)(mask_block[s].x | mask_block[s].y | mask_block[s].z | mask_block[s].w);
+        } else {
+#pragma unroll
+            for (int g = 0; g < NG; ++g) any |= mask_word[g];
+        }
+        any_masked = __builtin_amdgcn_ballot_w64(any != 0) != 0;
+    }
+    if (MASKKIND == 1 && any_masked) {
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s)
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[s][e] = add_table_entry(x[s][e], mask_block[s][e]);
     }
-    if (MASKKIND == 2) {
+    if (MASKKIND == 2 && any_masked) {
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s)
 #pragma unroll
