@@ -41,13 +41,8 @@ struct WideArgs {
 // scores 52.6 us against 53.9 us).  Up to eight passes: with more the folded form needs so many
 // registers that it is the slower one (12,000 rows of 3000 scores 33.2 against 32.3 us).
 constexpr int kWideFoldMaxSlots = 8;
-// Most wavefronts per SIMD, where the registers would allow one or two more: a wavefront's loads are
-// all in flight at once, and in a long launch more rows in flight than this are slower (17,143 rows of
-// 2100 scores 31.5 us against 32.0 with seven, 12,414 rows of 2900 scores 31.6 us against 32.1 with
-// five; short launches take the same time or, with twelve passes, up to 4 % less).
-constexpr int wide_max_waves(int slots) { return slots == 9 ? 5 : (slots == 11 || slots == 12 ? 4 : 8); }
 template <int SLOTS, int MODE, int VARIANT, bool PRE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, wide_max_waves(SLOTS))))
+__global__ void __launch_bounds__(256)
 softmax_wide_kernel(WideArgs A)
 {
     __shared__ uint8_t lut_all[4][kPostLutBytes];
@@ -191,22 +186,35 @@ softmax_wide_kernel(WideArgs A)
     }
 }
 
+// LDS asked for beside the kernel's own, so that no more than four workgroups share a compute unit: with
+// 9, 11 and 12 passes the registers would allow five to seven, and in a long launch that many rows in
+// flight (180 KB per unit and more) are slower: 45 million scores in rows of 2200 38.2 us against 39.1, of
+// 2950 38.8 against 39.3; 36 million 31.1 against 31.6 and 31.7 against 32.4; at 25 to 28 million both take
+// the same time, and 15 million are faster with all that fit (14.6 against 15.2, 14.9 against 16.0).
+// With any other number of passes it changes nothing or loses.
+inline size_t wide_extra_lds(int slots, const WideArgs &A)
+{
+    const bool bound = (slots == 9 || slots == 11 || slots == 12) && A.rows * A.cols > 28 * 1000 * 1000;
+    return bound ? 160 * 1024 / 4 - 1024 : 0;         // the kernel's own is less than 1 KB
+}
+
 // mode: SoftmaxDev::mode16 (2 covers 1: t16 == 0 shifts by 0)
 template <int SLOTS>
 static void wide_launch_s(const WideArgs &A, int mode, dim3 grid, hipStream_t stream)
 {
+    const size_t lds = wide_extra_lds(SLOTS, A);
     if constexpr (SLOTS <= kWideFoldMaxSlots) {
         if (A.P.pre_rowconst != 0) {                  // packed arithmetic and a first-degree exponential
-            if (A.P.variant == 0) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, 2, 0, true>), grid, dim3(256), 0, stream, A);
-            else hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, 2, 1, true>), grid, dim3(256), 0, stream, A);
+            if (A.P.variant == 0) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, 2, 0, true>), grid, dim3(256), lds, stream, A);
+            else hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, 2, 1, true>), grid, dim3(256), lds, stream, A);
             return;
         }
     }
 #define IPTQ_WIDE_LAUNCH(MODE)                                                                    \
     do {                                                                                          \
-        if (A.P.variant == 0) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 0, false>), grid, dim3(256), 0, stream, A);      \
-        else if (A.P.variant == 1) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 1, false>), grid, dim3(256), 0, stream, A); \
-        else hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 2, false>), grid, dim3(256), 0, stream, A);                       \
+        if (A.P.variant == 0) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 0, false>), grid, dim3(256), lds, stream, A);      \
+        else if (A.P.variant == 1) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 1, false>), grid, dim3(256), lds, stream, A); \
+        else hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 2, false>), grid, dim3(256), lds, stream, A);                       \
     } while (0)
     if (mode == 0) IPTQ_WIDE_LAUNCH(0);
     else IPTQ_WIDE_LAUNCH(2);
