@@ -34,6 +34,9 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
 // (*done == 0) if the row is too long or the pointers do not qualify.
 hipError_t softmax_rowsdyn_launch(const SoftmaxCall &c, int32_t cols, int post_mode, int64_t *done,
                                   hipStream_t stream);
+// The same for the calls of a batch that one launch can serve together (done[i]: rows served).
+hipError_t softmax_rowsdyn_launch_batch(const SoftmaxCall *calls, const int *post_modes, int n_calls, int32_t cols,
+                                        int64_t *done, hipStream_t stream);
 // One wavefront per row, row in registers, no LDS staging (rows of up to 4093 scores at any
 // alignment, 4096 if a multiple of 4): every row of one call, or none.
 hipError_t softmax_wide_launch(const SoftmaxCall &c, int32_t cols, int post_mode, int64_t *done,

@@ -257,6 +257,11 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
             done[i] = c.rows;
         }
         flush();
+        if (cnt > 1 && err == hipSuccess) {           // several calls of the run-time-row-length kernel in one launch
+            int post_modes[kBatchMax];
+            for (int i = 0; i < cnt; ++i) post_modes[i] = post_mode_of(calls[base + i].P, calls[base + i].out_bits);
+            err = softmax_rowsdyn_launch_batch(calls + base, post_modes, cnt, cols, done, stream);
+        }
         for (int i = 0; i < cnt && err == hipSuccess; ++i) {
             const SoftmaxCall &c = calls[base + i];
             const bool has_pre = !(c.P.pre_m == 1 && c.P.pre_s == 0);

@@ -51,6 +51,9 @@ struct DynArgs {
     int32_t cols_sh;
 };
 
+constexpr int kDynBatchMax = 14;                      // calls per launch of the batch kernel
+struct DynBatch;
+
 // Four entries of a row-major table of `total` entries from entry `idx` on, where idx may lie up
 // to three entries before the table or run past its end (the first and last block of a row that
 // starts off the 16-byte grid): the load is moved inside the table and the entries that exist are
@@ -92,22 +95,21 @@ IPTQ_DEV i32x4 table_block_at(const int32_t *table, int32_t idx, int32_t total)
 // PRE: the requantization in front folded into Eq. 6 where the parameters allow it
 // (SoftmaxDev::pre_rowconst, see softmax_rows_body): 153,984 rows of 401 scores 53.4 us (Bit-exp) and
 // 53.6 us (Shiftmax), what they take without a requantization, against 54.6 and 53.9 us.
+// (wg: this workgroup's index within the call; VARIANT < 0: by the parameters)
 template <int K, int SLOTS, int MODE, int MASKKIND, int VARIANT, bool PRE>
-__global__ void __launch_bounds__(256)
-softmax_rowsdyn_kernel(DynArgs A)
+IPTQ_DEV void softmax_rowsdyn_body(const DynArgs &A, uint32_t wg)
 {
     constexpr int RPW = 64 / K;                       // rows per wavefront, a multiple of 4
     extern __shared__ __attribute__((aligned(16))) uint8_t dyn_lds[];
-    touch_kernel_arguments<MASKKIND == 0 ? offsetof(DynArgs, mask) : sizeof(DynArgs)>();
     const SoftmaxDev &P = A.P;
     const int lane = threadIdx.x & 63;
     // (a scalar: the slab, its table offsets and every test on them then run on the scalar unit)
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t wpb = A.wpb;
-    int64_t slab = (int64_t)blockIdx.x * wpb + wv;
+    int64_t slab = (int64_t)wg * wpb + wv;
     if (A.share_q != 0) {
-        const uint32_t g = mulhi_u32(blockIdx.x, A.share_magic) >> A.share_sh;
-        slab = (int64_t)g * (wpb * A.share_q) + (uint32_t)wv * A.share_q + (blockIdx.x - g * A.share_q);
+        const uint32_t g = mulhi_u32(wg, A.share_magic) >> A.share_sh;
+        slab = (int64_t)g * (wpb * A.share_q) + (uint32_t)wv * A.share_q + (wg - g * A.share_q);
     }
     if (slab >= A.n_slabs) return;                    // no workgroup barrier below
 
@@ -371,7 +373,12 @@ softmax_rowsdyn_kernel(DynArgs A)
     const int32_t lower = low_row ? kI32Min : mx - D;
     const bool any_low = __builtin_amdgcn_ballot_w64(low_row) != 0;
 
-    softmax_slab_math<K, SLOTS, MODE, VARIANT, PM_NONE>(x, w, mx, lower, any_low, lut, P);
+    if (VARIANT == 0 || (VARIANT < 0 && P.variant == 0))
+        softmax_slab_math<K, SLOTS, MODE, 0, PM_NONE>(x, w, mx, lower, any_low, lut, P);
+    else if (VARIANT == 1 || (VARIANT < 0 && P.variant == 1))
+        softmax_slab_math<K, SLOTS, MODE, 1, PM_NONE>(x, w, mx, lower, any_low, lut, P);
+    else
+        softmax_slab_math<K, SLOTS, MODE, 2, PM_NONE>(x, w, mx, lower, any_low, lut, P);
     }
 
     // ---- post step on the packed bytes (a probability is at most 128)
@@ -439,6 +446,36 @@ softmax_rowsdyn_kernel(DynArgs A)
     }
 }
 
+template <int K, int SLOTS, int MODE, int MASKKIND, int VARIANT, bool PRE>
+__global__ void __launch_bounds__(256)
+softmax_rowsdyn_kernel(DynArgs A)
+{
+    touch_kernel_arguments<MASKKIND == 0 ? offsetof(DynArgs, mask) : sizeof(DynArgs)>();
+    softmax_rowsdyn_body<K, SLOTS, MODE, MASKKIND, VARIANT, PRE>(A, blockIdx.x);
+}
+
+// Several calls of one row length (the layers of a sweep) in one launch: packed arithmetic, no mask
+// and no requantization in front; the variant is a wavefront-uniform branch.  Launched one by one such
+// calls cost a launch each and its edges: 12 calls of 2303 x 145
+// scores and a GELU launch take 70.8 us, 15.0 through this kernel; 5 of 1007 x 196 28.8 and 9.2; 2 of
+// 13000 x 196 16.6 and 13.0.
+struct DynBatch {
+    int32_t n_items;
+    uint32_t first_wg[kDynBatchMax];                  // workgroups [first_wg[i], first_wg[i + 1]) serve item i
+    DynArgs item[kDynBatchMax];
+};
+static_assert(sizeof(DynBatch) <= 4096, "kernel arguments are limited to 4 KiB");
+template <int K, int SLOTS>
+__global__ void __launch_bounds__(256)
+softmax_rowsdyn_batch_kernel(DynBatch B)
+{
+    touch_kernel_arguments<64>();                     // where the items start
+    int it = 0;
+    for (int i = 1; i < B.n_items; ++i)
+        if (blockIdx.x >= B.first_wg[i]) it = i;
+    softmax_rowsdyn_body<K, SLOTS, 2, 0, -1, false>(B.item[it], blockIdx.x - B.first_wg[it]);
+}
+
 // mode: SoftmaxDev::mode16 (2 covers 1: t16 == 0 shifts by 0)
 template <int K, int SLOTS>
 static void rowsdyn_launch_ks(const DynArgs &A, int mode, dim3 grid, dim3 block, size_t lds, hipStream_t stream)
@@ -468,15 +505,19 @@ static void rowsdyn_launch_ks(const DynArgs &A, int mode, dim3 grid, dim3 block,
 }
 
 // One launcher per group of layouts, each defined in its own translation unit so that the
-// instantiations compile in parallel.  Each returns false for a slot count it does not hold.
-bool rowsdyn_launch_k1(const DynArgs &, int slots, int mode, dim3, dim3, size_t, hipStream_t);         // 1..8
-bool rowsdyn_launch_k2(const DynArgs &, int slots, int mode, dim3, dim3, size_t, hipStream_t);         // 5..8
-bool rowsdyn_launch_k4(const DynArgs &, int slots, int mode, dim3, dim3, size_t, hipStream_t);         // 5..8
-bool rowsdyn_launch_k8(const DynArgs &, int slots, int mode, dim3, dim3, size_t, hipStream_t);         // 5..8
-bool rowsdyn_launch_k16(const DynArgs &, int slots, int mode, dim3, dim3, size_t, hipStream_t);        // 5..8
-bool rowsdyn_launch_k16_long(const DynArgs &, int slots, int mode, dim3, dim3, size_t, hipStream_t);   // 9..10
+// instantiations compile in parallel: one call, or a batch of calls if the second pointer is set.
+// Each returns false for a slot count it does not hold.
+bool rowsdyn_launch_k1(const DynArgs *, const DynBatch *, int slots, int mode, dim3, dim3, size_t, hipStream_t);         // 1..8
+bool rowsdyn_launch_k2(const DynArgs *, const DynBatch *, int slots, int mode, dim3, dim3, size_t, hipStream_t);         // 5..8
+bool rowsdyn_launch_k4(const DynArgs *, const DynBatch *, int slots, int mode, dim3, dim3, size_t, hipStream_t);         // 5..8
+bool rowsdyn_launch_k8(const DynArgs *, const DynBatch *, int slots, int mode, dim3, dim3, size_t, hipStream_t);         // 5..8
+bool rowsdyn_launch_k16(const DynArgs *, const DynBatch *, int slots, int mode, dim3, dim3, size_t, hipStream_t);        // 5..8
+bool rowsdyn_launch_k16_long(const DynArgs *, const DynBatch *, int slots, int mode, dim3, dim3, size_t, hipStream_t);   // 9..10
 
 #define IPTQ_ROWSDYN_CASE(K, S)                                                                   \
-    case S: rowsdyn_launch_ks<K, S>(A, mode, grid, block, lds, stream); return true;
+    case S:                                                                                       \
+        if (B != nullptr) hipLaunchKernelGGL((softmax_rowsdyn_batch_kernel<K, S>), grid, block, lds, stream, *B); \
+        else rowsdyn_launch_ks<K, S>(*A, mode, grid, block, lds, stream);                         \
+        return true;
 
 }  // namespace iptq

@@ -57,14 +57,10 @@ static int64_t gcd_i64(int64_t a, int64_t b)
     return a;
 }
 
-// Every row of one call if the call qualifies; returns the number of rows served through
-// *done (0: not served, nothing enqueued).
-hipError_t softmax_rowsdyn_launch(const SoftmaxCall &c, int32_t cols, int post_mode, int64_t *done,
-                                  hipStream_t stream)
+// The kernel arguments of one call and its number of workgroups; false if this kernel does not serve it.
+static bool rowsdyn_arguments(const SoftmaxCall &c, int32_t cols, int post_mode, int k, DynArgs *args, int64_t *wgs)
 {
-    *done = 0;
-    int k = 0, slots = 0;
-    if (!rowsdyn_geometry(cols, &k, &slots)) return hipSuccess;
+    DynArgs &A = *args;
     const int rpw = 64 / k;
     const bool has_bias = c.bias != nullptr;
     const bool aligned = ((reinterpret_cast<uintptr_t>(c.scores) | reinterpret_cast<uintptr_t>(c.bias)) & 3) == 0;
@@ -75,12 +71,11 @@ hipError_t softmax_rowsdyn_launch(const SoftmaxCall &c, int32_t cols, int post_m
     // int32 masks are loaded in blocks of four entries at 32-bit byte offsets
     const bool int_mask = c.mask != nullptr;
     const int64_t mask_el = int_mask ? (int64_t)c.P.n_windows * cols * cols : 0;
-    if (int_mask && (mask_el < 4 || mask_el >= ((int64_t)1 << 30))) return hipSuccess;
+    if (int_mask && (mask_el < 4 || mask_el >= ((int64_t)1 << 30))) return false;
     if (c.mask_bits != nullptr && (int64_t)c.P.n_windows * cols * ((cols + 63) / 64) * 8 >= ((int64_t)1 << 31))
-        return hipSuccess;
+        return false;
     const int64_t n_slabs = (c.rows + rpw - 1) / rpw;
-    if (!aligned || !bias_ok || n_slabs == 0) return hipSuccess;
-    DynArgs A;
+    if (!aligned || !bias_ok || n_slabs == 0) return false;
     A.scores = c.scores; A.bias = c.bias; A.out = c.out;
     A.n_slabs = n_slabs; A.tail_rows = (int32_t)(c.rows % rpw);
     A.cols = cols; A.post_mode = post_mode;
@@ -89,13 +84,14 @@ hipError_t softmax_rowsdyn_launch(const SoftmaxCall &c, int32_t cols, int post_m
     A.cols_magic = 0; A.cols_sh = 0;
     if ((c.mask != nullptr || c.mask_bits != nullptr) && cols >= 2 &&
         !make_magic_u32((uint32_t)cols, 31, &A.cols_magic, &A.cols_sh))
-        return hipSuccess;
+        return false;
     A.P = c.P;
     int wpb = 65536 / A.wave_lds;                     // wavefronts per workgroup: 1..4
     if (wpb > 4) wpb = 4;
-    if (wpb < 1) return hipSuccess;
+    if (wpb < 1) return false;
     A.wpb = (uint32_t)wpb;
-    int64_t n_wgs = (n_slabs + wpb - 1) / wpb;
+    int64_t &n_wgs = *wgs;
+    n_wgs = (n_slabs + wpb - 1) / wpb;
     A.share_q = 0; A.share_magic = 0; A.share_sh = 0;
     auto share_every = [&](int64_t period) {          // wavefronts of a workgroup that many rows apart
         const int64_t q = period / gcd_i64(period, rpw);
@@ -116,18 +112,81 @@ hipError_t softmax_rowsdyn_launch(const SoftmaxCall &c, int32_t cols, int post_m
         }
         if (!shared && has_bias) share_every(c.P.bias_period_rows);
     }
-    const dim3 grid((unsigned)n_wgs), block(64 * wpb);
-    const size_t lds = (size_t)A.wave_lds * wpb;
-    bool launched;
-    if (k == 1) launched = rowsdyn_launch_k1(A, slots, c.P.mode16, grid, block, lds, stream);
-    else if (k == 2) launched = rowsdyn_launch_k2(A, slots, c.P.mode16, grid, block, lds, stream);
-    else if (k == 4) launched = rowsdyn_launch_k4(A, slots, c.P.mode16, grid, block, lds, stream);
-    else if (k == 8) launched = rowsdyn_launch_k8(A, slots, c.P.mode16, grid, block, lds, stream);
-    else launched = slots <= 8 ? rowsdyn_launch_k16(A, slots, c.P.mode16, grid, block, lds, stream)
-                               : rowsdyn_launch_k16_long(A, slots, c.P.mode16, grid, block, lds, stream);
-    if (!launched) return hipSuccess;                 // no such layout: the caller's next kernel serves it
+    return true;
+}
+
+static bool rowsdyn_launch(const DynArgs *A, const DynBatch *B, int k, int slots, int mode, dim3 grid, dim3 block,
+                           size_t lds, hipStream_t stream)
+{
+    if (k == 1) return rowsdyn_launch_k1(A, B, slots, mode, grid, block, lds, stream);
+    if (k == 2) return rowsdyn_launch_k2(A, B, slots, mode, grid, block, lds, stream);
+    if (k == 4) return rowsdyn_launch_k4(A, B, slots, mode, grid, block, lds, stream);
+    if (k == 8) return rowsdyn_launch_k8(A, B, slots, mode, grid, block, lds, stream);
+    return slots <= 8 ? rowsdyn_launch_k16(A, B, slots, mode, grid, block, lds, stream)
+                      : rowsdyn_launch_k16_long(A, B, slots, mode, grid, block, lds, stream);
+}
+
+// Every row of one call if the call qualifies; returns the number of rows served through
+// *done (0: not served, nothing enqueued).
+hipError_t softmax_rowsdyn_launch(const SoftmaxCall &c, int32_t cols, int post_mode, int64_t *done,
+                                  hipStream_t stream)
+{
+    *done = 0;
+    int k = 0, slots = 0;
+    if (!rowsdyn_geometry(cols, &k, &slots)) return hipSuccess;
+    DynArgs A;
+    int64_t n_wgs = 0;
+    if (!rowsdyn_arguments(c, cols, post_mode, k, &A, &n_wgs)) return hipSuccess;
+    if (!rowsdyn_launch(&A, nullptr, k, slots, c.P.mode16, dim3((unsigned)n_wgs), dim3(64 * A.wpb),
+                        (size_t)A.wave_lds * A.wpb, stream))
+        return hipSuccess;                            // no such layout: the caller's next kernel serves it
     *done = c.rows;
     return hipGetLastError();
+}
+
+// The calls of a batch that one launch can serve together: packed arithmetic without a mask and
+// without a requantization in front.  done[i] becomes the rows of every call that was served; fewer
+// than two such calls are left alone, and so is what does not qualify.
+hipError_t softmax_rowsdyn_launch_batch(const SoftmaxCall *calls, const int *post_modes, int n_calls, int32_t cols,
+                                        int64_t *done, hipStream_t stream)
+{
+    int k = 0, slots = 0;
+    if (!rowsdyn_geometry(cols, &k, &slots)) return hipSuccess;
+    DynBatch B;
+    int of[kDynBatchMax];                             // which call an item is
+    int64_t total_wgs = 0;
+    B.n_items = 0;
+    auto flush = [&]() -> hipError_t {
+        if (B.n_items >= 2) {
+            const uint32_t wpb = B.item[0].wpb;       // the same for every call of a row length
+            if (!rowsdyn_launch(nullptr, &B, k, slots, 2, dim3((unsigned)total_wgs), dim3(64 * wpb),
+                                (size_t)B.item[0].wave_lds * wpb, stream))
+                return hipSuccess;
+            for (int i = 0; i < B.n_items; ++i) done[of[i]] = calls[of[i]].rows;
+        }
+        B.n_items = 0;
+        total_wgs = 0;
+        return hipGetLastError();
+    };
+    for (int i = 0; i < n_calls; ++i) {
+        const SoftmaxCall &c = calls[i];
+        if (done[i] != 0 || c.mask != nullptr || c.mask_bits != nullptr || c.P.mode16 == 0 || c.P.pre_mode != 0 ||
+            !(c.algo == IPTQ_ALGO_AUTO || c.algo == IPTQ_ALGO_DYNAMIC || c.algo == IPTQ_ALGO_SLAB))
+            continue;
+        DynArgs A;
+        int64_t n_wgs = 0;
+        if (!rowsdyn_arguments(c, cols, post_modes[i], k, &A, &n_wgs)) continue;
+        // (a launch has fewer than 2^32 work-items)
+        if (B.n_items == kDynBatchMax || (total_wgs + n_wgs) * 256 >= ((int64_t)1 << 32)) {
+            const hipError_t e = flush();
+            if (e != hipSuccess) return e;
+        }
+        B.first_wg[B.n_items] = (uint32_t)total_wgs;
+        B.item[B.n_items] = A;
+        of[B.n_items++] = i;
+        total_wgs += n_wgs;
+    }
+    return flush();
 }
 
 }  // namespace iptq

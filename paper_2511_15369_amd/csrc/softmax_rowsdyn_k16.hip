@@ -2,7 +2,7 @@
 #include "softmax_rowsdyn.h"
 
 namespace iptq {
-bool rowsdyn_launch_k16(const DynArgs &A, int slots, int mode, dim3 grid, dim3 block, size_t lds, hipStream_t stream)
+bool rowsdyn_launch_k16(const DynArgs *A, const DynBatch *B, int slots, int mode, dim3 grid, dim3 block, size_t lds, hipStream_t stream)
 {
     switch (slots) {
     IPTQ_ROWSDYN_CASE(16, 5)
