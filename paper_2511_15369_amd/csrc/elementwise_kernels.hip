@@ -92,14 +92,8 @@ struct GeluBatch {
 };
 static_assert(sizeof(GeluBatch) <= 4096, "kernel arguments are limited to 4 KiB");
 
-__global__ void __launch_bounds__(256)
-gelu_i8_table_kernel(GeluBatch B)
+IPTQ_DEV void gelu_i8_table_body(const GeluItem &I)
 {
-    touch_kernel_arguments<8 + sizeof(GeluItem)>();       // the batch header and its first problem
-    int it = 0;
-    for (int i = 1; i < B.n_items; ++i)
-        if (blockIdx.x >= B.item[i].first_wg) it = i;
-    const GeluItem &I = B.item[it];
     __shared__ uint8_t table[256];
     const int64_t n = I.n;
     const int64_t n16 = n >> 4;
@@ -142,15 +136,36 @@ gelu_i8_table_kernel(GeluBatch B)
     }
 }
 
+// One problem: 112 bytes of arguments.  The host writes a launch's arguments into device memory, and
+// that is what a short call costs: an empty kernel takes 2.7 us of host time with 32 bytes of arguments,
+// 2.8 with 64, 3.5 with 256 and 3.9 from 1.7 KB on.  (No kernel of this file asks for its grid's size
+// either: it comes with 256 bytes of other implicit arguments.)
+__global__ void __launch_bounds__(256)
+gelu_i8_table_kernel(GeluItem I)
+{
+    touch_kernel_arguments<sizeof(GeluItem)>();
+    gelu_i8_table_body(I);
+}
+
+__global__ void __launch_bounds__(256)
+gelu_i8_table_batch_kernel(GeluBatch B)
+{
+    touch_kernel_arguments<8 + sizeof(GeluItem)>();       // the batch header and its first problem
+    int it = 0;
+    for (int i = 1; i < B.n_items; ++i)
+        if (blockIdx.x >= B.item[i].first_wg) it = i;
+    gelu_i8_table_body(B.item[it]);
+}
+
 // int8 -> int8, polynomial evaluated per element (no table).
 template <int MODE>   // 0: general evaluation, 1: short evaluation degree 2, 2: short evaluation degree 4
 __global__ void __launch_bounds__(256)
-gelu_i8_direct_kernel(const uint8_t *in, uint8_t *out, int64_t n, GeluDev P)
+gelu_i8_direct_kernel(const uint8_t *in, uint8_t *out, int64_t n, uint32_t wgs, GeluDev P)
 {
     const int64_t n16 = n >> 4;
     const u32x4 *in4 = reinterpret_cast<const u32x4 *>(in);
     u32x4 *out4 = reinterpret_cast<u32x4 *>(out);
-    const int64_t stride = (int64_t)gridDim.x * 256;
+    const int64_t stride = (int64_t)wgs * 256;
     auto one = [&](int32_t x) -> int32_t {
         if (MODE == 0) return gelu_eval_any(x, P);
         const int32_t q = clamp_i32(x - P.zp_in, -P.max_abs_q, P.max_abs_q);
@@ -174,9 +189,9 @@ gelu_i8_direct_kernel(const uint8_t *in, uint8_t *out, int64_t n, GeluDev P)
 
 // Unaligned or tiny int8 tensors: one element per thread.
 __global__ void __launch_bounds__(256)
-gelu_i8_bytes_kernel(const uint8_t *in, uint8_t *out, int64_t n, GeluDev P)
+gelu_i8_bytes_kernel(const uint8_t *in, uint8_t *out, int64_t n, uint32_t wgs, GeluDev P)
 {
-    const int64_t stride = (int64_t)gridDim.x * 256;
+    const int64_t stride = (int64_t)wgs * 256;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride)
         out[i] = (uint8_t)gelu_eval_any((int32_t)(int8_t)in[i], P);
 }
@@ -191,9 +206,9 @@ gelu_i8_bytes_kernel(const uint8_t *in, uint8_t *out, int64_t n, GeluDev P)
 // 16-byte grid and one off it.
 typedef i32x4 __attribute__((aligned(4))) i32x4_a4;
 template <bool ALIGNED, typename F>
-IPTQ_DEV void stream_i32_to_bytes(const int32_t *in, uint8_t *out, int64_t n, int32_t head, F one)
+IPTQ_DEV void stream_i32_to_bytes(const int32_t *in, uint8_t *out, int64_t n, int32_t head, uint32_t wgs, F one)
 {
-    const int64_t stride = (int64_t)gridDim.x * 256;
+    const int64_t stride = (int64_t)wgs * 256;
     const int64_t tid = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (ALIGNED) {
         const int64_t n4 = n >> 2;
@@ -221,7 +236,7 @@ IPTQ_DEV void stream_i32_to_bytes(const int32_t *in, uint8_t *out, int64_t n, in
 // (pre_s >= 15) pre-requantization.
 template <bool ALIGNED, int MODE>
 __global__ void __launch_bounds__(256)
-gelu_i32_kernel(const int32_t *in, uint8_t *out, int64_t n, int32_t head, GeluDev P)
+gelu_i32_kernel(const int32_t *in, uint8_t *out, int64_t n, int32_t head, uint32_t wgs, GeluDev P)
 {
     GeluDev Q = P;
     Q.zp_in = 0;
@@ -241,7 +256,7 @@ gelu_i32_kernel(const int32_t *in, uint8_t *out, int64_t n, int32_t head, GeluDe
         const int32_t q = clamp_i32(__builtin_elementwise_sub_sat(x, P.zp_in), -P.max_abs_q, P.max_abs_q);
         return gelu_eval_fast<MODE == 2>(q, P);
     };
-    stream_i32_to_bytes<ALIGNED>(in, out, n, head, one);
+    stream_i32_to_bytes<ALIGNED>(in, out, n, head, wgs, one);
 }
 
 // int32 accumulators -> int8 GELU through a table.  After the requantization in front the
@@ -271,7 +286,7 @@ bool gelu32_looping_grid(int64_t n, bool out_on_line)
 }
 template <bool ALIGNED>
 __global__ void __launch_bounds__(256)
-gelu_i32_table_kernel(const int32_t *in, uint8_t *out, int64_t n, int32_t head, GeluDev P)
+gelu_i32_table_kernel(const int32_t *in, uint8_t *out, int64_t n, int32_t head, uint32_t wgs, GeluDev P)
 {
     __shared__ uint8_t table[2 * kGelu32TableMaxQ + 2];
     GeluDev Q = P;
@@ -288,7 +303,7 @@ gelu_i32_table_kernel(const int32_t *in, uint8_t *out, int64_t n, int32_t head, 
     };
     if (ALIGNED) {
         // the first chunk's load is in flight while the table is built
-        const int64_t stride = (int64_t)gridDim.x * 256;
+        const int64_t stride = (int64_t)wgs * 256;
         const int64_t n4 = n >> 2;
         const i32x4_a4 *in4 = reinterpret_cast<const i32x4_a4 *>(in);
         uint32_t *out32 = reinterpret_cast<uint32_t *>(out);
@@ -316,19 +331,19 @@ gelu_i32_table_kernel(const int32_t *in, uint8_t *out, int64_t n, int32_t head, 
     for (int32_t e = threadIdx.x; e <= 2 * lim; e += 256)
         table[e] = (uint8_t)gelu_eval_any(e - lim, Q);
     __syncthreads();
-    stream_i32_to_bytes<ALIGNED>(in, out, n, head, one);
+    stream_i32_to_bytes<ALIGNED>(in, out, n, head, wgs, one);
 }
 
 // int32 -> int8 / uint8 requantization.
 template <bool ALIGNED>
 __global__ void __launch_bounds__(256)
-requant_kernel(const int32_t *in, uint8_t *out, int64_t n, int32_t head, DyadicDev P)
+requant_kernel(const int32_t *in, uint8_t *out, int64_t n, int32_t head, uint32_t wgs, DyadicDev P)
 {
     auto one = [&](int32_t x) -> int32_t {
         return P.s >= 16 ? requant_dev<true>(x, P.m, P.s, P.zp, P.qmin, P.qmax)
                          : requant_dev<false>(x, P.m, P.s, P.zp, P.qmin, P.qmax);
     };
-    stream_i32_to_bytes<ALIGNED>(in, out, n, head, one);
+    stream_i32_to_bytes<ALIGNED>(in, out, n, head, wgs, one);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -350,7 +365,8 @@ hipError_t gelu_i8_dispatch(const GeluCall *calls, int n_calls, hipStream_t stre
     unsigned total_wgs = 0;
     auto flush = [&]() {
         if (B.n_items == 0) return;
-        hipLaunchKernelGGL(gelu_i8_table_kernel, dim3(total_wgs), dim3(256), 0, stream, B);
+        if (B.n_items == 1) launch_kernel(gelu_i8_table_kernel, dim3(total_wgs), dim3(256), 0, stream, B.item[0]);
+        else launch_kernel(gelu_i8_table_batch_kernel, dim3(total_wgs), dim3(256), 0, stream, B);
         B.n_items = 0;
         total_wgs = 0;
     };
@@ -363,16 +379,16 @@ hipError_t gelu_i8_dispatch(const GeluCall *calls, int n_calls, hipStream_t stre
         // bytes in front of the output's first 16-byte boundary
         const uint32_t head = (uint32_t)((0 - reinterpret_cast<uintptr_t>(g.out)) & 15);
         if (!aligned && (g.force_direct || g.n < 64)) {
-            hipLaunchKernelGGL(gelu_i8_bytes_kernel, dim3(grid_for(g.n, 256)), dim3(256), 0, stream,
-                               uin, uout, g.n, g.P);
+            const dim3 grid(grid_for(g.n, 256));
+            launch_kernel(gelu_i8_bytes_kernel, grid, dim3(256), 0, stream, uin, uout, g.n, grid.x, g.P);
         } else if (g.force_direct) {
             const dim3 grid(grid_for(g.n >> 4, 256, 256 * 64));
             if (!g.P.fast)
-                hipLaunchKernelGGL(gelu_i8_direct_kernel<0>, grid, dim3(256), 0, stream, uin, uout, g.n, g.P);
+                launch_kernel(gelu_i8_direct_kernel<0>, grid, dim3(256), 0, stream, uin, uout, g.n, grid.x, g.P);
             else if (!g.P.quartic)
-                hipLaunchKernelGGL(gelu_i8_direct_kernel<1>, grid, dim3(256), 0, stream, uin, uout, g.n, g.P);
+                launch_kernel(gelu_i8_direct_kernel<1>, grid, dim3(256), 0, stream, uin, uout, g.n, grid.x, g.P);
             else
-                hipLaunchKernelGGL(gelu_i8_direct_kernel<2>, grid, dim3(256), 0, stream, uin, uout, g.n, g.P);
+                launch_kernel(gelu_i8_direct_kernel<2>, grid, dim3(256), 0, stream, uin, uout, g.n, grid.x, g.P);
         } else {
             if (B.n_items == kGeluBatchMax) flush();
             GeluItem &it = B.item[B.n_items++];
@@ -384,7 +400,7 @@ hipError_t gelu_i8_dispatch(const GeluCall *calls, int n_calls, hipStream_t stre
         }
     }
     flush();
-    return hipGetLastError();
+    return take_launch_status();
 }
 
 // The vector path of the int32-input kernels wants a 4-byte aligned output: the elements in
@@ -407,22 +423,23 @@ hipError_t gelu_i32_dispatch(const int32_t *in, int8_t *out, int64_t n, const Ge
     const int mode = (P.fast && P.pre_mode != 2) ? (P.quartic ? 2 : 1) : 0;
     const bool table = !force_direct && P.max_abs_q <= kGelu32TableMaxQ;
     if (aligned) {
-        const dim3 grid(grid_for(n >> 2, 256, 256 * 64)), block(256);
+        dim3 grid(grid_for(n >> 2, 256, 256 * 64));
+        const dim3 block(256);
         const bool looping = gelu32_looping_grid(n, (reinterpret_cast<uintptr_t>(uout) & 63) == 0);
         if (table)
-            hipLaunchKernelGGL(gelu_i32_table_kernel<true>, dim3(grid_for(n >> 2, 256, looping ? kGelu32ShortGridCap : kGelu32TableGridCap)),
-                               block, 0, stream, in, uout, n, head, P);
-        else if (mode == 0) hipLaunchKernelGGL((gelu_i32_kernel<true, 0>), grid, block, 0, stream, in, uout, n, head, P);
-        else if (mode == 1) hipLaunchKernelGGL((gelu_i32_kernel<true, 1>), grid, block, 0, stream, in, uout, n, head, P);
-        else hipLaunchKernelGGL((gelu_i32_kernel<true, 2>), grid, block, 0, stream, in, uout, n, head, P);
+            grid = dim3(grid_for(n >> 2, 256, looping ? kGelu32ShortGridCap : kGelu32TableGridCap));
+        if (table) launch_kernel(gelu_i32_table_kernel<true>, grid, block, 0, stream, in, uout, n, head, grid.x, P);
+        else if (mode == 0) launch_kernel((gelu_i32_kernel<true, 0>), grid, block, 0, stream, in, uout, n, head, grid.x, P);
+        else if (mode == 1) launch_kernel((gelu_i32_kernel<true, 1>), grid, block, 0, stream, in, uout, n, head, grid.x, P);
+        else launch_kernel((gelu_i32_kernel<true, 2>), grid, block, 0, stream, in, uout, n, head, grid.x, P);
     } else {
         const dim3 grid(grid_for(n, 256)), block(256);
-        if (table) hipLaunchKernelGGL(gelu_i32_table_kernel<false>, grid, block, 0, stream, in, uout, n, 0, P);
-        else if (mode == 0) hipLaunchKernelGGL((gelu_i32_kernel<false, 0>), grid, block, 0, stream, in, uout, n, 0, P);
-        else if (mode == 1) hipLaunchKernelGGL((gelu_i32_kernel<false, 1>), grid, block, 0, stream, in, uout, n, 0, P);
-        else hipLaunchKernelGGL((gelu_i32_kernel<false, 2>), grid, block, 0, stream, in, uout, n, 0, P);
+        if (table) launch_kernel(gelu_i32_table_kernel<false>, grid, block, 0, stream, in, uout, n, 0, grid.x, P);
+        else if (mode == 0) launch_kernel((gelu_i32_kernel<false, 0>), grid, block, 0, stream, in, uout, n, 0, grid.x, P);
+        else if (mode == 1) launch_kernel((gelu_i32_kernel<false, 1>), grid, block, 0, stream, in, uout, n, 0, grid.x, P);
+        else launch_kernel((gelu_i32_kernel<false, 2>), grid, block, 0, stream, in, uout, n, 0, grid.x, P);
     }
-    return hipGetLastError();
+    return take_launch_status();
 }
 
 hipError_t requant_dispatch(const int32_t *in, void *out, int64_t n, const DyadicDev &P,
@@ -435,13 +452,14 @@ hipError_t requant_dispatch(const int32_t *in, void *out, int64_t n, const Dyadi
     // 49 MB 9.4 against 10.7, 98 MB 16.7 against 18.2); from 200 MB on the order reverses
     // (298 MB: 48.8 against 47.3 us).
     const int64_t cap = n <= 25 * 1000 * 1000 ? 256 * 8 : 256 * 64;
-    if (peel_to_dword_out(in, uout, n, &head))
-        hipLaunchKernelGGL(requant_kernel<true>, dim3(grid_for(n >> 2, 256, cap)), dim3(256), 0, stream, in,
-                           uout, n, head, P);
-    else
-        hipLaunchKernelGGL(requant_kernel<false>, dim3(grid_for(n, 256)), dim3(256), 0, stream, in, uout,
-                           n, 0, P);
-    return hipGetLastError();
+    if (peel_to_dword_out(in, uout, n, &head)) {
+        const dim3 grid(grid_for(n >> 2, 256, cap));
+        launch_kernel(requant_kernel<true>, grid, dim3(256), 0, stream, in, uout, n, head, grid.x, P);
+    } else {
+        const dim3 grid(grid_for(n, 256));
+        launch_kernel(requant_kernel<false>, grid, dim3(256), 0, stream, in, uout, n, 0, grid.x, P);
+    }
+    return take_launch_status();
 }
 
 }  // namespace iptq

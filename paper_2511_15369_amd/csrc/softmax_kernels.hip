@@ -100,9 +100,9 @@ hipError_t pack_window_mask_dispatch(const int32_t *mask, int64_t n_queries, int
 {
     const int32_t words = (cols + 63) / 64;           // at most 1024
     if (n_queries <= 0) return hipSuccess;
-    hipLaunchKernelGGL(pack_window_mask_kernel, dim3((unsigned)((n_queries + 255) / 256), (unsigned)words),
+    launch_kernel(pack_window_mask_kernel, dim3((unsigned)((n_queries + 255) / 256), (unsigned)words),
                        dim3(256), 0, stream, mask, n_queries, cols, words, bits);
-    return hipGetLastError();
+    return take_launch_status();
 }
 
 // ---------------------------------------------------------------------------------------
@@ -125,15 +125,15 @@ static hipError_t launch_generic(const int32_t *scores, const int32_t *bias, con
     if (n <= 0) return hipSuccess;
     const dim3 grid((unsigned)((n + 3) / 4)), block(256);
     if (P.variant == 0)
-        hipLaunchKernelGGL(softmax_generic_kernel<0>, grid, block, 0, stream, scores, bias, mask, mask_bits, out,
+        launch_kernel(softmax_generic_kernel<0>, grid, block, 0, stream, scores, bias, mask, mask_bits, out,
                            row_begin, row_end, cols, (int32_t)has_bias, (int32_t)has_pre, P);
     else if (P.variant == 1)
-        hipLaunchKernelGGL(softmax_generic_kernel<1>, grid, block, 0, stream, scores, bias, mask, mask_bits, out,
+        launch_kernel(softmax_generic_kernel<1>, grid, block, 0, stream, scores, bias, mask, mask_bits, out,
                            row_begin, row_end, cols, (int32_t)has_bias, (int32_t)has_pre, P);
     else
-        hipLaunchKernelGGL(softmax_generic_kernel<2>, grid, block, 0, stream, scores, bias, mask, mask_bits, out,
+        launch_kernel(softmax_generic_kernel<2>, grid, block, 0, stream, scores, bias, mask, mask_bits, out,
                            row_begin, row_end, cols, (int32_t)has_bias, (int32_t)has_pre, P);
-    return hipGetLastError();
+    return take_launch_status();
 }
 
 // Enqueue the softmax of every call (all with the same row length).  Calls that can use a

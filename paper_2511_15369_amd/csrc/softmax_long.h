@@ -304,9 +304,9 @@ static void long_launch_s(const WideArgs &A, int mode, dim3 grid, hipStream_t st
 {
 #define IPTQ_LONG_LAUNCH(MODE, EXTRA)                                                             \
     do {                                                                                          \
-        if (A.P.variant == 0) hipLaunchKernelGGL((softmax_long_kernel<SLOTS, MODE, 0, EXTRA>), grid, dim3(64 * kLongWaves), 0, stream, A);      \
-        else if (A.P.variant == 1) hipLaunchKernelGGL((softmax_long_kernel<SLOTS, MODE, 1, EXTRA>), grid, dim3(64 * kLongWaves), 0, stream, A); \
-        else hipLaunchKernelGGL((softmax_long_kernel<SLOTS, MODE, 2, EXTRA>), grid, dim3(64 * kLongWaves), 0, stream, A);                       \
+        if (A.P.variant == 0) launch_kernel((softmax_long_kernel<SLOTS, MODE, 0, EXTRA>), grid, dim3(64 * kLongWaves), 0, stream, A);      \
+        else if (A.P.variant == 1) launch_kernel((softmax_long_kernel<SLOTS, MODE, 1, EXTRA>), grid, dim3(64 * kLongWaves), 0, stream, A); \
+        else launch_kernel((softmax_long_kernel<SLOTS, MODE, 2, EXTRA>), grid, dim3(64 * kLongWaves), 0, stream, A);                       \
     } while (0)
     const bool extra = A.bias != nullptr || A.P.pre_mode != 0;
     if (mode == 0 && extra) IPTQ_LONG_LAUNCH(0, true);

@@ -44,7 +44,7 @@ hipError_t softmax_long_launch(const SoftmaxCall &c, int32_t cols, int post_mode
                                       : long_launch_p13_16(A, slots, mode, grid, stream);
     if (!launched) return hipSuccess;
     *done = c.rows;
-    return hipGetLastError();
+    return take_launch_status();
 }
 
 }  // namespace iptq

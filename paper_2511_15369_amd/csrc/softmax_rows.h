@@ -954,11 +954,11 @@ IPTQ_ROWS_SHAPES_ALT(IPTQ_DECLARE_ROWS_LAUNCHER)
 #define IPTQ_ROWS_LAUNCH(COLS, K, MODE, BIAS, PM, MASK)                                           \
     do {                                                                                          \
         if constexpr (MASK == 1)                                                                  \
-            hipLaunchKernelGGL((softmax_rows_masked_kernel<COLS, K, MODE, PM>), grid, block, 0, stream, B);   \
+            launch_kernel((softmax_rows_masked_kernel<COLS, K, MODE, PM>), grid, block, 0, stream, B);   \
         else if constexpr (MASK == 2)                                                             \
-            hipLaunchKernelGGL((softmax_rows_maskbits_kernel<COLS, K, MODE, PM>), grid, block, 0, stream, B); \
+            launch_kernel((softmax_rows_maskbits_kernel<COLS, K, MODE, PM>), grid, block, 0, stream, B); \
         else                                                                                      \
-            hipLaunchKernelGGL((softmax_rows_kernel<COLS, K, MODE, BIAS, PM>), grid, block, 0, stream, B);    \
+            launch_kernel((softmax_rows_kernel<COLS, K, MODE, BIAS, PM>), grid, block, 0, stream, B);    \
     } while (0)
 
 template <int COLS, int K, bool BIAS, int MASK>
@@ -976,7 +976,7 @@ static hipError_t launch_rows_b(const SoftmaxBatch &B, unsigned total_wgs, int m
     else if (mode == 1) { IPTQ_ROWS_LAUNCH_PM(1) }
     else { IPTQ_ROWS_LAUNCH_PM(2) }
 #undef IPTQ_ROWS_LAUNCH_PM
-    return hipGetLastError();
+    return take_launch_status();
 }
 
 template <int COLS, int K>
@@ -985,14 +985,14 @@ static hipError_t launch_rows_requant(const SoftmaxBatch &B, unsigned total_wgs,
 {
     const dim3 grid(total_wgs), block(64 * kRowsWpb);
     if (mode == 1 && post_mode == PM_NONE)
-        hipLaunchKernelGGL((softmax_rows_requant_kernel<COLS, K, 1, PM_NONE>), grid, block, 0, stream, B);
+        launch_kernel((softmax_rows_requant_kernel<COLS, K, 1, PM_NONE>), grid, block, 0, stream, B);
     else if (mode == 1)
-        hipLaunchKernelGGL((softmax_rows_requant_kernel<COLS, K, 1, PM_CLAMP127>), grid, block, 0, stream, B);
+        launch_kernel((softmax_rows_requant_kernel<COLS, K, 1, PM_CLAMP127>), grid, block, 0, stream, B);
     else if (post_mode == PM_NONE)
-        hipLaunchKernelGGL((softmax_rows_requant_kernel<COLS, K, 2, PM_NONE>), grid, block, 0, stream, B);
+        launch_kernel((softmax_rows_requant_kernel<COLS, K, 2, PM_NONE>), grid, block, 0, stream, B);
     else
-        hipLaunchKernelGGL((softmax_rows_requant_kernel<COLS, K, 2, PM_CLAMP127>), grid, block, 0, stream, B);
-    return hipGetLastError();
+        launch_kernel((softmax_rows_requant_kernel<COLS, K, 2, PM_CLAMP127>), grid, block, 0, stream, B);
+    return take_launch_status();
 }
 
 template <int COLS, int K>

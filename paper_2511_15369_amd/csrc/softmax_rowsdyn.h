@@ -482,14 +482,14 @@ static void rowsdyn_launch_ks(const DynArgs &A, int mode, dim3 grid, dim3 block,
 {
 #define IPTQ_ROWSDYN_LAUNCH(MODE, MASKKIND)                                                       \
     do {                                                                                          \
-        if (A.P.variant == 0) hipLaunchKernelGGL((softmax_rowsdyn_kernel<K, SLOTS, MODE, MASKKIND, 0, false>), grid, block, lds, stream, A);      \
-        else if (A.P.variant == 1) hipLaunchKernelGGL((softmax_rowsdyn_kernel<K, SLOTS, MODE, MASKKIND, 1, false>), grid, block, lds, stream, A); \
-        else hipLaunchKernelGGL((softmax_rowsdyn_kernel<K, SLOTS, MODE, MASKKIND, 2, false>), grid, block, lds, stream, A);                       \
+        if (A.P.variant == 0) launch_kernel((softmax_rowsdyn_kernel<K, SLOTS, MODE, MASKKIND, 0, false>), grid, block, lds, stream, A);      \
+        else if (A.P.variant == 1) launch_kernel((softmax_rowsdyn_kernel<K, SLOTS, MODE, MASKKIND, 1, false>), grid, block, lds, stream, A); \
+        else launch_kernel((softmax_rowsdyn_kernel<K, SLOTS, MODE, MASKKIND, 2, false>), grid, block, lds, stream, A);                       \
     } while (0)
     // pre_rowconst: packed arithmetic and a first-degree exponential
     if (A.P.pre_rowconst != 0 && A.mask == nullptr && A.mask_bits == nullptr) {
-        if (A.P.variant == 0) hipLaunchKernelGGL((softmax_rowsdyn_kernel<K, SLOTS, 2, 0, 0, true>), grid, block, lds, stream, A);
-        else hipLaunchKernelGGL((softmax_rowsdyn_kernel<K, SLOTS, 2, 0, 1, true>), grid, block, lds, stream, A);
+        if (A.P.variant == 0) launch_kernel((softmax_rowsdyn_kernel<K, SLOTS, 2, 0, 0, true>), grid, block, lds, stream, A);
+        else launch_kernel((softmax_rowsdyn_kernel<K, SLOTS, 2, 0, 1, true>), grid, block, lds, stream, A);
         return;
     }
 #define IPTQ_ROWSDYN_LAUNCH_MASK(MODE)                                                            \
@@ -516,7 +516,7 @@ bool rowsdyn_launch_k16_long(const DynArgs *, const DynBatch *, int slots, int m
 
 #define IPTQ_ROWSDYN_CASE(K, S)                                                                   \
     case S:                                                                                       \
-        if (B != nullptr) hipLaunchKernelGGL((softmax_rowsdyn_batch_kernel<K, S>), grid, block, lds, stream, *B); \
+        if (B != nullptr) launch_kernel((softmax_rowsdyn_batch_kernel<K, S>), grid, block, lds, stream, *B); \
         else rowsdyn_launch_ks<K, S>(*A, mode, grid, block, lds, stream);                         \
         return true;
 

@@ -141,7 +141,7 @@ hipError_t softmax_rowsdyn_launch(const SoftmaxCall &c, int32_t cols, int post_m
                         (size_t)A.wave_lds * A.wpb, stream))
         return hipSuccess;                            // no such layout: the caller's next kernel serves it
     *done = c.rows;
-    return hipGetLastError();
+    return take_launch_status();
 }
 
 // The calls of a batch that one launch can serve together: packed arithmetic without a mask and
@@ -166,7 +166,7 @@ hipError_t softmax_rowsdyn_launch_batch(const SoftmaxCall *calls, const int *pos
         }
         B.n_items = 0;
         total_wgs = 0;
-        return hipGetLastError();
+        return take_launch_status();
     };
     for (int i = 0; i < n_calls; ++i) {
         const SoftmaxCall &c = calls[i];

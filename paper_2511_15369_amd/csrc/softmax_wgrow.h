@@ -185,11 +185,11 @@ static void wgrow_launch_ws(const WideArgs &A, int mode, dim3 grid, hipStream_t 
 {
 #define IPTQ_WGROW_LAUNCH(MODE)                                                                   \
     do {                                                                                          \
-        if constexpr (WAVES == 4) hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, kAnyVariant>), grid, dim3(64 * WAVES), 0, stream, A); \
-        else if constexpr (WAVES == 16) hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, kFirstDegree>), grid, dim3(64 * WAVES), 0, stream, A); \
-        else if (A.P.variant == 0) hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 0>), grid, dim3(64 * WAVES), 0, stream, A); \
-        else if (A.P.variant == 1) hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 1>), grid, dim3(64 * WAVES), 0, stream, A); \
-        else hipLaunchKernelGGL((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 2>), grid, dim3(64 * WAVES), 0, stream, A);                       \
+        if constexpr (WAVES == 4) launch_kernel((softmax_wgrow_kernel<WAVES, SLOTS, MODE, kAnyVariant>), grid, dim3(64 * WAVES), 0, stream, A); \
+        else if constexpr (WAVES == 16) launch_kernel((softmax_wgrow_kernel<WAVES, SLOTS, MODE, kFirstDegree>), grid, dim3(64 * WAVES), 0, stream, A); \
+        else if (A.P.variant == 0) launch_kernel((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 0>), grid, dim3(64 * WAVES), 0, stream, A); \
+        else if (A.P.variant == 1) launch_kernel((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 1>), grid, dim3(64 * WAVES), 0, stream, A); \
+        else launch_kernel((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 2>), grid, dim3(64 * WAVES), 0, stream, A);                       \
     } while (0)
     if (mode == 0) IPTQ_WGROW_LAUNCH(0);
     else IPTQ_WGROW_LAUNCH(2);

@@ -74,7 +74,7 @@ hipError_t softmax_wgrow_launch(const SoftmaxCall &c, int32_t cols, int post_mod
     else launched = wgrow_launch_w16(A, slots, mode, grid, stream);
     if (!launched) return hipSuccess;
     *done = rows;
-    return hipGetLastError();
+    return take_launch_status();
 }
 
 }  // namespace iptq

@@ -205,16 +205,16 @@ static void wide_launch_s(const WideArgs &A, int mode, dim3 grid, hipStream_t st
     const size_t lds = wide_extra_lds(SLOTS, A);
     if constexpr (SLOTS <= kWideFoldMaxSlots) {
         if (A.P.pre_rowconst != 0) {                  // packed arithmetic and a first-degree exponential
-            if (A.P.variant == 0) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, 2, 0, true>), grid, dim3(256), lds, stream, A);
-            else hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, 2, 1, true>), grid, dim3(256), lds, stream, A);
+            if (A.P.variant == 0) launch_kernel((softmax_wide_kernel<SLOTS, 2, 0, true>), grid, dim3(256), lds, stream, A);
+            else launch_kernel((softmax_wide_kernel<SLOTS, 2, 1, true>), grid, dim3(256), lds, stream, A);
             return;
         }
     }
 #define IPTQ_WIDE_LAUNCH(MODE)                                                                    \
     do {                                                                                          \
-        if (A.P.variant == 0) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 0, false>), grid, dim3(256), lds, stream, A);      \
-        else if (A.P.variant == 1) hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 1, false>), grid, dim3(256), lds, stream, A); \
-        else hipLaunchKernelGGL((softmax_wide_kernel<SLOTS, MODE, 2, false>), grid, dim3(256), lds, stream, A);                       \
+        if (A.P.variant == 0) launch_kernel((softmax_wide_kernel<SLOTS, MODE, 0, false>), grid, dim3(256), lds, stream, A);      \
+        else if (A.P.variant == 1) launch_kernel((softmax_wide_kernel<SLOTS, MODE, 1, false>), grid, dim3(256), lds, stream, A); \
+        else launch_kernel((softmax_wide_kernel<SLOTS, MODE, 2, false>), grid, dim3(256), lds, stream, A);                       \
     } while (0)
     if (mode == 0) IPTQ_WIDE_LAUNCH(0);
     else IPTQ_WIDE_LAUNCH(2);

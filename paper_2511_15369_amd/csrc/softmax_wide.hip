@@ -55,7 +55,7 @@ hipError_t softmax_wide_launch(const SoftmaxCall &c, int32_t cols, int post_mode
                                   : wide_launch_p14_16(A, n, mode, grid, stream);
     if (!launched) return hipSuccess;
     *done = rows;
-    return hipGetLastError();
+    return take_launch_status();
 }
 
 }  // namespace iptq
