@@ -9,12 +9,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libiptq.so")
+CALL_MODULE = os.path.join(HERE, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 TIMELINE_LIB = os.path.join(HERE, "libiptq_timeline.so")
 # the slowest translation units first (the pool takes them in this order)
 SOURCES = ["softmax_long_p13_16.hip", "softmax_long_p9_12.hip", "softmax_long_p7_8.hip", "softmax_wgrow_w4_hi.hip", "softmax_wgrow_w8_hi.hip", "softmax_wgrow_w16.hip", "softmax_wgrow_w4_lo.hip", "softmax_wgrow_w8_lo.hip",
@@ -50,6 +52,25 @@ def build(extra_flags=(), verbose: bool = False, lib: str = LIB, obj_dir: str = 
     return lib
 
 
+def build_call_module(verbose: bool = False) -> str:
+    """The Python extension module of the device calls (host code only): against the headers and
+    libraries of the torch that is installed, which the library shares its HIP runtime with."""
+    import torch
+    from torch.utils import cpp_extension
+    tmp = CALL_MODULE + ".tmp%d" % os.getpid()
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    includes = [sysconfig.get_paths()["include"]] + cpp_extension.include_paths()
+    includes.append(os.path.join(cpp_extension.ROCM_HOME or "/opt/rocm", "include"))
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch.compiled_with_cxx11_abi())]
+                          + ["-I" + i for i in includes] + [os.path.join(CSRC, "call_module.cpp"), "-o", tmp, "-L" + libs,
+                             "-ltorch_python", "-lc10_hip", "-lc10", "-ltorch_cpu"])
+    os.replace(tmp, CALL_MODULE)
+    if verbose:
+        print("built", CALL_MODULE)
+    return CALL_MODULE
+
+
 def build_timeline(verbose: bool = False) -> str:
     """The instrumented library for `python -m paper_2511_15369_amd.timeline` (per-wavefront phase
     timestamps in the compiled-row-length softmax kernels); never loaded by the product path."""
@@ -61,3 +82,4 @@ if __name__ == "__main__":
         build_timeline(verbose=True)
     else:
         build(sys.argv[1:], verbose=True)
+        build_call_module(verbose=True)
