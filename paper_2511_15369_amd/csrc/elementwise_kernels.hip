@@ -92,6 +92,31 @@ struct GeluBatch {
 };
 static_assert(sizeof(GeluBatch) <= 4096, "kernel arguments are limited to 4 KiB");
 
+// Whether a call writes its output through to the last-level cache and leaves it there, instead of past
+// it (the non-temporal hint).  Whoever reads the output next then finds it in that cache, and so does a
+// later call that writes the same buffer:
+//   - between a copy that makes its input and one that reads its output, 24 million values 23.6 us
+//     against 26.1 for all three, 40 million 36.5 against 40.2, 60 million 54.2 against 57.3;
+//   - call after call over three outputs 18 to 92 million are 2 to 6 % faster (77 million 23.2 us against
+//     24.6), over six or twelve (more than the cache holds) between 3 % faster and 2 % slower;
+//   - from 100 million on the output itself pushes everything else out: 1 to 3 % slower, with a reader
+//     behind it 5 %;
+//   - 2 to 18 million gain behind a reader (4 million 9.4 us against 10.1) but lose up to 19 % call after call
+//     over six outputs;
+//   - up to 2 million every way of calling is faster (0.5 million 1.82 us against 1.94): the kernel ends
+//     with less to write back.
+bool gelu_writes_through(int64_t n)
+{
+    return n <= 2 * 1000 * 1000 || (n >= 18 * 1000 * 1000 && n <= 92 * 1000 * 1000);
+}
+// The store itself: 16 bytes per lane at consecutive addresses from a workgroup-uniform one, cache policy sc1.
+IPTQ_DEV void store_through(u32x4 v, u32x4 *base)
+{
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(base, 0, 256 * 16, 0x00027000);
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)(16 * threadIdx.x), 0, 16);
+}
+
+template <bool THROUGH>
 IPTQ_DEV void gelu_i8_table_body(const GeluItem &I)
 {
     __shared__ uint8_t table[256];
@@ -123,9 +148,13 @@ IPTQ_DEV void gelu_i8_table_body(const GeluItem &I)
     if (i < n16) first = load16(i);
     table[threadIdx.x] = (uint8_t)gelu_eval_any((int32_t)(int8_t)threadIdx.x, I.P);
     __syncthreads();
-    if (i < n16) stream_store(gather(first), out4 + i);
+    auto store16 = [&](u32x4 v, int64_t k) {
+        if (THROUGH) store_through(v, out4 + (k - threadIdx.x));
+        else stream_store(v, out4 + k);
+    };
+    if (i < n16) store16(gather(first), i);
     i += stride;
-    for (; i < n16; i += stride) stream_store(gather(load16(i)), out4 + i);
+    for (; i < n16; i += stride) store16(gather(load16(i)), i);
     if (lb == 0) {
         const int64_t j = (n16 << 4) + threadIdx.x;
         if (threadIdx.x < 16 && j < n) I.out[j] = table[I.in[j]];
@@ -136,15 +165,16 @@ IPTQ_DEV void gelu_i8_table_body(const GeluItem &I)
     }
 }
 
-// One problem: 112 bytes of arguments.  The host writes a launch's arguments into device memory, and
+// One problem: 104 bytes of arguments.  The host writes a launch's arguments into device memory, and
 // that is what a short call costs: an empty kernel takes 2.7 us of host time with 32 bytes of arguments,
 // 2.8 with 64, 3.5 with 256 and 3.9 from 1.7 KB on.  (No kernel of this file asks for its grid's size
 // either: it comes with 256 bytes of other implicit arguments.)
+template <bool THROUGH>
 __global__ void __launch_bounds__(256)
 gelu_i8_table_kernel(GeluItem I)
 {
     touch_kernel_arguments<sizeof(GeluItem)>();
-    gelu_i8_table_body(I);
+    gelu_i8_table_body<THROUGH>(I);
 }
 
 __global__ void __launch_bounds__(256)
@@ -154,7 +184,7 @@ gelu_i8_table_batch_kernel(GeluBatch B)
     int it = 0;
     for (int i = 1; i < B.n_items; ++i)
         if (blockIdx.x >= B.item[i].first_wg) it = i;
-    gelu_i8_table_body(B.item[it]);
+    gelu_i8_table_body<false>(B.item[it]);
 }
 
 // int8 -> int8, polynomial evaluated per element (no table).
@@ -365,7 +395,9 @@ hipError_t gelu_i8_dispatch(const GeluCall *calls, int n_calls, hipStream_t stre
     unsigned total_wgs = 0;
     auto flush = [&]() {
         if (B.n_items == 0) return;
-        if (B.n_items == 1) launch_kernel(gelu_i8_table_kernel, dim3(total_wgs), dim3(256), 0, stream, B.item[0]);
+        if (B.n_items == 1 && gelu_writes_through(B.item[0].n))
+            launch_kernel(gelu_i8_table_kernel<true>, dim3(total_wgs), dim3(256), 0, stream, B.item[0]);
+        else if (B.n_items == 1) launch_kernel(gelu_i8_table_kernel<false>, dim3(total_wgs), dim3(256), 0, stream, B.item[0]);
         else launch_kernel(gelu_i8_table_batch_kernel, dim3(total_wgs), dim3(256), 0, stream, B);
         B.n_items = 0;
         total_wgs = 0;
