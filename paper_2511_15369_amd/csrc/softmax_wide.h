@@ -37,17 +37,85 @@ struct WideArgs {
     SoftmaxDev P;
 };
 
+// The same in 88 bytes instead of 208: a launch's arguments are written into device memory by the host,
+// about 0.3 us for the difference, and a call of one image lasts 3 us.  What fits a few bits shares a
+// word, and what follows from other fields is derived again.
+struct WidePacked {
+    const int32_t *scores, *bias;
+    uint8_t *out;
+    int32_t rows, cols;                               // rows < 2^31 (plan_softmax)
+    int32_t i0;
+    uint32_t magic;
+    int32_t d_clamp;
+    uint32_t mg24;
+    uint32_t w0;          // n_shift 5, magic_sh 5, t16 4, m_bits 5, p_shift 5, mode16 2, pre_mode 2, variant 2
+    uint32_t w1;          // pre_s 6, pre_sh2 5, pre_rowconst 1, post_s 6, d2_sh 5, period_sh 5, base_off 2, cut_el 2
+    uint32_t w2;          // pre_m 16, post_m 16 (signed)
+    uint32_t w3;          // qmin 10 (signed), qmax 10 (signed), post_mode 2, post_xor 1
+    int32_t post_zp;
+    uint32_t pre_dmax, d2_magic;
+    int32_t bias_period_rows;
+    uint32_t period_magic;
+};
+IPTQ_HD WidePacked wide_pack(const WideArgs &A)
+{
+    const SoftmaxDev &P = A.P;
+    WidePacked W;
+    W.scores = A.scores; W.bias = A.bias; W.out = A.out;
+    W.rows = (int32_t)A.rows; W.cols = A.cols;
+    W.i0 = P.i0; W.magic = P.magic; W.d_clamp = P.d_clamp; W.mg24 = P.mg24;
+    W.w0 = (uint32_t)P.n_shift | (uint32_t)P.magic_sh << 5 | (uint32_t)P.t16 << 10 | (uint32_t)P.m_bits << 14 |
+           (uint32_t)P.p_shift << 19 | (uint32_t)P.mode16 << 24 | (uint32_t)P.pre_mode << 26 | (uint32_t)P.variant << 28;
+    W.w1 = (uint32_t)P.pre_s | (uint32_t)P.pre_sh2 << 6 | (uint32_t)P.pre_rowconst << 11 | (uint32_t)P.post_s << 12 |
+           (uint32_t)P.d2_sh << 18 | (uint32_t)P.period_sh << 23 | (uint32_t)A.base_off << 28 | (uint32_t)A.cut_el << 30;
+    W.w2 = ((uint32_t)P.pre_m & 0xffffu) | (uint32_t)P.post_m << 16;
+    W.w3 = ((uint32_t)P.qmin & 0x3ffu) | ((uint32_t)P.qmax & 0x3ffu) << 10 | (uint32_t)A.post_mode << 20 |
+           (P.post_xor != 0 ? 1u << 22 : 0u);
+    W.post_zp = P.post_zp; W.pre_dmax = P.pre_dmax; W.d2_magic = P.d2_magic;
+    W.bias_period_rows = P.bias_period_rows; W.period_magic = P.period_magic;
+    return W;
+}
+IPTQ_HD WideArgs wide_unpack(const WidePacked &W)
+{
+    WideArgs A;
+    SoftmaxDev &P = A.P;
+    A.scores = W.scores; A.bias = W.bias; A.out = W.out;
+    A.rows = W.rows; A.cols = W.cols;
+    A.base_off = (int32_t)(W.w1 >> 28 & 3u); A.cut_el = (int32_t)(W.w1 >> 30);
+    A.post_mode = (int32_t)(W.w3 >> 20 & 3u);
+    P.i0 = W.i0; P.magic = W.magic; P.d_clamp = W.d_clamp; P.mg24 = W.mg24;
+    P.n_shift = (int32_t)(W.w0 & 31u); P.magic_sh = (int32_t)(W.w0 >> 5 & 31u); P.t16 = (int32_t)(W.w0 >> 10 & 15u);
+    P.m_bits = (int32_t)(W.w0 >> 14 & 31u); P.p_shift = (int32_t)(W.w0 >> 19 & 31u);
+    P.mode16 = (int32_t)(W.w0 >> 24 & 3u); P.pre_mode = (int32_t)(W.w0 >> 26 & 3u); P.variant = (int32_t)(W.w0 >> 28 & 3u);
+    P.i0n = P.i0 << P.n_shift;
+    P.pre_s = (int32_t)(W.w1 & 63u); P.pre_sh2 = (int32_t)(W.w1 >> 6 & 31u); P.pre_rowconst = (int32_t)(W.w1 >> 11 & 1u);
+    P.post_s = (int32_t)(W.w1 >> 12 & 63u); P.d2_sh = (int32_t)(W.w1 >> 18 & 31u); P.period_sh = (int32_t)(W.w1 >> 23 & 31u);
+    P.pre_m = (int32_t)(W.w2 & 0xffffu); P.post_m = (int32_t)W.w2 >> 16;
+    // as plan_softmax derives them (pre_mode 1 alone uses them)
+    P.pre_mul = P.pre_s <= 32 ? P.pre_m << ((32 - P.pre_s) & 31) : P.pre_m;
+    P.pre_rnd = (int64_t)1 << (P.pre_s <= 32 ? 31 : P.pre_s - 1);
+    P.qmin = (int32_t)(W.w3 << 22) >> 22; P.qmax = (int32_t)(W.w3 << 12) >> 22;
+    P.post_zp = W.post_zp;
+    P.post_xor = (W.w3 >> 22 & 1u) != 0 ? 0x80808080u : 0u;
+    P.pre_dmax = W.pre_dmax; P.d2_magic = W.d2_magic;
+    P.bias_period_rows = W.bias_period_rows; P.period_magic = W.period_magic;
+    P.n_windows = P.group_rows = P.mask_period_rows = P.mperiod_sh = P.group_sh = 0;     // no mask in these kernels
+    P.mperiod_magic = P.group_magic = 0;
+    return A;
+}
+
 // PRE: the requantization in front folded into Eq. 6, as in the slab kernel (60,000 rows of 1025
 // scores 52.6 us against 53.9 us).  Up to eight passes: with more the folded form needs so many
 // registers that it is the slower one (12,000 rows of 3000 scores 33.2 against 32.3 us).
 constexpr int kWideFoldMaxSlots = 8;
 template <int SLOTS, int MODE, int VARIANT, bool PRE>
 __global__ void __launch_bounds__(256)
-softmax_wide_kernel(WideArgs A)
+softmax_wide_kernel(WidePacked W)
 {
     __shared__ uint8_t lut_all[4][kPostLutBytes];
-    touch_kernel_arguments<sizeof(WideArgs)>();
-    const SoftmaxDev P = A.P;
+    touch_kernel_arguments<sizeof(WidePacked)>();
+    const WideArgs A = wide_unpack(W);
+    const SoftmaxDev &P = A.P;
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // the row index as a scalar
     const int64_t row = (int64_t)blockIdx.x * 4 + wv;
@@ -186,16 +254,21 @@ softmax_wide_kernel(WideArgs A)
     }
 }
 
-// LDS asked for beside the kernel's own, so that no more than four workgroups share a compute unit: with
-// 9, 11 and 12 passes the registers would allow five to seven, and in a long launch that many rows in
-// flight (180 KB per unit and more) are slower: 45 million scores in rows of 2200 38.2 us against 39.1, of
-// 2950 38.8 against 39.3; 36 million 31.1 against 31.6 and 31.7 against 32.4; at 25 to 28 million both take
-// the same time, and 15 million are faster with all that fit (14.6 against 15.2, 14.9 against 16.0).
-// With any other number of passes it changes nothing or loses.
+// Most workgroups per compute unit in a long launch, where registers would allow more of them than is
+// good: with that many rows in flight (180 KB per unit and more from nine passes on) it takes longer.  30
+// to 45 million scores in rows of 1500 25.9 us against 26.3 without the bound, of 2000 26.2 against 26.7,
+// of 2200 38.2 against 39.1, of 2950 38.8 against 39.3; other numbers of passes gain nothing or lose.  At 25
+// to 28 million both take the same time, and 15 million are faster with all that fit (rows of 2200 14.6
+// us against 15.2, of 2950 14.9 against 16.0).  0: no bound.
+constexpr int wide_most_workgroups(int slots)
+{
+    return slots >= 5 && slots <= 7 ? 6 : (slots == 8 ? 5 : (slots == 9 || slots == 11 || slots == 12 ? 4 : 0));
+}
+// The bound as LDS asked for beside the kernel's own (less than 1 KB).
 inline size_t wide_extra_lds(int slots, const WideArgs &A)
 {
-    const bool bound = (slots == 9 || slots == 11 || slots == 12) && A.rows * A.cols > 28 * 1000 * 1000;
-    return bound ? 160 * 1024 / 4 - 1024 : 0;         // the kernel's own is less than 1 KB
+    const int most = A.rows * A.cols > 28 * 1000 * 1000 ? wide_most_workgroups(slots) : 0;
+    return most != 0 ? 160 * 1024 / most - 1024 : 0;
 }
 
 // mode: SoftmaxDev::mode16 (2 covers 1: t16 == 0 shifts by 0)
@@ -203,18 +276,19 @@ template <int SLOTS>
 static void wide_launch_s(const WideArgs &A, int mode, dim3 grid, hipStream_t stream)
 {
     const size_t lds = wide_extra_lds(SLOTS, A);
+    const WidePacked W = wide_pack(A);
     if constexpr (SLOTS <= kWideFoldMaxSlots) {
         if (A.P.pre_rowconst != 0) {                  // packed arithmetic and a first-degree exponential
-            if (A.P.variant == 0) launch_kernel((softmax_wide_kernel<SLOTS, 2, 0, true>), grid, dim3(256), lds, stream, A);
-            else launch_kernel((softmax_wide_kernel<SLOTS, 2, 1, true>), grid, dim3(256), lds, stream, A);
+            if (A.P.variant == 0) launch_kernel((softmax_wide_kernel<SLOTS, 2, 0, true>), grid, dim3(256), lds, stream, W);
+            else launch_kernel((softmax_wide_kernel<SLOTS, 2, 1, true>), grid, dim3(256), lds, stream, W);
             return;
         }
     }
 #define IPTQ_WIDE_LAUNCH(MODE)                                                                    \
     do {                                                                                          \
-        if (A.P.variant == 0) launch_kernel((softmax_wide_kernel<SLOTS, MODE, 0, false>), grid, dim3(256), lds, stream, A);      \
-        else if (A.P.variant == 1) launch_kernel((softmax_wide_kernel<SLOTS, MODE, 1, false>), grid, dim3(256), lds, stream, A); \
-        else launch_kernel((softmax_wide_kernel<SLOTS, MODE, 2, false>), grid, dim3(256), lds, stream, A);                       \
+        if (A.P.variant == 0) launch_kernel((softmax_wide_kernel<SLOTS, MODE, 0, false>), grid, dim3(256), lds, stream, W);      \
+        else if (A.P.variant == 1) launch_kernel((softmax_wide_kernel<SLOTS, MODE, 1, false>), grid, dim3(256), lds, stream, W); \
+        else launch_kernel((softmax_wide_kernel<SLOTS, MODE, 2, false>), grid, dim3(256), lds, stream, W);                       \
     } while (0)
     if (mode == 0) IPTQ_WIDE_LAUNCH(0);
     else IPTQ_WIDE_LAUNCH(2);
