@@ -47,6 +47,10 @@ int iptq_debug_wgrow16_is_faster(int64_t rows, int32_t has_bias, int32_t has_pre
  * short-lived ones (0); out_on_line: its output starts on a 64-byte line. */
 int iptq_debug_gelu32_looping_grid(int64_t n, int32_t out_on_line);
 
+/* The packed arithmetic the kernels take for these parameters (0 none, 1 multiply-high divider, 2
+ * byte divider) and the byte divider's multiplier (negative; 0: not exact, not used). */
+int iptq_debug_softmax_packed(const iptq_softmax_params_t *p, int32_t *packed, int32_t *div8);
+
 /* Exponentials (Eq. 7-14) of n stabilised scores (row maximum 0; n even) through both arithmetic
  * paths of the softmax kernels: d_out32 from the 32-bit lanes, d_out16 from the packed 16-bit
  * lanes (0xFFFFFFFF where the parameters do not enable that path).  All three device arrays

@@ -31,6 +31,16 @@ extern "C" int iptq_debug_softmax_plan(const iptq_softmax_params_t *p, int64_t r
     return rc;
 }
 
+extern "C" int iptq_debug_softmax_packed(const iptq_softmax_params_t *p, int32_t *packed, int32_t *div8)
+{
+    SoftmaxDev dev;
+    const int rc = plan_softmax(p, 1, 1, 0, 0, &dev);
+    if (rc != IPTQ_OK || !packed || !div8) return rc;
+    *packed = dev.packed;
+    *div8 = dev.div8;
+    return rc;
+}
+
 // Layout the run-time-row-length kernels would use for a row length:
 // out12 = {slab ok, its lanes per row, its blocks per lane, the same again, wide ok, wide passes, wide slots,
 //          1 if the row length has a compiled kernel, passes of the walking workgroup (0: none),
@@ -90,14 +100,23 @@ debug_bit_exp_kernel(const int32_t *delta, uint32_t *out32, uint32_t *out16, int
         out32[i] = bit_exp_dev<2, true>(xa, lower, 0, P);
         out32[i + 1] = bit_exp_dev<2, true>(xb, lower, 0, P);
     }
-    if (P.mode16 == 0) {
+    if (P.packed == 0) {
         out16[i] = out16[i + 1] = 0xFFFFFFFFu;
     } else {
-        const u16x2 e = P.variant == 0 ? bit_exp_pair<0, true>(xa, xb, 0, P)
-                      : P.variant == 1 ? bit_exp_pair<1, true>(xa, xb, 0, P)
-                                       : bit_exp_pair<2, true>(xa, xb, 0, P);
-        out16[i] = e.x;
-        out16[i + 1] = e.y;
+        const int32_t x[4] = {xa, xb, xb, xa};
+        uint32_t e[2];
+        if (P.packed == 1) {
+            if (P.variant == 0) bit_exp_block<0, false>(x, 0, lower, P, e);
+            else if (P.variant == 1) bit_exp_block<1, false>(x, 0, lower, P, e);
+            else bit_exp_block<2, false>(x, 0, lower, P, e);
+        } else {
+            if (P.variant == 0) bit_exp_block<0, true>(x, 0, lower, P, e);
+            else if (P.variant == 1) bit_exp_block<1, true>(x, 0, lower, P, e);
+            else bit_exp_block<2, true>(x, 0, lower, P, e);
+        }
+        out16[i] = e[0] & 0xffffu;
+        out16[i + 1] = e[0] >> 16;
+        if ((e[1] >> 16 | e[1] << 16) != e[0]) out16[i] = 0xFFFFFFFEu;      // the halves of a block disagree
     }
 }
 

@@ -167,6 +167,15 @@ int plan_softmax(const iptq_softmax_params_t *p, int64_t rows, int32_t cols, int
             break;
         }
     }
+    // The byte divider: n ceil(2^24 / i0) < 2^29 has the quotient in its top byte as long as n e < 2^24
+    // with e = i0 ceil(2^24 / i0) - 2^24 < i0 (so for every i0 up to about 1050), and -n must fit 16 bits.
+    out->div8 = 0;
+    if (out->mode16 != 0 && n_max <= 32768) {
+        const int64_t m = (((int64_t)1 << 24) + p->i0 - 1) / p->i0;
+        const int64_t e = m * p->i0 - ((int64_t)1 << 24);
+        if (n_max * e < ((int64_t)1 << 24)) out->div8 = (int32_t)-m;
+    }
+    out->packed = out->div8 != 0 ? 2 : (out->mode16 == 1 ? 1 : 0);
     out->pre_rowconst = 0;
     out->pre_dmax = 0;
     // (the folded requantization is instantiated for the first-degree exponentials only)

@@ -220,12 +220,10 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
             const int64_t n_slabs = (c.rows + rpw - 1) / rpw;    // a partial last slab is served too
             if (n_slabs == 0) continue;
             const int pm = post_mode_of(c.P, c.out_bits);
-            const int mode = c.P.mode16;
-            const bool compatible = B.n_items == 0 || (has_bias == g_bias && has_mask == g_mask && pm == g_pm &&
-                                                       (mode == 0) == (g_mode == 0));
+            const int mode = c.P.packed;
+            const bool compatible = B.n_items == 0 || (has_bias == g_bias && has_mask == g_mask && pm == g_pm && mode == g_mode);
             if (!compatible || B.n_items == kBatchMax) flush();
             if (B.n_items == 0) { g_bias = has_bias; g_mask = has_mask; g_pm = pm; g_mode = mode; }
-            else if (mode > g_mode) g_mode = mode;       // 2 covers 1: items with t16 == 0 shift by 0
             if (c.P.pre_rowconst != 0) g_fold = true;
             SoftmaxItem &it = B.item[B.n_items++];
             it.scores = c.scores; it.bias = c.bias; it.mask = c.mask; it.mask_bits = c.mask_bits; it.out = c.out;

@@ -298,7 +298,7 @@ softmax_long_kernel(WideArgs A)
     }
 }
 
-// mode: SoftmaxDev::mode16 (2 covers 1: t16 == 0 shifts by 0)
+// mode: SoftmaxDev::packed
 template <int SLOTS>
 static void long_launch_s(const WideArgs &A, int mode, dim3 grid, hipStream_t stream)
 {
@@ -311,6 +311,8 @@ static void long_launch_s(const WideArgs &A, int mode, dim3 grid, hipStream_t st
     const bool extra = A.bias != nullptr || A.P.pre_mode != 0;
     if (mode == 0 && extra) IPTQ_LONG_LAUNCH(0, true);
     else if (mode == 0) IPTQ_LONG_LAUNCH(0, false);
+    else if (mode == 1 && extra) IPTQ_LONG_LAUNCH(1, true);
+    else if (mode == 1) IPTQ_LONG_LAUNCH(1, false);
     else if (extra) IPTQ_LONG_LAUNCH(2, true);
     else IPTQ_LONG_LAUNCH(2, false);
 #undef IPTQ_LONG_LAUNCH

@@ -38,7 +38,7 @@ hipError_t softmax_long_launch(const SoftmaxCall &c, int32_t cols, int post_mode
     // one workgroup per compute unit, walking over the rows (any number of workgroups is correct)
     const int64_t wgs = c.rows < kLongWorkgroups ? c.rows : kLongWorkgroups;
     const dim3 grid((unsigned)wgs);
-    const int mode = c.P.mode16;
+    const int mode = c.P.packed;
     const bool launched = slots <= 8 ? long_launch_p7_8(A, slots, mode, grid, stream)
                         : slots <= 12 ? long_launch_p9_12(A, slots, mode, grid, stream)
                                       : long_launch_p13_16(A, slots, mode, grid, stream);

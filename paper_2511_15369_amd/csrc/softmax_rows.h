@@ -12,9 +12,11 @@
 // Two arithmetic paths give identical results:
 //   MODE 0  every step in 32-bit lanes; valid for the whole parameter domain.
 //   MODE 1  two elements per 32-bit lane in packed 16-bit (v_pk_*), for the usual case
-//           where the clamped delta, n = -Qp and (i0 << N) all fit 16 bits.
-//   MODE 2  as MODE 1, with n pre-shifted so that the divider's multiplier fits 24 bits
-//           for small i0.
+//           where the clamped delta, n = -Qp and (i0 << N) all fit 16 bits; the divider is a
+//           multiply-high by a 24-bit constant (i0 >= 256).
+//   MODE 2  as MODE 1 with the divider's quotient in the top byte of a 24-bit product, which
+//           takes three instructions fewer per pair (every i0 up to about 1050, some beyond: all
+//           scales from 2^-10 on).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -26,7 +28,6 @@
 
 namespace iptq {
 
-typedef short s16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 enum { PM_NONE = 0, PM_CLAMP127 = 1, PM_GENERAL = 2 };
@@ -313,45 +314,57 @@ IPTQ_DEV uint32_t mulhi_u24(uint32_t a, uint32_t b)   // both below 2^24: bits 4
 }
 
 // Two exponentials at once in packed 16-bit lanes.  Preconditions (checked on the host,
-// SoftmaxDev::p16): D <= 32767, n_max <= 65535 >> t16, i0 << N < 2^15 (so q <= 15 at the
-// clamp), divider multiplier mg24 < 2^24 exact for (n << t16).
-// From the two stabilised scores of Eq. 6 (any value in [-32768, 0]) on.
-// N = 2: one pair; N = 4: the two pairs of a 16-byte block side by side, every packed step as two
-// independent instructions back to back (a single pair is one dependent chain, which leaves the
-// vector unit waiting on itself when few wavefronts share it, as at the end of a launch).
+// SoftmaxDev::packed): D <= 32767, n_max <= 65535, i0 << N < 2^15 (so q <= 15 at the clamp), and a divider
+// that is exact on [0, n_max].
+// N = 4: the two pairs of a 16-byte block side by side, every packed step as two independent
+// instructions back to back (a single pair is one dependent chain, which leaves the vector unit waiting
+// on itself when few wavefronts share it, as at the end of a launch).
 template <int N> struct Packed16;
-template <> struct Packed16<2> {
-    typedef s16x2 S;
-    typedef u16x2 U;
-    typedef uint32_t W __attribute__((ext_vector_type(1)));    // the same bits as 32-bit words
-};
 template <> struct Packed16<4> {
     typedef short S __attribute__((ext_vector_type(4)));
     typedef unsigned short U __attribute__((ext_vector_type(4)));
     typedef uint32_t W __attribute__((ext_vector_type(2)));
 };
 
-template <int VARIANT, bool SHIFTED, int N>
+// dl: the stabilised scores of Eq. 6, clamped at -D.  BYTE_DIV: the divider whose quotient is the top byte
+// of a 24-bit product (SoftmaxDev::div8), else the multiply-high by mg24 (t16 == 0).  Against a shifted
+// multiply-high, with the clamp below, a block of four scores costs 38 instructions instead of 44: the
+// four stages of a Swin-B backbone with packed masks 75.7 -> 73.6 us, 589,824 rows of 144 scores with an
+// int32 mask 77.1 -> 75.3, 49,152 of 196 (second degree) 26.6 -> 25.8, 2048 of 50176 94.5 -> 91.3; what HBM
+// bounds stays (302,592 x 197 48.7 -> 48.4).
+template <int VARIANT, bool BYTE_DIV, int N>
 IPTQ_DEV typename Packed16<N>::U bit_exp_of_deltas(typename Packed16<N>::S dl, const SoftmaxDev &P)
 {
     typedef typename Packed16<N>::S S;
     typedef typename Packed16<N>::U U;
-    const short nd = (short)(-P.d_clamp);
-    dl = __builtin_elementwise_max(dl, (S)nd);                 // Eq. 6 with the clamp at -D
-    const S s1 = dl >> 1, s4 = dl >> 4;
-    const U n = (U)((s4 - dl) - s1);                           // -Qp of Eq. 7
-    U ns = n;
-    if (SHIFTED) ns = n << (unsigned short)P.t16;
-    U q;
-#pragma unroll
-    for (int i = 0; i < N / 2; ++i) {                          // Eq. 8: n div i0, per 32-bit word of the vector
-        const uint32_t nw = __builtin_bit_cast(typename Packed16<N>::W, ns)[i];
-        q[2 * i] = (unsigned short)mulhi_u24(nw & 0xffffu, P.mg24);
-        // (a field extract folds into the multiply's operand select)
-        q[2 * i + 1] = (unsigned short)mulhi_u24(__builtin_amdgcn_ubfe(nw, 16, 16), P.mg24);
-    }
+    typedef typename Packed16<N>::W W;
+    const S m = (dl + (dl >> 1)) - (dl >> 4);                  // Qp of Eq. 7, in (-2^15, 0] with BYTE_DIV
     const unsigned short i0 = (unsigned short)P.i0;
-    const S nr = (S)(q * (U)i0 - n);                           // -r in (-i0, 0]
+    U q;
+    S nr;
+    if (BYTE_DIV) {
+        // Eq. 8: (-m) div i0 is the top byte of (-m) ceil(2^24 / i0), both factors negated
+        W qw;
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) {
+            const uint32_t mw = __builtin_bit_cast(W, m)[i];
+            const uint32_t a = (uint32_t)__mul24((int32_t)(int16_t)mw, P.div8);
+            const uint32_t b = (uint32_t)__mul24((int32_t)mw >> 16, P.div8);
+            qw[i] = __builtin_amdgcn_perm(b, a, 0x0c070c03u);
+        }
+        q = __builtin_bit_cast(U, qw);
+        nr = (S)(q * (U)i0 + (U)m);                            // -r in (-i0, 0]
+    } else {
+        const U n = (U)0 - (U)m;
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) {                      // Eq. 8: n div i0, per 32-bit word of the vector
+            const uint32_t nw = __builtin_bit_cast(W, n)[i];
+            q[2 * i] = (unsigned short)mulhi_u24(nw & 0xffffu, P.mg24);
+            // (a field extract folds into the multiply's operand select)
+            q[2 * i + 1] = (unsigned short)mulhi_u24(__builtin_amdgcn_ubfe(nw, 16, 16), P.mg24);
+        }
+        nr = (S)(q * (U)i0 - n);
+    }
     S fr = nr >> 1;                                            // Eq. 10
     if (VARIANT >= 1) fr = fr + (nr >> 3) + (nr >> 4);         // Eq. 13
     if (VARIANT == 2) {
@@ -371,46 +384,48 @@ IPTQ_DEV typename Packed16<N>::U bit_exp_of_deltas(typename Packed16<N>::S dl, c
     return base >> q;                                          // Eq. 9 (q <= 15)
 }
 
-template <int VARIANT, bool SHIFTED>
-IPTQ_DEV u16x2 bit_exp_pair_of_deltas(s16x2 dl, const SoftmaxDev &P)
+// The four scores of a 16-byte block, clamped at `lower` (the row maximum minus D), minus the row maximum as
+// packed 16-bit values: the clamp writes the low half of its result straight into one half of a
+// register (two instructions per pair, and one to subtract), where a saturating subtraction per score, a pack
+// and a packed clamp take four.  The four are interleaved: a partial write may not be followed by a read
+// of the same register.
+IPTQ_DEV Packed16<4>::S clamped_deltas(const int32_t (&x)[4], int32_t lower, int32_t mx)
 {
-    return bit_exp_of_deltas<VARIANT, SHIFTED, 2>(dl, P);
-}
-
-template <int VARIANT, bool SHIFTED>
-IPTQ_DEV u16x2 bit_exp_pair(int32_t xa, int32_t xb, int32_t mx, const SoftmaxDev &P)
-{
-    const int32_t da = __builtin_elementwise_sub_sat(xa, mx);
-    const int32_t db = __builtin_elementwise_sub_sat(xb, mx);
-    return bit_exp_pair_of_deltas<VARIANT, SHIFTED>(__builtin_amdgcn_cvt_pk_i16(da, db), P);   // saturating pack
+    uint32_t lo, hi;
+    asm("v_max_i32_sdwa %0, %2, %6 dst_sel:WORD_0 dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:DWORD\n\t"
+        "v_max_i32_sdwa %1, %4, %6 dst_sel:WORD_0 dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:DWORD\n\t"
+        "v_max_i32_sdwa %0, %3, %6 dst_sel:WORD_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD\n\t"
+        "v_max_i32_sdwa %1, %5, %6 dst_sel:WORD_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD"
+        : "=&v"(lo), "=&v"(hi)
+        : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(lower));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(Packed16<4>::S, (u32x2){lo, hi}) - (Packed16<4>::S)(short)mx;
 }
 
 // The four scores of a 16-byte block -> their exponentials as two packed words.
-template <int VARIANT, bool SHIFTED>
-IPTQ_DEV void bit_exp_block(const int32_t (&x)[4], int32_t mx, const SoftmaxDev &P, uint32_t (&e)[2])
+template <int VARIANT, bool BYTE_DIV>
+IPTQ_DEV void bit_exp_block(const int32_t (&x)[4], int32_t mx, int32_t lower, const SoftmaxDev &P, uint32_t (&e)[2])
 {
-    const s16x2 lo = __builtin_amdgcn_cvt_pk_i16(__builtin_elementwise_sub_sat(x[0], mx),
-                                                 __builtin_elementwise_sub_sat(x[1], mx));
-    const s16x2 hi = __builtin_amdgcn_cvt_pk_i16(__builtin_elementwise_sub_sat(x[2], mx),
-                                                 __builtin_elementwise_sub_sat(x[3], mx));
-    const Packed16<4>::U q = bit_exp_of_deltas<VARIANT, SHIFTED, 4>(__builtin_shufflevector(lo, hi, 0, 1, 2, 3), P);
+    const Packed16<4>::U q = bit_exp_of_deltas<VARIANT, BYTE_DIV, 4>(clamped_deltas(x, lower, mx), P);
     e[0] = __builtin_bit_cast(uint32_t, __builtin_shufflevector(q, q, 0, 1));
     e[1] = __builtin_bit_cast(uint32_t, __builtin_shufflevector(q, q, 2, 3));
 }
 
 // The same with the requantization of the scores folded in (SoftmaxDev::pre_rowconst): the scores
 // and mx are raw, c_row is the row's constant.
-template <int VARIANT, bool SHIFTED>
+template <int VARIANT, bool BYTE_DIV>
 IPTQ_DEV void bit_exp_block_requant(const int32_t (&x)[4], int32_t mx, uint32_t c_row, const SoftmaxDev &P,
                                     uint32_t (&e)[2])
 {
-    Packed16<4>::S d;
+    typedef Packed16<4>::S S;
+    S d;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const uint32_t dd = min((uint32_t)mx - (uint32_t)x[i], P.pre_dmax);     // mx >= x: exact as unsigned
         d[i] = (short)((__umul24(dd, (uint32_t)P.pre_m) + c_row) >> P.pre_s);    // r(mx) - r(x), at most D + 1
     }
-    const Packed16<4>::U q = bit_exp_of_deltas<VARIANT, SHIFTED, 4>((Packed16<4>::S)0 - d, P);
+    const S dl = __builtin_elementwise_max((S)0 - d, (S)(short)(-P.d_clamp));
+    const Packed16<4>::U q = bit_exp_of_deltas<VARIANT, BYTE_DIV, 4>(dl, P);
     e[0] = __builtin_bit_cast(uint32_t, __builtin_shufflevector(q, q, 0, 1));
     e[1] = __builtin_bit_cast(uint32_t, __builtin_shufflevector(q, q, 2, 3));
 }
@@ -438,7 +453,7 @@ IPTQ_DEV void softmax_slab_math(int32_t (&x)[SLOTS][4], uint32_t (&w)[SLOTS], in
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
             if (PRE) bit_exp_block_requant<VARIANT, MODE == 2>(x[s], mx, c_row, P, e2[s]);
-            else bit_exp_block<VARIANT, MODE == 2>(x[s], mx, P, e2[s]);
+            else bit_exp_block<VARIANT, MODE == 2>(x[s], mx, lower, P, e2[s]);
             sum = __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, e2[s][0]), (u16x2){1, 1}, sum, false);
             sum = __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, e2[s][1]), (u16x2){1, 1}, sum, false);
         }

@@ -476,7 +476,7 @@ softmax_rowsdyn_batch_kernel(DynBatch B)
     softmax_rowsdyn_body<K, SLOTS, 2, 0, -1, false>(B.item[it], blockIdx.x - B.first_wg[it]);
 }
 
-// mode: SoftmaxDev::mode16 (2 covers 1: t16 == 0 shifts by 0)
+// mode: SoftmaxDev::packed
 template <int K, int SLOTS>
 static void rowsdyn_launch_ks(const DynArgs &A, int mode, dim3 grid, dim3 block, size_t lds, hipStream_t stream)
 {
@@ -488,8 +488,10 @@ static void rowsdyn_launch_ks(const DynArgs &A, int mode, dim3 grid, dim3 block,
     } while (0)
     // pre_rowconst: packed arithmetic and a first-degree exponential
     if (A.P.pre_rowconst != 0 && A.mask == nullptr && A.mask_bits == nullptr) {
-        if (A.P.variant == 0) launch_kernel((softmax_rowsdyn_kernel<K, SLOTS, 2, 0, 0, true>), grid, block, lds, stream, A);
-        else launch_kernel((softmax_rowsdyn_kernel<K, SLOTS, 2, 0, 1, true>), grid, block, lds, stream, A);
+        if (mode == 2 && A.P.variant == 0) launch_kernel((softmax_rowsdyn_kernel<K, SLOTS, 2, 0, 0, true>), grid, block, lds, stream, A);
+        else if (mode == 2) launch_kernel((softmax_rowsdyn_kernel<K, SLOTS, 2, 0, 1, true>), grid, block, lds, stream, A);
+        else if (A.P.variant == 0) launch_kernel((softmax_rowsdyn_kernel<K, SLOTS, 1, 0, 0, true>), grid, block, lds, stream, A);
+        else launch_kernel((softmax_rowsdyn_kernel<K, SLOTS, 1, 0, 1, true>), grid, block, lds, stream, A);
         return;
     }
 #define IPTQ_ROWSDYN_LAUNCH_MASK(MODE)                                                            \
@@ -499,6 +501,7 @@ static void rowsdyn_launch_ks(const DynArgs &A, int mode, dim3 grid, dim3 block,
         else IPTQ_ROWSDYN_LAUNCH(MODE, 0);                                                        \
     } while (0)
     if (mode == 0) IPTQ_ROWSDYN_LAUNCH_MASK(0);
+    else if (mode == 1) IPTQ_ROWSDYN_LAUNCH_MASK(1);
     else IPTQ_ROWSDYN_LAUNCH_MASK(2);
 #undef IPTQ_ROWSDYN_LAUNCH_MASK
 #undef IPTQ_ROWSDYN_LAUNCH

@@ -137,7 +137,7 @@ hipError_t softmax_rowsdyn_launch(const SoftmaxCall &c, int32_t cols, int post_m
     DynArgs A;
     int64_t n_wgs = 0;
     if (!rowsdyn_arguments(c, cols, post_mode, k, &A, &n_wgs)) return hipSuccess;
-    if (!rowsdyn_launch(&A, nullptr, k, slots, c.P.mode16, dim3((unsigned)n_wgs), dim3(64 * A.wpb),
+    if (!rowsdyn_launch(&A, nullptr, k, slots, c.P.packed, dim3((unsigned)n_wgs), dim3(64 * A.wpb),
                         (size_t)A.wave_lds * A.wpb, stream))
         return hipSuccess;                            // no such layout: the caller's next kernel serves it
     *done = c.rows;
@@ -170,7 +170,7 @@ hipError_t softmax_rowsdyn_launch_batch(const SoftmaxCall *calls, const int *pos
     };
     for (int i = 0; i < n_calls; ++i) {
         const SoftmaxCall &c = calls[i];
-        if (done[i] != 0 || c.mask != nullptr || c.mask_bits != nullptr || c.P.mode16 == 0 || c.P.pre_mode != 0 ||
+        if (done[i] != 0 || c.mask != nullptr || c.mask_bits != nullptr || c.P.packed != 2 || c.P.pre_mode != 0 ||
             !(c.algo == IPTQ_ALGO_AUTO || c.algo == IPTQ_ALGO_DYNAMIC || c.algo == IPTQ_ALGO_SLAB))
             continue;
         DynArgs A;

@@ -179,7 +179,7 @@ softmax_wgrow_kernel(WideArgs A)
     }
 }
 
-// mode: SoftmaxDev::mode16 (2 covers 1: t16 == 0 shifts by 0)
+// mode: SoftmaxDev::packed
 template <int WAVES, int SLOTS>
 static void wgrow_launch_ws(const WideArgs &A, int mode, dim3 grid, hipStream_t stream)
 {
@@ -192,6 +192,7 @@ static void wgrow_launch_ws(const WideArgs &A, int mode, dim3 grid, hipStream_t 
         else launch_kernel((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 2>), grid, dim3(64 * WAVES), 0, stream, A);                       \
     } while (0)
     if (mode == 0) IPTQ_WGROW_LAUNCH(0);
+    else if (mode == 1) IPTQ_WGROW_LAUNCH(1);
     else IPTQ_WGROW_LAUNCH(2);
 #undef IPTQ_WGROW_LAUNCH
 }

@@ -67,7 +67,7 @@ hipError_t softmax_wgrow_launch(const SoftmaxCall &c, int32_t cols, int post_mod
     A.scores = c.scores - base_off; A.bias = c.bias; A.out = c.out - base_off; A.base_off = base_off; A.rows = rows; A.cols = cols; A.post_mode = post_mode; A.P = c.P;
     A.cut_el = cut_el;
     const dim3 grid((unsigned)rows);                  // one workgroup per row, exactly
-    const int mode = c.P.mode16;
+    const int mode = c.P.packed;
     bool launched;
     if (waves == 4) launched = slots <= 9 ? wgrow_launch_w4_lo(A, slots, mode, grid, stream) : wgrow_launch_w4_hi(A, slots, mode, grid, stream);
     else if (waves == 8) launched = slots <= 10 ? wgrow_launch_w8_lo(A, slots, mode, grid, stream) : wgrow_launch_w8_hi(A, slots, mode, grid, stream);

@@ -47,8 +47,8 @@ struct WidePacked {
     int32_t i0;
     uint32_t magic;
     int32_t d_clamp;
-    uint32_t mg24;
-    uint32_t w0;          // n_shift 5, magic_sh 5, t16 4, m_bits 5, p_shift 5, mode16 2, pre_mode 2, variant 2
+    uint32_t divider;     // div8 or mg24, whichever the kernel takes
+    uint32_t w0;          // n_shift 5, magic_sh 5, free 4, m_bits 5, p_shift 5, free 2, pre_mode 2, variant 2
     uint32_t w1;          // pre_s 6, pre_sh2 5, pre_rowconst 1, post_s 6, d2_sh 5, period_sh 5, base_off 2, cut_el 2
     uint32_t w2;          // pre_m 16, post_m 16 (signed)
     uint32_t w3;          // qmin 10 (signed), qmax 10 (signed), post_mode 2, post_xor 1
@@ -63,9 +63,9 @@ IPTQ_HD WidePacked wide_pack(const WideArgs &A)
     WidePacked W;
     W.scores = A.scores; W.bias = A.bias; W.out = A.out;
     W.rows = (int32_t)A.rows; W.cols = A.cols;
-    W.i0 = P.i0; W.magic = P.magic; W.d_clamp = P.d_clamp; W.mg24 = P.mg24;
-    W.w0 = (uint32_t)P.n_shift | (uint32_t)P.magic_sh << 5 | (uint32_t)P.t16 << 10 | (uint32_t)P.m_bits << 14 |
-           (uint32_t)P.p_shift << 19 | (uint32_t)P.mode16 << 24 | (uint32_t)P.pre_mode << 26 | (uint32_t)P.variant << 28;
+    W.i0 = P.i0; W.magic = P.magic; W.d_clamp = P.d_clamp; W.divider = P.packed == 2 ? (uint32_t)P.div8 : P.mg24;
+    W.w0 = (uint32_t)P.n_shift | (uint32_t)P.magic_sh << 5 | (uint32_t)P.m_bits << 14 |
+           (uint32_t)P.p_shift << 19 | (uint32_t)P.pre_mode << 26 | (uint32_t)P.variant << 28;
     W.w1 = (uint32_t)P.pre_s | (uint32_t)P.pre_sh2 << 6 | (uint32_t)P.pre_rowconst << 11 | (uint32_t)P.post_s << 12 |
            (uint32_t)P.d2_sh << 18 | (uint32_t)P.period_sh << 23 | (uint32_t)A.base_off << 28 | (uint32_t)A.cut_el << 30;
     W.w2 = ((uint32_t)P.pre_m & 0xffffu) | (uint32_t)P.post_m << 16;
@@ -83,10 +83,10 @@ IPTQ_HD WideArgs wide_unpack(const WidePacked &W)
     A.rows = W.rows; A.cols = W.cols;
     A.base_off = (int32_t)(W.w1 >> 28 & 3u); A.cut_el = (int32_t)(W.w1 >> 30);
     A.post_mode = (int32_t)(W.w3 >> 20 & 3u);
-    P.i0 = W.i0; P.magic = W.magic; P.d_clamp = W.d_clamp; P.mg24 = W.mg24;
-    P.n_shift = (int32_t)(W.w0 & 31u); P.magic_sh = (int32_t)(W.w0 >> 5 & 31u); P.t16 = (int32_t)(W.w0 >> 10 & 15u);
+    P.i0 = W.i0; P.magic = W.magic; P.d_clamp = W.d_clamp; P.div8 = (int32_t)W.divider; P.mg24 = W.divider;
+    P.n_shift = (int32_t)(W.w0 & 31u); P.magic_sh = (int32_t)(W.w0 >> 5 & 31u);
     P.m_bits = (int32_t)(W.w0 >> 14 & 31u); P.p_shift = (int32_t)(W.w0 >> 19 & 31u);
-    P.mode16 = (int32_t)(W.w0 >> 24 & 3u); P.pre_mode = (int32_t)(W.w0 >> 26 & 3u); P.variant = (int32_t)(W.w0 >> 28 & 3u);
+    P.pre_mode = (int32_t)(W.w0 >> 26 & 3u); P.variant = (int32_t)(W.w0 >> 28 & 3u);
     P.i0n = P.i0 << P.n_shift;
     P.pre_s = (int32_t)(W.w1 & 63u); P.pre_sh2 = (int32_t)(W.w1 >> 6 & 31u); P.pre_rowconst = (int32_t)(W.w1 >> 11 & 1u);
     P.post_s = (int32_t)(W.w1 >> 12 & 63u); P.d2_sh = (int32_t)(W.w1 >> 18 & 31u); P.period_sh = (int32_t)(W.w1 >> 23 & 31u);
@@ -99,6 +99,7 @@ IPTQ_HD WideArgs wide_unpack(const WidePacked &W)
     P.post_xor = (W.w3 >> 22 & 1u) != 0 ? 0x80808080u : 0u;
     P.pre_dmax = W.pre_dmax; P.d2_magic = W.d2_magic;
     P.bias_period_rows = W.bias_period_rows; P.period_magic = W.period_magic;
+    P.t16 = P.mode16 = P.packed = 0;                  // not read by these kernels
     P.n_windows = P.group_rows = P.mask_period_rows = P.mperiod_sh = P.group_sh = 0;     // no mask in these kernels
     P.mperiod_magic = P.group_magic = 0;
     return A;
@@ -271,7 +272,7 @@ inline size_t wide_extra_lds(int slots, const WideArgs &A)
     return most != 0 ? 160 * 1024 / most - 1024 : 0;
 }
 
-// mode: SoftmaxDev::mode16 (2 covers 1: t16 == 0 shifts by 0)
+// mode: SoftmaxDev::packed
 template <int SLOTS>
 static void wide_launch_s(const WideArgs &A, int mode, dim3 grid, hipStream_t stream)
 {
@@ -279,8 +280,10 @@ static void wide_launch_s(const WideArgs &A, int mode, dim3 grid, hipStream_t st
     const WidePacked W = wide_pack(A);
     if constexpr (SLOTS <= kWideFoldMaxSlots) {
         if (A.P.pre_rowconst != 0) {                  // packed arithmetic and a first-degree exponential
-            if (A.P.variant == 0) launch_kernel((softmax_wide_kernel<SLOTS, 2, 0, true>), grid, dim3(256), lds, stream, W);
-            else launch_kernel((softmax_wide_kernel<SLOTS, 2, 1, true>), grid, dim3(256), lds, stream, W);
+            if (mode == 2 && A.P.variant == 0) launch_kernel((softmax_wide_kernel<SLOTS, 2, 0, true>), grid, dim3(256), lds, stream, W);
+            else if (mode == 2) launch_kernel((softmax_wide_kernel<SLOTS, 2, 1, true>), grid, dim3(256), lds, stream, W);
+            else if (A.P.variant == 0) launch_kernel((softmax_wide_kernel<SLOTS, 1, 0, true>), grid, dim3(256), lds, stream, W);
+            else launch_kernel((softmax_wide_kernel<SLOTS, 1, 1, true>), grid, dim3(256), lds, stream, W);
             return;
         }
     }
@@ -291,6 +294,7 @@ static void wide_launch_s(const WideArgs &A, int mode, dim3 grid, hipStream_t st
         else launch_kernel((softmax_wide_kernel<SLOTS, MODE, 2, false>), grid, dim3(256), lds, stream, W);                       \
     } while (0)
     if (mode == 0) IPTQ_WIDE_LAUNCH(0);
+    else if (mode == 1) IPTQ_WIDE_LAUNCH(1);
     else IPTQ_WIDE_LAUNCH(2);
 #undef IPTQ_WIDE_LAUNCH
 }

@@ -48,7 +48,7 @@ hipError_t softmax_wide_launch(const SoftmaxCall &c, int32_t cols, int post_mode
     A.scores = c.scores - base_off; A.bias = c.bias; A.out = c.out - base_off; A.base_off = base_off; A.rows = rows; A.cols = cols; A.post_mode = post_mode; A.P = c.P;
     A.cut_el = cut_el;
     const dim3 grid((unsigned)((rows + 3) / 4));
-    const int mode = c.P.mode16;
+    const int mode = c.P.packed;
     const bool launched = n <= 6 ? wide_launch_p1_6(A, n, mode, grid, stream)
                         : n <= 10 ? wide_launch_p7_10(A, n, mode, grid, stream)
                         : n <= 13 ? wide_launch_p11_13(A, n, mode, grid, stream)
