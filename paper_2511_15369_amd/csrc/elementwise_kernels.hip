@@ -228,13 +228,44 @@ gelu_i8_bytes_kernel(const uint8_t *in, uint8_t *out, int64_t n, uint32_t wgs, G
 
 // int32 -> byte streaming skeleton shared by the int32 GELU and the requantization: lane i
 // of a pass owns the 4 consecutive elements of 16-byte chunk i (a wavefront reads 1 KiB
-// contiguous per load and writes 256 B contiguous per store).  One chunk in flight per thread
-// and many resident wavefronts measured fastest on MI355X (deeper per-thread unrolling lost
-// 10 %).  ALIGNED: `out` is 4-byte aligned (the host peels the `head` elements in front of
+// contiguous per load and writes 256 B contiguous per store).  One chunk in flight per thread beside
+// the one being computed and many resident wavefronts measured fastest on MI355X (four chunks per
+// thread lost 10 %).  ALIGNED: `out` is 4-byte aligned (the host peels the `head` elements in front of
 // that boundary off the tensor; the first workgroup does them too) and `in` is an int32
 // pointer anywhere on the 4-byte grid: the same global_load_dwordx4 serves an input on the
 // 16-byte grid and one off it.
 typedef i32x4 __attribute__((aligned(4))) i32x4_a4;
+constexpr int64_t kResidentWorkgroups = 256 * 8;      // of 256 threads: what the chip holds at once
+// A thread's chunks from the i-th on, `v` being that one: the next chunk's load is in flight while one is
+// computed (19.4 million values through the int32 GELU 17.2 -> 16.5 us, 7 million 7.6 -> 7.0, 40 million
+// 33.5 -> 32.7, requantized 32.5 -> 32.0).  Not in a grid of many short-lived workgroups that each make more
+// than four trips, from 67 million values on: there the workgroups in flight hide the latency, and with twice the
+// loads it is 2 % slower (100 million 82.6 us against 81.2).
+template <typename F>
+IPTQ_DEV void store_and_follow(i32x4 v, int64_t i, int64_t n4, int64_t stride, const i32x4_a4 *in4, uint32_t *out32, F one)
+{
+    if (n4 <= stride) {                               // (uniform) a grid of one chunk per thread
+        stream_store(pack4(one(v.x), one(v.y), one(v.z), one(v.w)), out32 + i);
+        return;
+    }
+    if (stride > 256 * kResidentWorkgroups && n4 > 4 * stride) {
+        for (;;) {
+            stream_store(pack4(one(v.x), one(v.y), one(v.z), one(v.w)), out32 + i);
+            i += stride;
+            if (i >= n4) return;
+            v = __builtin_nontemporal_load(in4 + i);
+        }
+    }
+    do {
+        const int64_t j = i + stride;
+        i32x4 next = v;
+        if (j < n4) next = __builtin_nontemporal_load(in4 + j);
+        stream_store(pack4(one(v.x), one(v.y), one(v.z), one(v.w)), out32 + i);
+        v = next;
+        i = j;
+    } while (i < n4);
+}
+
 template <bool ALIGNED, typename F>
 IPTQ_DEV void stream_i32_to_bytes(const int32_t *in, uint8_t *out, int64_t n, int32_t head, uint32_t wgs, F one)
 {
@@ -244,9 +275,10 @@ IPTQ_DEV void stream_i32_to_bytes(const int32_t *in, uint8_t *out, int64_t n, in
         const int64_t n4 = n >> 2;
         const i32x4_a4 *in4 = reinterpret_cast<const i32x4_a4 *>(in);
         uint32_t *out32 = reinterpret_cast<uint32_t *>(out);
-        for (int64_t i = tid; i < n4; i += stride) {
-            const i32x4 v = __builtin_nontemporal_load(in4 + i);
-            stream_store(pack4(one(v.x), one(v.y), one(v.z), one(v.w)), out32 + i);
+        int64_t i = tid;
+        if (i < n4) {
+            i32x4 v = __builtin_nontemporal_load(in4 + i);
+            store_and_follow(v, i, n4, stride, in4, out32, one);
         }
         if (blockIdx.x == 0) {
             const int64_t i = (n4 << 2) + threadIdx.x;
@@ -306,9 +338,11 @@ constexpr int64_t kGelu32TableGridCap = 256 * 64;
 //     24 M 22.6 against 22.7, 30 M 27.7 against 27.3, 36 M 32.5 against 32.1;
 //   - not where most of the generation would make a second trip while the others are done: 2.6 M 4.0
 //     against 4.2, 3.0 M 4.6 against 4.4, 3.4 M 5.1 against 4.7, 4.1 M 5.6 against 5.4, 4.3 M 5.6 against 5.7.
+// Those figures are of one chunk in flight per thread.  With the next one's load in flight as well
+// (store_and_follow) both grids are faster and the lines would lie elsewhere: 3.0 M 3.9 us against 4.4 and
+// 3.4 M 4.2 against 4.7 for the looping grid, 32 M 26.2 against 26.0 and 40 M 32.7 against 31.8 for the other.
 // Evening out the trips per workgroup is slower than either (19.4 M 23.5 us with a requantization
 // behind it, 22.9 as here).  The kernel for unaligned groups serves calls of less than 64 values only.
-constexpr int64_t kGelu32ShortGridCap = 256 * 8;
 bool gelu32_looping_grid(int64_t n, bool out_on_line)
 {
     if (n > 2800 * 1000 && n < 4200 * 1000) return false;
@@ -343,11 +377,7 @@ gelu_i32_table_kernel(const int32_t *in, uint8_t *out, int64_t n, int32_t head, 
         for (int32_t e = threadIdx.x; e <= 2 * lim; e += 256)
             table[e] = (uint8_t)gelu_eval_any(e - lim, Q);
         __syncthreads();
-        if (i < n4) stream_store(pack4(one(v.x), one(v.y), one(v.z), one(v.w)), out32 + i);
-        for (i += stride; i < n4; i += stride) {
-            v = __builtin_nontemporal_load(in4 + i);
-            stream_store(pack4(one(v.x), one(v.y), one(v.z), one(v.w)), out32 + i);
-        }
+        if (i < n4) store_and_follow(v, i, n4, stride, in4, out32, one);
         if (blockIdx.x == 0) {
             const int64_t j = (n4 << 2) + threadIdx.x;
             if (threadIdx.x < 4 && j < n) out[j] = (uint8_t)one(in[j]);
@@ -459,7 +489,7 @@ hipError_t gelu_i32_dispatch(const int32_t *in, int8_t *out, int64_t n, const Ge
         const dim3 block(256);
         const bool looping = gelu32_looping_grid(n, (reinterpret_cast<uintptr_t>(uout) & 63) == 0);
         if (table)
-            grid = dim3(grid_for(n >> 2, 256, looping ? kGelu32ShortGridCap : kGelu32TableGridCap));
+            grid = dim3(grid_for(n >> 2, 256, looping ? kResidentWorkgroups : kGelu32TableGridCap));
         if (table) launch_kernel(gelu_i32_table_kernel<true>, grid, block, 0, stream, in, uout, n, head, grid.x, P);
         else if (mode == 0) launch_kernel((gelu_i32_kernel<true, 0>), grid, block, 0, stream, in, uout, n, head, grid.x, P);
         else if (mode == 1) launch_kernel((gelu_i32_kernel<true, 1>), grid, block, 0, stream, in, uout, n, head, grid.x, P);
@@ -479,11 +509,11 @@ hipError_t requant_dispatch(const int32_t *in, void *out, int64_t n, const Dyadi
 {
     uint8_t *uout = reinterpret_cast<uint8_t *>(out);
     int32_t head = 0;
-    // Up to about 100 MB one resident generation of workgroups (8 per compute unit) that loop is
-    // faster than many short-lived ones (kernel-trace durations: 24.6 MB 5.8 against 6.7 us,
-    // 49 MB 9.4 against 10.7, 98 MB 16.7 against 18.2); from 200 MB on the order reverses
-    // (298 MB: 48.8 against 47.3 us).
-    const int64_t cap = n <= 25 * 1000 * 1000 ? 256 * 8 : 256 * 64;
+    // Up to about 150 MB one resident generation of workgroups (8 per compute unit) that loop is
+    // faster than many short-lived ones (5 million values 5.3 against 5.9 us, 19.4 million 16.3
+    // against 17.3, 25 million 20.6 against 21.1); from 32 million on the order reverses (26.2 against
+    // 25.9, 50 million 40.2 against 39.2).
+    const int64_t cap = n <= 30 * 1000 * 1000 ? kResidentWorkgroups : 256 * 64;
     if (peel_to_dword_out(in, uout, n, &head)) {
         const dim3 grid(grid_for(n >> 2, 256, cap));
         launch_kernel(requant_kernel<true>, grid, dim3(256), 0, stream, in, uout, n, head, grid.x, P);
