@@ -7,7 +7,7 @@
 // computed: the first LDS_PASSES passes straight into LDS (global_load_lds, no registers), the rest
 // into the registers that the scores leave when they have become exponentials.
 //   LDS: at most 9 passes of 16 KB of the 160 KB; registers: 128 per lane at 16 wavefronts.
-// 2048 rows of 50176 scores 93.6 us (5.5 TB/s; 1212 us in the three-pass kernel, one wavefront per
+// 2048 rows of 50176 scores 91.0 us (5.6 TB/s; 1212 us in the three-pass kernel, one wavefront per
 // row), of 65536 129 us (1567 us), 2000 rows of 32768 67.8 us (78.5 us as 16 wavefronts without the
 // prefetch), 10 rows of 62000 12.9 us (720 us).  What is left: the last passes are asked for while
 // the row is computed and not before, so the memory pipe still drains a little once per row; and the

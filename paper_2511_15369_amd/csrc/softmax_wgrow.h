@@ -179,17 +179,30 @@ softmax_wgrow_kernel(WideArgs A)
     }
 }
 
+// The bound of wide_most_workgroups for a workgroup per row, for launches of more than 60 million scores:
+// 90 / 190 million in rows of 7000 scores 74.4 / 157 us against 75.4 / 159 without it, of 7600 73.3 / 153
+// against 75.0 / 157, of 8192 72.3 / 151 against 75.1 / 158; at 45 million both take the same time.  Eight
+// passes of 8 wavefronts (14334 to 16384 scores) from 150 million on: 190 million in rows of 15500 157 us
+// against 159, of 16000 147 against 155, while at 62 million 55.0 against 54.0.
+constexpr int wgrow_most_workgroups(int waves, int slots, int64_t scores)
+{
+    if (scores <= 60 * 1000 * 1000) return 0;
+    if (waves == 4) return slots == 6 || slots == 7 ? 5 : (slots == 8 || slots == 9 ? 4 : 0);
+    return waves == 8 && slots == 8 && scores > 150 * 1000 * 1000 ? 2 : 0;
+}
+
 // mode: SoftmaxDev::packed
 template <int WAVES, int SLOTS>
 static void wgrow_launch_ws(const WideArgs &A, int mode, dim3 grid, hipStream_t stream)
 {
+    const size_t lds = lds_for_at_most(wgrow_most_workgroups(WAVES, SLOTS, A.rows * A.cols));
 #define IPTQ_WGROW_LAUNCH(MODE)                                                                   \
     do {                                                                                          \
-        if constexpr (WAVES == 4) launch_kernel((softmax_wgrow_kernel<WAVES, SLOTS, MODE, kAnyVariant>), grid, dim3(64 * WAVES), 0, stream, A); \
-        else if constexpr (WAVES == 16) launch_kernel((softmax_wgrow_kernel<WAVES, SLOTS, MODE, kFirstDegree>), grid, dim3(64 * WAVES), 0, stream, A); \
-        else if (A.P.variant == 0) launch_kernel((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 0>), grid, dim3(64 * WAVES), 0, stream, A); \
-        else if (A.P.variant == 1) launch_kernel((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 1>), grid, dim3(64 * WAVES), 0, stream, A); \
-        else launch_kernel((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 2>), grid, dim3(64 * WAVES), 0, stream, A);                       \
+        if constexpr (WAVES == 4) launch_kernel((softmax_wgrow_kernel<WAVES, SLOTS, MODE, kAnyVariant>), grid, dim3(64 * WAVES), lds, stream, A); \
+        else if constexpr (WAVES == 16) launch_kernel((softmax_wgrow_kernel<WAVES, SLOTS, MODE, kFirstDegree>), grid, dim3(64 * WAVES), lds, stream, A); \
+        else if (A.P.variant == 0) launch_kernel((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 0>), grid, dim3(64 * WAVES), lds, stream, A); \
+        else if (A.P.variant == 1) launch_kernel((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 1>), grid, dim3(64 * WAVES), lds, stream, A); \
+        else launch_kernel((softmax_wgrow_kernel<WAVES, SLOTS, MODE, 2>), grid, dim3(64 * WAVES), lds, stream, A);                       \
     } while (0)
     if (mode == 0) IPTQ_WGROW_LAUNCH(0);
     else if (mode == 1) IPTQ_WGROW_LAUNCH(1);

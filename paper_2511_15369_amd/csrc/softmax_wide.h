@@ -255,21 +255,30 @@ softmax_wide_kernel(WidePacked W)
     }
 }
 
+// LDS to ask for beside a kernel's own (less than 1 KB), so that no more than `most` of its workgroups
+// share a compute unit; LDS is handed out in units of 1280 bytes.  0: no bound.
+constexpr size_t lds_for_at_most(int most) { return most != 0 ? 160 * 1024 / most / 1280 * 1280 - 1024 : 0; }
+
 // Most workgroups per compute unit in a long launch, where registers would allow more of them than is
-// good: with that many rows in flight (180 KB per unit and more from nine passes on) it takes longer.  30
-// to 45 million scores in rows of 1500 25.9 us against 26.3 without the bound, of 2000 26.2 against 26.7,
-// of 2200 38.2 against 39.1, of 2950 38.8 against 39.3; other numbers of passes gain nothing or lose.  At 25
-// to 28 million both take the same time, and 15 million are faster with all that fit (rows of 2200 14.6
-// us against 15.2, of 2950 14.9 against 16.0).  0: no bound.
-constexpr int wide_most_workgroups(int slots)
+// good: with that many rows in flight it takes longer.  0: no bound; the numbers of passes without one
+// gain nothing by it or lose.
+// More than 28 million scores: 30 to 45 million in rows of 1500 25.9 us against 26.3 without the bound,
+// of 2000 26.2 against 26.7, of 2200 38.2 against 39.1, of 2950 38.8 against 39.3.  At 25 to 28 million
+// both take the same time, and 15 million are faster with all that fit (rows of 2200 14.6 us against
+// 15.2, of 2950 14.9 against 16.0).
+// More than 60 million: 90 / 190 million in rows of 1500 72.7 / 150 us with four against 73.6 / 155 with
+// five, of 2500 73.8 / 153 with four against 75.0 / 156 without a bound, of 3800 73.8 / 150 with two
+// against 75.8 / 157, of 4096 72.4 / 148 against 78.1 / 162.  At 45 million two are no faster.
+constexpr int wide_most_workgroups(int slots, bool very_long)
 {
-    return slots >= 5 && slots <= 7 ? 6 : (slots == 8 ? 5 : (slots == 9 || slots == 11 || slots == 12 ? 4 : 0));
+    if (very_long && slots >= 14) return 2;
+    if (very_long && (slots == 6 || slots == 10)) return 4;
+    return slots >= 5 && slots <= 7 ? 5 : (slots == 8 || slots == 9 || slots == 11 || slots == 12 ? 4 : 0);
 }
-// The bound as LDS asked for beside the kernel's own (less than 1 KB).
 inline size_t wide_extra_lds(int slots, const WideArgs &A)
 {
-    const int most = A.rows * A.cols > 28 * 1000 * 1000 ? wide_most_workgroups(slots) : 0;
-    return most != 0 ? 160 * 1024 / most - 1024 : 0;
+    const int64_t scores = A.rows * A.cols;
+    return scores > 28 * 1000 * 1000 ? lds_for_at_most(wide_most_workgroups(slots, scores > 60 * 1000 * 1000)) : 0;
 }
 
 // mode: SoftmaxDev::packed
