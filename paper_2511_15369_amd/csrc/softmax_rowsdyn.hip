@@ -157,13 +157,11 @@ hipError_t softmax_rowsdyn_launch_batch(const SoftmaxCall *calls, const int *pos
     int64_t total_wgs = 0;
     B.n_items = 0;
     auto flush = [&]() -> hipError_t {
-        if (B.n_items >= 2) {
-            const uint32_t wpb = B.item[0].wpb;       // the same for every call of a row length
-            if (!rowsdyn_launch(nullptr, &B, k, slots, 2, dim3((unsigned)total_wgs), dim3(64 * wpb),
-                                (size_t)B.item[0].wave_lds * wpb, stream))
-                return hipSuccess;
+        // (false: no such layout, the caller's next kernel serves these calls; wavefronts per workgroup and
+        // their LDS are the same for every call of a row length)
+        if (B.n_items >= 2 && rowsdyn_launch(nullptr, &B, k, slots, 2, dim3((unsigned)total_wgs), dim3(64 * B.item[0].wpb),
+                                             (size_t)B.item[0].wave_lds * B.item[0].wpb, stream))
             for (int i = 0; i < B.n_items; ++i) done[of[i]] = calls[of[i]].rows;
-        }
         B.n_items = 0;
         total_wgs = 0;
         return take_launch_status();
