@@ -49,3 +49,36 @@ assert len(got) == 16 and {l.kernel for l in got} == {"softmax_wide_kernel"}, go
 """
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     subprocess.run([sys.executable, "-c", code, str(tmp_path)], cwd=root, check=True)
+
+
+def test_batch_of_dependent_problems_keeps_its_order(lib):
+    """Problems that write what another one reads or writes: one launch each, in their order.  Problems
+    that only read the same memory share a launch."""
+    p = ip.softmax_prepare(0.01, 145, 1, 0)
+    n = 4000 * 145
+
+    def starts(*fields, cols=145):
+        got = batch(lib, [(4000, p, f) for f in fields], cols)
+        return [l.kernel for l in got], [l.first_word for l in got]
+
+    one_launch = (["softmax_rowsdyn_batch_kernel"], [2])
+    apart = ["softmax_rowsdyn_kernel"] * 2
+    shared = SCORES + (1 << 30)
+    assert starts({}, {}) == one_launch
+    assert starts(dict(d_scores=SCORES), dict(d_scores=SCORES)) == one_launch
+    assert starts(dict(d_bias=shared, bias_period_rows=64), dict(d_bias=shared, bias_period_rows=64)) == one_launch
+    assert starts(dict(d_out=OUT), dict(d_out=OUT + n)) == one_launch                  # side by side
+    for fields in ((dict(d_out=OUT), dict(d_out=OUT)),                                 # the last one wins
+                   (dict(d_out=OUT), dict(d_out=OUT + n - 1)),
+                   (dict(d_scores=SCORES, d_out=OUT), dict(d_scores=SCORES + (1 << 35), d_out=SCORES + 4 * n - 1)),
+                   (dict(d_out=SCORES + (1 << 35) + 4 * n - 1), dict(d_scores=SCORES + (1 << 35))),
+                   (dict(d_out=shared), dict(d_bias=shared, bias_period_rows=64)),
+                   (dict(d_bias=shared, bias_period_rows=64), dict(d_out=shared + 4 * 64 * 145 - 1))):
+        kernels, words = starts(*fields)
+        assert kernels == apart, fields
+        first = [f.get("d_scores", SCORES + (i << 34)) & 0xffffffff for i, f in enumerate(fields)]
+        assert words == first                                                          # the first argument: d_scores
+    # beside a call that the batch kernel does not take (a window mask), and one of its own output
+    assert starts({}, dict(d_mask=shared, n_windows=2, heads=1), dict(d_out=OUT))[0] == ["softmax_rowsdyn_kernel"] * 3
+    assert starts({}, dict(d_mask=shared, n_windows=2, heads=1), dict(d_out=shared))[0] == ["softmax_rowsdyn_kernel"] * 3
+    assert starts({}, dict(d_mask=shared, n_windows=2, heads=1), {})[0] == ["softmax_rowsdyn_batch_kernel", "softmax_rowsdyn_kernel"]

@@ -52,3 +52,17 @@ def test_batch_of_run_time_row_lengths(cols, n_problems):
         assert np.array_equal(d_y.cpu().numpy().reshape(x.shape), ref.softmax_i32(x, p, bias, period))
         g = guarded.cpu().numpy()
         assert (g[:32 + off] == 0x5A).all() and (g[32 + off + x.size:] == 0x5A).all()
+
+
+def test_problems_that_share_memory_keep_their_order():
+    """Two problems into one output: the bytes are those of the second, as one call after the other
+    leaves them."""
+    import torch
+    import paper_2511_15369_amd as ip
+    rng = np.random.default_rng(7)
+    x = np.rint(rng.standard_normal((9000, 145)) * 900).astype(np.int32)
+    p0, p1 = prepare.softmax_prepare(2.0 ** -9, 145, 1, 0), prepare.softmax_prepare(2.0 ** -5, 145, 0, 0)
+    d_x, d_y = torch.from_numpy(x).cuda(), torch.full(x.shape, 0x5A, dtype=torch.uint8, device="cuda")
+    probs = [ip.softmax_problem(d_x, None, 0, d_y, len(x), 145, lib_softmax(p)) for p in (p0, p1)]
+    ip.softmax_i32_batch(probs, 2, 145)
+    assert np.array_equal(d_y.cpu().numpy(), ref.softmax_i32(x, p1))
