@@ -180,7 +180,7 @@ static bool independent(const SoftmaxCall *calls, int n_calls, int32_t cols)
 
 // Enqueue the softmax of every call (all with the same row length).  Calls that can use a
 // fixed-row-length kernel are grouped, up to kBatchMax per launch, while they agree on what
-// the kernel instantiation fixes (bias or not, post step, packed or 32-bit arithmetic); the
+// the kernel instantiation fixes (bias or not, post step, arithmetic); the
 // rows a slab decomposition leaves over, and calls it cannot serve, go to the generic kernel.
 bool softmax_rows_compiled(int32_t cols)
 {
@@ -219,22 +219,39 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
         IPTQ_ROWS_SHAPES_ALT(IPTQ_PICK_ROWS_SHAPE)
     }
 #undef IPTQ_PICK_ROWS_SHAPE
-    SoftmaxBatch B;
-    B.n_items = 0;
-    unsigned total_wgs = 0;
-    bool g_bias = false, g_fold = false;
-    int g_mask = 0, g_pm = 0, g_mode = 0;             // g_mask: 0 none, 1 int32 table, 2 one bit per key
+    // Calls of either packed arithmetic are collected side by side (a kernel has one of the dividers), so
+    // that layers whose scales lie on both sides of the byte divider's range take two launches, in
+    // whatever order they come: [1] multiply-high divider, [0] the rest.  One launch where every call can
+    // have the multiply-high divider (i0 > 256): a launch costs 3 us, its six more instructions per four
+    // scores less than that.
+    struct Group {
+        SoftmaxBatch B;
+        unsigned total_wgs;
+        bool fold;
+    } group[2];
+    for (Group &g : group) { g.B.n_items = 0; g.total_wgs = 0; g.fold = false; }
+    bool g_bias = false;
+    int g_mask = 0, g_pm = 0, g_mode = 0;             // g_mask: 0 none, 1 int32 table, 2 one bit per key; g_mode: group[0]'s
     hipError_t err = hipSuccess;
     auto flush = [&]() {
-        if (B.n_items == 0 || err != hipSuccess) return;
-        err = launch(B, total_wgs, g_bias, g_mask, g_fold, g_mode, g_pm, stream);
-        g_fold = false;
-        B.n_items = 0;
-        total_wgs = 0;
+        for (int i = 0; i < 2; ++i) {
+            Group &g = group[i];
+            if (g.B.n_items == 0 || err != hipSuccess) continue;
+            err = launch(g.B, g.total_wgs, g_bias, g_mask, g.fold, i == 1 ? 1 : g_mode, g_pm, stream);
+            g.fold = false;
+            g.B.n_items = 0;
+            g.total_wgs = 0;
+        }
     };
     int64_t done[kBatchMax];
     for (int base = 0; base < n_calls; base += kBatchMax) {
         const int cnt = n_calls - base < kBatchMax ? n_calls - base : kBatchMax;
+        bool any_high = false, all_high = true;
+        for (int i = 0; i < cnt; ++i) {
+            const SoftmaxDev &P = calls[base + i].P;
+            any_high = any_high || P.packed == 1;
+            all_high = all_high && (P.packed != 2 || (P.mode16 == 1 && P.t16 == 0));
+        }
         for (int i = 0; i < cnt; ++i) {
             const SoftmaxCall &c = calls[base + i];
             done[i] = 0;
@@ -262,14 +279,17 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
             const int64_t n_slabs = (c.rows + rpw - 1) / rpw;    // a partial last slab is served too
             if (n_slabs == 0) continue;
             const int pm = post_mode_of(c.P, c.out_bits);
-            const int mode = c.P.packed;
-            const bool compatible = B.n_items == 0 || (has_bias == g_bias && has_mask == g_mask && pm == g_pm && mode == g_mode);
-            if (!compatible || B.n_items == kBatchMax) flush();
-            if (B.n_items == 0) { g_bias = has_bias; g_mask = has_mask; g_pm = pm; g_mode = mode; }
-            if (c.P.pre_rowconst != 0) g_fold = true;
-            SoftmaxItem &it = B.item[B.n_items++];
+            const int mode = c.P.packed == 2 && any_high && all_high ? 1 : c.P.packed;
+            const bool first = group[0].B.n_items == 0 && group[1].B.n_items == 0;
+            // (32-bit arithmetic is a launch of its own, and ends the ones in front of it)
+            const bool compatible = first || (has_bias == g_bias && has_mask == g_mask && pm == g_pm && (mode == 0) == (g_mode == 0));
+            if (!compatible) flush();
+            if (first || !compatible) { g_bias = has_bias; g_mask = has_mask; g_pm = pm; g_mode = mode == 0 ? 0 : 2; }
+            Group &g = group[mode == 1 ? 1 : 0];      // (at most kBatchMax calls before the flush below)
+            if (c.P.pre_rowconst != 0) g.fold = true;
+            SoftmaxItem &it = g.B.item[g.B.n_items++];
             it.scores = c.scores; it.bias = c.bias; it.mask = c.mask; it.mask_bits = c.mask_bits; it.out = c.out;
-            it.n_slabs = n_slabs; it.first_wg = total_wgs; it.P = c.P;
+            it.n_slabs = n_slabs; it.first_wg = g.total_wgs; it.P = c.P;
             it.tail_rows = (int32_t)(c.rows % rpw);
             it.share_q = 0; it.share_magic = 0; it.share_sh = 0;
             int64_t n_wgs = (n_slabs + kRowsWpb - 1) / kRowsWpb;
@@ -293,7 +313,7 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
                     n_wgs = (n_slabs + kRowsWpb * q - 1) / (kRowsWpb * q) * q;
                 }
             }
-            total_wgs += (unsigned)n_wgs;
+            g.total_wgs += (unsigned)n_wgs;
             done[i] = c.rows;
         }
         flush();

@@ -82,3 +82,30 @@ def test_batch_of_dependent_problems_keeps_its_order(lib):
     assert starts({}, dict(d_mask=shared, n_windows=2, heads=1), dict(d_out=OUT))[0] == ["softmax_rowsdyn_kernel"] * 3
     assert starts({}, dict(d_mask=shared, n_windows=2, heads=1), dict(d_out=shared))[0] == ["softmax_rowsdyn_kernel"] * 3
     assert starts({}, dict(d_mask=shared, n_windows=2, heads=1), {})[0] == ["softmax_rowsdyn_batch_kernel", "softmax_rowsdyn_kernel"]
+
+
+def packed_softmax(i0, cols, variant=1):
+    """Parameters with that i0: packed arithmetic with the byte divider (i0 up to about 1050), with the
+    multiply-high divider (to about 3270), or none."""
+    p = ip.softmax_prepare(0.01, cols, variant, 0)
+    p.i0, p.n_shift = i0, max(0, 15 - i0.bit_length())
+    return p
+
+
+@pytest.mark.parametrize("order", [(100, 1100), (1100, 100), (1100, 1100, 100, 100, 2000)])
+def test_batch_with_both_dividers(lib, order):
+    """Layers of a compiled row length whose scales lie on both sides of the byte divider's range: one
+    launch for each divider, in whatever order they come."""
+    specs = [(4000, packed_softmax(order[i % len(order)], 197)) for i in range(16)]
+    got = batch(lib, specs, 197)
+    high = sum(q.i0 > 1050 for _, q in specs)
+    assert sorted((l.kernel, l.arguments[2], l.first_word) for l in got) == [
+        ("softmax_rows_kernel", 1, high), ("softmax_rows_kernel", 2, 16 - high)]
+    # one launch where each can have the multiply-high divider
+    wide = [(4000, packed_softmax(max(q.i0, 257 + i), 197)) for i, (_, q) in enumerate(specs)]
+    assert [l.arguments[2] for l in batch(lib, wide, 197)] == [1]
+    assert [l.arguments[2] for l in batch(lib, [w for w in wide if w[1].i0 < 1000], 197)] == [2]
+    # a layer in 32-bit arithmetic ends the launches in front of it, as it always did
+    specs[8] = (4000, packed_softmax(2 ** 14, 197))
+    got = batch(lib, specs, 197)
+    assert [l.arguments[2] for l in got] == [2, 1, 0, 2, 1] and sum(l.first_word for l in got) == 16
