@@ -317,11 +317,23 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
             done[i] = c.rows;
         }
         flush();
-        // several calls of the run-time-row-length kernel in one launch; where one writes what another one
-        // reads or writes, they are made in their order, one launch each
-        int pending = 0;
-        for (int i = 0; i < cnt; ++i) pending += done[i] == 0;
-        if (pending > 1 && err == hipSuccess && independent(calls + base, cnt, cols)) {
+        // a call no compiled row length served goes to the run-time-row-length kernels; the slab kernel
+        // leaves short calls with a mask, a second-degree exponential or a table of fewer rows than its
+        // slab to the others where they are faster (n: that many of them in one launch)
+        auto leave = [&](const SoftmaxCall &c, int n) {
+            const bool may_lose = slab_only(c) || c.P.variant == 2 || (c.bias != nullptr && c.P.bias_period_rows < 64 && cols <= 29);
+            return c.algo == IPTQ_ALGO_AUTO && may_lose &&
+                   rowsdyn_loses_short_call(c.rows, cols, c.bias != nullptr, c.mask != nullptr, c.mask_bits != nullptr, n);
+        };
+        // several calls of the run-time-row-length kernel in one launch, but for two that are sooner done
+        // apart; where one writes what another one reads or writes, they are made in their order, one
+        // launch each
+        int pending = 0, left = 0;
+        for (int i = 0; i < cnt; ++i) {
+            pending += done[i] == 0;
+            left += done[i] == 0 && leave(calls[base + i], 2);
+        }
+        if (pending > 1 && !(pending == 2 && left == 2) && err == hipSuccess && independent(calls + base, cnt, cols)) {
             int post_modes[kBatchMax];
             for (int i = 0; i < cnt; ++i) post_modes[i] = post_mode_of(calls[base + i].P, calls[base + i].out_bits);
             err = softmax_rowsdyn_launch_batch(calls + base, post_modes, cnt, cols, done, stream);
@@ -329,13 +341,7 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
         for (int i = 0; i < cnt && err == hipSuccess; ++i) {
             const SoftmaxCall &c = calls[base + i];
             const bool has_pre = !(c.P.pre_m == 1 && c.P.pre_s == 0);
-            // a call no compiled row length served goes to the run-time-row-length kernels; the slab
-            // kernel leaves short calls with a mask, a second-degree exponential or a table of fewer
-            // rows than its slab to the others where they are faster
-            const bool may_lose = slab_only(c) || c.P.variant == 2 || (c.bias != nullptr && c.P.bias_period_rows < 64 && cols <= 29);
-            const bool leave = c.algo == IPTQ_ALGO_AUTO && may_lose &&
-                               rowsdyn_loses_short_call(c.rows, cols, c.bias != nullptr, c.mask != nullptr, c.mask_bits != nullptr);
-            if (done[i] == 0 && !leave && (c.algo == IPTQ_ALGO_AUTO || c.algo == IPTQ_ALGO_DYNAMIC || c.algo == IPTQ_ALGO_SLAB)) {
+            if (done[i] == 0 && !leave(c, 1) && (c.algo == IPTQ_ALGO_AUTO || c.algo == IPTQ_ALGO_DYNAMIC || c.algo == IPTQ_ALGO_SLAB)) {
                 err = softmax_rowsdyn_launch(c, cols, post_mode_of(c.P, c.out_bits), &done[i], stream);
                 if (err != hipSuccess) break;
             }

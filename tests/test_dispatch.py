@@ -109,3 +109,23 @@ def test_batch_with_both_dividers(lib, order):
     specs[8] = (4000, packed_softmax(2 ** 14, 197))
     got = batch(lib, specs, 197)
     assert [l.arguments[2] for l in got] == [2, 1, 0, 2, 1] and sum(l.first_word for l in got) == 16
+
+
+def test_two_short_calls_that_are_sooner_done_apart(lib):
+    """Two short calls of the second degree or with a short table, where two launches of a shorter chain
+    end sooner; three of them, other calls and longer ones share a launch."""
+    table = dict(d_bias=SCORES + (1 << 30), bias_period_rows=40)
+
+    def kernels(n, rows, cols, variant, fields, algo=0):
+        p = ip.softmax_prepare(0.0085, cols, variant, 0)
+        p.algo = algo
+        return [l.kernel for l in batch(lib, [(rows, p, fields)] * n, cols)]
+
+    together = ["softmax_rowsdyn_batch_kernel"]
+    for args in ((600, 25, 1, table), (1000, 29, 2, table), (600, 64, 2, {})):
+        assert kernels(2, *args) == ["softmax_wide_kernel"] * 2
+        assert kernels(2, *args, algo=ip.ALGO_DYNAMIC) == together
+        assert kernels(3, *args) == together
+    for args in ((64, 25, 1, table), (4000, 25, 1, table), (600, 16, 1, table), (600, 25, 1, {}), (600, 64, 1, {}), (600, 145, 2, {}),
+                 (600, 25, 1, dict(table, bias_period_rows=64))):
+        assert kernels(2, *args) == together, args
