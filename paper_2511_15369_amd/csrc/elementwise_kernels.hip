@@ -330,23 +330,19 @@ constexpr int64_t kGelu32TableGridCap = 256 * 64;
 // Whether one resident generation of workgroups (8 per compute unit) that loop is faster than as
 // many short-lived ones as there are values, each of which builds the table.  (n: values in groups
 // that start on a dword of the output; measured against the uncapped grid.)
-//   - up to 40 million values: 5 M 6.0 us against 6.3, 12 M 11.5 against 11.9, 19.4 M 17.3 against 18.2,
-//     38.4 M 32.4 against 33.0; from 40 M on both grids take the same time up to 46 M, and 76.8 M take
-//     69.2 against 66.6;
-//   - up to 24 million if the output does not start on a 64-byte line (neighbouring wavefronts then
-//     share lines, and the short-lived workgroups write them closer together): 19 M 18.4 against 18.7,
-//     24 M 22.6 against 22.7, 30 M 27.7 against 27.3, 36 M 32.5 against 32.1;
-//   - not where most of the generation would make a second trip while the others are done: 2.6 M 4.0
-//     against 4.2, 3.0 M 4.6 against 4.4, 3.4 M 5.1 against 4.7, 4.1 M 5.6 against 5.4, 4.3 M 5.6 against 5.7.
-// Those figures are of one chunk in flight per thread.  With the next one's load in flight as well
-// (store_and_follow) both grids are faster and the lines would lie elsewhere: 3.0 M 3.9 us against 4.4 and
-// 3.4 M 4.2 against 4.7 for the looping grid, 32 M 26.2 against 26.0 and 40 M 32.7 against 31.8 for the other.
+//   - up to 29 million values: 2.4 M 3.62 us against 3.98, 3.4 M 4.22 against 4.65, 5.5 M 5.85 against 6.48,
+//     10 M 9.5 against 10.3, 19.4 M 17.0 against 18.3, 28 M 23.9 against 24.3; 30 M 25.5 against 25.4, 34 M 28.8
+//     against 28.3, 40 M 33.8 against 32.7, 60 M 49.8 against 48.9;
+//   - up to 25 million if the output does not start on a 64-byte line (neighbouring wavefronts then
+//     share lines, and the short-lived workgroups write them closer together): 5 bytes off 24 M 22.5
+//     against 22.8, 30 M 28.1 against 27.0, 40 M 37.4 against 34.7; 16 bytes off 28 M 25.0 against 25.3, 30 M
+//     26.8 against 26.5.
 // Evening out the trips per workgroup is slower than either (19.4 M 23.5 us with a requantization
-// behind it, 22.9 as here).  The kernel for unaligned groups serves calls of less than 64 values only.
+// behind it, 22.9 with uneven ones, before the next chunk's load was kept in flight).  The kernel for
+// unaligned groups serves calls of less than 64 values only.
 bool gelu32_looping_grid(int64_t n, bool out_on_line)
 {
-    if (n > 2800 * 1000 && n < 4200 * 1000) return false;
-    return n <= (out_on_line ? 40 : 24) * 1000 * 1000;
+    return n <= (out_on_line ? 29 : 25) * 1000 * 1000;
 }
 template <bool ALIGNED>
 __global__ void __launch_bounds__(256)

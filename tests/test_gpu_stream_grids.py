@@ -13,7 +13,7 @@ LONG = 4 * 256 * 16384 * 4                               # and four chunks to ev
 
 
 @pytest.mark.parametrize("n", [63, 64, 67, 1025, ONE - 4, ONE, ONE + 1, ONE + 1027, 2 * ONE + 5, 2_800_001, 4_200_003,
-                               24_000_002, 30_000_000, 30_000_001, 40_000_003, LONG, LONG + 9])
+                               24_000_002, 25_000_000, 25_000_003, 29_000_000, 29_000_003, 30_000_000, 30_000_001, 40_000_003, LONG, LONG + 9])
 @pytest.mark.parametrize("offset", [0, 3])
 def test_gelu_i32_and_requant_over_the_grids(n, offset):
     import torch
