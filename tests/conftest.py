@@ -1,4 +1,5 @@
 import os
+import shutil
 import sys
 
 import pytest
@@ -15,3 +16,12 @@ def pytest_configure(config):
 @pytest.fixture(scope="session")
 def golden_dir():
     return os.path.join(ROOT, "tests", "golden")
+
+
+@pytest.fixture(scope="session")
+def recording_library(tmp_path_factory):
+    """The library's host code on a runtime that records launches (tests/host_library.py)."""
+    if shutil.which("hipcc") is None:
+        pytest.skip("hipcc not installed")
+    from tests import host_library
+    return host_library.build(str(tmp_path_factory.mktemp("recording")))

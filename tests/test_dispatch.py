@@ -14,9 +14,9 @@ pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not
 SCORES, OUT = 1 << 40, 1 << 44                            # addresses that nothing follows
 
 
-@pytest.fixture(scope="module")
-def lib(tmp_path_factory):
-    return host_library.build(str(tmp_path_factory.mktemp("recording")))
+@pytest.fixture
+def lib(recording_library):
+    return recording_library
 
 
 def problems(specs, cols):

@@ -89,39 +89,50 @@ def test_tables_requantization_and_post_steps(cols):
         _check(x, p, bias, 2, 0, 5)
 
 
-def _mode16(p, cols):
-    fn = ip.load().iptq_debug_softmax_plan
-    fn.argtypes = [ctypes.POINTER(ip.SoftmaxParams), ctypes.c_int64, ctypes.c_int32, ctypes.c_int32,
-                   ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]
-    out = (ctypes.c_int64 * 12)()
+def _packed(p):
+    fn = ip.load().iptq_debug_softmax_packed
+    fn.argtypes = [ctypes.POINTER(ip.SoftmaxParams), ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]
+    packed, div8 = ctypes.c_int32(-1), ctypes.c_int32()
     lp = lib_softmax(p)
-    assert fn(ctypes.byref(lp), 1, cols, 0, 0, out) == 0
-    return int(out[8])
+    assert fn(ctypes.byref(lp), ctypes.byref(packed), ctypes.byref(div8)) == 0
+    return packed.value
 
 
 # five rows for most workgroups, and more than a requantization in front leaves to a workgroup per row
 WALKED_ROWS = 1200
 WALKS = [
-    # variant, scale, packed arithmetic, requantization in front, post step, table
-    (0, 2.0 ** -7, True, (1, 0), None, False),
-    (1, 2.0 ** -13, False, (1, 0), None, False),
-    (1, 2.0 ** -6, True, (1, 0), (3, 2, 5), False),
-    (2, 2.0 ** -6, True, (1, 0), (1, 0, -128), False),
-    (1, 2.0 ** -6, True, (20000, 20), None, False),
-    (0, 2.0 ** -13, False, (300, 9), (3, 2, 5), False),
-    (2, 2.0 ** -6, True, (1, 0), None, True),
-    (1, 2.0 ** -6, True, (1, 0), (3, 2, 5), True),
-    (0, 2.0 ** -13, False, (20000, 20), None, True),
-    (2, 2.0 ** -12, False, (300, 9), (1, 0, -128), True),
+    # variant, scale, packed arithmetic (0 none, 1 multiply-high divider, 2 byte divider), requantization in
+    # front, post step, table: each arithmetic with and without either of the last two, in every variant
+    (0, 2.0 ** -7, 2, (1, 0), None, False),
+    (1, 2.0 ** -13, 0, (1, 0), None, False),
+    (1, 2.0 ** -6, 2, (1, 0), (3, 2, 5), False),
+    (2, 2.0 ** -6, 2, (1, 0), (1, 0, -128), False),
+    (1, 2.0 ** -6, 2, (20000, 20), None, False),
+    (0, 2.0 ** -13, 0, (300, 9), (3, 2, 5), False),
+    (2, 2.0 ** -6, 2, (1, 0), None, True),
+    (1, 2.0 ** -6, 2, (1, 0), (3, 2, 5), True),
+    (0, 2.0 ** -13, 0, (20000, 20), None, True),
+    (2, 2.0 ** -12, 0, (300, 9), (1, 0, -128), True),
+    (0, 2.0 ** -13, 0, (1, 0), None, False),
+    (2, 2.0 ** -13, 0, (1, 0), None, False),
+    (1, 2.0 ** -13, 0, (300, 9), None, True),
+    (0, 2.0 ** -6, 2, (1, 0), (3, 2, 5), True),
+    (0, 1 / 2000.5, 1, (1, 0), None, False),
+    (1, 1 / 2896.5, 1, (1, 0), (3, 2, 5), False),
+    (2, 1 / 3139.5, 1, (1, 0), (1, 0, -128), False),
+    (0, 1 / 2896.5, 1, (20000, 16), None, False),
+    (1, 1 / 2000.5, 1, (1, 0), None, True),
+    (2, 1 / 2000.5, 1, (20000, 16), (3, 2, 5), True),
 ]
 
 
 @pytest.mark.parametrize("cols", [26625, 28672, 33001, 36864, 36866, 40957, 41000, 53251, 65533])
 @pytest.mark.parametrize("walk", range(len(WALKS)))
 def test_every_kernel_walks(cols, walk):
-    """Several rows per workgroup in every instantiation: the prefetch of the next row beside a table,
-    a requantization, 32-bit lanes, every variant and post step, 7 passes to 16, either side of the 9
-    passes that LDS holds and 10 of the workgroup per row, tensors that start and end off the grid."""
+    """Several rows per workgroup in every instantiation (three arithmetics, three variants, with and without
+    a table or a requantization): the prefetch of the next row beside them, every post step, 7 passes to 16,
+    either side of the 9 passes that LDS holds and 10 of the workgroup per row, tensors that start and end
+    off the grid."""
     import torch
     variant, s_delta, packed, pre, post, table = WALKS[walk]
     signed = 1 if post == (1, 0, -128) else 0
@@ -130,7 +141,7 @@ def test_every_kernel_walks(cols, walk):
     p.pre_m, p.pre_s = pre
     if post is not None:
         p.post = ref.Dyadic(post[0], post[1], post[2], -128 if signed else 0, 127 if signed else 255)
-    assert (_mode16(p, cols) != 0) == packed
+    assert _packed(p) == packed
     unit = p.i0 * (1 << pre[1]) // pre[0]
     few = _scores(rng, 28, cols, unit)                                # a multiple of four: the table's size too
     few[4:26:2] = _scores(rng, 15, cols, 4 * unit)[3:14]              # rows with large probabilities
