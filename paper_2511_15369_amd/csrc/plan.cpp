@@ -127,11 +127,9 @@ int plan_softmax(const iptq_softmax_params_t *p, int64_t rows, int32_t cols, int
     if (p->pre_m == 1 && p->pre_s == 0) {
         out->pre_mode = 0;
     } else if (p->pre_s >= 16) {
-        // (x m + 2^(s-1)) >> s == (x m 2^(32-s) + 2^31) >> 32 for s <= 32, and
-        // ((x m + 2^(s-1)) >> 32) >> (s - 32) beyond; |x m| < 2^46, so the result fits 32 bits
         out->pre_mode = 1;
-        out->pre_mul = p->pre_s <= 32 ? p->pre_m << (32 - p->pre_s) : p->pre_m;
-        out->pre_rnd = p->pre_s <= 32 ? ((int64_t)1 << 31) : ((int64_t)1 << (p->pre_s - 1));
+        out->pre_mul = pre_mul_of(p->pre_m, p->pre_s);
+        out->pre_rnd = pre_rnd_of(p->pre_s);
         out->pre_sh2 = p->pre_s <= 32 ? 0 : p->pre_s - 32;
     } else {
         out->pre_mode = 2;
@@ -139,7 +137,7 @@ int plan_softmax(const iptq_softmax_params_t *p, int64_t rows, int32_t cols, int
     out->post_m = p->post.m; out->post_s = p->post.s; out->post_zp = p->post.zp;
     out->qmin = p->post.qmin; out->qmax = p->post.qmax;
     out->post_xor = (p->out_is_signed == 1 && p->post.m == 1 && p->post.s == 0 && p->post.zp == -128 &&
-                     p->post.qmin == -128 && p->post.qmax >= 0) ? 0x80808080u : 0u;
+                     p->post.qmin == -128 && p->post.qmax >= 0) ? kPostXor : 0u;
     out->variant = p->variant;
     out->d2_magic = 0;
     out->d2_sh = 0;

@@ -79,6 +79,14 @@ struct DyadicDev {
     int32_t m, s, zp, qmin, qmax;
 };
 
+// Constants that follow from others.  The plan derives them with these functions, and so does a kernel
+// whose arguments leave them out.
+// pre_mode 1: (x m + 2^(s-1)) >> s == (x m 2^(32-s) + 2^31) >> 32 for s <= 32, and
+// ((x m + 2^(s-1)) >> 32) >> (s - 32) beyond; |x m| < 2^46, so the result fits 32 bits.
+constexpr int32_t pre_mul_of(int32_t pre_m, int32_t pre_s) { return pre_s <= 32 ? pre_m << ((32 - pre_s) & 31) : pre_m; }
+constexpr int64_t pre_rnd_of(int32_t pre_s) { return (int64_t)1 << (pre_s <= 32 ? 31 : pre_s - 1); }
+constexpr uint32_t kPostXor = 0x80808080u;            // post_xor where it applies
+
 // Unsigned division by a constant through multiply-high: for every 0 <= n < 2^nbits,
 // (mulhi32(n, magic) >> sh) == n / d.  Requires 1 <= d < 2^nbits and nbits <= 31.
 // Returns false if no 32-bit magic exists for that range (cannot happen for nbits <= 31).

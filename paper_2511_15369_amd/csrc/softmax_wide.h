@@ -39,7 +39,8 @@ struct WideArgs {
 
 // The same in 88 bytes instead of 208: a launch's arguments are written into device memory by the host,
 // about 0.3 us for the difference, and a call of one image lasts 3 us.  What fits a few bits shares a
-// word, and what follows from other fields is derived again.
+// word, and what follows from other fields is derived again.  (The fields have no room to spare and are not
+// masked: tests/test_wide_arguments.py holds them against plan_softmax over its whole domain.)
 struct WidePacked {
     const int32_t *scores, *bias;
     uint8_t *out;
@@ -91,12 +92,11 @@ IPTQ_HD WideArgs wide_unpack(const WidePacked &W)
     P.pre_s = (int32_t)(W.w1 & 63u); P.pre_sh2 = (int32_t)(W.w1 >> 6 & 31u); P.pre_rowconst = (int32_t)(W.w1 >> 11 & 1u);
     P.post_s = (int32_t)(W.w1 >> 12 & 63u); P.d2_sh = (int32_t)(W.w1 >> 18 & 31u); P.period_sh = (int32_t)(W.w1 >> 23 & 31u);
     P.pre_m = (int32_t)(W.w2 & 0xffffu); P.post_m = (int32_t)W.w2 >> 16;
-    // as plan_softmax derives them (pre_mode 1 alone uses them)
-    P.pre_mul = P.pre_s <= 32 ? P.pre_m << ((32 - P.pre_s) & 31) : P.pre_m;
-    P.pre_rnd = (int64_t)1 << (P.pre_s <= 32 ? 31 : P.pre_s - 1);
+    P.pre_mul = pre_mul_of(P.pre_m, P.pre_s);         // (pre_mode 1 alone uses them)
+    P.pre_rnd = pre_rnd_of(P.pre_s);
     P.qmin = (int32_t)(W.w3 << 22) >> 22; P.qmax = (int32_t)(W.w3 << 12) >> 22;
     P.post_zp = W.post_zp;
-    P.post_xor = (W.w3 >> 22 & 1u) != 0 ? 0x80808080u : 0u;
+    P.post_xor = (W.w3 >> 22 & 1u) != 0 ? kPostXor : 0u;
     P.pre_dmax = W.pre_dmax; P.d2_magic = W.d2_magic;
     P.bias_period_rows = W.bias_period_rows; P.period_magic = W.period_magic;
     P.t16 = P.mode16 = P.packed = 0;                  // not read by these kernels
