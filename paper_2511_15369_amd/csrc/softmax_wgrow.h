@@ -46,6 +46,12 @@ struct WorkgroupSum {
 // against 162.8); 16 wavefronts serve the first-degree variants only (wgrow16_is_faster).
 constexpr int kAnyVariant = -1;                       // by the parameters
 constexpr int kFirstDegree = -2;                      // 0 or 1, by the parameters
+// Loads of the table in flight (add_table_blocks; 0: in the compiler's order): no more than leave the
+// registers for as many workgroups as without a table (11 passes: three with four loads, two with more).
+constexpr int wgrow_table_ahead(int waves, int slots)
+{
+    return waves != 8 ? 0 : (slots == 8 || slots == 9 ? 8 : (slots == 11 ? 4 : 0));
+}
 template <int WAVES, int SLOTS, int MODE, int VARIANT>
 __global__ void __launch_bounds__(64 * WAVES)
 softmax_wgrow_kernel(WideArgs A)
@@ -100,10 +106,14 @@ softmax_wgrow_kernel(WideArgs A)
     if (A.bias != nullptr) {
         const int64_t eb = (int64_t)row_mod_period((uint32_t)row, P) * cols;
         const i32x4 *bsrc = reinterpret_cast<const i32x4 *>(A.bias) + (eb >> 2);
+        if constexpr (wgrow_table_ahead(WAVES, SLOTS) != 0) {
+            add_table_blocks<SLOTS, wgrow_table_ahead(WAVES, SLOTS)>(v, [&](int s) { return bsrc[block_of(s, nb)]; });
+        } else {
 #pragma unroll
-        for (int s = 0; s < SLOTS; ++s) {
-            const i32x4 bv = bsrc[block_of(s, nb)];
-            v[s] = add_table_chunk(v[s], bv);
+            for (int s = 0; s < SLOTS; ++s) {
+                const i32x4 bv = bsrc[block_of(s, nb)];
+                v[s] = add_table_chunk(v[s], bv);
+            }
         }
     }
 

@@ -109,6 +109,8 @@ IPTQ_HD WideArgs wide_unpack(const WidePacked &W)
 // scores 52.6 us against 53.9 us).  Up to eight passes: with more the folded form needs so many
 // registers that it is the slower one (12,000 rows of 3000 scores 33.2 against 32.3 us).
 constexpr int kWideFoldMaxSlots = 8;
+// Loads of the table in flight (add_table_blocks; 0: in the compiler's order).
+constexpr int wide_table_ahead(int slots) { return slots == 8 || slots == 9 ? 8 : 0; }
 template <int SLOTS, int MODE, int VARIANT, bool PRE>
 __global__ void __launch_bounds__(256)
 softmax_wide_kernel(WidePacked W)
@@ -165,10 +167,14 @@ softmax_wide_kernel(WidePacked W)
         // the bias row starts at the same offset inside a block (period * cols % 4 == 0)
         const int64_t eb = (int64_t)row_mod_period((uint32_t)row, P) * cols;
         const i32x4 *bsrc = reinterpret_cast<const i32x4 *>(A.bias) + (eb >> 2);
+        if constexpr (wide_table_ahead(SLOTS) != 0) {
+            add_table_blocks<SLOTS, wide_table_ahead(SLOTS)>(v, [&](int s) { return bsrc[block_of(s, nb)]; });
+        } else {
 #pragma unroll
-        for (int s = 0; s < SLOTS; ++s) {
-            const i32x4 bv = bsrc[block_of(s, nb)];
-            v[s] = add_table_chunk(v[s], bv);
+            for (int s = 0; s < SLOTS; ++s) {
+                const i32x4 bv = bsrc[block_of(s, nb)];
+                v[s] = add_table_chunk(v[s], bv);
+            }
         }
     }
 
