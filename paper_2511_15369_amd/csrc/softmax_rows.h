@@ -185,6 +185,9 @@ IPTQ_DEV i32x4 bias_chunk_wrapping(const int32_t *bias, uint32_t o, uint32_t pe,
     return bias_chunk_wrapped(load_i32x4(bias + min(o, pe - 4u)), o, pe, first4);
 }
 
+// Whether the scores go into the exponentials of the first degree as they are.
+inline bool plain_arithmetic(const SoftmaxDev &P) { return P.variant != 2 && P.pre_mode == 0; }
+
 // A row's blocks plus its table row's (load(s): block s), AHEAD loads of the table kept in flight.  In the
 // compiler's own order, which follows the kernel's register need, nearly every load was waited for by itself
 // where the arithmetic needs few: 35 million scores in rows of 2200 with a table 39.5 us against 35.4 before
@@ -990,6 +993,22 @@ constexpr bool rows_maskbits_compiled(int cols) { return cols == 49 || cols == 1
 IPTQ_ROWS_SHAPES(IPTQ_DECLARE_ROWS_LAUNCHER)
 IPTQ_ROWS_SHAPES_ALT(IPTQ_DECLARE_ROWS_LAUNCHER)
 
+// LDS to ask for beside a kernel's own, so that two workgroups share a compute unit instead of three in the
+// longest launches: with as many rows in flight as fit, the shorter arithmetic made rows of 198 2 to 3 % slower
+// than they had been.  95 / 130 / 190 million scores 76.0 / 101.5 / 148.0 us with two, 77.5 / 105.3 / 152.9 with three; of
+// 197 78.4 / 103.9 / 147.5 and 78.8 / 105.5 / 151.3, but 94.0 and 93.4 at 115 million.  Not with a table, a requantization
+// in front or the second degree (190 million of 197: 173, 164 and 158 us with two, 160, 151 and 149 with three).
+// Rows of 144 and 577 gain nothing, of 257 not on every card, of 49 less than 1 %.
+inline size_t rows_extra_lds(int cols, int k, unsigned total_wgs, const SoftmaxBatch &B)
+{
+    if (!((cols == 197 || cols == 198) && k == 4)) return 0;
+    if (cols == 197 && (int64_t)total_wgs * kRowsWpb * (64 / k) * cols <= 120 * 1000 * 1000) return 0;
+    for (int i = 0; i < B.n_items; ++i)
+        if (!plain_arithmetic(B.item[i].P)) return 0;
+    const int own = kRowsWpb * (64 / k) * cols * 4;   // LDS is handed out in units of 1280 bytes
+    return (size_t)(160 * 1024 / 3 / 1280 * 1280 + 1280 - own);
+}
+
 #define IPTQ_ROWS_LAUNCH(COLS, K, MODE, BIAS, PM, MASK)                                           \
     do {                                                                                          \
         if constexpr (MASK == 1)                                                                  \
@@ -997,7 +1016,7 @@ IPTQ_ROWS_SHAPES_ALT(IPTQ_DECLARE_ROWS_LAUNCHER)
         else if constexpr (MASK == 2)                                                             \
             launch_kernel((softmax_rows_maskbits_kernel<COLS, K, MODE, PM>), grid, block, 0, stream, B); \
         else                                                                                      \
-            launch_kernel((softmax_rows_kernel<COLS, K, MODE, BIAS, PM>), grid, block, 0, stream, B);    \
+            launch_kernel((softmax_rows_kernel<COLS, K, MODE, BIAS, PM>), grid, block, lds, stream, B);    \
     } while (0)
 
 template <int COLS, int K, bool BIAS, int MASK>
@@ -1005,6 +1024,7 @@ static hipError_t launch_rows_b(const SoftmaxBatch &B, unsigned total_wgs, int m
                                 hipStream_t stream)
 {
     const dim3 grid(total_wgs), block(64 * kRowsWpb);
+    [[maybe_unused]] const size_t lds = BIAS || MASK != 0 ? 0 : rows_extra_lds(COLS, K, total_wgs, B);
 #define IPTQ_ROWS_LAUNCH_PM(MODE)                                                                 \
     switch (post_mode) {                                                                          \
     case PM_NONE: IPTQ_ROWS_LAUNCH(COLS, K, MODE, BIAS, PM_NONE, MASK); break;                    \

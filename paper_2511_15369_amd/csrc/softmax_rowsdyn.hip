@@ -133,6 +133,22 @@ static bool rowsdyn_launch(const DynArgs *A, const DynBatch *B, int k, int slots
                       : rowsdyn_launch_k16_long(A, B, slots, mode, grid, block, lds, stream);
 }
 
+// LDS to ask for in the longest launches: one workgroup per compute unit less than would fit, where three are
+// left.  16 lanes per row, up to 8 blocks each, or 10 on the 16-byte grid: 130 / 190 million scores in rows of
+// 401 107.8 / 157.4 us against 109.8 / 160.2, of 430 106.8 / 154.8 against 108.6 / 159.2, of 600 102.5 / 147.1 against
+// 106.1 / 155.4 (95 million 76.2 and 78.2, 65 million the same).  9 blocks gain nothing (570 109.3 / 156.1 against
+// 107.6 / 155.8), and with a table, a requantization in front or the second degree it is slower (600 162 against
+// 152, 155 against 151, 151.6 against 151.2).
+static size_t rowsdyn_lds(const DynArgs &A, int lanes, int slots, int64_t scores)
+{
+    const size_t own = (size_t)A.wave_lds * A.wpb;
+    if (lanes != 16 || scores <= 110 * 1000 * 1000 || A.bias != nullptr || A.mask != nullptr || A.mask_bits != nullptr ||
+        !plain_arithmetic(A.P) || !(slots <= 8 || (slots == 10 && A.cols % 4 == 0)))
+        return own;
+    const int fit = 160 * 1024 / (int)((own + 1279) / 1280 * 1280);       // handed out in units of 1280 bytes
+    return fit >= 4 ? (size_t)(160 * 1024 / (fit - 1) / 1280 * 1280) : own;
+}
+
 // Every row of one call if the call qualifies; returns the number of rows served through
 // *done (0: not served, nothing enqueued).
 hipError_t softmax_rowsdyn_launch(const SoftmaxCall &c, int32_t cols, int post_mode, int64_t *done,
@@ -145,7 +161,7 @@ hipError_t softmax_rowsdyn_launch(const SoftmaxCall &c, int32_t cols, int post_m
     int64_t n_wgs = 0;
     if (!rowsdyn_arguments(c, cols, post_mode, k, &A, &n_wgs)) return hipSuccess;
     if (!rowsdyn_launch(&A, nullptr, k, slots, c.P.packed, dim3((unsigned)n_wgs), dim3(64 * A.wpb),
-                        (size_t)A.wave_lds * A.wpb, stream))
+                        rowsdyn_lds(A, k, slots, c.rows * cols), stream))
         return hipSuccess;                            // no such layout: the caller's next kernel serves it
     *done = c.rows;
     return take_launch_status();

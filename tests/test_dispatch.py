@@ -129,3 +129,67 @@ def test_two_short_calls_that_are_sooner_done_apart(lib):
     for args in ((64, 25, 1, table), (4000, 25, 1, table), (600, 16, 1, table), (600, 25, 1, {}), (600, 64, 1, {}), (600, 145, 2, {}),
                  (600, 25, 1, dict(table, bias_period_rows=64))):
         assert kernels(2, *args) == together, args
+
+
+@pytest.mark.parametrize("rows,cols,most", [
+    # one wavefront per row: the fewest and the most passes with each bound, and the lines between
+    (60_000_000 // 816 + 1, 816, 0), (60_000_000 // 820 + 1, 820, 6), (60_000_000 // 948 + 1, 948, 6), (60_000_000 // 952 + 1, 952, 5),
+    (60_000_000 // 949 + 1, 949, 0), (60_000_000 // 950 + 1, 950, 6), (60_000_000 // 952, 952, 0),
+    (60_000_000 // 1500 + 1, 1500, 4), (28_000_000 // 1500 + 1, 1500, 5), (28_000_000 // 1500, 1500, 0), (60_000_000 // 2500 + 1, 2500, 4),
+    (60_000_000 // 3330 + 1, 3330, 3), (60_000_000 // 3756 + 1, 3756, 3), (60_000_000 // 3760 + 1, 3760, 2), (60_000_000 // 4093 + 1, 4093, 2),
+    # one workgroup per row
+    (60_000_000 // 6001 + 1, 6001, 5),
+    (60_000_000 // 8000 + 1, 8000, 4), (60_000_000 // 8150 + 1, 8150, 4), (60_000_000 // 8192 + 1, 8192, 3), (60_000_000 // 8192, 8192, 0),
+    (60_000_000 // 9000 + 1, 9000, 4), (110_000_000 // 9300, 9300, 0), (110_000_000 // 9300 + 1, 9300, 3), (110_000_000 // 10240 + 1, 10240, 3),
+    (150_000_000 // 16000 + 1, 16000, 2), (150_000_000 // 16000, 16000, 0)])
+def test_workgroups_per_compute_unit(lib, rows, cols, most):
+    """The LDS that long launches ask for: that many workgroups fit the 160 KB of a compute unit beside their
+    own (less than 1 KB), handed out in units of 1280 bytes, and one more does not."""
+    got = batch(lib, [(rows, ip.softmax_prepare(0.0085, cols, 1, 0))], cols)
+    assert len(got) == 1 and got[0].kernel in ("softmax_wide_kernel", "softmax_wgrow_kernel")
+    if most == 0:
+        assert got[0].lds == 0
+    else:
+        for own in (1, 1024):
+            assert 128 // -(-(got[0].lds + own) // 1280) == most
+
+
+@pytest.mark.parametrize("rows,cols,plain,others", [
+    # (with a table, with a requantization in front, of the second degree)
+    (70_000, 900, 6, (0, 0, 0)), (70_000, 1000, 5, (5, 0, 5)), (20_000, 3400, 3, (2, 3, 3)), (20_000, 3600, 3, (2, 3, 3)),
+    (20_000, 3800, 2, (2, 2, 2)), (20_000, 4096, 2, (2, 2, 2)), (8_000, 8192, 3, (4, 4, 4)), (12_000, 9300, 3, (0, 0, 0)),
+    (12_000, 6400, 5, (5, 5, 5)), (45_000, 1500, 4, (4, 4, 4))])
+def test_workgroups_beside_more_arithmetic(lib, rows, cols, plain, others):
+    """Where a table, a requantization or the second degree fills the time, fewer bounds apply."""
+    def fits(variant, fields, pre):
+        p = ip.softmax_prepare(0.0085, cols, variant, 0)
+        if pre:
+            p.pre_m, p.pre_s = 300, 9
+        lds = batch(lib, [(rows, p, fields)], cols)[0].lds
+        return 0 if lds == 0 else 128 // -(-(lds + 1024) // 1280)
+
+    table = dict(d_bias=SCORES + (1 << 38), bias_period_rows=64)
+    assert (fits(1, {}, False), (fits(1, table, False), fits(1, {}, True), fits(2, {}, False))) == (plain, others)
+
+
+@pytest.mark.parametrize("rows,cols,own,fit", [
+    (612_000, 197, 4 * 16 * 197 * 4, 2), (455_000, 198, 4 * 16 * 198 * 4, 2), (600_000, 197, None, None), (454_000, 198, None, None),
+    (340_000, 577, None, None), (275_000, 401, 0, 5), (274_000, 401, None, None), (185_000, 600, 0, 3), (183_000, 600, None, None),
+    (196_000, 566, None, None), (196_000, 568, None, None), (175_000, 632, None, None)])
+def test_slabs_per_compute_unit(lib, rows, cols, own, fit):
+    """The same for the slab kernels, whose workgroups keep their rows in LDS."""
+    def lds(n, variant=1, pre=False, **fields):
+        p = ip.softmax_prepare(0.0085, cols, variant, 0)
+        if pre:
+            p.pre_m, p.pre_s = 300, 9
+        got = batch(lib, [(n, p, fields)], cols)
+        assert len(got) == 1
+        return got[0].lds
+
+    short = lds(6400)
+    if fit is None:
+        assert lds(rows) == short
+    else:
+        for lut in (16, 1024 if own else 0):
+            assert 128 // -(-(lds(rows) + own + lut * bool(own)) // 1280) == fit
+    assert lds(rows, variant=2) == lds(rows, pre=True) == lds(rows, d_bias=SCORES + (1 << 38), bias_period_rows=64) == short

@@ -1,6 +1,6 @@
-"""Launches of more than 60 (150) million scores, where the kernels for long rows ask for LDS to bound the
+"""Launches of more than 60 (90, 110, 120, 150) million scores, where the kernels ask for LDS to bound the
 workgroups that share a compute unit: the same bytes as the rows give in short launches (unbounded),
-and the oracle's on the first and the last row."""
+and the oracle's on the first and the last row.  (tests/test_dispatch.py: that these launches are bounded.)"""
 import numpy as np
 import pytest
 
@@ -11,11 +11,15 @@ from tests.helpers import lib_softmax
 pytestmark = pytest.mark.gpu
 
 
-# one row length for each bound: 6, 10 and 16 passes of a wavefront, 6 and 9 of four, 8 of eight
-@pytest.mark.parametrize("cols", [1500, 2500, 4095, 6001, 8192, 16000])
+# one row length for each bound: slabs of 4 and 16 lanes per row; 4, 6, 10, 14, 15 and 16 passes of a
+# wavefront; 6, 8, 9 and 10 of four, 8 of eight
+LONGEST = {197: 120, 198: 90, 401: 110, 600: 110, 9300: 110, 16000: 150}
+
+
+@pytest.mark.parametrize("cols", [197, 198, 401, 600, 900, 1000, 1500, 2500, 3400, 3600, 4093, 6001, 8150, 8192, 9000, 9300, 16000])
 def test_long_launch_equals_short_ones(cols):
     import torch
-    rows = (150_000_000 if cols == 16000 else 60_000_000) // cols + 3
+    rows = LONGEST.get(cols, 60) * 1_000_000 // cols + 3
     gen = torch.Generator(device="cuda").manual_seed(cols)
     x = torch.randint(-9000, 9000, (rows, cols), generator=gen, device="cuda", dtype=torch.int32)
     p = ref.SoftmaxParams(variant=1, i0=117, n_shift=8, m_bits=31)
