@@ -82,19 +82,41 @@ def test_the_two_paths_agree(name, monkeypatch):
     assert binding._fast is not None                              # the first device call brought it up
     native = make()
     assert getattr(binding._fast, name)(*native) == 0             # taken, not left to the long way
-    side = torch.cuda.Stream()                                    # and on the stream that is current
-    other = make()
-    side.wait_stream(torch.cuda.current_stream())
-    with torch.cuda.stream(side):
-        assert fn(*other) is None
-    side.synchronize()
     with monkeypatch.context() as m:
         m.setattr(binding, "_fast", None)
         long_way = make()
         assert fn(*long_way) is None
     torch.cuda.synchronize()
-    assert torch.equal(native[at], long_way[at]) and torch.equal(other[at], long_way[at])
+    assert torch.equal(native[at], long_way[at])
     assert int(long_way[at].ne(0).sum()) > 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", NAMES)
+@pytest.mark.parametrize("native", [True, False])
+def test_calls_go_to_the_current_stream(name, native, monkeypatch):
+    """The input arrives late, on a side stream: a call that ran on any other stream would have read what
+    was there before it (and its output is not the one of the input that arrives)."""
+    import torch
+    make, at = _cases()[name], OUT_AT[name]
+    fn = getattr(binding._fast, name) if native else getattr(ip, name)
+    if not native:
+        monkeypatch.setattr(binding, "_fast", None)
+    want, early, late = make(), list(make()), list(make())
+    fn(*want)
+    early[0] = torch.zeros_like(want[0])
+    fn(*early)
+    late[0] = torch.zeros_like(want[0])
+    torch.cuda.synchronize()
+    assert not torch.equal(early[at], want[at])
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(20_000_000)
+        late[0].copy_(want[0])
+        assert fn(*late) in (0, None)
+    torch.cuda.default_stream().synchronize()
+    side.synchronize()
+    assert torch.equal(late[at], want[at])
 
 
 @pytest.mark.gpu
