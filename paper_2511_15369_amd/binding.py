@@ -15,6 +15,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Sequence
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -193,11 +194,14 @@ def _stream() -> int:
 
 
 def _bind_calls():
-    """From here on the device calls go through the native module, if it was built for this Python."""
+    """From here on the device calls go through the native module, if it was built for this Python and
+    torch; if not, that is said once."""
     global _fast
     try:
         from . import _call
-    except ImportError:
+    except ImportError as e:
+        warnings.warn("device calls go through ctypes, about 1.5 us slower each: the native call module cannot be loaded "
+                      "(%s); build it with python -m paper_2511_15369_amd.build" % e, RuntimeWarning, stacklevel=4)
         return
     names = ("requant", "softmax_i32", "softmax_i32_windowed", "softmax_i32_windowed_bits", "gelu_i8", "gelu_i32",
              "softmax_i32_layers", "gelu_i8_layers")

@@ -37,6 +37,31 @@ def test_arguments_it_does_not_take_are_left_alone():
         call.bind(1, 2, 3)
 
 
+def test_the_library_builds_and_runs_without_it(monkeypatch, tmp_path, capfd):
+    """Where torch's headers are missing the build says so and goes on, and takes an older module away;
+    where the module cannot be loaded the binding says so and takes the ctypes path."""
+    import sys
+    from torch.utils import cpp_extension
+    from paper_2511_15369_amd import build
+    older = tmp_path / "_call.so"
+    older.write_bytes(b"older")
+    with monkeypatch.context() as m:
+        m.setattr(build, "CALL_MODULE", str(older))
+        m.setattr(cpp_extension, "include_paths", lambda *a, **k: [])
+        assert build.build_call_module() == ""
+        assert "_call.so was not built" in capfd.readouterr().err and not list(tmp_path.iterdir())
+        m.setattr(build.subprocess, "check_call", lambda *a, **k: (_ for _ in ()).throw(FileNotFoundError("g++")))
+        assert build.build_call_module() == "" and "g++" in capfd.readouterr().err
+    ip.load()
+    with monkeypatch.context() as m:
+        m.setitem(sys.modules, "paper_2511_15369_amd._call", None)
+        m.delattr(sys.modules["paper_2511_15369_amd"], "_call", raising=False)
+        m.setattr(binding, "_fast", None)
+        with pytest.warns(RuntimeWarning, match="ctypes"):
+            binding._bind_calls()
+        assert binding._fast is None
+
+
 def _cases():
     import torch
     g = torch.Generator(device="cuda")
