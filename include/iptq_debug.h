@@ -22,7 +22,8 @@ uint32_t iptq_debug_floor_pow2_div(int32_t m_bits, uint32_t sigma);
 
 /* The constants the host derives for one softmax launch.  out12 (12 values, may be NULL):
  * {divider multiplier, its shift, clamp D, i0 << N, p shift, period multiplier, its shift,
- *  n(D), packed-16-bit mode, its 24-bit multiplier, its pre-shift,
+ *  n(D), packed arithmetic (0 none, 1 multiply-high divider, 2 byte divider), the multiply-high
+ *  divider's 24-bit multiplier and the byte divider's (0: not exact on [0, n(D)]),
  *  the clamp of the raw score difference when the requantization in front is folded into Eq. 6
  *  (0: it is not)}. */
 int iptq_debug_softmax_plan(const iptq_softmax_params_t *p, int64_t rows, int32_t cols,

@@ -145,39 +145,25 @@ int plan_softmax(const iptq_softmax_params_t *p, int64_t rows, int32_t cols, int
         !make_magic_u32((uint32_t)(2 * p->i0), 31, &out->d2_magic, &out->d2_sh))
         return IPTQ_ERR_RANGE;
     // Packed 16-bit path: clamped delta, n and (i0 << N) must fit 16 bits, the per-row factor
-    // shifted to the top byte must fit 24 bits, and a 24-bit divider multiplier must be exact.
-    out->mode16 = 0;
+    // shifted to the top byte must fit 24 bits, and one of two dividers must be exact.
     out->mg24 = 0;
-    out->t16 = 0;
-    if (D <= 32767 && i0n < (1 << 15) && out->p_shift <= 24 && i0n >= ((int64_t)1 << p->out_bits)) {
-        for (int t = 0; t <= 12; ++t) {
-            const uint64_t two = (uint64_t)1 << (32 - t);
-            const uint64_t mg = two / (uint64_t)p->i0 + 1;
-            if (mg >= ((uint64_t)1 << 24)) continue;
-            const uint64_t e = mg * (uint64_t)p->i0 - two;      // 0 < e <= i0
-            const bool fits = ((uint64_t)n_max << t) <= 65535;
-            const bool exact = e > 0 && e <= (uint64_t)p->i0 && (uint64_t)n_max * e < two;
-            if (fits && exact) {
-                out->mode16 = t == 0 ? 1 : 2;
-                out->mg24 = (uint32_t)mg;
-                out->t16 = t;
-            }
-            break;
-        }
-    }
-    // The byte divider: n ceil(2^24 / i0) < 2^29 has the quotient in its top byte as long as n e < 2^24
-    // with e = i0 ceil(2^24 / i0) - 2^24 < i0 (so for every i0 up to about 1050), and -n must fit 16 bits.
     out->div8 = 0;
-    if (out->mode16 != 0 && n_max <= 32768) {
+    if (D <= 32767 && i0n < (1 << 15) && out->p_shift <= 24 && i0n >= ((int64_t)1 << p->out_bits)) {
+        // The byte divider: n ceil(2^24 / i0) < 2^29 has the quotient in its top byte as long as n e < 2^24
+        // with e = i0 ceil(2^24 / i0) - 2^24 < i0 (so for every i0 up to about 1050), and -n must fit 16 bits.
         const int64_t m = (((int64_t)1 << 24) + p->i0 - 1) / p->i0;
         const int64_t e = m * p->i0 - ((int64_t)1 << 24);
-        if (n_max * e < ((int64_t)1 << 24)) out->div8 = (int32_t)-m;
+        if (n_max <= 32768 && n_max * e < ((int64_t)1 << 24)) out->div8 = (int32_t)-m;
+        // The multiply-high divider by a 24-bit constant (i0 > 256).
+        const int64_t mg = ((int64_t)1 << 32) / p->i0 + 1;
+        const int64_t eh = mg * p->i0 - ((int64_t)1 << 32);
+        if (mg < ((int64_t)1 << 24) && n_max <= 65535 && n_max * eh < ((int64_t)1 << 32)) out->mg24 = (uint32_t)mg;
     }
-    out->packed = out->div8 != 0 ? 2 : (out->mode16 == 1 ? 1 : 0);
+    out->packed = out->div8 != 0 ? 2 : (out->mg24 != 0 ? 1 : 0);
     out->pre_rowconst = 0;
     out->pre_dmax = 0;
     // (the folded requantization is instantiated for the first-degree exponentials only)
-    if (out->pre_mode == 1 && out->mode16 != 0 && p->pre_s <= 31 && p->variant != IPTQ_SOFTMAX_BITEXP_DEGREE2) {
+    if (out->pre_mode == 1 && out->packed != 0 && p->pre_s <= 31 && p->variant != IPTQ_SOFTMAX_BITEXP_DEGREE2) {
         const int64_t two_s = (int64_t)1 << p->pre_s;
         const int64_t dmax = (D * two_s + p->pre_m - 1) / p->pre_m;
         if (dmax < ((int64_t)1 << 24) && dmax * p->pre_m + two_s <= ((int64_t)1 << 32)) {

@@ -250,7 +250,7 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
         for (int i = 0; i < cnt; ++i) {
             const SoftmaxDev &P = calls[base + i].P;
             any_high = any_high || P.packed == 1;
-            all_high = all_high && (P.packed != 2 || (P.mode16 == 1 && P.t16 == 0));
+            all_high = all_high && (P.packed != 2 || P.mg24 != 0);
         }
         for (int i = 0; i < cnt; ++i) {
             const SoftmaxCall &c = calls[base + i];

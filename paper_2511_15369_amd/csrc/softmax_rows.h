@@ -340,41 +340,37 @@ IPTQ_DEV uint32_t mulhi_u24(uint32_t a, uint32_t b)   // both below 2^24: bits 4
     return (uint32_t)(((uint64_t)(a & 0xffffffu) * (uint64_t)(b & 0xffffffu)) >> 32);
 }
 
-// Two exponentials at once in packed 16-bit lanes.  Preconditions (checked on the host,
+// The four exponentials of a 16-byte block in packed 16-bit lanes.  Preconditions (checked on the host,
 // SoftmaxDev::packed): D <= 32767, n_max <= 65535, i0 << N < 2^15 (so q <= 15 at the clamp), and a divider
 // that is exact on [0, n_max].
-// N = 4: the two pairs of a 16-byte block side by side, every packed step as two independent
-// instructions back to back (a single pair is one dependent chain, which leaves the vector unit waiting
-// on itself when few wavefronts share it, as at the end of a launch).
-template <int N> struct Packed16;
-template <> struct Packed16<4> {
-    typedef short S __attribute__((ext_vector_type(4)));
-    typedef unsigned short U __attribute__((ext_vector_type(4)));
-    typedef uint32_t W __attribute__((ext_vector_type(2)));
-};
+// The block's two pairs side by side, every packed step as two independent instructions back to back (a
+// single pair is one dependent chain, which leaves the vector unit waiting on itself when few wavefronts
+// share it, as at the end of a launch).
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // dl: the stabilised scores of Eq. 6, clamped at -D.  BYTE_DIV: the divider whose quotient is the top byte
-// of a 24-bit product (SoftmaxDev::div8), else the multiply-high by mg24 (t16 == 0).  Against a shifted
+// of a 24-bit product (SoftmaxDev::div8), else the multiply-high by mg24.  Against a shifted
 // multiply-high, with the clamp below, a block of four scores costs 38 instructions instead of 44: the
 // four stages of a Swin-B backbone with packed masks 75.7 -> 73.6 us, 589,824 rows of 144 scores with an
 // int32 mask 77.1 -> 75.3, 49,152 of 196 (second degree) 26.6 -> 25.8, 2048 of 50176 94.5 -> 91.3; what HBM
 // bounds stays (302,592 x 197 48.7 -> 48.4).
-template <int VARIANT, bool BYTE_DIV, int N>
-IPTQ_DEV typename Packed16<N>::U bit_exp_of_deltas(typename Packed16<N>::S dl, const SoftmaxDev &P)
+template <int VARIANT, bool BYTE_DIV>
+IPTQ_DEV u16x4 bit_exp_of_deltas(s16x4 dl, const SoftmaxDev &P)
 {
-    typedef typename Packed16<N>::S S;
-    typedef typename Packed16<N>::U U;
-    typedef typename Packed16<N>::W W;
+    typedef s16x4 S;
+    typedef u16x4 U;
     const S m = (dl + (dl >> 1)) - (dl >> 4);                  // Qp of Eq. 7, in (-2^15, 0] with BYTE_DIV
     const unsigned short i0 = (unsigned short)P.i0;
     U q;
     S nr;
     if (BYTE_DIV) {
         // Eq. 8: (-m) div i0 is the top byte of (-m) ceil(2^24 / i0), both factors negated
-        W qw;
+        u32x2 qw;
 #pragma unroll
-        for (int i = 0; i < N / 2; ++i) {
-            const uint32_t mw = __builtin_bit_cast(W, m)[i];
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t mw = __builtin_bit_cast(u32x2, m)[i];
             const uint32_t a = (uint32_t)__mul24((int32_t)(int16_t)mw, P.div8);
             const uint32_t b = (uint32_t)__mul24((int32_t)mw >> 16, P.div8);
             qw[i] = __builtin_amdgcn_perm(b, a, 0x0c070c03u);
@@ -384,8 +380,8 @@ IPTQ_DEV typename Packed16<N>::U bit_exp_of_deltas(typename Packed16<N>::S dl, c
     } else {
         const U n = (U)0 - (U)m;
 #pragma unroll
-        for (int i = 0; i < N / 2; ++i) {                      // Eq. 8: n div i0, per 32-bit word of the vector
-            const uint32_t nw = __builtin_bit_cast(W, n)[i];
+        for (int i = 0; i < 2; ++i) {                      // Eq. 8: n div i0, per 32-bit word of the vector
+            const uint32_t nw = __builtin_bit_cast(u32x2, n)[i];
             q[2 * i] = (unsigned short)mulhi_u24(nw & 0xffffu, P.mg24);
             // (a field extract folds into the multiply's operand select)
             q[2 * i + 1] = (unsigned short)mulhi_u24(__builtin_amdgcn_ubfe(nw, 16, 16), P.mg24);
@@ -400,7 +396,7 @@ IPTQ_DEV typename Packed16<N>::U bit_exp_of_deltas(typename Packed16<N>::S dl, c
         // quotient is below i0 / 4 and goes back into the packed vector.
         S t;
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
+        for (int i = 0; i < 4; ++i) {
             const int32_t y = fr[i];
             t[i] = (short)(mulhi_u32((uint32_t)__mul24(y, y), P.d2_magic) >> P.d2_sh);
         }
@@ -416,7 +412,7 @@ IPTQ_DEV typename Packed16<N>::U bit_exp_of_deltas(typename Packed16<N>::S dl, c
 // register (two instructions per pair, and one to subtract), where a saturating subtraction per score, a pack
 // and a packed clamp take four.  The four are interleaved: a partial write may not be followed by a read
 // of the same register.
-IPTQ_DEV Packed16<4>::S clamped_deltas(const int32_t (&x)[4], int32_t lower, int32_t mx)
+IPTQ_DEV s16x4 clamped_deltas(const int32_t (&x)[4], int32_t lower, int32_t mx)
 {
     uint32_t lo, hi;
     asm("v_max_i32_sdwa %0, %2, %6 dst_sel:WORD_0 dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:DWORD\n\t"
@@ -425,15 +421,14 @@ IPTQ_DEV Packed16<4>::S clamped_deltas(const int32_t (&x)[4], int32_t lower, int
         "v_max_i32_sdwa %1, %5, %6 dst_sel:WORD_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD"
         : "=&v"(lo), "=&v"(hi)
         : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(lower));
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(Packed16<4>::S, (u32x2){lo, hi}) - (Packed16<4>::S)(short)mx;
+    return __builtin_bit_cast(s16x4, (u32x2){lo, hi}) - (s16x4)(short)mx;
 }
 
 // The four scores of a 16-byte block -> their exponentials as two packed words.
 template <int VARIANT, bool BYTE_DIV>
 IPTQ_DEV void bit_exp_block(const int32_t (&x)[4], int32_t mx, int32_t lower, const SoftmaxDev &P, uint32_t (&e)[2])
 {
-    const Packed16<4>::U q = bit_exp_of_deltas<VARIANT, BYTE_DIV, 4>(clamped_deltas(x, lower, mx), P);
+    const u16x4 q = bit_exp_of_deltas<VARIANT, BYTE_DIV>(clamped_deltas(x, lower, mx), P);
     e[0] = __builtin_bit_cast(uint32_t, __builtin_shufflevector(q, q, 0, 1));
     e[1] = __builtin_bit_cast(uint32_t, __builtin_shufflevector(q, q, 2, 3));
 }
@@ -444,15 +439,14 @@ template <int VARIANT, bool BYTE_DIV>
 IPTQ_DEV void bit_exp_block_requant(const int32_t (&x)[4], int32_t mx, uint32_t c_row, const SoftmaxDev &P,
                                     uint32_t (&e)[2])
 {
-    typedef Packed16<4>::S S;
-    S d;
+    s16x4 d;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const uint32_t dd = min((uint32_t)mx - (uint32_t)x[i], P.pre_dmax);     // mx >= x: exact as unsigned
         d[i] = (short)((__umul24(dd, (uint32_t)P.pre_m) + c_row) >> P.pre_s);    // r(mx) - r(x), at most D + 1
     }
-    const S dl = __builtin_elementwise_max((S)0 - d, (S)(short)(-P.d_clamp));
-    const Packed16<4>::U q = bit_exp_of_deltas<VARIANT, BYTE_DIV, 4>(dl, P);
+    const s16x4 dl = __builtin_elementwise_max((s16x4)0 - d, (s16x4)(short)(-P.d_clamp));
+    const u16x4 q = bit_exp_of_deltas<VARIANT, BYTE_DIV>(dl, P);
     e[0] = __builtin_bit_cast(uint32_t, __builtin_shufflevector(q, q, 0, 1));
     e[1] = __builtin_bit_cast(uint32_t, __builtin_shufflevector(q, q, 2, 3));
 }

@@ -99,7 +99,7 @@ IPTQ_HD WideArgs wide_unpack(const WidePacked &W)
     P.post_xor = (W.w3 >> 22 & 1u) != 0 ? kPostXor : 0u;
     P.pre_dmax = W.pre_dmax; P.d2_magic = W.d2_magic;
     P.bias_period_rows = W.bias_period_rows; P.period_magic = W.period_magic;
-    P.t16 = P.mode16 = P.packed = 0;                  // not read by these kernels
+    P.packed = 0;                                     // not read by these kernels
     P.n_windows = P.group_rows = P.mask_period_rows = P.mperiod_sh = P.group_sh = 0;     // no mask in these kernels
     P.mperiod_magic = P.group_magic = 0;
     return A;

@@ -18,14 +18,14 @@ def _packed(p):
     return packed.value, div8.value
 
 
-def _n_max(p):
+def _plan(p):
     fn = ip.load().iptq_debug_softmax_plan
     fn.restype = ctypes.c_int
     fn.argtypes = [ctypes.POINTER(ip.SoftmaxParams), ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int64,
                    ctypes.POINTER(ctypes.c_int64)]
     out = (ctypes.c_int64 * 12)()
     assert fn(ctypes.byref(p), 1, 1, 0, 0, out) == 0
-    return out[7], out[8], out[10]
+    return list(out)
 
 
 def test_byte_divider_is_exact_wherever_it_is_enabled():
@@ -34,10 +34,16 @@ def test_byte_divider_is_exact_wherever_it_is_enabled():
         for n_shift in {max(0, 15 - i0.bit_length()), 0}:
             p = lib_softmax(ref.SoftmaxParams(variant=1, i0=i0, n_shift=n_shift))
             packed, div8 = _packed(p)
-            n_max, mode16, t16 = _n_max(p)
+            o = _plan(p)
+            D, i0n, p_shift, n_max, mg24 = o[2], o[3], o[4], o[7], o[9]
             kinds[packed] += 1
-            assert (packed == 0) == (mode16 == 0)                 # no parameter set loses the packed path
-            assert packed != 1 or t16 == 0                        # the other divider is used unshifted
+            # everything that fits 16 bits has one of the dividers (a shifted multiply-high one, exact for
+            # every such n, shows what fits)
+            fits = D <= 32767 and i0n < 2 ** 15 and p_shift <= 24 and i0n >= 2 ** p.out_bits
+            t = max(0, (2 ** 32 // i0 + 1).bit_length() - 24)
+            fits = fits and (n_max << t) <= 65535
+            assert (packed != 0) == fits, i0
+            assert packed != 1 or mg24 != 0
             assert (packed == 2) == (div8 != 0)
             if packed != 2:
                 continue

@@ -110,24 +110,26 @@ def test_softmax_plan_divider_and_clamp(i0, n):
 
 
 def test_packed_path_divider_is_exact_wherever_it_is_enabled():
-    """Every i0 of the usual scale range: when the plan enables the packed 16-bit path, its
-    24-bit divider must give n div i0 for every reachable n, and all values must fit."""
+    """Every i0 of the usual scale range: when the plan enables the packed 16-bit path, each of its
+    dividers that it enables must give n div i0 for every reachable n, and all values must fit."""
     enabled = 0
     for i0 in list(range(16, 3400)) + [4000, 5000, 2 ** 14, 2 ** 15 - 1]:
         for n_shift in {max(0, 15 - i0.bit_length()), 0}:
             p = lib_softmax(ref.SoftmaxParams(variant=1, i0=i0, n_shift=n_shift))
             rc, o = _plan(p, 10, 49)
             assert rc == 0
-            D, n_max, mode, mg24, t16 = o[2], o[7], o[8], o[9], o[10]
+            D, n_max, mode, mg24, div8 = o[2], o[7], o[8], o[9], o[10]
             if mode == 0:
                 continue
             enabled += 1
-            assert mode == (1 if t16 == 0 else 2)
-            assert D <= 32767 and (n_max << t16) <= 65535 and mg24 < 2 ** 24 and (i0 << n_shift) < 2 ** 15
+            assert mode == (2 if div8 else 1) and (mg24 or div8)
+            assert D <= 32767 and n_max <= 65535 and mg24 < 2 ** 24 and div8 < 2 ** 23 and (i0 << n_shift) < 2 ** 15
             n = np.arange(0, n_max + 1, dtype=np.uint64)
-            q = ((n << np.uint64(t16)) * np.uint64(mg24)) >> np.uint64(32)
-            assert np.array_equal(q, n // np.uint64(i0)), i0
-            assert int(q.max()) <= 15
+            for multiplier, shift in ((mg24, 32), (div8, 24)):
+                if multiplier:
+                    q = (n * np.uint64(multiplier)) >> np.uint64(shift)
+                    assert np.array_equal(q, n // np.uint64(i0)), (i0, shift)
+                    assert int(q.max()) <= 15
     assert enabled > 3000
     # default parameters of the whole benchmark scale range take the packed path
     for log2s in np.linspace(-10, -4, 25):
