@@ -192,4 +192,8 @@ def test_slabs_per_compute_unit(lib, rows, cols, own, fit):
     else:
         for lut in (16, 1024 if own else 0):
             assert 128 // -(-(lds(rows) + own + lut * bool(own)) // 1280) == fit
+    if cols == 198:                                   # one problem or three, not four
+        p = ip.softmax_prepare(0.0085, cols, 1, 0)
+        of_batch = [batch(lib, [(rows // n + 1, p)] * n, cols)[0].lds for n in (1, 3, 4)]
+        assert of_batch == [lds(rows)] * 2 + [short]
     assert lds(rows, variant=2) == lds(rows, pre=True) == lds(rows, d_bias=SCORES + (1 << 38), bias_period_rows=64) == short
