@@ -189,20 +189,21 @@ softmax_wgrow_kernel(WideArgs A)
     }
 }
 
-// The bound of wide_most_workgroups for a workgroup per row, for launches of more than 60 million scores:
+// The bound of wide_most_workgroups for a workgroup per row, for launches of more than 50 million scores:
 // 90 / 190 million in rows of 7000 scores 74.4 / 157 us against 75.4 / 159 without it, of 7600 73.3 / 153
-// against 75.0 / 157; at 45 million both take the same time.  Where nothing is added to the arithmetic
-// (plain_arithmetic): of 8192 72.0 / 148 with three against 72.6 / 152 with four and 75.4 / 159 without, of 8064 71.7 /
-// 146.6 against 71.9 / 149.2 (rows between them that are no multiple of 64 are slower with three, 8150 74.2 / 153.1
-// against 72.7 / 151.6; with a table 65.2 against 59.4 at 70 million), and ten passes from 110 million on: 130 / 190
-// million in rows of 9300 104.1 / 150.9 with three against 104.6 / 152.5 without, of 10240 100.6 / 145.5 against
-// 105.8 / 155.3 (with a requantization in front 9300 161.9 against 150.2).
+// against 75.0 / 157, 52 / 60 million of 8192 42.7 / 48.7 against 43.5 / 50.2; at 45 million both take the same
+// time.  Where nothing is added to the arithmetic (plain_arithmetic): of 8192 72.0 / 148 with three against 72.6 /
+// 152 with four and 75.4 / 159 without (66 million 53.6 and 53.1: from 75 million on), of 8064 71.7 / 146.6 against
+// 71.9 / 149.2 (rows between them that are no multiple of 64 are slower with three, 8150 74.2 / 153.1 against 72.7 /
+// 151.6; with a table 102 against 94 at 115 million), and ten passes from 110 million on: 130 / 190 million in
+// rows of 9300 104.1 / 150.9 with three against 104.6 / 152.5 without, of 10240 100.6 / 145.5 against 105.8 /
+// 155.3 (with a requantization in front 9300 161.9 against 150.2).
 // Eight passes of 8 wavefronts (14334 to 16384 scores) from 150 million on: 190 million in rows of 15500
 // 157 us against 159, of 16000 147 against 155, while at 62 million 55.0 against 54.0.
 constexpr int wgrow_most_workgroups(int waves, int slots, int32_t cols, int64_t scores, bool plain)
 {
-    if (scores <= 60 * 1000 * 1000) return 0;
-    if (waves == 4 && slots == 8 && plain && cols >= 8064 && cols % 64 == 0) return 3;
+    if (scores <= 50 * 1000 * 1000) return 0;
+    if (waves == 4 && slots == 8 && plain && scores > 75 * 1000 * 1000 && cols >= 8064 && cols % 64 == 0) return 3;
     if (waves == 4 && slots == 10 && plain && scores > 110 * 1000 * 1000) return 3;
     if (waves == 4) return slots == 6 || slots == 7 ? 5 : (slots == 8 || slots == 9 ? 4 : 0);
     return waves == 8 && slots == 8 && scores > 150 * 1000 * 1000 ? 2 : 0;

@@ -272,17 +272,19 @@ constexpr size_t lds_for_at_most(int most) { return most != 0 ? 160 * 1024 / mos
 // of 2000 26.2 against 26.7, of 2200 38.2 against 39.1, of 2950 38.8 against 39.3.  At 25 to 28 million
 // both take the same time, and 15 million are faster with all that fit (rows of 2200 14.6 us against
 // 15.2, of 2950 14.9 against 16.0).
-// More than 60 million: 90 / 190 million in rows of 1500 72.7 / 150 us with four against 73.6 / 155 with
-// five, of 2500 73.8 / 153 with four against 75.0 / 156 without a bound, of 3800 73.8 / 150 with two
-// against 75.8 / 157, of 4096 72.4 / 148 against 78.1 / 162.  At 45 million two are no faster.  Rows of 3330
-// 79.1 / 155.0 with three, 81.6 / 159.9 with two, 79.6 / 156.8 without; of 3600 78.0 / 151.4, 78.8 / 153.2 and
-// 79.4 / 155.7; from 3760 on, and with a table (3400 105.7 us at 115 million against 108.1), two are as good or
-// better.  Four passes, which shorter arithmetic had made up to 4 % slower: rows of 880 70.6 / 146.6 with six
-// against 72.0 / 150.7 without, of 900 72.7 / 152.4 against 73.8 / 155.2, of 960 70.8 / 146.3 with five against
-// 72.7 / 154.5, of 1000 71.6 / 149.0 against 73.6 / 157.0 (with a table 80.5 / 167.5 against 81.9 / 172.6, second
-// degree 71.7 / 148.1 against 73.1 / 155.6), of 1001 151.9 with six against 152.8; below 820 six are slower (800
-// 72.9 us against 69.9), and so are six and five where more arithmetic fills the time (900 of the second degree
-// 151.2 against 150.9, 1000 with a requantization in front 95.2 against 92.9 at 115 million).
+// More than 50 million, with a table or a requantization in front 60 (56 million of 4096 with a table 51.9 us
+// with what fits, 54.2 with two; of 1500 requantized 46.7 and 47.6 with four): 90 / 190 million in rows of 1500
+// 72.7 / 150 us with four against 73.6 / 155 with five, of 2500 73.8 / 153 with four against 75.0 / 156 without a
+// bound, of 3800 73.8 / 150 with two against 75.8 / 157, of 4096 72.4 / 148 against 78.1 / 162 (52 / 60 million 44.3 /
+// 50.1 against 45.7 / 52.2); at 45 million none is more than 2 % faster than what fits.  Rows of 3330 79.1 / 155.0
+// with three, 81.6 / 159.9 with two, 79.6 / 156.8 without; of 3600 78.0 / 151.4, 78.8 / 153.2 and 79.4 / 155.7; from
+// 3760 on, and with a table (3400 105.7 us at 115 million against 108.1), two are as good or better.  Four passes,
+// which shorter arithmetic had made up to 4 % slower: rows of 880 70.6 / 146.6 with six against 72.0 / 150.7
+// without, of 900 72.7 / 152.4 against 73.8 / 155.2, of 960 70.8 / 146.3 with five against 72.7 / 154.5, of 1000 71.6 /
+// 149.0 against 73.6 / 157.0 (with a table 80.5 / 167.5 against 81.9 / 172.6, second degree 71.7 / 148.1 against 73.1 /
+// 155.6), of 1001 151.9 with six against 152.8; below 820 six are slower (800 72.9 us against 69.9), and so are
+// six and five where more arithmetic fills the time (900 of the second degree 151.2 against 150.9, 1000 with a
+// requantization in front 95.2 against 92.9 at 115 million).
 constexpr int wide_most_workgroups(int slots, int32_t cols, bool very_long, bool bias, bool pre, bool degree2)
 {
     if (very_long && slots >= 14) return slots == 16 || cols >= 3760 || bias ? 2 : 3;
@@ -296,8 +298,9 @@ constexpr int wide_most_workgroups(int slots, int32_t cols, bool very_long, bool
 inline size_t wide_extra_lds(int slots, const WideArgs &A)
 {
     const int64_t scores = A.rows * A.cols;
+    const bool bias = A.bias != nullptr, pre = A.P.pre_mode != 0;
     if (scores <= 28 * 1000 * 1000) return 0;
-    return lds_for_at_most(wide_most_workgroups(slots, A.cols, scores > 60 * 1000 * 1000, A.bias != nullptr, A.P.pre_mode != 0,
+    return lds_for_at_most(wide_most_workgroups(slots, A.cols, scores > (bias || pre ? 60 : 50) * 1000 * 1000, bias, pre,
                                                 A.P.variant == 2));
 }
 

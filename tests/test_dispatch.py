@@ -133,14 +133,14 @@ def test_two_short_calls_that_are_sooner_done_apart(lib):
 
 @pytest.mark.parametrize("rows,cols,most", [
     # one wavefront per row: the fewest and the most passes with each bound, and the lines between
-    (60_000_000 // 816 + 1, 816, 0), (60_000_000 // 820 + 1, 820, 6), (60_000_000 // 948 + 1, 948, 6), (60_000_000 // 952 + 1, 952, 5),
-    (60_000_000 // 949 + 1, 949, 0), (60_000_000 // 950 + 1, 950, 6), (60_000_000 // 952, 952, 0),
-    (60_000_000 // 1500 + 1, 1500, 4), (28_000_000 // 1500 + 1, 1500, 5), (28_000_000 // 1500, 1500, 0), (60_000_000 // 2500 + 1, 2500, 4),
-    (60_000_000 // 3330 + 1, 3330, 3), (60_000_000 // 3756 + 1, 3756, 3), (60_000_000 // 3760 + 1, 3760, 2), (60_000_000 // 4093 + 1, 4093, 2),
+    (50_000_000 // 816 + 1, 816, 0), (50_000_000 // 820 + 1, 820, 6), (50_000_000 // 948 + 1, 948, 6), (50_000_000 // 952 + 1, 952, 5),
+    (50_000_000 // 949 + 1, 949, 0), (50_000_000 // 950 + 1, 950, 6), (50_000_000 // 952, 952, 0),
+    (50_000_000 // 1500 + 1, 1500, 4), (28_000_000 // 1500 + 1, 1500, 5), (28_000_000 // 1500, 1500, 0), (50_000_000 // 2500 + 1, 2500, 4),
+    (50_000_000 // 3330 + 1, 3330, 3), (50_000_000 // 3756 + 1, 3756, 3), (50_000_000 // 3760 + 1, 3760, 2), (50_000_000 // 4093 + 1, 4093, 2),
     # one workgroup per row
-    (60_000_000 // 6001 + 1, 6001, 5),
-    (60_000_000 // 8000 + 1, 8000, 4), (60_000_000 // 8150 + 1, 8150, 4), (60_000_000 // 8192 + 1, 8192, 3), (60_000_000 // 8192, 8192, 0),
-    (60_000_000 // 9000 + 1, 9000, 4), (110_000_000 // 9300, 9300, 0), (110_000_000 // 9300 + 1, 9300, 3), (110_000_000 // 10240 + 1, 10240, 3),
+    (50_000_000 // 6001 + 1, 6001, 5),
+    (50_000_000 // 8000 + 1, 8000, 4), (50_000_000 // 8150 + 1, 8150, 4), (75_000_000 // 8192 + 1, 8192, 3), (75_000_000 // 8192, 8192, 4), (50_000_000 // 8192, 8192, 0),
+    (50_000_000 // 9000 + 1, 9000, 4), (110_000_000 // 9300, 9300, 0), (110_000_000 // 9300 + 1, 9300, 3), (110_000_000 // 10240 + 1, 10240, 3),
     (150_000_000 // 16000 + 1, 16000, 2), (150_000_000 // 16000, 16000, 0)])
 def test_workgroups_per_compute_unit(lib, rows, cols, most):
     """The LDS that long launches ask for: that many workgroups fit the 160 KB of a compute unit beside their
@@ -157,7 +157,7 @@ def test_workgroups_per_compute_unit(lib, rows, cols, most):
 @pytest.mark.parametrize("rows,cols,plain,others", [
     # (with a table, with a requantization in front, of the second degree)
     (70_000, 900, 6, (0, 0, 0)), (70_000, 1000, 5, (5, 0, 5)), (20_000, 3400, 3, (2, 3, 3)), (20_000, 3600, 3, (2, 3, 3)),
-    (20_000, 3800, 2, (2, 2, 2)), (20_000, 4096, 2, (2, 2, 2)), (8_000, 8192, 3, (4, 4, 4)), (12_000, 9300, 3, (0, 0, 0)),
+    (14_000, 3800, 2, (2, 2, 2)), (14_000, 4096, 2, (2, 2, 2)), (9_200, 8192, 3, (4, 4, 4)), (12_000, 9300, 3, (0, 0, 0)),
     (12_000, 6400, 5, (5, 5, 5)), (45_000, 1500, 4, (4, 4, 4))])
 def test_workgroups_beside_more_arithmetic(lib, rows, cols, plain, others):
     """Where a table, a requantization or the second degree fills the time, fewer bounds apply."""
@@ -169,6 +169,9 @@ def test_workgroups_beside_more_arithmetic(lib, rows, cols, plain, others):
         return 0 if lds == 0 else 128 // -(-(lds + 1024) // 1280)
 
     table = dict(d_bias=SCORES + (1 << 38), bias_period_rows=64)
+    if 50 < rows * cols / 1e6 < 60:
+        assert fits(1, table, False) == fits(1, {}, True) == 0
+        rows = 60_000_000 // cols + 1
     assert (fits(1, {}, False), (fits(1, table, False), fits(1, {}, True), fits(2, {}, False))) == (plain, others)
 
 

@@ -1,4 +1,4 @@
-"""Launches of more than 60 (90, 110, 120, 150) million scores, where the kernels ask for LDS to bound the
+"""Launches of more than 50 (75, 90, 110, 120, 150) million scores, where the kernels ask for LDS to bound the
 workgroups that share a compute unit: the same bytes as the rows give in short launches (unbounded),
 and the oracle's on the first and the last row.  (tests/test_dispatch.py: that these launches are bounded.)"""
 import numpy as np
@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 # one row length for each bound: slabs of 4 and 16 lanes per row; 4, 6, 10, 14, 15 and 16 passes of a
 # wavefront; 6, 8, 9 and 10 of four, 8 of eight
-LONGEST = {197: 120, 198: 90, 401: 110, 600: 110, 9300: 110, 16000: 150}
+LONGEST = {197: 120, 198: 90, 401: 110, 600: 110, 8192: 75, 9300: 110, 16000: 150}
 
 
 @pytest.mark.parametrize("cols", [197, 198, 401, 600, 900, 1000, 1500, 2500, 3400, 3600, 4093, 6001, 8150, 8192, 9000, 9300, 16000])
