@@ -170,20 +170,60 @@ IPTQ_DEV int32_t clamp_i32(int32_t v, int32_t lo, int32_t hi)
 
 // Every launch starts with a cold scalar cache, and a kernel that reads its arguments in dependent
 // steps (which problem of the batch, then that problem's sizes, then its table constants) waits
-// for memory once per step before it can issue its first load.  This touches the first BYTES of
-// the kernel-argument segment at once, one load per 64-byte line, so that one wait covers them
-// all and the steps that follow hit in the cache.
+// for memory once per step before it can issue its first load.  This touches BYTES of the
+// kernel-argument segment at once, from byte `from` (a wavefront-uniform multiple of four) on, one load
+// per 64-byte line, so that one wait covers them all and the steps that follow hit in the cache.
 template <int BYTES>
-IPTQ_DEV void touch_kernel_arguments()
+IPTQ_DEV void touch_kernel_arguments(uint32_t from = 0)
 {
     typedef const __attribute__((address_space(4))) uint32_t *ArgWords;
-    ArgWords ka = (ArgWords)__builtin_amdgcn_kernarg_segment_ptr();
+    ArgWords ka = (ArgWords)__builtin_amdgcn_kernarg_segment_ptr() + from / 4;
     static_assert(BYTES > 0 && BYTES <= 512, "at most eight lines");
     constexpr int LINES = (BYTES + 63) / 64;
     uint32_t t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < LINES; ++i) t[i] = ka[16 * i];
     asm volatile("" ::"s"(t[0]), "s"(t[1]), "s"(t[2]), "s"(t[3]), "s"(t[4]), "s"(t[5]), "s"(t[6]), "s"(t[7]));
+}
+
+// The head of a batch's arguments, one 64-byte line: workgroups [first, next one's first) serve problem i.
+// The first workgroups lie here side by side and come in one load; kept in the problems themselves they
+// were a cold load each, one after the other, and call after call (where the arguments are cold in every
+// cache) those waits were most of what a batch took beyond its bytes.  Twelve layers of 2739 x 145 scores and
+// their GELU (25 MB) 17.4 us before and 14.5 now, nine of 3349 x 257 (46 MB) 24.1 and 20.4, sixteen of 6000 x 49
+// (37 MB) 29.5 and 21.9, eleven of 11332 x 197 (383 MB) 92.8 and 84.9; the GELU launches alone 8.7 and 6.7, 11.6
+// and 9.5, 17.8 and 13.9, 67.9 and 62.0.  Two or three problems take as long as they did.
+struct BatchHead {
+    static constexpr int kMost = 16;
+    int32_t n_items;
+    uint32_t later[kMost - 1];    // first workgroup of the second problem and so on, 0xffffffff where there is none
+    void clear()
+    {
+        n_items = 0;
+        for (uint32_t &f : later) f = 0xffffffffu;
+    }
+    int add(uint32_t first_wg)    // the problem's index
+    {
+        if (n_items > 0) later[n_items - 1] = first_wg;
+        return n_items++;
+    }
+};
+struct Problem { uint32_t index, wg; };               // wg: the workgroup's number within its problem
+IPTQ_DEV Problem problem_of(const BatchHead &H, uint32_t wg)
+{
+    uint32_t it = 0, first = 0;
+    auto look_at = [&](int from, int to) {
+#pragma unroll
+        for (int i = from; i < to; ++i) {
+            const uint32_t f = H.later[i - 1];
+            it = wg >= f ? (uint32_t)i : it;
+            first = wg >= f ? f : first;
+        }
+    };
+    look_at(1, 4);
+    if (H.n_items > 4)                                // (looking at all of them costs two problems 0.05 us)
+        look_at(4, BatchHead::kMost);
+    return {it, wg - first};
 }
 
 // (mask & a) | (~mask & b) in one instruction (written out, the compiler turns a select on a

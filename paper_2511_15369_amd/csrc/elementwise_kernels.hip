@@ -3,6 +3,8 @@
 // written once with dwordx4 accesses.
 #include <hip/hip_runtime.h>
 
+#include <stddef.h>
+
 #include "device_common.h"
 #include "kernels.h"
 #include "plan.h"
@@ -69,25 +71,24 @@ IPTQ_DEV int32_t sbyte(uint32_t w, int i) { return (int32_t)(int8_t)(w >> (8 * i
 // int8 -> int8 through a per-workgroup table: the polynomial is evaluated once for each of
 // the 256 input codes with the exact integer formula, then every element is one byte
 // gather from LDS.  One launch serves up to kGeluBatchMax independent problems (the layers
-// of a sweep): workgroups [first_wg, first_wg + n_wgs) stream item i.  The last (n & 15)
+// of a sweep): n_wgs workgroups stream an item.  The last (n & 15)
 // bytes of an item are done by its first workgroup.  `out` is 16-byte aligned: the host
 // peels the `head` bytes in front of that boundary off the tensor (the item's first
 // workgroup does them too).  `in` is then aligned as well if the two tensors sit at the same
 // offset (in place, or views cut at the same element); if not, its 16-byte loads are
 // unaligned ones.  in and out may be the same buffer.
-constexpr int kGeluBatchMax = 16;
+constexpr int kGeluBatchMax = BatchHead::kMost;
 constexpr int64_t kGeluTableGridCap = 256 * 56;
 struct GeluItem {
     const uint8_t *in;
     uint8_t *out;
     int64_t n;
-    uint32_t first_wg;
     uint32_t n_wgs;
     uint32_t head;          // bytes in front of in / out that belong to the tensor: 0..15
     GeluDev P;
 };
 struct GeluBatch {
-    int32_t n_items;
+    BatchHead head;
     GeluItem item[kGeluBatchMax];
 };
 static_assert(sizeof(GeluBatch) <= 4096, "kernel arguments are limited to 4 KiB");
@@ -123,13 +124,12 @@ IPTQ_DEV void store_through(u32x4 v, u32x4 *base)
 }
 
 template <bool THROUGH>
-IPTQ_DEV void gelu_i8_table_body(const GeluItem &I)
+IPTQ_DEV void gelu_i8_table_body(const GeluItem &I, uint32_t lb)
 {
     __shared__ uint8_t table[256];
     const int64_t n = I.n;
     const int64_t n16 = n >> 4;
     u32x4 *out4 = reinterpret_cast<u32x4 *>(I.out);
-    const uint32_t lb = blockIdx.x - I.first_wg;
     const int64_t stride = (int64_t)I.n_wgs * 256;
     auto gather = [&](const u32x4 v) -> u32x4 {
         u32x4 r;
@@ -180,17 +180,15 @@ __global__ void __launch_bounds__(256)
 gelu_i8_table_kernel(GeluItem I)
 {
     touch_kernel_arguments<sizeof(GeluItem)>();
-    gelu_i8_table_body<THROUGH>(I);
+    gelu_i8_table_body<THROUGH>(I, blockIdx.x);
 }
 
 __global__ void __launch_bounds__(256)
 gelu_i8_table_batch_kernel(GeluBatch B)
 {
-    touch_kernel_arguments<8 + sizeof(GeluItem)>();       // the batch header and its first problem
-    int it = 0;
-    for (int i = 1; i < B.n_items; ++i)
-        if (blockIdx.x >= B.item[i].first_wg) it = i;
-    gelu_i8_table_body<false>(B.item[it]);
+    const Problem p = problem_of(B.head, blockIdx.x);
+    touch_kernel_arguments<sizeof(GeluItem)>((uint32_t)offsetof(GeluBatch, item) + p.index * (uint32_t)sizeof(GeluItem));
+    gelu_i8_table_body<false>(B.item[p.index], p.wg);
 }
 
 // int8 -> int8, polynomial evaluated per element (no table).
@@ -423,15 +421,16 @@ static unsigned grid_for(int64_t work_items, int per_block, int64_t cap = 256 * 
 hipError_t gelu_i8_dispatch(const GeluCall *calls, int n_calls, hipStream_t stream)
 {
     GeluBatch B;
-    B.n_items = 0;
+    B.head.clear();
     unsigned total_wgs = 0;
     auto flush = [&]() {
-        if (B.n_items == 0) return;
-        if (B.n_items == 1 && gelu_writes_through(B.item[0].n))
+        const int n_items = B.head.n_items;
+        if (n_items == 0) return;
+        if (n_items == 1 && gelu_writes_through(B.item[0].n))
             launch_kernel(gelu_i8_table_kernel<true>, dim3(total_wgs), dim3(256), 0, stream, B.item[0]);
-        else if (B.n_items == 1) launch_kernel(gelu_i8_table_kernel<false>, dim3(total_wgs), dim3(256), 0, stream, B.item[0]);
+        else if (n_items == 1) launch_kernel(gelu_i8_table_kernel<false>, dim3(total_wgs), dim3(256), 0, stream, B.item[0]);
         else launch_kernel(gelu_i8_table_batch_kernel, dim3(total_wgs), dim3(256), 0, stream, B);
-        B.n_items = 0;
+        B.head.clear();
         total_wgs = 0;
     };
     for (int c = 0; c < n_calls; ++c) {
@@ -454,11 +453,10 @@ hipError_t gelu_i8_dispatch(const GeluCall *calls, int n_calls, hipStream_t stre
             else
                 launch_kernel(gelu_i8_direct_kernel<2>, grid, dim3(256), 0, stream, uin, uout, g.n, grid.x, g.P);
         } else {
-            if (B.n_items == kGeluBatchMax) flush();
-            GeluItem &it = B.item[B.n_items++];
+            if (B.head.n_items == kGeluBatchMax) flush();
+            GeluItem &it = B.item[B.head.add(total_wgs)];
             it.in = uin + head; it.out = uout + head; it.n = g.n - head; it.P = g.P;
             it.head = head;
-            it.first_wg = total_wgs;
             it.n_wgs = grid_for(it.n >> 4, 256, kGeluTableGridCap);
             total_wgs += it.n_wgs;
         }

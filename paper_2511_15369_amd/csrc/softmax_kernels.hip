@@ -229,17 +229,17 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
         unsigned total_wgs;
         bool fold;
     } group[2];
-    for (Group &g : group) { g.B.n_items = 0; g.total_wgs = 0; g.fold = false; }
+    for (Group &g : group) { g.B.head.clear(); g.total_wgs = 0; g.fold = false; }
     bool g_bias = false;
     int g_mask = 0, g_pm = 0, g_mode = 0;             // g_mask: 0 none, 1 int32 table, 2 one bit per key; g_mode: group[0]'s
     hipError_t err = hipSuccess;
     auto flush = [&]() {
         for (int i = 0; i < 2; ++i) {
             Group &g = group[i];
-            if (g.B.n_items == 0 || err != hipSuccess) continue;
+            if (g.B.head.n_items == 0 || err != hipSuccess) continue;
             err = launch(g.B, g.total_wgs, g_bias, g_mask, g.fold, i == 1 ? 1 : g_mode, g_pm, stream);
             g.fold = false;
-            g.B.n_items = 0;
+            g.B.head.clear();
             g.total_wgs = 0;
         }
     };
@@ -280,16 +280,16 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
             if (n_slabs == 0) continue;
             const int pm = post_mode_of(c.P, c.out_bits);
             const int mode = c.P.packed == 2 && any_high && all_high ? 1 : c.P.packed;
-            const bool first = group[0].B.n_items == 0 && group[1].B.n_items == 0;
+            const bool first = group[0].B.head.n_items == 0 && group[1].B.head.n_items == 0;
             // (32-bit arithmetic is a launch of its own, and ends the ones in front of it)
             const bool compatible = first || (has_bias == g_bias && has_mask == g_mask && pm == g_pm && (mode == 0) == (g_mode == 0));
             if (!compatible) flush();
             if (first || !compatible) { g_bias = has_bias; g_mask = has_mask; g_pm = pm; g_mode = mode == 0 ? 0 : 2; }
             Group &g = group[mode == 1 ? 1 : 0];      // (at most kBatchMax calls before the flush below)
             if (c.P.pre_rowconst != 0) g.fold = true;
-            SoftmaxItem &it = g.B.item[g.B.n_items++];
+            SoftmaxItem &it = g.B.item[g.B.head.add(g.total_wgs)];
             it.scores = c.scores; it.bias = c.bias; it.mask = c.mask; it.mask_bits = c.mask_bits; it.out = c.out;
-            it.n_slabs = n_slabs; it.first_wg = g.total_wgs; it.P = c.P;
+            it.n_slabs = n_slabs; it.P = c.P;
             it.tail_rows = (int32_t)(c.rows % rpw);
             it.share_q = 0; it.share_magic = 0; it.share_sh = 0;
             int64_t n_wgs = (n_slabs + kRowsWpb - 1) / kRowsWpb;

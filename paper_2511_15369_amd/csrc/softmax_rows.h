@@ -21,6 +21,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <stddef.h>
+
 #include <type_traits>
 
 #include "device_common.h"
@@ -33,9 +35,8 @@ typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 enum { PM_NONE = 0, PM_CLAMP127 = 1, PM_GENERAL = 2 };
 
 // One launch serves up to kBatchMax independent problems of the same row length (the layers
-// of a model sweep, the stages of a Swin backbone): workgroups [first_wg, next first_wg)
-// belong to item i.  The table travels in the kernel arguments.
-constexpr int kBatchMax = 16;
+// of a model sweep, the stages of a Swin backbone).  The table travels in the kernel arguments.
+constexpr int kBatchMax = BatchHead::kMost;
 // wavefronts per workgroup of the row kernel; they do not cooperate, so this only sets the
 // granularity at which the dispatcher hands out work and LDS
 constexpr int kRowsWpb = 4;
@@ -46,7 +47,6 @@ struct SoftmaxItem {
     const uint64_t *mask_bits;   // the same mask one bit per key, [n_windows, cols, ceil(cols / 64)] words, or nullptr
     uint8_t *out;
     int64_t n_slabs;      // the last one may be partial
-    uint32_t first_wg;
     int32_t tail_rows;    // rows of the last slab if it is partial, else 0
     // Slabs whose first rows are congruent modulo the bias period read the same rows of the
     // additive table.  share_q = period / gcd(period, rows per slab) is the distance, in slabs,
@@ -59,7 +59,7 @@ struct SoftmaxItem {
     SoftmaxDev P;
 };
 struct SoftmaxBatch {
-    int32_t n_items;
+    BatchHead head;
     SoftmaxItem item[kBatchMax];
 };
 static_assert(sizeof(SoftmaxBatch) <= 4096, "kernel arguments are limited to 4 KiB");
@@ -559,22 +559,24 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxBatch &B)
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[kRowsWpb][SLAB * 4];
     __shared__ uint8_t lut_all[kRowsWpb][POSTMODE == PM_GENERAL ? kPostLutBytes : 4];
 
-    touch_kernel_arguments<8 + sizeof(SoftmaxItem)>();   // the batch header and its first problem
+    touch_kernel_arguments<sizeof(BatchHead) + sizeof(SoftmaxItem)>();   // the batch's head and its first problem
     const int lane = threadIdx.x & 63;
     // (the wavefront index as a scalar: everything derived from it - the slab, its table offsets,
     // the runs of mask entries - is then computed on the scalar unit)
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    int it = 0;                                       // which problem this workgroup serves
-    for (int i = 1; i < B.n_items; ++i)
-        if (blockIdx.x >= B.item[i].first_wg) it = i;
-    const SoftmaxItem &I = B.item[it];
+    Problem problem = {0, blockIdx.x};                // which problem this workgroup serves
+    if (B.head.n_items > 1) {
+        problem = problem_of(B.head, blockIdx.x);
+        touch_kernel_arguments<sizeof(SoftmaxItem)>((uint32_t)offsetof(SoftmaxBatch, item) + problem.index * (uint32_t)sizeof(SoftmaxItem));
+    }
+    const SoftmaxItem &I = B.item[problem.index];
     const SoftmaxDev P = I.P;                         // by value: every field loaded once, up front
     const int32_t *__restrict__ scores = I.scores;
     const int32_t *__restrict__ bias = I.bias;
     uint8_t *__restrict__ out = I.out;
     static_assert(!MASK || RPW <= COLS, "a slab may cross one wrap of the query index at most");
     constexpr int MW = MASKKIND == 2 ? (COLS + 63) / 64 : 1;   // 64-bit words of packed mask per query
-    const uint32_t lw = blockIdx.x - I.first_wg;
+    const uint32_t lw = problem.wg;
     int64_t slab = (int64_t)lw * kRowsWpb + wv;
     if (BIAS && I.share_q != 0) {
         const uint32_t g = mulhi_u32(lw, I.share_magic) >> I.share_sh;
@@ -997,9 +999,9 @@ IPTQ_ROWS_SHAPES_ALT(IPTQ_DECLARE_ROWS_LAUNCHER)
 // 577 gain nothing, of 257 not on every card, of 49 less than 1 %.
 inline size_t rows_extra_lds(int cols, int k, unsigned total_wgs, const SoftmaxBatch &B)
 {
-    if (!((cols == 197 || cols == 198) && k == 4) || B.n_items > 3) return 0;
+    if (!((cols == 197 || cols == 198) && k == 4) || B.head.n_items > 3) return 0;
     if (cols == 197 && (int64_t)total_wgs * kRowsWpb * (64 / k) * cols <= 120 * 1000 * 1000) return 0;
-    for (int i = 0; i < B.n_items; ++i)
+    for (int i = 0; i < B.head.n_items; ++i)
         if (!plain_arithmetic(B.item[i].P)) return 0;
     const int own = kRowsWpb * (64 / k) * cols * 4;   // LDS is handed out in units of 1280 bytes
     return (size_t)(160 * 1024 / 3 / 1280 * 1280 + 1280 - own);

@@ -462,20 +462,17 @@ softmax_rowsdyn_kernel(DynArgs A)
 // 36.7 and 34.2 (second degree 37.1 and 34.4), 2 of 200,000 x 64 with a table 28.3 and 24.4, 4 of
 // 40,000 x 600 of the second degree 92.8 and 80.1.
 struct DynBatch {
-    int32_t n_items;
-    uint32_t first_wg[kDynBatchMax];                  // workgroups [first_wg[i], first_wg[i + 1]) serve item i
+    BatchHead head;
     DynArgs item[kDynBatchMax];
 };
-static_assert(sizeof(DynBatch) <= 4096, "kernel arguments are limited to 4 KiB");
+static_assert(kDynBatchMax <= BatchHead::kMost && sizeof(DynBatch) <= 4096, "kernel arguments are limited to 4 KiB");
 template <int K, int SLOTS>
 __global__ void __launch_bounds__(256)
 softmax_rowsdyn_batch_kernel(DynBatch B)
 {
-    touch_kernel_arguments<64>();                     // where the items start
-    int it = 0;
-    for (int i = 1; i < B.n_items; ++i)
-        if (blockIdx.x >= B.first_wg[i]) it = i;
-    softmax_rowsdyn_body<K, SLOTS, 2, 0, -1, false>(B.item[it], blockIdx.x - B.first_wg[it]);
+    const Problem p = problem_of(B.head, blockIdx.x);
+    touch_kernel_arguments<offsetof(DynArgs, mask)>((uint32_t)offsetof(DynBatch, item) + p.index * (uint32_t)sizeof(DynArgs));
+    softmax_rowsdyn_body<K, SLOTS, 2, 0, -1, false>(B.item[p.index], p.wg);
 }
 
 // mode: SoftmaxDev::packed

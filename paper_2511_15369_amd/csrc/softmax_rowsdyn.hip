@@ -178,14 +178,14 @@ hipError_t softmax_rowsdyn_launch_batch(const SoftmaxCall *calls, const int *pos
     DynBatch B;
     int of[kDynBatchMax];                             // which call an item is
     int64_t total_wgs = 0;
-    B.n_items = 0;
+    B.head.clear();
     auto flush = [&]() -> hipError_t {
         // (false: no such layout, the caller's next kernel serves these calls; wavefronts per workgroup and
         // their LDS are the same for every call of a row length)
-        if (B.n_items >= 2 && rowsdyn_launch(nullptr, &B, k, slots, 2, dim3((unsigned)total_wgs), dim3(64 * B.item[0].wpb),
+        if (B.head.n_items >= 2 && rowsdyn_launch(nullptr, &B, k, slots, 2, dim3((unsigned)total_wgs), dim3(64 * B.item[0].wpb),
                                              (size_t)B.item[0].wave_lds * B.item[0].wpb, stream))
-            for (int i = 0; i < B.n_items; ++i) done[of[i]] = calls[of[i]].rows;
-        B.n_items = 0;
+            for (int i = 0; i < B.head.n_items; ++i) done[of[i]] = calls[of[i]].rows;
+        B.head.clear();
         total_wgs = 0;
         return take_launch_status();
     };
@@ -198,13 +198,13 @@ hipError_t softmax_rowsdyn_launch_batch(const SoftmaxCall *calls, const int *pos
         int64_t n_wgs = 0;
         if (!rowsdyn_arguments(c, cols, post_modes[i], k, &A, &n_wgs)) continue;
         // (a launch has fewer than 2^32 work-items)
-        if (B.n_items == kDynBatchMax || (total_wgs + n_wgs) * 256 >= ((int64_t)1 << 32)) {
+        if (B.head.n_items == kDynBatchMax || (total_wgs + n_wgs) * 256 >= ((int64_t)1 << 32)) {
             const hipError_t e = flush();
             if (e != hipSuccess) return e;
         }
-        B.first_wg[B.n_items] = (uint32_t)total_wgs;
-        B.item[B.n_items] = A;
-        of[B.n_items++] = i;
+        const int at = B.head.add((uint32_t)total_wgs);
+        B.item[at] = A;
+        of[at] = i;
         total_wgs += n_wgs;
     }
     return flush();
