@@ -634,53 +634,41 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxBatch &B)
     // INT32_MIN; the smallest operand is tracked beside it (two lane-ops per score in all), and
     // the function returns whether any lane of the wavefront met INT32_MIN, in which case the
     // caller runs the exact form over the slab again.
-    auto copy_in = [&](auto tag, auto straddle_tag, auto exact_tag) -> bool {
+    // LINEAR: the slab's rows of both tables follow each other as its own rows do, so their chunks lie at the
+    // scores' own offsets from a scalar base and need no address arithmetic.
+    auto copy_in = [&](auto tag, auto straddle_tag, auto exact_tag, auto linear_tag) -> bool {
         constexpr bool PARTIAL = decltype(tag)::value;
         constexpr bool STRADDLE = decltype(straddle_tag)::value;
         constexpr bool EXACT = decltype(exact_tag)::value;
+        constexpr bool LINEAR = decltype(linear_tag)::value;
         i32x4 lowest = {0, 0, 0, 0};
         i32x4 *lds4 = reinterpret_cast<i32x4 *>(lds);
         i32x4 first4 = {0, 0, 0, 0};
         if (BIAS && STRADDLE) first4 = load_i32x4(bias);
         constexpr int NPASS = (IN_CHUNKS + 63) / 64;
-        // With the mask there are three loads per chunk: the scores (the loads that go to HBM) are all
-        // issued first,
-        i32x4 sv[MASK ? NPASS : 1];
-        if (MASK) {
-#pragma unroll
-            for (int i = 0; i < NPASS; ++i) {
-                const int idx = i * 64 + lane;
-                const bool full_pass = (i + 1) * 64 <= IN_CHUNKS;
-                const int li = (PARTIAL || full_pass) ? idx : min(idx, IN_CHUNKS - 1);
-                if (!PARTIAL || 4 * idx + 3 < valid_el) {
-                    sv[i] = stream_load_i32x4(src + 4 * li);
-                } else {
-                    const int32_t *s = src + 4 * idx;
-                    sv[i] = (i32x4){0, 0, 0, 0};
-                    if (4 * idx < valid_el) sv[i].x = s[0];
-                    if (4 * idx + 1 < valid_el) sv[i].y = s[1];
-                    if (4 * idx + 2 < valid_el) sv[i].z = s[2];
-                }
-            }
-        }
-        // then both tables' entries (cache hits), and only then is any of them waited for.  Pass by pass,
-        // as the sums left registers free, every pass waited for an L2 access of its own: 589,824 rows
-        // of 12 x 12-token windows 78.4 us against 77.1, 7 x 7 tokens 42.4 against 41.6 (401,408 rows) and
-        // 6.87 against 6.58 (50,176 rows).  Leaving the mask out where a slab's entries are all zero brings
-        // nothing more here (41.2 us against 41.3): the loads are what it costs.
-        constexpr bool AHEAD = MASK && BIAS && !PARTIAL;
-        i32x4 mvs[AHEAD ? NPASS : 1], bvs[AHEAD ? NPASS : 1];
         auto bias_at = [&](int li) -> uint32_t {
             const uint32_t o = boff + 4u * (uint32_t)li;
             return o >= pe ? o - pe : o;
         };
+        // With the mask there are three loads per chunk, and all of them are issued before the first is waited
+        // for: pass by pass, as the sums left registers free, every pass waited for an L2 access of its own.
+        // In the order of the chunks (score, bias, mask), so that a chunk can be added up as it arrives; with all
+        // scores issued first the last score held up the first sum: 589,824 rows of 12 x 12-token windows 76.9 us
+        // against 75.3, 147,456 22.8 against 22.0, 7 x 7 tokens 23.1 against 22.7 (401,408 rows), 9.6 against 9.1
+        // (100,352) and 7.0 against 6.6 (50,176).  Leaving the mask out where a slab's entries are all zero
+        // brings nothing more here (41.2 us against 41.3): the loads are what it costs.
+        constexpr bool AHEAD = MASK && BIAS && !PARTIAL;
+        i32x4 svs[AHEAD ? NPASS : 1], mvs[AHEAD ? NPASS : 1], bvs[AHEAD ? NPASS : 1];
         if (AHEAD) {
-            auto chunk_of = [&](int i) { return (i + 1) * 64 <= IN_CHUNKS ? i * 64 + lane : min(i * 64 + lane, IN_CHUNKS - 1); };
 #pragma unroll
             for (int i = 0; i < NPASS; ++i) {
-                const uint32_t o = bias_at(chunk_of(i));
-                bvs[i] = load_i32x4_at(bias, 4u * (STRADDLE ? min(o, pe - 4u) : o));
-                mvs[i] = mask_chunk_load<COLS>(I.mask, MR, 4u * (uint32_t)chunk_of(i));
+                const int li = (i + 1) * 64 <= IN_CHUNKS ? i * 64 + lane : min(i * 64 + lane, IN_CHUNKS - 1);
+                svs[i] = stream_load_i32x4(src + 4 * li);
+                const uint32_t o = bias_at(li);
+                bvs[i] = LINEAR ? load_i32x4_at(bias + boff, 16u * (uint32_t)li)
+                                : load_i32x4_at(bias, 4u * (STRADDLE ? min(o, pe - 4u) : o));
+                mvs[i] = LINEAR ? load_i32x4_at(I.mask + MR.off1, 16u * (uint32_t)li)
+                                : mask_chunk_load<COLS>(I.mask, MR, 4u * (uint32_t)li);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -695,8 +683,8 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxBatch &B)
             // memory round trip per wavefront.
             const int li = (PARTIAL || full_pass) ? idx : min(idx, IN_CHUNKS - 1);
             i32x4 v;
-            if (MASK) {
-                v = sv[i];
+            if (AHEAD) {
+                v = svs[AHEAD ? i : 0];
             } else if (!PARTIAL || 4 * idx + 3 < valid_el) {
                 v = stream_load_i32x4(src + 4 * li);
             } else {
@@ -713,7 +701,8 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxBatch &B)
                 else bv = STRADDLE ? bias_chunk_wrapping(bias, o, pe, first4) : load_i32x4_at(bias, 4u * o);   // table below 4 GiB
             }
             if (MASK) {
-                const i32x4 mv = mask_chunk_entries<COLS>(AHEAD ? mvs[AHEAD ? i : 0] : mask_chunk_load<COLS>(I.mask, MR, 4u * (uint32_t)li), MR, 4u * (uint32_t)li);
+                i32x4 mv = AHEAD ? mvs[AHEAD ? i : 0] : mask_chunk_load<COLS>(I.mask, MR, 4u * (uint32_t)li);
+                if (!LINEAR) mv = mask_chunk_entries<COLS>(mv, MR, 4u * (uint32_t)li);
                 if (BIAS) {
                     v.x = add_two_table_entries(v.x, bv.x, mv.x);
                     v.y = add_two_table_entries(v.y, bv.y, mv.y);
@@ -740,9 +729,18 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxBatch &B)
     bool redo = false;                                // wavefront-uniform
     // (the rare forms are marked so that the compiler lays the common path out contiguously: every
     // launch starts with a cold instruction cache)
-    if (__builtin_expect(partial, 0)) copy_in(std::true_type{}, std::integral_constant<bool, BIAS>{}, std::true_type{});
-    else if (__builtin_expect(straddle, 0)) redo = copy_in(std::false_type{}, std::true_type{}, std::integral_constant<bool, !FAST_ADD>{});
-    else redo = copy_in(std::false_type{}, std::false_type{}, std::integral_constant<bool, !FAST_ADD>{});
+    const std::false_type no;
+    const std::true_type yes;
+    const std::integral_constant<bool, !FAST_ADD> exact;
+    // (147,456 rows of 12 x 12-token windows 22.0 us with the linear form and 22.2 without; 401,408 of 7 x 7
+    // tokens, whose rows are not a whole number of chunks, 22.8 with and 22.5 without, and beside a bias alone
+    // it changes nothing at either: so only there)
+    constexpr bool MAY_BE_LINEAR = MASK && BIAS && COLS % 4 == 0;
+    const bool linear = MAY_BE_LINEAR && boff + (uint32_t)SLAB <= pe && MR.e1 >= (uint32_t)SLAB;
+    if (__builtin_expect(partial, 0)) copy_in(yes, std::integral_constant<bool, BIAS>{}, yes, no);
+    else if (linear) copy_in(no, no, exact, std::integral_constant<bool, MAY_BE_LINEAR>{});
+    else if (__builtin_expect(straddle, 0)) redo = copy_in(no, yes, exact, no);
+    else redo = copy_in(no, no, exact, no);
     if (FAST_ADD && __builtin_expect(redo, 0)) {
         // Some score or table entry of this slab is INT32_MIN: the slab once more with the exact
         // addition, one chunk at a time (a rare path: it must cost no registers, not no time).
