@@ -539,8 +539,9 @@ static __device__ uint64_t g_timeline[5 * kTimelineSlabs];
 #endif
 
 // MASKKIND: 0 no per-window mask, 1 the int32 table read beside the bias, 2 one bit per key.
+// lw: this workgroup's number within the problem.
 template <int COLS, int K, int MODE, bool BIAS, int POSTMODE, int MASKKIND, bool PRE = false>
-IPTQ_DEV void softmax_rows_body(const SoftmaxBatch &B)
+IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
 {
     constexpr bool MASK = MASKKIND == 1;
 #ifdef IPTQ_TIMELINE
@@ -559,24 +560,16 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxBatch &B)
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[kRowsWpb][SLAB * 4];
     __shared__ uint8_t lut_all[kRowsWpb][POSTMODE == PM_GENERAL ? kPostLutBytes : 4];
 
-    touch_kernel_arguments<sizeof(BatchHead) + sizeof(SoftmaxItem)>();   // the batch's head and its first problem
     const int lane = threadIdx.x & 63;
     // (the wavefront index as a scalar: everything derived from it - the slab, its table offsets,
     // the runs of mask entries - is then computed on the scalar unit)
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    Problem problem = {0, blockIdx.x};                // which problem this workgroup serves
-    if (B.head.n_items > 1) {
-        problem = problem_of(B.head, blockIdx.x);
-        touch_kernel_arguments<sizeof(SoftmaxItem)>((uint32_t)offsetof(SoftmaxBatch, item) + problem.index * (uint32_t)sizeof(SoftmaxItem));
-    }
-    const SoftmaxItem &I = B.item[problem.index];
     const SoftmaxDev P = I.P;                         // by value: every field loaded once, up front
     const int32_t *__restrict__ scores = I.scores;
     const int32_t *__restrict__ bias = I.bias;
     uint8_t *__restrict__ out = I.out;
     static_assert(!MASK || RPW <= COLS, "a slab may cross one wrap of the query index at most");
     constexpr int MW = MASKKIND == 2 ? (COLS + 63) / 64 : 1;   // 64-bit words of packed mask per query
-    const uint32_t lw = problem.wg;
     int64_t slab = (int64_t)lw * kRowsWpb + wv;
     if (BIAS && I.share_q != 0) {
         const uint32_t g = mulhi_u32(lw, I.share_magic) >> I.share_sh;
@@ -925,39 +918,60 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxBatch &B)
 #endif
 }
 
-template <int COLS, int K, int MODE, bool BIAS, int POSTMODE>
-__global__ void __launch_bounds__(64 * kRowsWpb)
-softmax_rows_kernel(SoftmaxBatch B)
+// Every kernel takes one problem's arguments (224 bytes) or a table of up to kBatchMax (3.6 KB).  An ordinary
+// call is one problem, and the host writes a launch's arguments into device memory: 4704 rows of 49 scores
+// and their GELU 7.2 us call after call, 7.7 with the table of one.  On the GPU it saves the search and a
+// dynamic address: 4736 rows of 197 4.06 us against 4.21, 37,824 of the second degree 9.3 against 9.5.
+// (The arguments of one problem are few enough to be asked for together without touching their lines first,
+// but for the mask's, which the compiler leaves for later: with them touched 589,824 rows of 144 scores with an
+// int32 mask take 75.3 us instead of 76.0, with a bias alone 66.4 instead of 65.8.)
+template <int COLS, int K, int MODE, bool BIAS, int POSTMODE, int MASKKIND, bool PRE>
+IPTQ_DEV void softmax_rows_problem(const SoftmaxItem &I)
 {
-    softmax_rows_body<COLS, K, MODE, BIAS, POSTMODE, 0>(B);
+    if (MASKKIND != 0) touch_kernel_arguments<sizeof(SoftmaxItem)>();
+    softmax_rows_body<COLS, K, MODE, BIAS, POSTMODE, MASKKIND, PRE>(I, blockIdx.x);
+}
+template <int COLS, int K, int MODE, bool BIAS, int POSTMODE, int MASKKIND, bool PRE>
+IPTQ_DEV void softmax_rows_problem(const SoftmaxBatch &B)
+{
+    const Problem p = problem_of(B.head, blockIdx.x);
+    touch_kernel_arguments<sizeof(SoftmaxItem)>((uint32_t)offsetof(SoftmaxBatch, item) + p.index * (uint32_t)sizeof(SoftmaxItem));
+    softmax_rows_body<COLS, K, MODE, BIAS, POSTMODE, MASKKIND, PRE>(B.item[p.index], p.wg);
+}
+
+template <int COLS, int K, int MODE, bool BIAS, int POSTMODE, class ARGS>
+__global__ void __launch_bounds__(64 * kRowsWpb)
+softmax_rows_kernel(ARGS A)
+{
+    softmax_rows_problem<COLS, K, MODE, BIAS, POSTMODE, 0, false>(A);
 }
 
 // The same with the per-window mask beside the bias: three loads per chunk.  Compiled for four or
 // five wavefronts per SIMD (LDS would allow six with 49 tokens), so that a wavefront has the
 // registers to keep all its loads in flight at once.
-template <int COLS, int K, int MODE, int POSTMODE>
+template <int COLS, int K, int MODE, int POSTMODE, class ARGS>
 __global__ void __launch_bounds__(64 * kRowsWpb) __attribute__((amdgpu_waves_per_eu(4, 5)))
-softmax_rows_masked_kernel(SoftmaxBatch B)
+softmax_rows_masked_kernel(ARGS A)
 {
-    softmax_rows_body<COLS, K, MODE, true, POSTMODE, 1>(B);
+    softmax_rows_problem<COLS, K, MODE, true, POSTMODE, 1, false>(A);
 }
 
 // The mask one bit per key: one to three 8-byte loads per lane (49- and 144-token windows) and
 // two instructions per score instead of a third table.
-template <int COLS, int K, int MODE, int POSTMODE>
+template <int COLS, int K, int MODE, int POSTMODE, class ARGS>
 __global__ void __launch_bounds__(64 * kRowsWpb)
-softmax_rows_maskbits_kernel(SoftmaxBatch B)
+softmax_rows_maskbits_kernel(ARGS A)
 {
-    softmax_rows_body<COLS, K, MODE, true, POSTMODE, 2>(B);
+    softmax_rows_problem<COLS, K, MODE, true, POSTMODE, 2, false>(A);
 }
 
 // The same with the requantization of the scores folded into Eq. 6 where the parameters allow it
 // (no tables, packed arithmetic, identity or clip post step).
-template <int COLS, int K, int MODE, int POSTMODE>
+template <int COLS, int K, int MODE, int POSTMODE, class ARGS>
 __global__ void __launch_bounds__(64 * kRowsWpb)
-softmax_rows_requant_kernel(SoftmaxBatch B)
+softmax_rows_requant_kernel(ARGS A)
 {
-    softmax_rows_body<COLS, K, MODE, false, POSTMODE, 0, true>(B);
+    softmax_rows_problem<COLS, K, MODE, false, POSTMODE, 0, true>(A);
 }
 
 // Launch helper, defined once per row length in softmax_rows_<cols>.hip so that the
@@ -1005,14 +1019,16 @@ inline size_t rows_extra_lds(int cols, int k, unsigned total_wgs, const SoftmaxB
     return (size_t)(160 * 1024 / 3 / 1280 * 1280 + 1280 - own);
 }
 
+#define IPTQ_ROWS_LAUNCH_AS(KERNEL, ...)                                                          \
+    do {                                                                                          \
+        if (B.head.n_items == 1) launch_kernel((KERNEL<__VA_ARGS__, SoftmaxItem>), grid, block, lds, stream, B.item[0]);  \
+        else launch_kernel((KERNEL<__VA_ARGS__, SoftmaxBatch>), grid, block, lds, stream, B);     \
+    } while (0)
 #define IPTQ_ROWS_LAUNCH(COLS, K, MODE, BIAS, PM, MASK)                                           \
     do {                                                                                          \
-        if constexpr (MASK == 1)                                                                  \
-            launch_kernel((softmax_rows_masked_kernel<COLS, K, MODE, PM>), grid, block, 0, stream, B);   \
-        else if constexpr (MASK == 2)                                                             \
-            launch_kernel((softmax_rows_maskbits_kernel<COLS, K, MODE, PM>), grid, block, 0, stream, B); \
-        else                                                                                      \
-            launch_kernel((softmax_rows_kernel<COLS, K, MODE, BIAS, PM>), grid, block, lds, stream, B);    \
+        if constexpr (MASK == 1) IPTQ_ROWS_LAUNCH_AS(softmax_rows_masked_kernel, COLS, K, MODE, PM);          \
+        else if constexpr (MASK == 2) IPTQ_ROWS_LAUNCH_AS(softmax_rows_maskbits_kernel, COLS, K, MODE, PM);   \
+        else IPTQ_ROWS_LAUNCH_AS(softmax_rows_kernel, COLS, K, MODE, BIAS, PM);                   \
     } while (0)
 
 template <int COLS, int K, bool BIAS, int MASK>
@@ -1020,7 +1036,7 @@ static hipError_t launch_rows_b(const SoftmaxBatch &B, unsigned total_wgs, int m
                                 hipStream_t stream)
 {
     const dim3 grid(total_wgs), block(64 * kRowsWpb);
-    [[maybe_unused]] const size_t lds = BIAS || MASK != 0 ? 0 : rows_extra_lds(COLS, K, total_wgs, B);
+    const size_t lds = BIAS || MASK != 0 ? 0 : rows_extra_lds(COLS, K, total_wgs, B);
 #define IPTQ_ROWS_LAUNCH_PM(MODE)                                                                 \
     switch (post_mode) {                                                                          \
     case PM_NONE: IPTQ_ROWS_LAUNCH(COLS, K, MODE, BIAS, PM_NONE, MASK); break;                    \
@@ -1039,14 +1055,11 @@ static hipError_t launch_rows_requant(const SoftmaxBatch &B, unsigned total_wgs,
                                       hipStream_t stream)
 {
     const dim3 grid(total_wgs), block(64 * kRowsWpb);
-    if (mode == 1 && post_mode == PM_NONE)
-        launch_kernel((softmax_rows_requant_kernel<COLS, K, 1, PM_NONE>), grid, block, 0, stream, B);
-    else if (mode == 1)
-        launch_kernel((softmax_rows_requant_kernel<COLS, K, 1, PM_CLAMP127>), grid, block, 0, stream, B);
-    else if (post_mode == PM_NONE)
-        launch_kernel((softmax_rows_requant_kernel<COLS, K, 2, PM_NONE>), grid, block, 0, stream, B);
-    else
-        launch_kernel((softmax_rows_requant_kernel<COLS, K, 2, PM_CLAMP127>), grid, block, 0, stream, B);
+    const size_t lds = 0;
+    if (mode == 1 && post_mode == PM_NONE) IPTQ_ROWS_LAUNCH_AS(softmax_rows_requant_kernel, COLS, K, 1, PM_NONE);
+    else if (mode == 1) IPTQ_ROWS_LAUNCH_AS(softmax_rows_requant_kernel, COLS, K, 1, PM_CLAMP127);
+    else if (post_mode == PM_NONE) IPTQ_ROWS_LAUNCH_AS(softmax_rows_requant_kernel, COLS, K, 2, PM_NONE);
+    else IPTQ_ROWS_LAUNCH_AS(softmax_rows_requant_kernel, COLS, K, 2, PM_CLAMP127);
     return take_launch_status();
 }
 
