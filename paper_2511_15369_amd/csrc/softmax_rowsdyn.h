@@ -198,8 +198,13 @@ IPTQ_DEV void softmax_rowsdyn_body(const DynArgs &A, uint32_t wg)
     // unless a score or an entry is INT32_MIN, and the smallest operand is tracked beside it (two
     // lane-ops per score instead of four); returns whether any lane met INT32_MIN, in which case
     // the caller copies the slab in again with the exact rule.
-    auto copy_in = [&](auto bias_tag, auto straddle_tag) -> bool {
+    // LINEAR: the slab's table rows lie one after the other like the slab itself, so a chunk of them sits at
+    // the chunk's own offset from a scalar base and needs no address of its own (28 vector instructions per
+    // wavefront less: 189,728 rows of 11 x 11 tokens with an int32 mask 29.4 -> 28.8 us, 248,430 of 13 x 13 with a
+    // packed one 43.5 -> 42.5, 15,876 of 9 x 9 8.1 -> 7.85).
+    auto copy_in = [&](auto bias_tag, auto straddle_tag, auto linear_tag) -> bool {
         constexpr bool BIAS = decltype(bias_tag)::value;
+        constexpr bool LINEAR = decltype(linear_tag)::value;
         i32x4 lowest = {0, 0, 0, 0};
         // the additive table's size is not a multiple of four scores and its end falls inside
         // this slab: one chunk takes entries from both ends of the table
@@ -219,6 +224,7 @@ IPTQ_DEV void softmax_rowsdyn_body(const DynArgs &A, uint32_t wg)
         i32x4 first4 = {0, 0, 0, 0};
         if (STRADDLE) first4 = load_i32x4(bias);
         auto bias_chunk = [&](int i) {
+            if (LINEAR) return load_i32x4_at(bias + boff, 16u * (uint32_t)chunk_of(i));
             uint32_t o = wrap(boff + 4u * (uint32_t)chunk_of(i), pe);
             return STRADDLE ? bias_chunk_wrapping(bias, o, pe, first4) : load_i32x4(bias + o);
         };
@@ -268,13 +274,14 @@ IPTQ_DEV void softmax_rowsdyn_body(const DynArgs &A, uint32_t wg)
         wave_lds_fence();
     };
     if (__builtin_expect(partial, 0)) copy_in_partial();
-    else if (bias == nullptr) copy_in(std::false_type{}, std::false_type{});
+    else if (bias == nullptr) copy_in(std::false_type{}, std::false_type{}, std::false_type{});
     else {
         const uint32_t pe = (uint32_t)P.bias_period_rows * (uint32_t)cols;
         const uint32_t boff = row_mod_period((uint32_t)(slab * RPW), P) * (uint32_t)cols;
         bool redo;
-        if ((pe & 3u) != 0 && boff + (uint32_t)slab_el > pe) redo = copy_in(std::true_type{}, std::true_type{});
-        else redo = copy_in(std::true_type{}, std::false_type{});
+        if (boff + (uint32_t)slab_el <= pe) redo = copy_in(std::true_type{}, std::false_type{}, std::true_type{});
+        else if ((pe & 3u) != 0) redo = copy_in(std::true_type{}, std::true_type{}, std::false_type{});
+        else redo = copy_in(std::true_type{}, std::false_type{}, std::false_type{});
         if (__builtin_expect(redo, 0)) copy_in_partial();
     }
 
