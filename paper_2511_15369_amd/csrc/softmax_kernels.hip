@@ -276,8 +276,7 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
                 mask_ok = has_bias && rows_maskbits_compiled(cols) &&
                           (reinterpret_cast<uintptr_t>(c.mask_bits) & 7) == 0;
             if (rpw == 0 || !slab_algo || !aligned || !bias_ok || !mask_ok) continue;
-            const int64_t n_slabs = (c.rows + rpw - 1) / rpw;    // a partial last slab is served too
-            if (n_slabs == 0) continue;
+            if (c.rows == 0) continue;
             const int pm = post_mode_of(c.P, c.out_bits);
             const int mode = c.P.packed == 2 && any_high && all_high ? 1 : c.P.packed;
             const bool first = group[0].B.head.n_items == 0 && group[1].B.head.n_items == 0;
@@ -289,8 +288,9 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
             if (c.P.pre_rowconst != 0) g.fold = true;
             SoftmaxItem &it = g.B.item[g.B.head.add(g.total_wgs)];
             it.scores = c.scores; it.bias = c.bias; it.mask = c.mask; it.mask_bits = c.mask_bits; it.out = c.out;
-            it.n_slabs = n_slabs; it.P = c.P;
-            it.tail_rows = (int32_t)(c.rows % rpw);
+            it.P = c.P;
+            it.set_rows(c.rows, rpw);
+            const int64_t n_slabs = it.n_slabs;
             it.share_q = 0; it.share_magic = 0; it.share_sh = 0;
             int64_t n_wgs = (n_slabs + kRowsWpb - 1) / kRowsWpb;
             if (has_bias) {

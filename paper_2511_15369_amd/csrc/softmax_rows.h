@@ -46,8 +46,12 @@ struct SoftmaxItem {
     const int32_t *mask;  // per-window mask [n_windows, cols, cols] or nullptr
     const uint64_t *mask_bits;   // the same mask one bit per key, [n_windows, cols, ceil(cols / 64)] words, or nullptr
     uint8_t *out;
-    int64_t n_slabs;      // the last one may be partial
-    int32_t tail_rows;    // rows of the last slab if it is partial, else 0
+    uint32_t n_slabs;
+    // The first row of the last slab, which ends with the tensor: it starts earlier than the slab before it
+    // ends where the row count is no multiple of the slab's.  Some rows are then made twice, by two
+    // wavefronts that write the same bytes.
+    uint32_t last_row0;
+    int32_t few_rows;     // fewer rows than a slab has: their number (one partial slab), else 0
     // Slabs whose first rows are congruent modulo the bias period read the same rows of the
     // additive table.  share_q = period / gcd(period, rows per slab) is the distance, in slabs,
     // between two such slabs; with share_q != 0 the wavefronts of a workgroup take slabs
@@ -57,6 +61,12 @@ struct SoftmaxItem {
     uint32_t share_q, share_magic;
     int32_t share_sh;     // w / share_q == mulhi(w, share_magic) >> share_sh
     SoftmaxDev P;
+    void set_rows(int64_t rows, int rows_per_slab)    // (rows < 2^31)
+    {
+        n_slabs = (uint32_t)((rows + rows_per_slab - 1) / rows_per_slab);
+        few_rows = rows < rows_per_slab ? (int32_t)rows : 0;
+        last_row0 = few_rows != 0 ? 0u : (uint32_t)(rows - rows_per_slab);
+    }
 };
 struct SoftmaxBatch {
     BatchHead head;
@@ -570,10 +580,10 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
     uint8_t *__restrict__ out = I.out;
     static_assert(!MASK || RPW <= COLS, "a slab may cross one wrap of the query index at most");
     constexpr int MW = MASKKIND == 2 ? (COLS + 63) / 64 : 1;   // 64-bit words of packed mask per query
-    int64_t slab = (int64_t)lw * kRowsWpb + wv;
+    uint32_t slab = lw * (uint32_t)kRowsWpb + (uint32_t)wv;
     if (BIAS && I.share_q != 0) {
         const uint32_t g = mulhi_u32(lw, I.share_magic) >> I.share_sh;
-        slab = (int64_t)g * (kRowsWpb * I.share_q) + (uint32_t)wv * I.share_q + (lw - g * I.share_q);
+        slab = g * (kRowsWpb * I.share_q) + (uint32_t)wv * I.share_q + (lw - g * I.share_q);
     }
     if (slab >= I.n_slabs) return;                    // no workgroup barrier below
 
@@ -586,7 +596,8 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
         const int p_max = 1 << (P.m_bits - P.p_shift);    // 2^(b-1) <= 128
         for (int p = lane; p <= p_max; p += 64) lut[p] = (uint8_t)post_dev<PM_GENERAL>((uint32_t)p, P);
     }
-    const int32_t *src = scores + slab * SLAB;       // anywhere on the 4-byte grid
+    const uint32_t row0 = min(slab * (uint32_t)RPW, I.last_row0);
+    const int32_t *src = scores + (uint64_t)row0 * (uint32_t)COLS;     // anywhere on the 4-byte grid
     const int lr = lane / K;                          // row inside the slab
     const int j = lane % K;                           // lane inside the row
     const int e_r = lr * COLS;                        // first element of the row in the slab
@@ -597,7 +608,7 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
     // after the slab has been read back from LDS
     uint64_t mask_words[MW] = {};
     if (MASKKIND == 2) {
-        const uint32_t row = (uint32_t)(slab * RPW) + (uint32_t)lr;
+        const uint32_t row = row0 + (uint32_t)lr;
         uint32_t rm = 0;
         if (P.mask_period_rows >= 2)
             rm = row - (mulhi_u32(row, P.mperiod_magic) >> P.mperiod_sh) * (uint32_t)P.mask_period_rows;
@@ -608,20 +619,23 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
         for (int i = 0; i < MW; ++i) mask_words[i] = mw[i];
     }
 
-    // ---- flat copy of the slab into LDS, bias added on the way.  A partial last slab (the
-    // tensor's row count is not a multiple of RPW) reads nothing beyond its last valid
-    // element and zero-fills the rest; its surplus rows are computed and never stored.
-    const bool partial = I.tail_rows != 0 && slab == I.n_slabs - 1;
-    const int valid_el = (partial ? I.tail_rows : RPW) * COLS;
-    // STRADDLE: the additive table's size is not a multiple of four scores and its end falls
-    // inside this slab, so one of the slab's chunks takes entries from both ends of the table.
+    // ---- flat copy of the slab into LDS, bias added on the way.  A partial slab (the tensor has fewer
+    // rows than a slab) reads nothing beyond its last valid element and zero-fills the rest; its surplus
+    // rows are computed and never stored.  (A ragged row count used to end in such a slab, whose guarded loads and
+    // byte stores lie in the wavefront that starts last: 9252 rows of 257 scores 6.7 us, 5.6 with a whole one
+    // that starts earlier; 9254 of 198 6.0 and 4.8, 4681 of 27 4.35 and 3.45, 23,102 of 222 8.95 and 7.3, 93,600 of
+    // 25 with a table 7.4 and 5.8, 153,984 of 401 with a requantization 52.8 and 52.0.)
+    const bool partial = I.few_rows != 0;
+    const int valid_el = (partial ? I.few_rows : RPW) * COLS;
+    // STRADDLE: the additive table's end falls inside this slab and inside one of its chunks, which takes
+    // entries from both ends of the table.
     uint32_t boff = 0;
-    if (BIAS) boff = row_mod_period((uint32_t)(slab * RPW), P) * (uint32_t)COLS;
+    if (BIAS) boff = row_mod_period(row0, P) * (uint32_t)COLS;
     const uint32_t pe = (uint32_t)P.bias_period_rows * (uint32_t)COLS;
-    const bool straddle = BIAS && (pe & 3u) != 0 && boff + (uint32_t)SLAB > pe;    // wavefront-uniform
+    const bool straddle = BIAS && ((boff | pe) & 3u) != 0 && boff + (uint32_t)SLAB > pe;    // wavefront-uniform
     // the per-window mask: at most two runs of entries (MaskRuns)
     MaskRuns MR = {};
-    if (MASK) MR = mask_runs_of_slab<COLS, RPW>(I.mask, (uint32_t)(slab * RPW), P);
+    if (MASK) MR = mask_runs_of_slab<COLS, RPW>(I.mask, row0, P);
     // EXACT: the bias is added with the minus-infinity rule per score (four lane-ops).  Otherwise
     // with the saturating sum alone, which is the same value unless a score or a table entry is
     // INT32_MIN; the smallest operand is tracked beside it (two lane-ops per score in all), and
@@ -892,7 +906,7 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
     auto copy_out = [&](auto tag) {
         constexpr bool PARTIAL = decltype(tag)::value;
         constexpr int CB = OUT16 ? 16 : 4;            // bytes per store
-        uint8_t *dst8 = out + slab * SLAB;
+        uint8_t *dst8 = out + (uint64_t)row0 * (uint32_t)COLS;
 #pragma unroll
         for (int i = 0; i < (OUT_CHUNKS + 63) / 64; ++i) {
             const int idx = i * 64 + lane;

@@ -31,8 +31,8 @@ struct DynArgs {
     const int32_t *scores;
     const int32_t *bias;
     uint8_t *out;
-    int64_t n_slabs;      // the last one may be partial
-    int32_t tail_rows;    // rows of the last slab if it is partial, else 0
+    uint32_t n_slabs, last_row0;      // as in SoftmaxItem, and so is few_rows
+    int32_t few_rows;
     int32_t cols;
     int32_t wave_lds;     // LDS bytes per wavefront: slab (16-byte multiple) + post table
     int32_t post_mode;    // PM_NONE / PM_CLAMP127 / PM_GENERAL, applied to the packed bytes
@@ -106,10 +106,10 @@ IPTQ_DEV void softmax_rowsdyn_body(const DynArgs &A, uint32_t wg)
     // (a scalar: the slab, its table offsets and every test on them then run on the scalar unit)
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t wpb = A.wpb;
-    int64_t slab = (int64_t)wg * wpb + wv;
+    uint32_t slab = wg * wpb + (uint32_t)wv;
     if (A.share_q != 0) {
         const uint32_t g = mulhi_u32(wg, A.share_magic) >> A.share_sh;
-        slab = (int64_t)g * (wpb * A.share_q) + (uint32_t)wv * A.share_q + (wg - g * A.share_q);
+        slab = g * (wpb * A.share_q) + (uint32_t)wv * A.share_q + (wg - g * A.share_q);
     }
     if (slab >= A.n_slabs) return;                    // no workgroup barrier below
 
@@ -123,10 +123,11 @@ IPTQ_DEV void softmax_rowsdyn_body(const DynArgs &A, uint32_t wg)
         const int p_max = 1 << (P.m_bits - P.p_shift);
         for (int p = lane; p <= p_max; p += 64) lut[p] = (uint8_t)post_dev<PM_GENERAL>((uint32_t)p, P);
     }
-    const int32_t *src1 = A.scores + slab * slab_el;
+    const uint32_t row0 = min(slab * (uint32_t)RPW, A.last_row0);
+    const int32_t *src1 = A.scores + (uint64_t)row0 * (uint32_t)cols;
     const int32_t *__restrict__ bias = A.bias;
-    const bool partial = A.tail_rows != 0 && slab == A.n_slabs - 1;
-    const int valid_el = (partial ? A.tail_rows : RPW) * cols;
+    const bool partial = A.few_rows != 0;
+    const int valid_el = (partial ? A.few_rows : RPW) * cols;
 
     // ---- the mask of this lane's blocks, in flight with the scores.  Packed form: the bits of
     // slot s start at key 4 (s K + j) - phi; one 4-byte load at the byte that holds that key
@@ -141,7 +142,7 @@ IPTQ_DEV void softmax_rowsdyn_body(const DynArgs &A, uint32_t wg)
     if (MASKKIND != 0) {
         const int lr = lane / K, j = lane % K, phi = (lr * cols) & 3;    // as below
         // rows past the end of a partial slab take the last row's mask (never stored)
-        const uint32_t row = (uint32_t)(slab * RPW) + (uint32_t)(partial ? min(lr, A.tail_rows - 1) : lr);
+        const uint32_t row = row0 + (uint32_t)(partial ? min(lr, A.few_rows - 1) : lr);
         uint32_t rm = 0;
         if (P.mask_period_rows >= 2)
             rm = row - (mulhi_u32(row, P.mperiod_magic) >> P.mperiod_sh) * (uint32_t)P.mask_period_rows;
@@ -206,8 +207,8 @@ IPTQ_DEV void softmax_rowsdyn_body(const DynArgs &A, uint32_t wg)
         constexpr bool BIAS = decltype(bias_tag)::value;
         constexpr bool LINEAR = decltype(linear_tag)::value;
         i32x4 lowest = {0, 0, 0, 0};
-        // the additive table's size is not a multiple of four scores and its end falls inside
-        // this slab: one chunk takes entries from both ends of the table
+        // the additive table's end falls inside this slab and inside a chunk, which takes entries from both
+        // ends of the table
         constexpr bool STRADDLE = decltype(straddle_tag)::value;
         i32x4 *lds4 = reinterpret_cast<i32x4 *>(lds);
         const int last = in_chunks - 1;
@@ -216,7 +217,7 @@ IPTQ_DEV void softmax_rowsdyn_body(const DynArgs &A, uint32_t wg)
             return i >= SLOTS - 2 ? min(idx, last) : idx;
         };
         uint32_t boff = 0;
-        if (BIAS) boff = row_mod_period((uint32_t)(slab * RPW), P) * (uint32_t)cols;
+        if (BIAS) boff = row_mod_period(row0, P) * (uint32_t)cols;
         const uint32_t pe = (uint32_t)P.bias_period_rows * (uint32_t)cols;
         // bias chunks come from L2: a ring of kAhead loads in flight behind the score loads
         // keeps the staging registers at 4 * (SLOTS + kAhead)
@@ -248,12 +249,12 @@ IPTQ_DEV void softmax_rowsdyn_body(const DynArgs &A, uint32_t wg)
         wave_lds_fence();
         return BIAS && __builtin_amdgcn_ballot_w64(min(min(lowest.x, lowest.y), min(lowest.z, lowest.w)) == kI32Min) != 0;
     };
-    // the one partial slab of a launch, and a slab that holds an INT32_MIN operand: guarded loads
-    // and the exact addition, chunk by chunk
+    // a partial slab (a call of fewer rows than a slab has), and a slab that holds an INT32_MIN operand:
+    // guarded loads and the exact addition, chunk by chunk
     auto copy_in_partial = [&]() {
         i32x4 *lds4 = reinterpret_cast<i32x4 *>(lds);
         uint32_t boff = 0;
-        if (bias != nullptr) boff = row_mod_period((uint32_t)(slab * RPW), P) * (uint32_t)cols;
+        if (bias != nullptr) boff = row_mod_period(row0, P) * (uint32_t)cols;
         const uint32_t pe = (uint32_t)P.bias_period_rows * (uint32_t)cols;
         for (int idx = lane; idx < in_chunks; idx += 64) {
             i32x4 v;
@@ -277,10 +278,10 @@ IPTQ_DEV void softmax_rowsdyn_body(const DynArgs &A, uint32_t wg)
     else if (bias == nullptr) copy_in(std::false_type{}, std::false_type{}, std::false_type{});
     else {
         const uint32_t pe = (uint32_t)P.bias_period_rows * (uint32_t)cols;
-        const uint32_t boff = row_mod_period((uint32_t)(slab * RPW), P) * (uint32_t)cols;
+        const uint32_t boff = row_mod_period(row0, P) * (uint32_t)cols;
         bool redo;
         if (boff + (uint32_t)slab_el <= pe) redo = copy_in(std::true_type{}, std::false_type{}, std::true_type{});
-        else if ((pe & 3u) != 0) redo = copy_in(std::true_type{}, std::true_type{}, std::false_type{});
+        else if (((boff | pe) & 3u) != 0) redo = copy_in(std::true_type{}, std::true_type{}, std::false_type{});
         else redo = copy_in(std::true_type{}, std::false_type{}, std::false_type{});
         if (__builtin_expect(redo, 0)) copy_in_partial();
     }
@@ -422,35 +423,40 @@ IPTQ_DEV void softmax_rowsdyn_body(const DynArgs &A, uint32_t wg)
     wave_lds_fence();
 
     // ---- flat, fully coalesced store (byte stores at the end of a partial slab)
-    uint8_t *dst8 = A.out + slab * slab_el;
-    if ((slab_el & 15) == 0) {
-        const int n16 = slab_el >> 4;
+    uint8_t *dst8 = A.out + (uint64_t)row0 * (uint32_t)cols;
+    auto copy_out = [&](auto tag) {
+        constexpr bool PARTIAL = decltype(tag)::value;
+        if ((slab_el & 15) == 0) {
+            const int n16 = slab_el >> 4;
 #pragma unroll
-        for (int i = 0; i < (SLOTS + 3) / 4; ++i) {
-            const int idx = i * 64 + lane;
-            if (idx < n16) {
-                if (16 * idx + 15 < valid_el) {
-                    stream_store_bytes16(reinterpret_cast<const u32x4 *>(lds)[idx], dst8 + 16 * idx);
-                } else {
+            for (int i = 0; i < (SLOTS + 3) / 4; ++i) {
+                const int idx = i * 64 + lane;
+                if (idx < n16) {
+                    if (!PARTIAL || 16 * idx + 15 < valid_el) {
+                        stream_store_bytes16(reinterpret_cast<const u32x4 *>(lds)[idx], dst8 + 16 * idx);
+                    } else {
 #pragma unroll 1
-                    for (int b = 16 * idx; b < valid_el && b < 16 * idx + 16; ++b) dst8[b] = lds[b];
+                        for (int b = 16 * idx; b < valid_el && b < 16 * idx + 16; ++b) dst8[b] = lds[b];
+                    }
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < SLOTS; ++i) {
+                const int idx = i * 64 + lane;
+                if (idx < in_chunks) {
+                    if (!PARTIAL || 4 * idx + 3 < valid_el) {
+                        stream_store_bytes4(lds32[idx], dst8 + 4 * idx);
+                    } else {
+#pragma unroll 1
+                        for (int b = 4 * idx; b < valid_el && b < 4 * idx + 4; ++b) dst8[b] = lds[b];
+                    }
                 }
             }
         }
-    } else {
-#pragma unroll
-        for (int i = 0; i < SLOTS; ++i) {
-            const int idx = i * 64 + lane;
-            if (idx < in_chunks) {
-                if (4 * idx + 3 < valid_el) {
-                    stream_store_bytes4(lds32[idx], dst8 + 4 * idx);
-                } else {
-#pragma unroll 1
-                    for (int b = 4 * idx; b < valid_el && b < 4 * idx + 4; ++b) dst8[b] = lds[b];
-                }
-            }
-        }
-    }
+    };
+    if (__builtin_expect(partial, 0)) copy_out(std::true_type{});
+    else copy_out(std::false_type{});
 }
 
 template <int K, int SLOTS, int MODE, int MASKKIND, int VARIANT, bool PRE>

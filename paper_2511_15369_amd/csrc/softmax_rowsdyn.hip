@@ -84,7 +84,9 @@ static bool rowsdyn_arguments(const SoftmaxCall &c, int32_t cols, int post_mode,
     const int64_t n_slabs = (c.rows + rpw - 1) / rpw;
     if (!aligned || !bias_ok || n_slabs == 0) return false;
     A.scores = c.scores; A.bias = c.bias; A.out = c.out;
-    A.n_slabs = n_slabs; A.tail_rows = (int32_t)(c.rows % rpw);
+    A.n_slabs = (uint32_t)n_slabs;
+    A.few_rows = c.rows < rpw ? (int32_t)c.rows : 0;
+    A.last_row0 = A.few_rows != 0 ? 0u : (uint32_t)(c.rows - rpw);
     A.cols = cols; A.post_mode = post_mode;
     A.wave_lds = (int32_t)((((int64_t)rpw * cols * 4 + 15) & ~(int64_t)15) + kPostLutBytes);
     A.mask = c.mask; A.mask_bits = c.mask_bits;
