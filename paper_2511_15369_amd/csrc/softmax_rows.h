@@ -657,15 +657,18 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
             const uint32_t o = boff + 4u * (uint32_t)li;
             return o >= pe ? o - pe : o;
         };
-        // With the mask there are three loads per chunk, and all of them are issued before the first is waited
-        // for: pass by pass, as the sums left registers free, every pass waited for an L2 access of its own.
-        // In the order of the chunks (score, bias, mask), so that a chunk can be added up as it arrives; with all
-        // scores issued first the last score held up the first sum: 589,824 rows of 12 x 12-token windows 76.9 us
-        // against 75.3, 147,456 22.8 against 22.0, 7 x 7 tokens 23.1 against 22.7 (401,408 rows), 9.6 against 9.1
-        // (100,352) and 7.0 against 6.6 (50,176).  Leaving the mask out where a slab's entries are all zero
-        // brings nothing more here (41.2 us against 41.3): the loads are what it costs.
-        constexpr bool AHEAD = MASK && BIAS && !PARTIAL;
-        i32x4 svs[AHEAD ? NPASS : 1], mvs[AHEAD ? NPASS : 1], bvs[AHEAD ? NPASS : 1];
+        // With a table there are two or three loads per chunk, and all of them are issued before the first is
+        // waited for, in the order of the chunks (score, bias, mask), so that a chunk can be added up as it
+        // arrives.  Left to itself the compiler asked for the tables pass by pass as the sums left registers
+        // free, so that every pass waited for an L2 access of its own, or put several table loads in front of
+        // the scores'.  With a bias, in this order and with LINEAR: 802,816 rows of 7 x 7 tokens 35.6 -> 33.4 us (3
+        // heads), with a packed mask 34.5 -> 33.8 (4 heads), 200,704 11.9 -> 11.4, 147,456 of 12 x 12 tokens 19.1 ->
+        // 18.6.  With an int32 mask, against all scores first: 589,824 of 12 x 12 tokens 76.9 -> 75.3, 100,352 of
+        // 7 x 7 9.6 -> 9.1; there a fixed order within the loads costs 1.5 %, beside a bias alone it is what
+        // gains the last per cent.  Leaving the int32 mask out where a slab's entries are all zero brings
+        // nothing more (41.2 us against 41.3): the loads are what it costs.
+        constexpr bool AHEAD = BIAS && !PARTIAL;
+        i32x4 svs[AHEAD ? NPASS : 1], mvs[AHEAD && MASK ? NPASS : 1], bvs[AHEAD ? NPASS : 1];
         if (AHEAD) {
 #pragma unroll
             for (int i = 0; i < NPASS; ++i) {
@@ -674,8 +677,10 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
                 const uint32_t o = bias_at(li);
                 bvs[i] = LINEAR ? load_i32x4_at(bias + boff, 16u * (uint32_t)li)
                                 : load_i32x4_at(bias, 4u * (STRADDLE ? min(o, pe - 4u) : o));
-                mvs[i] = LINEAR ? load_i32x4_at(I.mask + MR.off1, 16u * (uint32_t)li)
-                                : mask_chunk_load<COLS>(I.mask, MR, 4u * (uint32_t)li);
+                if (MASK)
+                    mvs[MASK ? i : 0] = LINEAR ? load_i32x4_at(I.mask + MR.off1, 16u * (uint32_t)li)
+                                               : mask_chunk_load<COLS>(I.mask, MR, 4u * (uint32_t)li);
+                else __builtin_amdgcn_sched_barrier(0);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -705,10 +710,10 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
             if (BIAS) {
                 const uint32_t o = bias_at(li);
                 if (AHEAD) bv = STRADDLE ? bias_chunk_wrapped(bvs[AHEAD ? i : 0], o, pe, first4) : bvs[AHEAD ? i : 0];
-                else bv = STRADDLE ? bias_chunk_wrapping(bias, o, pe, first4) : load_i32x4_at(bias, 4u * o);   // table below 4 GiB
+                else bv = bias_chunk_wrapping(bias, o, pe, first4);
             }
             if (MASK) {
-                i32x4 mv = AHEAD ? mvs[AHEAD ? i : 0] : mask_chunk_load<COLS>(I.mask, MR, 4u * (uint32_t)li);
+                i32x4 mv = AHEAD ? mvs[AHEAD && MASK ? i : 0] : mask_chunk_load<COLS>(I.mask, MR, 4u * (uint32_t)li);
                 if (!LINEAR) mv = mask_chunk_entries<COLS>(mv, MR, 4u * (uint32_t)li);
                 if (BIAS) {
                     v.x = add_two_table_entries(v.x, bv.x, mv.x);
@@ -739,13 +744,12 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
     const std::false_type no;
     const std::true_type yes;
     const std::integral_constant<bool, !FAST_ADD> exact;
-    // (147,456 rows of 12 x 12-token windows 22.0 us with the linear form and 22.2 without; 401,408 of 7 x 7
-    // tokens, whose rows are not a whole number of chunks, 22.8 with and 22.5 without, and beside a bias alone
-    // it changes nothing at either: so only there)
-    constexpr bool MAY_BE_LINEAR = MASK && BIAS && COLS % 4 == 0;
-    const bool linear = MAY_BE_LINEAR && boff + (uint32_t)SLAB <= pe && MR.e1 >= (uint32_t)SLAB;
+    // (401,408 rows of 7 x 7 tokens with an int32 mask, whose rows are not a whole number of chunks, 22.8 us
+    // with the linear form and 22.5 without: not there)
+    constexpr bool MAY_BE_LINEAR = BIAS && (!MASK || COLS % 4 == 0);
+    const bool linear = MAY_BE_LINEAR && boff + (uint32_t)SLAB <= pe && (!MASK || MR.e1 >= (uint32_t)SLAB);
     if (__builtin_expect(partial, 0)) copy_in(yes, std::integral_constant<bool, BIAS>{}, yes, no);
-    else if (linear) copy_in(no, no, exact, std::integral_constant<bool, MAY_BE_LINEAR>{});
+    else if (linear) redo = copy_in(no, no, exact, std::integral_constant<bool, MAY_BE_LINEAR>{});
     else if (__builtin_expect(straddle, 0)) redo = copy_in(no, yes, exact, no);
     else redo = copy_in(no, no, exact, no);
     if (FAST_ADD && __builtin_expect(redo, 0)) {

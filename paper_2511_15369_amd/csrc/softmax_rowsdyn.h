@@ -219,32 +219,42 @@ IPTQ_DEV void softmax_rowsdyn_body(const DynArgs &A, uint32_t wg)
         uint32_t boff = 0;
         if (BIAS) boff = row_mod_period(row0, P) * (uint32_t)cols;
         const uint32_t pe = (uint32_t)P.bias_period_rows * (uint32_t)cols;
-        // bias chunks come from L2: a ring of kAhead loads in flight behind the score loads
-        // keeps the staging registers at 4 * (SLOTS + kAhead)
-        constexpr int kAhead = 4;
         i32x4 first4 = {0, 0, 0, 0};
         if (STRADDLE) first4 = load_i32x4(bias);
         auto bias_chunk = [&](int i) {
             if (LINEAR) return load_i32x4_at(bias + boff, 16u * (uint32_t)chunk_of(i));
-            uint32_t o = wrap(boff + 4u * (uint32_t)chunk_of(i), pe);
-            return STRADDLE ? bias_chunk_wrapping(bias, o, pe, first4) : load_i32x4(bias + o);
+            const uint32_t o = wrap(boff + 4u * (uint32_t)chunk_of(i), pe);
+            return load_i32x4(bias + (STRADDLE ? min(o, pe - 4u) : o));
         };
-        i32x4 v[SLOTS], bv[BIAS ? kAhead : 1];
+        // With a table every load is in flight before the first is waited for, in the order of the chunks, so
+        // that a chunk can be added up as it arrives (see softmax_rows_body): 62,720 rows of 196 scores 13.5 ->
+        // 13.1 us, 100,352 of 256 22.9 -> 22.3, 93,600 of 25 5.75 -> 5.5, 524,288 of 64 with a packed mask 31.0 ->
+        // 30.4.  Not beside an int32 mask, whose entries are in flight as well: there four table loads behind
+        // all the scores' are faster (345,600 rows of 100 37.3 us against 38.1, 189,728 of 121 28.3 against 29.0).
+        constexpr bool IN_ORDER = MASKKIND != 1;
+        constexpr int AHEAD = IN_ORDER || SLOTS < 4 ? SLOTS : 4;
+        i32x4 v[SLOTS], bv[BIAS ? AHEAD : 1];
 #pragma unroll
-        for (int i = 0; i < SLOTS; ++i) v[i] = stream_load_i32x4(src1 + 4 * chunk_of(i));
-        if (BIAS) {
+        for (int i = 0; i < SLOTS; ++i) {
+            v[i] = stream_load_i32x4(src1 + 4 * chunk_of(i));
+            if (BIAS && IN_ORDER) {
+                bv[BIAS ? i : 0] = bias_chunk(i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (BIAS && !IN_ORDER) {
 #pragma unroll
-            for (int i = 0; i < kAhead && i < SLOTS; ++i) bv[i] = bias_chunk(i);
+            for (int i = 0; i < AHEAD; ++i) bv[BIAS ? i : 0] = bias_chunk(i);
         }
 #pragma unroll
         for (int i = 0; i < SLOTS; ++i) {
-            i32x4 t = v[i];
             if (BIAS) {
-                const i32x4 b = bv[i % kAhead];
-                t = add_tracking_lowest(t, b, lowest);
+                i32x4 b = bv[BIAS ? i % AHEAD : 0];
+                if (STRADDLE) b = bias_chunk_wrapped(b, wrap(boff + 4u * (uint32_t)chunk_of(i), pe), pe, first4);
+                v[i] = add_tracking_lowest(v[i], b, lowest);
+                if (i + AHEAD < SLOTS) bv[BIAS ? i % AHEAD : 0] = bias_chunk(i + AHEAD);
             }
-            if (BIAS && i + kAhead < SLOTS) bv[i % kAhead] = bias_chunk(i + kAhead);
-            lds4[chunk_of(i)] = t;
+            lds4[chunk_of(i)] = v[i];
         }
         wave_lds_fence();
         return BIAS && __builtin_amdgcn_ballot_w64(min(min(lowest.x, lowest.y), min(lowest.z, lowest.w)) == kI32Min) != 0;
