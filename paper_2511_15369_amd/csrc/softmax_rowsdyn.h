@@ -469,8 +469,19 @@ IPTQ_DEV void softmax_rowsdyn_body(const DynArgs &A, uint32_t wg)
     else copy_out(std::false_type{});
 }
 
+// Wavefronts per SIMD that an unmasked kernel is held to.  Every form gets by with eight registers per block
+// of a lane and about 20 more; since a table's loads are all in flight the scheduler, left to itself, takes up to 29
+// beyond that for the second degree's arithmetic (6 to 8 blocks, also in a call without a table), which costs up
+// to two wavefronts per SIMD (up to 7 blocks six are enough; seven at 6 blocks gain nothing, 400,000 rows of 81
+// 27.5 us against 27.1): 150,528 rows of 196 scores of the second degree 26.3 us, 25.3 held to six, 120,000 of
+// 401 43.0 and 41.2, 250,880 of 196 with a table 44.3 and 42.6; the first degree the same.
+constexpr int rowsdyn_least_waves(int slots, int maskkind)
+{
+    return maskkind != 0 ? 1 : slots <= 7 ? 6 : 512 / (8 * slots + 24);
+}
+
 template <int K, int SLOTS, int MODE, int MASKKIND, int VARIANT, bool PRE>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(rowsdyn_least_waves(SLOTS, MASKKIND))))
 softmax_rowsdyn_kernel(DynArgs A)
 {
     touch_kernel_arguments<MASKKIND == 0 ? offsetof(DynArgs, mask) : sizeof(DynArgs)>();
@@ -490,7 +501,7 @@ struct DynBatch {
 };
 static_assert(kDynBatchMax <= BatchHead::kMost && sizeof(DynBatch) <= 4096, "kernel arguments are limited to 4 KiB");
 template <int K, int SLOTS>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(rowsdyn_least_waves(SLOTS, 0))))
 softmax_rowsdyn_batch_kernel(DynBatch B)
 {
     const Problem p = problem_of(B.head, blockIdx.x);
