@@ -28,11 +28,13 @@ bool rowsdyn_geometry(int32_t cols, int *lanes, int *slots)
 // Whether a short call is faster in the three-pass kernel (or one wavefront per row, where the call
 // qualifies for it).  A call of a few thousand rows lasts as long as one wavefront takes from a cold
 // start: here that grows with the code, which is unrolled over the blocks per lane, more so with an
-// int32 mask, for odd row lengths and where the last slab is a partial one (a second copy loop); the
+// int32 mask, for odd row lengths and, when it was fitted, where the last slab was a partial one (a second copy loop); the
 // three-pass kernel's code is short, and it pays per 64 scores of a row and per row.  Both times as
 // linear models, in nanoseconds without what they share, fitted to 2556 calls of 256 to 8192 rows of 7
 // to 200 scores with either mask, the second-degree exponential or a short table: the choice is at most
-// 15 % and on average 0.4 % slower than the faster kernel (always this one: 117 % and 12 %).  With
+// 15 % and on average 0.4 % slower than the faster kernel (always this one: 117 % and 12 %).  (The last slab of a
+// ragged row count has since become a whole one, so that such a call is sooner done here than its terms say:
+// they are as they were fitted, and what they send to the other kernels takes what it took there.)  With
 // fewer than three blocks per lane this kernel is always the faster one, beyond 256 scores nearly
 // always.  600 rows of 25 scores with an int32 mask and a table 3.2 us in the three-pass kernel, 6.2
 // here; 9600 rows 6.7 and 5.5; 768 rows of 64 with a packed mask and a table 3.2 and 4.8.
