@@ -53,7 +53,7 @@ hipError_t softmax_long_launch(const SoftmaxCall &c, int32_t cols, int post_mode
 // serve that row length).
 bool softmax_rows_compiled(int32_t cols);         // a kernel with this row length compiled in exists
 bool rowsdyn_geometry(int32_t cols, int *lanes, int *slots);
-bool rowsdyn_loses_short_call(int64_t rows, int32_t cols, bool has_bias, bool int_mask, bool bit_mask, int calls = 1);
+bool rowsdyn_loses_short_call(int64_t rows, int32_t cols, bool has_bias, bool int_mask, bool bit_mask);
 bool wide_geometry(int32_t cols, int *passes, int *slots, bool off_grid = false);
 bool wgrow_geometry(int32_t cols, int *waves, int *slots, bool off_grid = false);
 bool long_geometry(int32_t cols, int *slots, bool off_grid = false);

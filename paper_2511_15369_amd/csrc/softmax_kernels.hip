@@ -319,21 +319,20 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
         flush();
         // a call no compiled row length served goes to the run-time-row-length kernels; the slab kernel
         // leaves short calls with a mask, a second-degree exponential or a table of fewer rows than its
-        // slab to the others where they are faster (n: that many of them in one launch)
-        auto leave = [&](const SoftmaxCall &c, int n) {
+        // slab to the others where they are faster
+        auto leave = [&](const SoftmaxCall &c) {
             const bool may_lose = slab_only(c) || c.P.variant == 2 || (c.bias != nullptr && c.P.bias_period_rows < 64 && cols <= 29);
             return c.algo == IPTQ_ALGO_AUTO && may_lose &&
-                   rowsdyn_loses_short_call(c.rows, cols, c.bias != nullptr, c.mask != nullptr, c.mask_bits != nullptr, n);
+                   rowsdyn_loses_short_call(c.rows, cols, c.bias != nullptr, c.mask != nullptr, c.mask_bits != nullptr);
         };
-        // several calls of the run-time-row-length kernel in one launch, but for two that are sooner done
-        // apart; where one writes what another one reads or writes, they are made in their order, one
-        // launch each
-        int pending = 0, left = 0;
-        for (int i = 0; i < cnt; ++i) {
-            pending += done[i] == 0;
-            left += done[i] == 0 && leave(calls[base + i], 2);
-        }
-        if (pending > 1 && !(pending == 2 && left == 2) && err == hipSuccess && independent(calls + base, cnt, cols)) {
+        // several calls of the run-time-row-length kernel in one launch, also the short ones that it would leave
+        // one by one: a launch costs more than their chains differ (two calls of 64 to 4000 rows of 25 to 121
+        // scores, second degree or a table, 4.8 to 5.4 us call after call, 6.3 to 7.6 as two launches of one
+        // wavefront per row; in a graph 420 such pairs 3.4 to 5.2 us against 4.5 to 7.3, at most 8 % slower).  Where
+        // one writes what another one reads or writes, they are made in their order, one launch each
+        int pending = 0;
+        for (int i = 0; i < cnt; ++i) pending += done[i] == 0;
+        if (pending > 1 && err == hipSuccess && independent(calls + base, cnt, cols)) {
             int post_modes[kBatchMax];
             for (int i = 0; i < cnt; ++i) post_modes[i] = post_mode_of(calls[base + i].P, calls[base + i].out_bits);
             err = softmax_rowsdyn_launch_batch(calls + base, post_modes, cnt, cols, done, stream);
@@ -341,7 +340,7 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
         for (int i = 0; i < cnt && err == hipSuccess; ++i) {
             const SoftmaxCall &c = calls[base + i];
             const bool has_pre = !(c.P.pre_m == 1 && c.P.pre_s == 0);
-            if (done[i] == 0 && !leave(c, 1) && (c.algo == IPTQ_ALGO_AUTO || c.algo == IPTQ_ALGO_DYNAMIC || c.algo == IPTQ_ALGO_SLAB)) {
+            if (done[i] == 0 && !leave(c) && (c.algo == IPTQ_ALGO_AUTO || c.algo == IPTQ_ALGO_DYNAMIC || c.algo == IPTQ_ALGO_SLAB)) {
                 err = softmax_rowsdyn_launch(c, cols, post_mode_of(c.P, c.out_bits), &done[i], stream);
                 if (err != hipSuccess) break;
             }

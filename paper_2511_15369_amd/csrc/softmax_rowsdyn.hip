@@ -38,17 +38,10 @@ bool rowsdyn_geometry(int32_t cols, int *lanes, int *slots)
 // fewer than three blocks per lane this kernel is always the faster one, beyond 256 scores nearly
 // always.  600 rows of 25 scores with an int32 mask and a table 3.2 us in the three-pass kernel, 6.2
 // here; 9600 rows 6.7 and 5.5; 768 rows of 64 with a packed mask and a table 3.2 and 4.8.
-// calls: that many such calls of a batch, in one launch here against one launch each: three and more
-// are always faster here (three of 600 x 25 with a short table 6.3 us against 8.1), two unless this
-// chain is 1.15 us longer than twice the other (two of 600 x 25 6.0 against 5.4, of 600 x 29 6.5 against
-// 5.7, of 600 x 64 of the second degree 5.5 against 4.9; of 4000 x 25 6.6 against 7.6; over 203 pairs of
-// 64 to 4000 rows at most 18 % and on average 0.5 % slower than the faster form, one launch always 24 %
-// and 2.3 %).
-bool rowsdyn_loses_short_call(int64_t rows, int32_t cols, bool has_bias, bool int_mask, bool bit_mask, int calls)
+bool rowsdyn_loses_short_call(int64_t rows, int32_t cols, bool has_bias, bool int_mask, bool bit_mask)
 {
     int lanes = 0, slots = 0;
     if (rows > 8192 || cols > 256 || !rowsdyn_geometry(cols, &lanes, &slots) || slots < 3) return false;
-    if (calls > 2 || (calls == 2 && rows < 256)) return false;
     const bool partial = rows % (64 / lanes) != 0;
     int64_t here = 960 + slots * (210 + (int_mask ? 70 : 0) + (partial ? 100 : 0));
     if (cols % 2 != 0) here += 360;
@@ -57,7 +50,7 @@ bool rowsdyn_loses_short_call(int64_t rows, int32_t cols, bool has_bias, bool in
     const int64_t passes = (cols + 63) / 64;
     int64_t three_pass = 810 * passes + (int_mask || bit_mask ? 440 : 0);
     if (rows > 1024) three_pass += 170 * (passes + 1) * (rows - 1024) / 1024;
-    return calls == 2 ? 2 * three_pass + 1150 < here : three_pass < here;
+    return three_pass < here;
 }
 
 static int64_t gcd_i64(int64_t a, int64_t b)
