@@ -39,6 +39,7 @@ hipError_t softmax_rowsdyn_launch_batch(const SoftmaxCall *calls, const int *pos
                                         int64_t *done, hipStream_t stream);
 // One wavefront per row, row in registers, no LDS staging (rows of up to 4093 scores at any
 // alignment, 4096 if a multiple of 4): every row of one call, or none.
+bool softmax_wide_serves(const SoftmaxCall &c, int32_t cols);
 hipError_t softmax_wide_launch(const SoftmaxCall &c, int32_t cols, int post_mode, int64_t *done,
                                hipStream_t stream);
 // One workgroup per row, row in the workgroup's registers (rows of up to 26621 scores, 26624 if a
@@ -54,6 +55,7 @@ hipError_t softmax_long_launch(const SoftmaxCall &c, int32_t cols, int post_mode
 bool softmax_rows_compiled(int32_t cols);         // a kernel with this row length compiled in exists
 bool rowsdyn_geometry(int32_t cols, int *lanes, int *slots);
 bool rowsdyn_loses_short_call(int64_t rows, int32_t cols, bool has_bias, bool int_mask, bool bit_mask);
+bool rowsdyn_loses_to_wavefronts(int64_t rows, int32_t cols);
 bool wide_geometry(int32_t cols, int *passes, int *slots, bool off_grid = false);
 bool wgrow_geometry(int32_t cols, int *waves, int *slots, bool off_grid = false);
 bool long_geometry(int32_t cols, int *slots, bool off_grid = false);

@@ -322,13 +322,15 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
         // slab to the others where they are faster
         auto leave = [&](const SoftmaxCall &c) {
             const bool may_lose = slab_only(c) || c.P.variant == 2 || (c.bias != nullptr && c.P.bias_period_rows < 64 && cols <= 29);
-            return c.algo == IPTQ_ALGO_AUTO && may_lose &&
-                   rowsdyn_loses_short_call(c.rows, cols, c.bias != nullptr, c.mask != nullptr, c.mask_bits != nullptr);
+            if (c.algo != IPTQ_ALGO_AUTO || !may_lose) return false;
+            if (!slab_only(c) && softmax_wide_serves(c, cols)) return rowsdyn_loses_to_wavefronts(c.rows, cols);
+            return rowsdyn_loses_short_call(c.rows, cols, c.bias != nullptr, c.mask != nullptr, c.mask_bits != nullptr);
         };
         // several calls of the run-time-row-length kernel in one launch, also the short ones that it would leave
         // one by one: a launch costs more than their chains differ (two calls of 64 to 4000 rows of 25 to 121
         // scores, second degree or a table, 4.8 to 5.4 us call after call, 6.3 to 7.6 as two launches of one
-        // wavefront per row; in a graph 420 such pairs 3.4 to 5.2 us against 4.5 to 7.3, at most 8 % slower).  Where
+        // wavefront per row; 960 such pairs in a graph 2.9 to 6.9 us against 4.3 to 12, at most 8 % and on average
+        // 0.1 % slower).  Where
         // one writes what another one reads or writes, they are made in their order, one launch each
         int pending = 0;
         for (int i = 0; i < cnt; ++i) pending += done[i] == 0;

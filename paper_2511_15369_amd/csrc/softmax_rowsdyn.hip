@@ -25,32 +25,45 @@ bool rowsdyn_geometry(int32_t cols, int *lanes, int *slots)
     return true;
 }
 
-// Whether a short call is faster in the three-pass kernel (or one wavefront per row, where the call
-// qualifies for it).  A call of a few thousand rows lasts as long as one wavefront takes from a cold
-// start: here that grows with the code, which is unrolled over the blocks per lane, more so with an
-// int32 mask, for odd row lengths and, when it was fitted, where the last slab was a partial one (a second copy loop); the
-// three-pass kernel's code is short, and it pays per 64 scores of a row and per row.  Both times as
-// linear models, in nanoseconds without what they share, fitted to 2556 calls of 256 to 8192 rows of 7
-// to 200 scores with either mask, the second-degree exponential or a short table: the choice is at most
-// 15 % and on average 0.4 % slower than the faster kernel (always this one: 117 % and 12 %).  (The last slab of a
-// ragged row count has since become a whole one, so that such a call is sooner done here than its terms say:
-// they are as they were fitted, and what they send to the other kernels takes what it took there.)  With
-// fewer than three blocks per lane this kernel is always the faster one, beyond 256 scores nearly
-// always.  600 rows of 25 scores with an int32 mask and a table 3.2 us in the three-pass kernel, 6.2
-// here; 9600 rows 6.7 and 5.5; 768 rows of 64 with a packed mask and a table 3.2 and 4.8.
+// Whether a short call is faster in the three-pass kernel: a masked one, or one beside a table that one
+// wavefront per row does not take.  A call of a few thousand rows lasts as long as one wavefront takes from a
+// cold start: here that grows with the code, which is unrolled over the blocks per lane, more so with an int32 mask
+// and for odd row lengths; the three-pass kernel's code is short, and it pays per 64 scores of a row and per
+// row.  Both times as linear models, in nanoseconds without what they share.  Of 5708 masked calls of 256 to
+// 8192 rows of 9 to 256 scores, either mask, with and without a table, first and second degree, whole and ragged
+// row counts, in a graph: the choice is at most 24 % and on average 0.7 % slower than the faster kernel (always
+// this one: 71 % and 4.8 %); of 1172 beside a table alone 23 % and 1.2 %.  With fewer than three blocks per lane
+// this kernel is always the faster one, beyond 256 scores nearly always.  704 rows of 64 scores with an int32 mask and a
+// table 3.3 us in the three-pass kernel, 4.9 here, 6147 of 29 with a packed mask 5.0 and 3.8.  (A ragged row count has no term of
+// its own: since its last slab is a whole one it takes what a whole one takes, 706 of 29 with an int32 mask and a table 5.5
+// here, 704 5.1; charged for a partial one, 3075 x 100 went to the three-pass kernel, 5.1 us against 4.8, 258 x 196 6.0 against 4.1.)
 bool rowsdyn_loses_short_call(int64_t rows, int32_t cols, bool has_bias, bool int_mask, bool bit_mask)
 {
     int lanes = 0, slots = 0;
     if (rows > 8192 || cols > 256 || !rowsdyn_geometry(cols, &lanes, &slots) || slots < 3) return false;
-    const bool partial = rows % (64 / lanes) != 0;
-    int64_t here = 960 + slots * (210 + (int_mask ? 70 : 0) + (partial ? 100 : 0));
+    int64_t here = 960 + slots * (210 + (int_mask ? 70 : 0));
     if (cols % 2 != 0) here += 360;
     if (lanes == 1) here -= 440;
-    if (partial) here += has_bias ? 310 : -360;
     const int64_t passes = (cols + 63) / 64;
     int64_t three_pass = 810 * passes + (int_mask || bit_mask ? 440 : 0);
     if (rows > 1024) three_pass += 170 * (passes + 1) * (rows - 1024) / 1024;
     return three_pass < here;
+}
+
+// The same against one wavefront per row, which takes unmasked calls (one pass up to 256 scores): how much
+// longer this kernel's chain is, by its blocks and the steps of its reduction, against what the rows add
+// there.  Rows that are whole 64-byte lines are 0.3 us faster there.  Fitted to 1120 calls of 3073 to 8192 rows of 9 to 256
+// scores of the second degree, with and without a table, or with a table of 40 rows, in a graph: at most 18 % and on
+// average 0.3 % slower than the faster kernel (always this one: 43 % and 7.4 %; by the model above, whose other side is three
+// passes, 43 % and 5.9 %).  4096 rows of 256 scores of the second degree 4.3 us here, 3.2 there; 8192 of 25 3.7 and 4.6.
+bool rowsdyn_loses_to_wavefronts(int64_t rows, int32_t cols)
+{
+    int lanes = 0, slots = 0;
+    if (rows > 8192 || cols > 256 || !rowsdyn_geometry(cols, &lanes, &slots) || slots < 3) return false;
+    int64_t longer = 210 * slots - 1130;
+    for (int k = lanes; k > 1; k /= 2) longer += 190;
+    if (cols % 16 == 0) longer += 350;
+    return longer > 230 * (rows - 3072) / 1024;
 }
 
 static int64_t gcd_i64(int64_t a, int64_t b)

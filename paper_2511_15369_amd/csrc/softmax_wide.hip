@@ -21,28 +21,34 @@ bool wide_geometry(int32_t cols, int *passes, int *slots, bool off_grid)
     return true;
 }
 
-// Every row of one call if the call qualifies (rows of up to 16 passes, pointers as checked
-// below); *done receives the number of rows served (0: not served, nothing enqueued).
+// Whether the kernel takes a call.  The tensor may start anywhere on the 4-byte grid (rows are addressed on
+// the 16-byte grid below it) and the output anywhere; the additive table is indexed block by block and needs
+// both tensors on the 16-byte grid.  A tensor that ends off that grid: the kernel loads the last row's final
+// block element by element, which takes rows of at least 8 scores (a whole block before it).
+bool softmax_wide_serves(const SoftmaxCall &c, int32_t cols)
+{
+    int n = 0, slots = 0;
+    const uintptr_t sa = reinterpret_cast<uintptr_t>(c.scores);
+    const int base_off = (int)((sa & 15) >> 2);
+    if ((sa & 3) != 0 || !wide_geometry(cols, &n, &slots, base_off != 0)) return false;
+    if (c.bias != nullptr && (base_off != 0 || (reinterpret_cast<uintptr_t>(c.bias) & 15) != 0 ||
+                              ((int64_t)c.P.bias_period_rows * cols) % 4 != 0))
+        return false;
+    const int cut_el = (int)((base_off + c.rows * cols) & 3);
+    return c.rows > 0 && (cut_el == 0 || cols >= 8);
+}
+
+// Every row of one call if the call qualifies (rows of up to 16 passes); *done receives the number of rows
+// served (0: not served, nothing enqueued).
 hipError_t softmax_wide_launch(const SoftmaxCall &c, int32_t cols, int post_mode, int64_t *done,
                                hipStream_t stream)
 {
     *done = 0;
+    if (!softmax_wide_serves(c, cols)) return hipSuccess;
     int n = 0, slots = 0;
-    // The tensor may start anywhere on the 4-byte grid (rows are addressed on the 16-byte grid
-    // below it) and the output anywhere; the additive table is indexed block by block and needs
-    // both tensors on the 16-byte grid.
-    const uintptr_t sa = reinterpret_cast<uintptr_t>(c.scores);
-    const int base_off = (int)((sa & 15) >> 2);
-    if ((sa & 3) != 0) return hipSuccess;
-    if (!wide_geometry(cols, &n, &slots, base_off != 0)) return hipSuccess;
-    const bool has_bias = c.bias != nullptr;
-    const bool bias_ok = !has_bias || (base_off == 0 && (reinterpret_cast<uintptr_t>(c.bias) & 15) == 0 &&
-                                       ((int64_t)c.P.bias_period_rows * cols) % 4 == 0);
-    if (!bias_ok) return hipSuccess;
-    // A tensor that ends off the 16-byte grid: the kernel loads the last row's final block
-    // element by element, which takes rows of at least 8 scores (a whole block before it).
+    const int base_off = (int)((reinterpret_cast<uintptr_t>(c.scores) & 15) >> 2);
+    wide_geometry(cols, &n, &slots, base_off != 0);
     const int cut_el = (int)((base_off + c.rows * cols) & 3);
-    if (c.rows <= 0 || (cut_el != 0 && cols < 8)) return hipSuccess;
     const int64_t rows = c.rows;
     WideArgs A;
     A.scores = c.scores - base_off; A.bias = c.bias; A.out = c.out - base_off; A.base_off = base_off; A.rows = rows; A.cols = cols; A.post_mode = post_mode; A.P = c.P;

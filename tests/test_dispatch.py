@@ -129,6 +129,28 @@ def test_two_short_calls_share_a_launch(lib):
         assert kernels(2, *args) == kernels(3, *args) == kernels(2, *args, algo=ip.ALGO_DYNAMIC) == together, args
 
 
+@pytest.mark.parametrize("cols,variant,fields,other", [
+    (100, 1, dict(d_bias=SCORES + (1 << 30), bias_period_rows=200, d_mask=SCORES + (1 << 31), n_windows=4, heads=2), "softmax_generic_kernel"),
+    (81, 1, dict(d_mask=SCORES + (1 << 31), n_windows=4, heads=2), "softmax_generic_kernel"),
+    (121, 1, dict(d_bias=SCORES + (1 << 30), bias_period_rows=242, d_mask_bits=SCORES + (1 << 31), n_windows=4, heads=2), "softmax_generic_kernel"),
+    (29, 2, dict(d_mask_bits=SCORES + (1 << 31), n_windows=4, heads=2), "softmax_generic_kernel"),
+    (64, 2, {}, "softmax_wide_kernel"), (225, 2, {}, "softmax_wide_kernel"), (9, 2, {}, "softmax_wide_kernel"),
+    (81, 2, dict(d_bias=SCORES + (1 << 30), bias_period_rows=100), "softmax_wide_kernel"),
+    (25, 1, dict(d_bias=SCORES + (1 << 30), bias_period_rows=40), "softmax_wide_kernel"),
+    (25, 1, dict(d_bias=SCORES + (1 << 30), bias_period_rows=41), "softmax_generic_kernel"),      # not a multiple of four scores
+    (25, 2, dict(d_bias=SCORES + (1 << 30) + 4, bias_period_rows=40), "softmax_generic_kernel")])  # off the 16-byte grid
+def test_ragged_short_calls_are_chosen_like_whole_ones(lib, cols, variant, fields, other):
+    """A short call leaves the run-time-row-length slab kernel up to some number of rows and stays from there
+    on, whatever the row count is a multiple of."""
+    p = ip.softmax_prepare(0.0085, cols, variant, 0)
+    seen = []
+    for rows in range(600, 9300, 61):
+        got = [l.kernel for l in batch(lib, [(rows, p, fields)], cols)]
+        assert got in ([other], ["softmax_rowsdyn_kernel"]), (rows, got)
+        seen.append(got[0] == other)
+    assert seen == sorted(seen, reverse=True) and seen[0] and not seen[-1]
+
+
 @pytest.mark.parametrize("rows,cols,most", [
     # one wavefront per row: the fewest and the most passes with each bound, and the lines between
     (50_000_000 // 816 + 1, 816, 0), (50_000_000 // 820 + 1, 820, 6), (50_000_000 // 948 + 1, 948, 6), (50_000_000 // 952 + 1, 952, 5),
