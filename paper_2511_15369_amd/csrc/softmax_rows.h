@@ -72,12 +72,6 @@ struct SoftmaxBatch {
     BatchHead head;
     SoftmaxItem item[kBatchMax];
 };
-// The arguments of a launch of one problem: the number of problems comes first here too, so that whoever looks
-// at a launch's arguments finds it in one place.
-struct SoftmaxOne {
-    uint32_t n_items;                                 // 1
-    SoftmaxItem item;
-};
 static_assert(sizeof(SoftmaxBatch) <= 4096, "kernel arguments are limited to 4 KiB");
 
 // rshr_round(x * pre_m, pre_s) for pre_s >= 16 (SoftmaxDev::pre_mode 1): one 64-bit
@@ -942,7 +936,7 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
 #endif
 }
 
-// Every kernel takes one problem's arguments (232 bytes) or a table of up to kBatchMax (3.6 KB).  An ordinary
+// Every kernel takes one problem's arguments (224 bytes) or a table of up to kBatchMax (3.6 KB).  An ordinary
 // call is one problem, and the host writes a launch's arguments into device memory: 4704 rows of 49 scores
 // and their GELU 7.2 us call after call, 7.7 with the table of one.  On the GPU it saves the search and a
 // dynamic address: 4736 rows of 197 4.06 us against 4.21, 37,824 of the second degree 9.3 against 9.5.
@@ -950,10 +944,10 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
 // but for the mask's, which the compiler leaves for later: with them touched 589,824 rows of 144 scores with an
 // int32 mask take 75.3 us instead of 76.0, with a bias alone 66.4 instead of 65.8.)
 template <int COLS, int K, int MODE, bool BIAS, int POSTMODE, int MASKKIND, bool PRE>
-IPTQ_DEV void softmax_rows_problem(const SoftmaxOne &A)
+IPTQ_DEV void softmax_rows_problem(const SoftmaxItem &I)
 {
-    if (MASKKIND != 0) touch_kernel_arguments<sizeof(SoftmaxOne)>();
-    softmax_rows_body<COLS, K, MODE, BIAS, POSTMODE, MASKKIND, PRE>(A.item, blockIdx.x);
+    if (MASKKIND != 0) touch_kernel_arguments<sizeof(SoftmaxItem)>();
+    softmax_rows_body<COLS, K, MODE, BIAS, POSTMODE, MASKKIND, PRE>(I, blockIdx.x);
 }
 template <int COLS, int K, int MODE, bool BIAS, int POSTMODE, int MASKKIND, bool PRE>
 IPTQ_DEV void softmax_rows_problem(const SoftmaxBatch &B)
@@ -1045,7 +1039,7 @@ inline size_t rows_extra_lds(int cols, int k, unsigned total_wgs, const SoftmaxB
 
 #define IPTQ_ROWS_LAUNCH_AS(KERNEL, ...)                                                          \
     do {                                                                                          \
-        if (B.head.n_items == 1) launch_kernel((KERNEL<__VA_ARGS__, SoftmaxOne>), grid, block, lds, stream, SoftmaxOne{1, B.item[0]});  \
+        if (B.head.n_items == 1) launch_kernel((KERNEL<__VA_ARGS__, SoftmaxItem>), grid, block, lds, stream, B.item[0]);  \
         else launch_kernel((KERNEL<__VA_ARGS__, SoftmaxBatch>), grid, block, lds, stream, B);     \
     } while (0)
 #define IPTQ_ROWS_LAUNCH(COLS, K, MODE, BIAS, PM, MASK)                                           \

@@ -56,7 +56,8 @@ const char *recorded(int i, uint32_t *grid, uint32_t *block, uint64_t *lds, uint
 }
 """
 
-Launch = namedtuple("Launch", "kernel arguments grid block lds first_word")
+# (problems: how many a batch's table holds, which its arguments begin with; 1 where the kernel takes one problem's)
+Launch = namedtuple("Launch", "kernel arguments grid block lds first_word problems")
 
 
 def build(folder, replaced=None):
@@ -103,5 +104,6 @@ def launches(so, call):
         name = so.recorded(i, ctypes.byref(grid), ctypes.byref(block), ctypes.byref(lds), ctypes.byref(word)).decode()
         m = re.search(r"iptq::(\w+)(?:<([^>]*)>)?", name)
         args = tuple(int(a) if a.lstrip("-").isdigit() else a for a in re.split(r",\s*", m.group(2))) if m.group(2) else ()
-        out.append(Launch(m.group(1), args, grid.value, block.value, lds.value, word.value))
+        table = "batch" in m.group(1) or any("Batch" in a for a in args if isinstance(a, str))
+        out.append(Launch(m.group(1), args, grid.value, block.value, lds.value, word.value, word.value if table else 1))
     return out

@@ -99,7 +99,7 @@ def test_batch_with_both_dividers(lib, order):
     specs = [(4000, packed_softmax(order[i % len(order)], 197)) for i in range(16)]
     got = batch(lib, specs, 197)
     high = sum(q.i0 > 1050 for _, q in specs)
-    assert sorted((l.kernel, l.arguments[2], l.first_word) for l in got) == [
+    assert sorted((l.kernel, l.arguments[2], l.problems) for l in got) == [
         ("softmax_rows_kernel", 1, high), ("softmax_rows_kernel", 2, 16 - high)]
     # one launch where each can have the multiply-high divider
     wide = [(4000, packed_softmax(max(q.i0, 257 + i), 197)) for i, (_, q) in enumerate(specs)]
@@ -108,7 +108,7 @@ def test_batch_with_both_dividers(lib, order):
     # a layer in 32-bit arithmetic ends the launches in front of it, as it always did
     specs[8] = (4000, packed_softmax(2 ** 14, 197))
     got = batch(lib, specs, 197)
-    assert [l.arguments[2] for l in got] == [2, 1, 0, 2, 1] and sum(l.first_word for l in got) == 16
+    assert [l.arguments[2] for l in got] == [2, 1, 0, 2, 1] and sum(l.problems for l in got) == 16
 
 
 def test_two_short_calls_share_a_launch(lib):
