@@ -549,8 +549,8 @@ static __device__ uint64_t g_timeline[5 * kTimelineSlabs];
 #endif
 
 // MASKKIND: 0 no per-window mask, 1 the int32 table read beside the bias, 2 one bit per key.
-// lw: this workgroup's number within the problem.
-template <int COLS, int K, int MODE, bool BIAS, int POSTMODE, int MASKKIND, bool PRE = false>
+// lw: this workgroup's number within the problem.  ONE: the launch's arguments are this problem's alone.
+template <int COLS, int K, int MODE, bool BIAS, int POSTMODE, int MASKKIND, bool PRE, bool ONE>
 IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
 {
     constexpr bool MASK = MASKKIND == 1;
@@ -581,11 +581,30 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
     static_assert(!MASK || RPW <= COLS, "a slab may cross one wrap of the query index at most");
     constexpr int MW = MASKKIND == 2 ? (COLS + 63) / 64 : 1;   // 64-bit words of packed mask per query
     uint32_t slab = lw * (uint32_t)kRowsWpb + (uint32_t)wv;
-    if (BIAS && I.share_q != 0) {
-        const uint32_t g = mulhi_u32(lw, I.share_magic) >> I.share_sh;
-        slab = g * (kRowsWpb * I.share_q) + (uint32_t)wv * I.share_q + (lw - g * I.share_q);
+    if constexpr (ONE && BIAS && MASKKIND == 0) {
+        // With a table alone everything that the slab's place in both tensors follows from is wanted here, so that it
+        // comes in one wait for all four lines of the arguments.  Left to itself the compiler asked for it in four
+        // steps, each a cold line call after call: 10,000 rows of 49 scores with a table 4.5 us, 4.6 in steps (4.2 and 4.3
+        // in a graph), of 144 in 32-bit arithmetic 4.9 and 5.4, 10,000 of 577 8.6 and 8.7, 200,000 of 49 10.8 and 11.1.
+        // Touching the lines first is a wait more, and its volatile asm makes a vector load with a wait of its own out of
+        // the table's first entries, which are a scalar load otherwise (800,000 rows with 3 heads 34.1 us against 33.4):
+        // the asm here must not be volatile.  A batch's arguments have been touched already (16 problems of 20,000 x 197
+        // 58.1 us, 60.6 with this).
+        uint32_t n_slabs = I.n_slabs, q = I.share_q, magic = I.share_magic;
+        int32_t sh = I.share_sh;
+        asm("" : "+s"(n_slabs), "+s"(q), "+s"(magic), "+s"(sh) : "s"(P.bias_period_rows), "s"(P.period_magic), "s"(P.period_sh));
+        if (q != 0) {
+            const uint32_t g = mulhi_u32(lw, magic) >> sh;
+            slab = g * (kRowsWpb * q) + (uint32_t)wv * q + (lw - g * q);
+        }
+        if (slab >= n_slabs) return;                  // no workgroup barrier below
+    } else {
+        if (BIAS && I.share_q != 0) {
+            const uint32_t g = mulhi_u32(lw, I.share_magic) >> I.share_sh;
+            slab = g * (kRowsWpb * I.share_q) + (uint32_t)wv * I.share_q + (lw - g * I.share_q);
+        }
+        if (slab >= I.n_slabs) return;
     }
-    if (slab >= I.n_slabs) return;                    // no workgroup barrier below
 
 #ifdef IPTQ_TIMELINE
     IPTQ_TL(0, t_entry);
@@ -940,21 +959,21 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
 // call is one problem, and the host writes a launch's arguments into device memory: 4704 rows of 49 scores
 // and their GELU 7.2 us call after call, 7.7 with the table of one.  On the GPU it saves the search and a
 // dynamic address: 4736 rows of 197 4.06 us against 4.21, 37,824 of the second degree 9.3 against 9.5.
-// (The arguments of one problem are few enough to be asked for together without touching their lines first,
-// but for the mask's, which the compiler leaves for later: with them touched 589,824 rows of 144 scores with an
-// int32 mask take 75.3 us instead of 76.0, with a bias alone 66.4 instead of 65.8.)
+// (Without a mask the arguments of one problem are asked for together as they are, see softmax_rows_body; the mask's
+// the compiler leaves for later: with all lines touched first 589,824 rows of 144 scores with an int32 mask take
+// 75.3 us instead of 76.0.)
 template <int COLS, int K, int MODE, bool BIAS, int POSTMODE, int MASKKIND, bool PRE>
 IPTQ_DEV void softmax_rows_problem(const SoftmaxItem &I)
 {
     if (MASKKIND != 0) touch_kernel_arguments<sizeof(SoftmaxItem)>();
-    softmax_rows_body<COLS, K, MODE, BIAS, POSTMODE, MASKKIND, PRE>(I, blockIdx.x);
+    softmax_rows_body<COLS, K, MODE, BIAS, POSTMODE, MASKKIND, PRE, true>(I, blockIdx.x);
 }
 template <int COLS, int K, int MODE, bool BIAS, int POSTMODE, int MASKKIND, bool PRE>
 IPTQ_DEV void softmax_rows_problem(const SoftmaxBatch &B)
 {
     const Problem p = problem_of(B.head, blockIdx.x);
     touch_kernel_arguments<sizeof(SoftmaxItem)>((uint32_t)offsetof(SoftmaxBatch, item) + p.index * (uint32_t)sizeof(SoftmaxItem));
-    softmax_rows_body<COLS, K, MODE, BIAS, POSTMODE, MASKKIND, PRE>(B.item[p.index], p.wg);
+    softmax_rows_body<COLS, K, MODE, BIAS, POSTMODE, MASKKIND, PRE, false>(B.item[p.index], p.wg);
 }
 
 template <int COLS, int K, int MODE, bool BIAS, int POSTMODE, class ARGS>

@@ -56,3 +56,16 @@ def test_no_floating_point_instructions(src, assembly):
     # argument struct the compiler had to copy to private memory to index it)
     scratch = re.findall(r"\.amdhsa_private_segment_fixed_size (\d+)", text)
     assert scratch and all(int(b) == 0 for b in scratch), scratch
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not installed")
+@pytest.mark.parametrize("cols", [49, 144])
+def test_arguments_of_a_table_call_come_in_two_steps(cols, assembly):
+    """A launch's arguments are cold in every cache: the kernel of one problem with an additive table has its
+    first load in flight after two waits for them (where the slab lies; the pointers), not after one per line."""
+    text = assembly("softmax_rows_%d.hip" % cols)
+    bodies = re.findall(r"^_ZN4iptq19softmax_rows_kernelILi%dELi\dELi[012]ELb1ELi0ENS_11SoftmaxItemE\w*:(.*?)^\.Lfunc_end" % cols,
+                        text, re.M | re.S)
+    assert len(bodies) == 3                            # both dividers and 32-bit arithmetic
+    for body in bodies:
+        assert len(re.findall(r"s_waitcnt.*lgkmcnt", body[:body.index("global_load")])) <= 2
