@@ -172,7 +172,9 @@ IPTQ_DEV int32_t clamp_i32(int32_t v, int32_t lo, int32_t hi)
 // steps (which problem of the batch, then that problem's sizes, then its table constants) waits
 // for memory once per step before it can issue its first load.  This touches BYTES of the
 // kernel-argument segment at once, from byte `from` (a wavefront-uniform multiple of four) on, one load
-// per 64-byte line, so that one wait covers them all and the steps that follow hit in the cache.
+// per 64 bytes, so that one wait covers them and the steps that follow hit in the cache.  Those are all their
+// lines where they start on one, or fill their last one from where they start (the 224 and 96 bytes of the compiled
+// row lengths' and the GELU's batches).
 template <int BYTES>
 IPTQ_DEV void touch_kernel_arguments(uint32_t from = 0)
 {

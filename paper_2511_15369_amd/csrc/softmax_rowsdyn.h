@@ -505,6 +505,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(rowsdy
 softmax_rowsdyn_batch_kernel(DynBatch B)
 {
     const Problem p = problem_of(B.head, blockIdx.x);
+    // (an item's 248 bytes start anywhere in a line, so that of 6 of the 14 the last line, the end of the plan's
+    // constants, is not touched; with items of 256 bytes 421 batches of 2 to 14 problems take the same on average, 300
+    // rows of 100 and 145 scores 2 % more)
     touch_kernel_arguments<offsetof(DynArgs, mask)>((uint32_t)offsetof(DynBatch, item) + p.index * (uint32_t)sizeof(DynArgs));
     softmax_rowsdyn_body<K, SLOTS, 2, 0, -1, false>(B.item[p.index], p.wg);
 }
