@@ -194,9 +194,12 @@ hipError_t softmax_dispatch(const SoftmaxCall *calls, int n_calls, int32_t cols,
 {
     // A single call of a few thousand rows is one generation of wavefronts whatever the kernel:
     // its duration is one wavefront's chain of load, arithmetic and store, and one wavefront per
-    // row has the shortest (kernel-trace durations, 591 / 2364 / 4728 rows of 197 scores: 3.6 /
-    // 4.1 / 4.9 us against 5.5 / 5.3 / 4.9 us with the slab kernel; 392 to 3136 rows of 49 with a
-    // table: 3.5-4.2 against 5.3-4.7 us; the slab kernels win from about 4000 rows on).
+    // row has the shortest.  Graph times, one wavefront per row and the slab kernel: 512 / 2560 / 3072 / 4608 rows of
+    // 197 scores 2.8 / 3.57 / 3.65 / 4.05 us and 3.35 / 3.84 / 3.91 / 4.01, of 49 with a table 3.06 / 3.61 / 3.62 / 4.08
+    // and 3.85 / 4.01 / 4.03 / 3.97, of 577 3.31 / 4.67 / 4.77 / 5.63 and 3.99 / 4.85 / 4.96 / 6.36; ragged row counts the
+    // same.  They cross between 2300 rows (of 36 scores) and 7000 (of 64 and 256): of 600 calls of 256 to 3072 rows of
+    // 16 to 600 scores, with and without a table, this line loses in 7, at most 7 % (the slab kernel always: 20 % on
+    // average); from there to 8192 rows the slab kernel is 4.8 % slower on average, most in rows of 64 and 256.
     constexpr int64_t kTinyRows = 3072;
     // (a per-window mask exists in the slab kernels, compiled and run-time row length, and in the
     // three-pass kernel)

@@ -682,7 +682,9 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
         // free, so that every pass waited for an L2 access of its own, or put several table loads in front of
         // the scores'.  With a bias, in this order and with LINEAR: 802,816 rows of 7 x 7 tokens 35.6 -> 33.4 us (3
         // heads), with a packed mask 34.5 -> 33.8 (4 heads), 200,704 11.9 -> 11.4, 147,456 of 12 x 12 tokens 19.1 ->
-        // 18.6.  With an int32 mask, against all scores first: 589,824 of 12 x 12 tokens 76.9 -> 75.3, 100,352 of
+        // 18.6; together with the whole last slab and the arguments of one problem 1522 rows of 197 5.3 -> 3.9, 176,768 of 198
+        // 31.1 -> 30.1, 136,187 of 257 34.2 -> 33.0, 60,658 of 577 38.2 -> 35.1, 507,614 of 197 85.5 -> 81.8.  With an int32
+        // mask, against all scores first: 589,824 of 12 x 12 tokens 76.9 -> 75.3, 100,352 of
         // 7 x 7 9.6 -> 9.1; there a fixed order within the loads costs 1.5 %, beside a bias alone it is what
         // gains the last per cent.  Leaving the int32 mask out where a slab's entries are all zero brings
         // nothing more (41.2 us against 41.3): the loads are what it costs.
@@ -958,7 +960,11 @@ IPTQ_DEV void softmax_rows_body(const SoftmaxItem &I, uint32_t lw)
 // Every kernel takes one problem's arguments (224 bytes) or a table of up to kBatchMax (3.6 KB).  An ordinary
 // call is one problem, and the host writes a launch's arguments into device memory: 4704 rows of 49 scores
 // and their GELU 7.2 us call after call, 7.7 with the table of one.  On the GPU it saves the search and a
-// dynamic address: 4736 rows of 197 4.06 us against 4.21, 37,824 of the second degree 9.3 against 9.5.
+// dynamic address: 4736 rows of 197 4.06 us against 4.21, 37,824 of the second degree 9.3 against 9.5.  Every form
+// gains, so each exists twice (10 of the library's 47 MB): 3500 to 10,000 rows of all six lengths on average, in a graph
+// and call after call, plain 0.20 and 0.46 us, requantized in front 0.19 and 0.40, in 32-bit arithmetic 0.15 and 0.19,
+// with the multiply-high divider 0.21 and 0.44, with a table 0.13 and, asked for as in softmax_rows_body, 0.25; of 49 and
+// 144 with an int32 mask 0.25 and 0.48, with a packed one 0.30 and 0.50, either in 32-bit arithmetic 0.13 and 0.34.
 // (Without a mask the arguments of one problem are asked for together as they are, see softmax_rows_body; the mask's
 // the compiler leaves for later: with all lines touched first 589,824 rows of 144 scores with an int32 mask take
 // 75.3 us instead of 76.0.)
