@@ -39,7 +39,10 @@ SOFTMAX_BYTES_PER_EL = 5       # int32 in, one byte out
 GELU_BYTES_PER_EL = 2          # int8 in, int8 out
 CACHE_FLUSH_BYTES = 512e6      # bytes that must be touched before a buffer is used again
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "softmax_gelu_hbm_traffic.md")
-KERNEL_SOURCES = ("softmax_rows.h", "device_common.h", "softmax_kernels.hip", "elementwise_kernels.hip")
+# every file that holds kernels of the workloads and cases, and the rules that choose among them
+KERNEL_SOURCES = ("device_common.h", "softmax_rows.h", "softmax_rowsdyn.h", "softmax_rowsdyn.hip", "softmax_wide.h", "softmax_wide.hip",
+                  "softmax_wgrow.h", "softmax_wgrow.hip", "softmax_long.h", "softmax_long.hip", "softmax_kernels.hip",
+                  "elementwise_kernels.hip")
 
 
 def kernel_source_hash():

@@ -18,6 +18,14 @@ def test_more_than_one_gpu_is_refused_with_a_message():
     assert "one GPU" in r.stderr and r.stdout.strip() == ""
 
 
+def test_the_profiles_identity_covers_every_kernel():
+    """A profile is quoted while the kernel sources still hash to what it was taken with."""
+    import bench
+    csrc = os.path.join(ROOT, "paper_2511_15369_amd", "csrc")
+    with_kernels = [f for f in os.listdir(csrc) if f.endswith((".h", ".hip")) and "__global__" in open(os.path.join(csrc, f)).read()]
+    assert len(with_kernels) > 5 and set(with_kernels) - {"debug_hooks.hip"} <= set(bench.KERNEL_SOURCES)
+
+
 def test_workload_shapes_match_the_benchmark_configurations():
     c = workloads.CONFIGS
     assert set(c) == {"deit_t", "vit_s", "vit_b", "swin_b", "swin_s_det"}
