@@ -490,8 +490,8 @@ softmax_rowsdyn_kernel(DynArgs A)
 
 // Several calls of one row length (the layers of a sweep) in one launch: packed arithmetic, no mask
 // and no requantization in front; the variant is a wavefront-uniform branch.  Launched one by one such
-// calls cost a launch each and its edges: 12 calls of 2303 x 145
-// scores and a GELU launch take 70.8 us, 15.0 through this kernel; 5 of 1007 x 196 28.8 and 9.2; 2 of
+// calls cost a launch each and its edges: 12 calls of 2303 x 145 scores and a GELU launch of 12 times 145 x 384
+// values take 59 us call after call, 10.4 through this kernel; 5 of 1007 x 196 28.8 and 9.2; 2 of
 // 13000 x 196 16.6 and 13.0.  Calls that each fill the chip gain their edges still: 2 of 100,000 x 196
 // 36.7 and 34.2 (second degree 37.1 and 34.4), 2 of 200,000 x 64 with a table 28.3 and 24.4, 4 of
 // 40,000 x 600 of the second degree 92.8 and 80.1.
