@@ -69,3 +69,17 @@ def test_arguments_of_a_table_call_come_in_two_steps(cols, assembly):
     assert len(bodies) == 3                            # both dividers and 32-bit arithmetic
     for body in bodies:
         assert len(re.findall(r"s_waitcnt.*lgkmcnt", body[:body.index("global_load")])) <= 2
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not installed")
+@pytest.mark.parametrize("src,kernel,item", [("softmax_rows_49.hip", r"softmax_rows\w*_kernelI\w*SoftmaxBatch\w*", 224),
+                                             ("softmax_rowsdyn_k1.hip", r"softmax_rowsdyn_batch_kernel\w*", 248),
+                                             ("elementwise_kernels.hip", r"gelu_i8_table_batch_kernel\w*", 96)])
+def test_a_batch_finds_its_problem_on_the_scalar_unit(src, kernel, item, assembly):
+    """The number of the workgroup's problem is counted in a scalar register: the compiler's own choice was a vector
+    one, a chain of selects and three reads of a lane in front of every argument."""
+    bodies = re.findall(r"^_ZN4iptq\d+%s:(.*?)^\.Lfunc_end" % kernel, assembly(src), re.M | re.S)
+    assert bodies
+    for body in bodies:
+        at = re.search(r"s_mul_i32 s\d+, s\d+, 0x%x\b" % item, body)
+        assert at and not re.search(r"^\s+v_", body[:at.start()], re.M)
