@@ -1049,13 +1049,16 @@ IPTQ_ROWS_SHAPES_ALT(IPTQ_DECLARE_ROWS_LAUNCHER)
 // than they had been.  95 / 130 / 190 million scores 76.0 / 101.5 / 148.0 us with two, 77.5 / 105.3 / 152.9 with three; of
 // 197 78.4 / 103.9 / 147.5 and 78.8 / 105.5 / 151.3, but 94.0 and 93.4 at 115 million.  Not with a table, a requantization
 // in front or the second degree (190 million of 197: 173, 164 and 158 us with two, 160, 151 and 149 with three).
-// Nor with many problems, where a wavefront also looks for its own: three of 302,592 rows of 198 140.9 us with
-// two and 144.6 with three, but twelve of 75,648 rows of 197 150.3 and 144.3, of 302,592 595 and 580.  Rows of 144 and
+// More than three problems in one launch gain later: rows of 198 from 100 million scores on at the latest (12 problems of
+// 302,592 rows 567 us with two, 599 with three; 8 of 75,648, 120 million, 93.4 and 94.4), of 197 from 200 million (16 of
+// 302,592 768 and 777, 12 of 100,000 183.8 and 185.6, but 5 of 151,296 117.6 and 116.5, 12 of 75,648 140.1 and 139.7).  Rows of 144 and
 // 577 gain nothing, of 257 not on every card, of 49 less than 1 %.
 inline size_t rows_extra_lds(int cols, int k, unsigned total_wgs, const SoftmaxBatch &B)
 {
-    if (!((cols == 197 || cols == 198) && k == 4) || B.head.n_items > 3) return 0;
-    if (cols == 197 && (int64_t)total_wgs * kRowsWpb * (64 / k) * cols <= 120 * 1000 * 1000) return 0;
+    if (!((cols == 197 || cols == 198) && k == 4)) return 0;
+    const bool many = B.head.n_items > 3;
+    const int64_t from = (cols == 197 ? (many ? 200 : 120) : many ? 100 : 0) * 1000 * 1000;
+    if ((int64_t)total_wgs * kRowsWpb * (64 / k) * cols <= from) return 0;
     for (int i = 0; i < B.head.n_items; ++i)
         if (!plain_arithmetic(B.item[i].P)) return 0;
     const int own = kRowsWpb * (64 / k) * cols * 4;   // LDS is handed out in units of 1280 bytes

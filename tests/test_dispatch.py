@@ -174,6 +174,20 @@ def test_workgroups_per_compute_unit(lib, rows, cols, most):
             assert 128 // -(-(got[0].lds + own) // 1280) == most
 
 
+@pytest.mark.parametrize("problems,rows,cols,bounded", [
+    (1, 115_000_000 // 197, 197, False), (1, 121_000_000 // 197, 197, True), (3, 302_592, 197, True), (4, 245_000, 197, False),
+    (4, 260_000, 197, True), (16, 63_000, 197, False), (16, 64_000, 197, True), (1, 95_000_000 // 198, 198, True), (3, 302_592, 198, True),
+    (4, 125_000, 198, False), (8, 64_000, 198, True), (12, 302_592, 198, True), (12, 37_000, 198, False)])
+def test_slab_kernels_bound_their_long_launches(lib, problems, rows, cols, bounded):
+    """Rows of 197 and 198 scores, four lanes per row: two workgroups on a compute unit instead of three, single
+    calls and batches; not beside the second degree."""
+    got = batch(lib, [(rows, packed_softmax(100, cols))] * problems, cols)
+    assert [(l.kernel, l.problems, l.lds > 0) for l in got] == [("softmax_rows_kernel", problems, bounded)]
+    own = 4 * 16 * cols * 4
+    assert not bounded or (128 // -(-(got[0].lds + own) // 1280), 128 // -(-own // 1280)) == (2, 3)
+    assert batch(lib, [(rows, ip.softmax_prepare(0.0085, cols, 2, 0))] * problems, cols)[0].lds == 0
+
+
 @pytest.mark.parametrize("rows,cols,plain,others", [
     # (with a table, with a requantization in front, of the second degree)
     (70_000, 900, 6, (0, 0, 0)), (70_000, 1000, 5, (5, 0, 5)), (20_000, 3400, 3, (2, 3, 3)), (20_000, 3600, 3, (2, 3, 3)),
